@@ -201,7 +201,11 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * block of at most 2048 rows and the column offset from the block's first
  * column; possible when no block has to span 65536 columns or more (banded
  * and stencil matrices, small matrices).  The wavefronts stream the
- * entries and add up each row's run with a segmented scan.  LILAC_LAYOUT_AUTO
+ * entries and add up each row's run with a segmented scan.  Where the rows
+ * of each 64 in a row have nearly one length (padding them to the longest
+ * adds at most 15%) and span less than 65536 columns, the matrix is instead
+ * copied column by column of such slices with 16-bit column offsets, one
+ * lane per row.  LILAC_LAYOUT_AUTO
  * picks it for matrices with at least 16384 non-zeros whose columns are
  * local (sampled distinct 128-byte x lines per non-zero below 0.3) when it
  * is possible and its blocks average at least 1024 non-zeros (rows whose

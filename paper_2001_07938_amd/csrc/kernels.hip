@@ -223,6 +223,8 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 // VEC consecutive values / column indices in one 16-byte (8-byte for the
 // float64 indices) streaming load.  `p` is VEC-element aligned.
@@ -1497,6 +1499,164 @@ __device__ __forceinline__ void band_block(const BandDesc &bd, int32_t b,
     }
 }
 
+// One group of a lane's entries in a sliced block (see SellSlice): N values
+// and N 16-bit column offsets, by 16-byte (8-byte) streaming loads.
+template <typename V, int N> struct SellGroup;
+template <> struct SellGroup<double, 4> {
+    f64x2 a, b;
+    u16x4 o;
+    __device__ __forceinline__ void load(const double *v, const uint16_t *off, int lane)
+    {
+        a = ld_stream((const f64x2 *)v + lane);
+        b = ld_stream((const f64x2 *)v + 64 + lane);
+        o = ld_stream((const u16x4 *)off + lane);
+    }
+    __device__ __forceinline__ double val(int t) const
+    {
+        return t == 0 ? a.x : t == 1 ? a.y : t == 2 ? b.x : b.y;
+    }
+};
+template <> struct SellGroup<float, 4> {
+    f32x4 a;
+    u16x4 o;
+    __device__ __forceinline__ void load(const float *v, const uint16_t *off, int lane)
+    {
+        a = ld_stream((const f32x4 *)v + lane);
+        o = ld_stream((const u16x4 *)off + lane);
+    }
+    __device__ __forceinline__ double val(int t) const { return (double)a[t]; }
+};
+template <typename V> struct SellGroup<V, 2> {
+    typedef V pair_t __attribute__((ext_vector_type(2)));
+    pair_t a;
+    u16x2 o;
+    __device__ __forceinline__ void load(const V *v, const uint16_t *off, int lane)
+    {
+        a = ld_stream((const pair_t *)v + lane);
+        o = ld_stream((const u16x2 *)off + lane);
+    }
+    __device__ __forceinline__ double val(int t) const { return (double)a[t]; }
+};
+
+// Row blocks of the sliced form: a workgroup takes `spb` consecutive slices,
+// its wavefronts in turn; one lane per row adds the row up in order.  No
+// scan, no LDS, and neighbouring lanes gather neighbouring entries of x
+// where neighbouring rows reach shifted columns (stencils), so the product
+// is bound by the 10 (float32: 6) bytes per entry it streams: 27-point
+// stencil of 128^3 (55.7 M entries) 105 us float64 = 5.9 TB/s of its own
+// bytes (scan form: 146 us), 60.5 us float32.  Two groups of four in flight:
+// one took 107 us, four 105 but 40 against 36 us on the 7-point rows (more
+// registers, fewer wavefronts); ordinary loads instead of non-temporal 113.
+template <typename V, bool DOT>
+__device__ __forceinline__ void sell_block(const BandDesc &bd, int32_t b,
+                                           const V *__restrict__ x,
+                                           V *__restrict__ y, const Epi &epi,
+                                           const V *__restrict__ w,
+                                           double *__restrict__ dot_part, double *lds)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int32_t s1 = min((b + 1) * bd.spb, bd.nslice);
+    double dacc = 0.0;
+    for (int32_t s = b * bd.spb + wave; s < s1; s += kBandWaves) {
+        const i32x4 sl = *(const __attribute__((address_space(4))) i32x4 *)(bd.slice + s);
+        const int32_t wmin = sl.z, wmax = sl.w;
+        const int32_t row = s * 64 + lane;
+        const V *pv = (const V *)bd.vals + (int64_t)sl.x * 64;
+        const uint16_t *po = bd.off + (int64_t)sl.x * 64;
+        const V *xb = x + sl.y;
+        const int32_t nq = wmax >> 2;
+        // the entries past the groups of four are requested first
+        SellGroup<V, 2> pr;
+        V v1 = (V)0;
+        uint16_t o1 = 0;
+        const int32_t tail = wmax & ~3;
+        if (wmax & 2)
+            pr.load(pv + tail * 64, po + tail * 64, lane);
+        if (wmax & 1) {
+            v1 = ld_stream(pv + (wmax - 1) * 64 + lane);
+            o1 = ld_stream(po + (wmax - 1) * 64 + lane);
+        }
+        int32_t len = wmax;
+        if (wmin < wmax)
+            len = (row < bd.rows) ? gld(bd.row_ptr + row + 1) - gld(bd.row_ptr + row) : 0;
+        double acc = 0.0;
+        auto add = [&](int32_t j, double v, double xv) {
+            if (j < len)
+                acc = fma(v, xv, acc);
+        };
+        int32_t q = 0;
+        for (; q + 2 <= nq; q += 2) {
+            SellGroup<V, 4> g[2];
+            V xv[8];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                g[u].load(pv + (q + u) * 256, po + (q + u) * 256, lane);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    xv[u * 4 + t] = gld(xb + g[u].o[t]);
+            if (q * 4 + 8 <= wmin) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    acc = fma(g[t >> 2].val(t & 3), (double)xv[t], acc);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    add(q * 4 + t, g[t >> 2].val(t & 3), (double)xv[t]);
+            }
+        }
+        if (q < nq) {
+            SellGroup<V, 4> g;
+            V xv[4];
+            g.load(pv + q * 256, po + q * 256, lane);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                xv[t] = gld(xb + g.o[t]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                add(q * 4 + t, g.val(t), (double)xv[t]);
+        }
+        if (wmax & 2) {
+            const V xa = gld(xb + pr.o.x), xc = gld(xb + pr.o.y);
+            add(tail, pr.val(0), (double)xa);
+            add(tail + 1, pr.val(1), (double)xc);
+        }
+        if (wmax & 1)
+            add(wmax - 1, (double)v1, (double)gld(xb + o1));
+        if (row < bd.rows) {
+            const V out = epilogue<V>(acc, epi);
+            gst(y + row, out);
+            if (DOT)
+                dacc = fma((double)gld(w + row), (double)out, dacc);
+        }
+    }
+    if (DOT) {
+        const double tot = block_sum<kBandWaves>(dacc, lds);
+        if (threadIdx.x == 0)
+            dot_part[b] = tot;
+    }
+}
+
+// Row block of the i-th of n workgroups: the workgroups i, i + 8, ... share
+// an XCD and take neighbouring blocks, so that the x a block shares with its
+// neighbours is read into that XCD's L2 once.
+__device__ __forceinline__ int32_t xcd_block(int32_t i, int32_t n)
+{
+    const int32_t per = n >> 3;
+    return (i < per * 8) ? (i & 7) * per + (i >> 3) : i;
+}
+
+template <typename V, bool DOT>
+__global__ __launch_bounds__(kBandThreads) void k_spmv_sell(
+    BandDesc bd, const V *__restrict__ x, V *__restrict__ y, Epi epi,
+    const V *__restrict__ w, double *__restrict__ dot_part)
+{
+    __shared__ double lds[kBandWaves];
+    sell_block<V, DOT>(bd, xcd_block(blockIdx.x, bd.nblk), x, y, epi, w, dot_part, lds);
+}
+
 template <typename V, bool DOT>
 __global__ __launch_bounds__(kBandThreads) void k_spmv_band(
     BandDesc bd, const V *__restrict__ x, V *__restrict__ y, Epi epi,
@@ -1526,6 +1686,19 @@ __global__ __launch_bounds__(kBandThreads) void k_spmv_band_grouped(
     const BandDesc bd = descs[lo];
     const Epi epi{EPI_NONE, 0, 0.0, 0.0};
     const PanelIO bio = io[lo];
+    if (bd.nslice > 0) {
+        const int32_t b = g - prefix[lo];
+        if constexpr (sizeof(V) == 8) {
+            if (bio.dot) {
+                sell_block<V, true>(bd, b, (const V *)bio.x, (V *)bio.y, epi,
+                                    (const V *)bio.x, bio.dot, (double *)smem);
+                return;
+            }
+        }
+        sell_block<V, false>(bd, b, (const V *)bio.x, (V *)bio.y, epi, nullptr, nullptr,
+                             (double *)smem);
+        return;
+    }
     if constexpr (sizeof(V) == 8) {
         if (bio.dot) {
             band_block<V, true>(bd, g - prefix[lo], (const V *)bio.x, (V *)bio.y, epi,
@@ -1577,6 +1750,96 @@ __global__ __launch_bounds__(kBlock) void k_band_pack(BandDesc bd,
     const int32_t base = bd.cbase[lo];
     for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
         rc[k] = (rl << 16) | (uint32_t)(col[k] - base);
+}
+
+// Column span and row lengths of every slice of 64 rows: one wavefront per
+// slice, its entries read in order.
+__global__ __launch_bounds__(kBlock) void k_slice_span(int32_t rows,
+                                                       const int32_t *__restrict__ rp,
+                                                       const int32_t *__restrict__ col,
+                                                       int32_t nslice,
+                                                       i32x4 *__restrict__ out)
+{
+    const int32_t s = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (s >= nslice)
+        return;  // whole wavefronts
+    const int64_t row = (int64_t)s * 64 + lane;
+    const int32_t a = rp[min(row, (int64_t)rows)], z = rp[min(row + 1, (int64_t)rows)];
+    const int32_t k0 = __shfl(a, 0, 64), k1 = __shfl(z, 63, 64);
+    int32_t lo = INT_MAX, hi = -1;
+    for (int64_t k = (int64_t)k0 + lane; k < k1; k += 64) {
+        const int32_t c = col[k];
+        lo = min(lo, c);
+        hi = max(hi, c);
+    }
+    const int32_t wmax = lane_group_max<64>(z - a);
+    const int32_t wmin = -lane_group_max<64>(a - z);
+    lo = -lane_group_max<64>(-lo);
+    hi = lane_group_max<64>(hi);
+    if (lane == 0)
+        out[s] = i32x4{lo, hi, wmin, wmax};
+}
+
+// Place of entry j of lane l in a slice (see SellSlice): values (VV to a
+// 16-byte load) and offsets.
+template <int VV>
+__device__ __forceinline__ int64_t sell_value_at(const i32x4 &sl, int32_t j, int32_t l)
+{
+    const int32_t w = sl.w, full = w & ~3;
+    if (j < full)
+        return VV == 4 ? ((int64_t)sl.x + (j & ~3)) * 64 + l * 4 + (j & 3)
+                       : ((int64_t)sl.x + (j & ~1)) * 64 + l * 2 + (j & 1);
+    if ((w & 2) && j < full + 2)
+        return ((int64_t)sl.x + full) * 64 + l * 2 + (j - full);
+    return ((int64_t)sl.x + j) * 64 + l;
+}
+
+// Fills the sliced form: one wavefront per slice reads its entries in order
+// and writes each to its place; then every lane pads its row.
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_sell_pack(BandDesc bd,
+                                                      const int32_t *__restrict__ col,
+                                                      const V *__restrict__ vals,
+                                                      V *__restrict__ sv,
+                                                      uint16_t *__restrict__ so)
+{
+    __shared__ int32_t starts[kWaves][65];
+    constexpr int VV = 16 / sizeof(V);
+    const int wave = threadIdx.x >> 6;
+    const int32_t s = blockIdx.x * kWaves + wave;
+    const int lane = threadIdx.x & 63;
+    const bool on = s < bd.nslice;
+    const int64_t row = (int64_t)s * 64 + lane;
+    const int64_t rows = bd.rows;
+    const int32_t a = on ? bd.row_ptr[min(row, rows)] : 0;
+    const int32_t z = on ? bd.row_ptr[min(row + 1, rows)] : 0;
+    int32_t *st = starts[wave];
+    st[lane] = a;
+    if (lane == 63)
+        st[64] = z;
+    __syncthreads();
+    if (!on)
+        return;
+    const i32x4 sl = *(const i32x4 *)(bd.slice + s);
+    const int32_t k0 = st[0], k1 = st[64];
+    for (int64_t k = (int64_t)k0 + lane; k < k1; k += 64) {
+        int32_t lo = 0, hi = 63;   // the last row that starts at or before k
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (st[mid] <= k)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        const int32_t j = (int32_t)(k - st[lo]);
+        sv[sell_value_at<VV>(sl, j, lo)] = vals[k];
+        so[sell_value_at<4>(sl, j, lo)] = (uint16_t)(col[k] - sl.y);
+    }
+    for (int32_t j = z - a; j < sl.w; ++j) {
+        sv[sell_value_at<VV>(sl, j, lane)] = (V)0;
+        so[sell_value_at<4>(sl, j, lane)] = 0;
+    }
 }
 
 // Hot entries of each row: one wavefront per row, 64 entries at a time.
@@ -2730,6 +2993,21 @@ void launch_spmv_band(lilac_dtype dt, const BandDesc &bd, const void *x, void *y
     if (bd.nblk <= 0)
         return;
     dim3 g(bd.nblk), b(kBandThreads);
+    if (bd.nslice > 0) {
+        if (dt == LILAC_F32 && dot_part)
+            fail(LILAC_ERR_UNSUPPORTED, "fused dot is only provided for float64");
+        if (dt == LILAC_F32)
+            hipLaunchKernelGGL((k_spmv_sell<float, false>), g, b, 0, s, bd,
+                               (const float *)x, (float *)y, epi, (const float *)w, dot_part);
+        else if (dot_part)
+            hipLaunchKernelGGL((k_spmv_sell<double, true>), g, b, 0, s, bd,
+                               (const double *)x, (double *)y, epi, (const double *)w, dot_part);
+        else
+            hipLaunchKernelGGL((k_spmv_sell<double, false>), g, b, 0, s, bd,
+                               (const double *)x, (double *)y, epi, (const double *)w, dot_part);
+        check_launch("k_spmv_sell");
+        return;
+    }
     if (dt == LILAC_F64) {
         if (dot_part)
             hipLaunchKernelGGL((k_spmv_band<double, true>), g, b, 0, s, bd,
@@ -2776,6 +3054,31 @@ void launch_band_pack(const BandDesc &bd, const int32_t *rp, const int32_t *col,
     hipLaunchKernelGGL(k_band_pack, dim3(grid_for(bd.rows, kBlock, INT_MAX)), dim3(kBlock),
                        0, s, bd, rp, col, rc);
     check_launch("k_band_pack");
+}
+
+void launch_slice_span(int32_t rows, const int32_t *rp, const int32_t *col, int32_t nslice,
+                       int32_t *out, hipStream_t s)
+{
+    if (nslice <= 0)
+        return;
+    hipLaunchKernelGGL(k_slice_span, dim3(grid_for(nslice, kWaves, INT_MAX)), dim3(kBlock), 0,
+                       s, rows, rp, col, nslice, (i32x4 *)out);
+    check_launch("k_slice_span");
+}
+
+void launch_sell_pack(lilac_dtype dt, const BandDesc &bd, const int32_t *col,
+                      const void *vals, void *sv, uint16_t *so, hipStream_t s)
+{
+    if (bd.nslice <= 0)
+        return;
+    dim3 g(grid_for(bd.nslice, kWaves, INT_MAX)), b(kBlock);
+    if (dt == LILAC_F64)
+        hipLaunchKernelGGL(k_sell_pack<double>, g, b, 0, s, bd, col, (const double *)vals,
+                           (double *)sv, so);
+    else
+        hipLaunchKernelGGL(k_sell_pack<float>, g, b, 0, s, bd, col, (const float *)vals,
+                           (float *)sv, so);
+    check_launch("k_sell_pack");
 }
 
 void launch_line_reuse(int32_t rows, const int32_t *rp, const int32_t *col,

@@ -179,7 +179,28 @@ struct BandDesc {
     const int32_t *brow;     // [nblk + 1]
     const int32_t *bent;     // [nblk + 1]
     const int32_t *cbase;    // [nblk]
-    int32_t rows, cols, nblk, pad;
+    int32_t rows, cols, nblk;
+    // sliced form (nslice > 0): vals, off and slice replace the arrays above
+    int32_t nslice, spb;     // slices, slices per workgroup
+    const int32_t *row_ptr;
+    const uint16_t *off;
+    const struct SellSlice *slice;   // [nslice]
+};
+// Sliced form of the band layout, for rows of nearly one length: rows are cut
+// into slices of 64 (one lane each), a slice is as wide as its longest row,
+// and its entries are stored column by column of the slice, so that the 64
+// lanes read consecutive memory: four columns together, then a pair, then a
+// single one, each lane's entries of a group side by side.  Entry j of lane
+// l in a slice at column `at` of width w:
+//   groups of four (j < w & ~3): column at + (j & ~3), place l * 4 + (j & 3)
+//     (float64 values: two pairs, column at + (j & ~1), place l * 2 + (j & 1))
+//   pair (w & 2): column at + (w & ~3), place l * 2 + (j & 1)
+//   last (w & 1): column at + w - 1, place l
+// A column holds 64 values and 64 16-bit column offsets from `base`.  Rows
+// shorter than the slice are padded; lanes stop at their row's length.
+struct SellSlice {
+    int32_t at, base;        // first column, smallest column index
+    int32_t wmin, wmax;      // shortest and longest row (wmin 0 in a short slice)
 };
 constexpr int kBandThreads = 256;
 constexpr int kBandWaves = kBandThreads / 64;
@@ -231,6 +252,9 @@ struct CsrHandle {
     BandDesc band{};
     uint32_t *d_brc = nullptr;
     int32_t *d_bb = nullptr;        // brow | bent | cbase
+    void *d_sv = nullptr;           // sliced form: values | offsets | slices
+    uint16_t *d_so = nullptr;       // the offsets in it
+    int64_t sell_cols = 0;          // columns of 64 entries it holds
     std::vector<int32_t> bin_off;   // NCLASS+1
     int64_t nchunks = 0;
     int32_t nsplit = 0;
@@ -367,6 +391,12 @@ void launch_row_span(int32_t rows, const int32_t *rp, const int32_t *col, int32_
                      int32_t *hi, hipStream_t s);
 void launch_band_pack(const BandDesc &bd, const int32_t *rp, const int32_t *col,
                       uint32_t *rc, hipStream_t s);
+// Per slice of 64 rows (see SellSlice): {smallest column, largest column,
+// shortest row, longest row}; INT_MAX, -1 for a slice with no entries.
+void launch_slice_span(int32_t rows, const int32_t *rp, const int32_t *col, int32_t nslice,
+                       int32_t *out, hipStream_t s);
+void launch_sell_pack(lilac_dtype dt, const BandDesc &bd, const int32_t *col,
+                      const void *vals, void *sv, uint16_t *so, hipStream_t s);
 // For ngroups groups of 64 consecutive rows spread over the matrix:
 // out[2g] = non-zeros looked at (at most 8192), out[2g+1] = distinct
 // (col >> shift) among them, hashed into 16384 bins.

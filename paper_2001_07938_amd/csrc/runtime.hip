@@ -376,6 +376,9 @@ static void free_analysis(CsrHandle &h)
     dev_free_reset(h.d_hb);
     dev_free_reset(h.d_brc);
     dev_free_reset(h.d_bb);
+    dev_free_reset(h.d_sv);
+    h.d_so = nullptr;
+    h.sell_cols = 0;
     h.use_band = false;
     h.band = BandDesc{};
     h.use_panels = false;
@@ -400,7 +403,10 @@ static int64_t analysis_bytes(const CsrHandle &h)
     if (h.use_hot)
         b += (h.nnz + kPad) * ((int64_t)dtype_size(h.dt) + 6) + (int64_t)h.rows * 2 +
              (int64_t)(4 * h.hot.nblk + h.hot.grid + 3) * 4;
-    if (h.use_band)
+    if (h.use_band && h.band.nslice > 0)
+        b += h.sell_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
+             (int64_t)h.band.nslice * (int64_t)sizeof(SellSlice);
+    else if (h.use_band)
         b += (h.nnz + kPad) * 4 + (int64_t)(3 * h.band.nblk + 2) * 4;
     return b;
 }
@@ -659,6 +665,89 @@ static void build_hot(CsrHandle &h, hipStream_t s)
     h.use_hot = true;
 }
 
+// Sliced form of the band layout (see SellSlice): when every slice of 64
+// rows spans fewer than 65536 columns and padding the rows to their slice's
+// longest adds at most kSellPad to the entries.  Rows longer than kSellWidth
+// need kSellMinSlices slices: one lane adds up a row, so a few long rows
+// would leave the chip idle (the scan kernel splits them).  27-point stencil
+// of 128^3, float64: scan form 146 us, sliced 105 us per product (5.9 TB/s);
+// float32 7-point rows pad nothing either.  Past the padding bound the 10
+// bytes of an entry reach the 12 of the scan form's.
+constexpr double kSellPad = 1.15;
+constexpr int32_t kSellWidth = 32;
+constexpr int32_t kSellMinSlices = 1024;
+// Workgroups of a product at most (8192; the fused dot has a partial of
+// each).  Eight per CU in a loop of slices took 119.5 us where this takes
+// 105 (sixteen: 109.5): the slices of one workgroup follow one another.
+constexpr int32_t kSellBlocksPerCu = 32;
+
+static bool build_sell(CsrHandle &h, hipStream_t s)
+{
+    if (h.rows > INT_MAX - 64)
+        return false;   // row numbers of a whole last slice must fit
+    const int32_t nslice = (int32_t)(((int64_t)h.rows + 63) / 64);
+    std::vector<int32_t> span((size_t)nslice * 4);
+    int32_t *d = (int32_t *)tmp_alloc(span.size() * 4);
+    try {
+        launch_slice_span(h.rows, h.d_row_ptr, h.d_col, nslice, d, s);
+        HIPC(hipMemcpyAsync(span.data(), d, span.size() * 4, hipMemcpyDeviceToHost, s));
+        HIPC(hipStreamSynchronize(s));
+    } catch (...) {
+        tmp_free(d);
+        throw;
+    }
+    tmp_free(d);
+    std::vector<SellSlice> slices((size_t)nslice);
+    int64_t at = 0;
+    int32_t widest = 0;
+    for (int32_t i = 0; i < nslice; ++i) {
+        const int32_t lo = span[4 * (size_t)i], hi = span[4 * (size_t)i + 1];
+        if (hi >= 0 && (int64_t)hi - lo >= 65536)
+            return false;
+        const int32_t w = span[4 * (size_t)i + 3];
+        slices[i] = SellSlice{(int32_t)at, hi >= 0 ? lo : 0, span[4 * (size_t)i + 2], w};
+        at += w;
+        widest = std::max(widest, w);
+        if ((double)at * 64.0 > kSellPad * (double)h.nnz)
+            return false;
+    }
+    if (widest > kSellWidth && nslice < kSellMinSlices)
+        return false;
+    if (h.rows & 63)
+        slices.back().wmin = 0;   // lanes past the last row have no entries
+    BandDesc bd{};
+    bd.rows = h.rows;
+    bd.cols = h.cols;
+    bd.row_ptr = h.d_row_ptr;
+    bd.nslice = nslice;
+    const int32_t most = ctx().cu * kSellBlocksPerCu;
+    bd.spb = kBandWaves * (int32_t)(((int64_t)nslice + (int64_t)kBandWaves * most - 1) /
+                                    ((int64_t)kBandWaves * most));
+    bd.nblk = (nslice + bd.spb - 1) / bd.spb;
+    // one allocation: values, offsets, slices
+    const size_t vbytes = (size_t)at * 64 * dtype_size(h.dt), obytes = (size_t)at * 64 * 2;
+    try {
+        h.d_sv = dev_alloc(vbytes + obytes + slices.size() * sizeof(SellSlice));
+    } catch (const Error &e) {
+        if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+            throw;
+        return false;   // the scan form needs less (no copy of the values)
+    }
+    h.sell_cols = at;
+    h.d_so = (uint16_t *)((char *)h.d_sv + vbytes);
+    void *d_slices = (char *)h.d_so + obytes;
+    HIPC(hipMemcpyAsync(d_slices, slices.data(), slices.size() * sizeof(SellSlice),
+                        hipMemcpyHostToDevice, s));
+    bd.vals = h.d_sv;
+    bd.off = h.d_so;
+    bd.slice = (const SellSlice *)d_slices;
+    launch_sell_pack(h.dt, bd, h.d_col, h.d_vals, h.d_sv, h.d_so, s);
+    HIPC(hipStreamSynchronize(s));
+    h.band = bd;
+    h.use_band = true;
+    return true;
+}
+
 // Builds the band copy of the matrix (see BandDesc) if every row spans
 // fewer than 65536 columns; returns whether it did.  Block bounds are chosen
 // on the host: a new block starts when the current one has kBandRows rows,
@@ -670,6 +759,8 @@ static bool build_band(CsrHandle &h, hipStream_t s, bool automatic)
 {
     if (h.rows == 0 || h.nnz == 0)
         return false;
+    if (build_sell(h, s))
+        return true;
     std::vector<int32_t> lo((size_t)h.rows), hi((size_t)h.rows), rp((size_t)h.rows + 1);
     int32_t *d = (int32_t *)tmp_alloc((size_t)h.rows * 8);
     try {
@@ -1105,13 +1196,18 @@ void destroy_handle(CsrHandle *h)
 // hot columns, the relabelled PageRank graph): rebuild those.
 static void values_changed(CsrHandle &h, hipStream_t s)
 {
-    if (h.use_panels || h.use_hot) {  // the band layout reads the CSR values
+    if (h.use_panels || h.use_hot) {
         h.dev_bytes -= analysis_bytes(h);
         analyse(h, s);
         h.dev_bytes += analysis_bytes(h);
-    } else if (h.pr && h.pr->g) {
-        drop_graphs(h);
+        return;
     }
+    // the scan form of the band layout reads the CSR values; the sliced form
+    // is filled again in place
+    if (h.use_band && h.band.nslice > 0)
+        launch_sell_pack(h.dt, h.band, h.d_col, h.d_vals, h.d_sv, h.d_so, s);
+    if (h.pr && h.pr->g)
+        drop_graphs(h);
 }
 
 // Bring a handle up to date before use (ReadObject: re-construct after a
