@@ -737,6 +737,188 @@ __device__ __forceinline__ void panel_block(const PanelDesc &pd, int32_t b,
     }
 }
 
+// Product over the lane form of the column-panel layout: as panel_block, but
+// each lane walks its own piece of the wavefront's run, entry after entry:
+// value times the LDS copy of x, added up in a register, and at a row's last
+// entry one LDS add to the row's sum.  Only what a lane holds of a row that
+// goes on in the next lane takes the scan across the wavefront, once a run.
+// Bound by the stream of entries (10 bytes each, 12 in the scan form): 150,000
+// rows of 241 random columns, float64, 74.5 -> 63.5 us a product (5.85 TB/s of
+// its bytes; 60.5 us with one panel copied instead of eight, 62.6 without the
+// scan).  Three pairs of columns in flight: two and four took 1% longer, six
+// 5% (registers).
+template <typename V, bool DOT>
+__device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
+                                           const V *__restrict__ x,
+                                           V *__restrict__ y, const Epi &epi,
+                                           const V *__restrict__ w,
+                                           double *__restrict__ dot_part,
+                                           unsigned char *smem)
+{
+    constexpr int B = kLanePairs;
+    constexpr int VV = 16 / sizeof(V);
+    typedef V pair_t __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(4))) int32_t *cptr;
+    double *acc = (double *)smem;                                 // row sums
+    V *xs = (V *)(smem + panel_sum_bytes(pd.rb));                 // x panel
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int32_t r0 = b * pd.rb;
+    const int32_t nr = min(pd.rb, pd.rows - r0);
+    const V *pv = (const V *)pd.vals;
+    for (int i = threadIdx.x; i < pd.rb; i += kPanelThreads)
+        acc[i] = 0.0;
+    if (threadIdx.x == 0)
+        xs[pd.pw] = (V)0;
+    double wrow = 0.0;
+    if (DOT && (int32_t)threadIdx.x < nr)
+        wrow = (double)gld(w + r0 + threadIdx.x);
+    const bool aligned = (((uintptr_t)x) & 15) == 0;
+    const int32_t rot =
+        (pd.np > 1 && pd.nblk >= kPanelRotateBlocks) ? (int32_t)((b >> 3) % pd.np) : 0;
+    auto panel_at = [&](int32_t i) { return (i + rot < pd.np) ? i + rot : i + rot - pd.np; };
+    // a run: its first column, its pairs, whether a single column follows
+    struct Run {
+        int32_t at, pairs, odd;
+    };
+    auto run_of = [&](int32_t p) {
+        const int32_t q = (b * pd.np + p) * kPanelWaves + wv;
+        const int32_t c0 = ((cptr)pd.col0)[q], k = ((cptr)pd.col0)[q + 1] - c0;
+        return Run{c0, k >> 1, k & 1};
+    };
+    pair_t nv[B];
+    u16x2 nw[B];
+    V nv1 = (V)0;
+    uint16_t nw1 = 0;
+    int32_t nstart = 0;
+    auto request = [&](const Run &r, int32_t k) {
+        const V *v = pv + ((int64_t)r.at + 2 * k) * 64;
+        const uint16_t *o = pd.words + ((int64_t)r.at + 2 * k) * 64;
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < r.pairs) {
+                nv[u] = ld_stream((const pair_t *)(v + u * 128) + lane);
+                nw[u] = ld_stream((const u16x2 *)(o + u * 128) + lane);
+            }
+    };
+    auto request_first = [&](const Run &r, int32_t p) {
+        request(r, 0);
+        if (r.odd) {
+            const int64_t at = ((int64_t)r.at + 2 * r.pairs) * 64 + lane;
+            nv1 = ld_stream(pv + at);
+            nw1 = ld_stream(pd.words + at);
+        }
+        nstart = gld(pd.start + ((int64_t)(b * pd.np + p) * kPanelWaves + wv) * 64 + lane);
+    };
+    Run cur{0, 0, 0}, next{0, 0, 0};
+    if (pd.np > 0) {
+        next = run_of(panel_at(0));
+        request_first(next, panel_at(0));
+    }
+    for (int32_t pk = 0; pk < pd.np; ++pk) {
+        const int32_t c0 = panel_at(pk) * pd.pw;
+        const int32_t width = min(pd.pw, pd.cols - c0);
+        cur = next;
+        const bool more = pk + 1 < pd.np;
+        const int32_t pn = more ? panel_at(pk + 1) : 0;
+        if (more)
+            next = run_of(pn);
+        __syncthreads();  // the previous panel is no longer read
+        const int32_t nvec = aligned ? width / VV : 0;
+        for (int32_t c = wv; c * 64 < nvec; c += kPanelWaves) {
+            const int32_t i = c * 64 + lane;
+            if (i < nvec)
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)(x + c0 + i * VV),
+                    (__attribute__((address_space(3))) void *)(xs + c * 64 * VV), 16, 0, 0);
+        }
+        for (int32_t e = nvec * VV + threadIdx.x; e < width; e += kPanelThreads)
+            xs[e] = gld(x + c0 + e);
+        __builtin_amdgcn_s_waitcnt(0);  // the direct loads have landed
+        __syncthreads();                 // the panel is in LDS
+        int32_t row = wv * pd.rw + nstart;
+        const V v1 = nv1;
+        const uint32_t w1 = nw1;
+        double sum = 0.0;
+        auto step = [&](V v, V xv, uint32_t word) {
+            sum = fma((double)v, (double)xv, sum);
+            if (word & kLaneEnd) {
+                lds_add_f64(&acc[row], sum);
+                ++row;
+                sum = 0.0;
+            }
+        };
+        for (int32_t k = 0; k < cur.pairs; k += B) {
+            pair_t v[B];
+            u16x2 o[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                v[u] = nv[u];
+                o[u] = nw[u];
+            }
+            if (k + B < cur.pairs)
+                request(cur, k + B);
+            else if (more)
+                request_first(next, pn);
+            if (k + B <= cur.pairs) {
+                V xa[B], xb[B];
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    xa[u] = xs[o[u].x & 0x7FFFu];
+                    xb[u] = xs[o[u].y & 0x7FFFu];
+                }
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    step(v[u].x, xa[u], o[u].x);
+                    step(v[u].y, xb[u], o[u].y);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < B - 1; ++u)
+                    if (k + u < cur.pairs) {
+                        const V xa = xs[o[u].x & 0x7FFFu], xb = xs[o[u].y & 0x7FFFu];
+                        step(v[u].x, xa, o[u].x);
+                        step(v[u].y, xb, o[u].y);
+                    }
+            }
+        }
+        if (cur.pairs == 0 && more)
+            request_first(next, pn);
+        if (cur.odd)
+            step(v1, xs[w1 & 0x7FFFu], w1);
+        // rows that go on in the next lane, and the run's last row: rows ascend
+        // along the lanes, the last lane of a row adds what they hold of it
+        if (cur.pairs + cur.odd > 0) {
+            const double part = seg_scan64<true>(sum, row);
+            if (next_lane_key(row) != row)
+                lds_add_f64(&acc[row], part);
+        }
+    }
+    __syncthreads();
+    double dacc = 0.0;
+    for (int32_t i = threadIdx.x; i < nr; i += kPanelThreads) {
+        const V out = epilogue<V>(acc[i], epi);
+        gst(y + r0 + i, out);
+        if (DOT)
+            dacc = fma(i == (int32_t)threadIdx.x ? wrow : (double)gld(w + r0 + i),
+                       (double)out, dacc);
+    }
+    if (DOT) {
+        const double tot = block_sum<kPanelWaves>(dacc, (double *)xs);
+        if (threadIdx.x == 0)
+            dot_part[b] = tot;
+    }
+}
+
+template <typename V, bool DOT>
+__global__ __launch_bounds__(kPanelThreads) void k_spmv_lanes(
+    PanelDesc pd, const V *__restrict__ x, V *__restrict__ y, Epi epi,
+    const V *__restrict__ w, double *__restrict__ dot_part)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    lane_block<V, DOT>(pd, blockIdx.x, x, y, epi, w, dot_part, smem);
+}
+
 template <typename V, bool DOT>
 __global__ __launch_bounds__(kPanelThreads) void k_spmv_panels(
     PanelDesc pd, const V *__restrict__ x, V *__restrict__ y, Epi epi,
@@ -767,6 +949,18 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_panels_grouped(
     const PanelDesc pd = descs[lo];
     const Epi epi{EPI_NONE, 0, 0.0, 0.0};
     const PanelIO pio = io[lo];
+    if (pd.col0) {
+        if constexpr (sizeof(V) == 8) {
+            if (pio.dot) {
+                lane_block<V, true>(pd, g - prefix[lo], (const V *)pio.x, (V *)pio.y, epi,
+                                    (const V *)pio.x, pio.dot, smem);
+                return;
+            }
+        }
+        lane_block<V, false>(pd, g - prefix[lo], (const V *)pio.x, (V *)pio.y, epi, nullptr,
+                             nullptr, smem);
+        return;
+    }
     if constexpr (sizeof(V) == 8) {
         if (pio.dot) {
             panel_block<V, true>(pd, g - prefix[lo], (const V *)pio.x, (V *)pio.y, epi,
@@ -880,6 +1074,153 @@ __global__ __launch_bounds__(kBlock) void k_panel_scatter(
         if (k < e) {
             pv[pos] = vals[k];
             prc[pos] = ((uint32_t)rl << 16) | (uint32_t)(c - pan * pd.pw);
+        }
+    }
+}
+
+// Lane form, per run (one wavefront each): rows without an entry between the
+// run's first and last row that have one get a filler (count 1), and the run
+// as many columns as 64 equal pieces of it take.
+__global__ __launch_bounds__(kBlock) void k_lane_runs(PanelDesc pd, int32_t *__restrict__ cnt,
+                                                      int32_t *__restrict__ kc)
+{
+    const int64_t q = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
+    if (q >= (int64_t)pd.nblk * pd.np * kPanelWaves)
+        return;  // whole wavefronts
+    const int64_t seg = q / kPanelWaves;
+    const int32_t a = min((int32_t)(q - seg * kPanelWaves) * pd.rw, pd.rb);
+    const int32_t z = min(a + pd.rw, pd.rb);
+    int32_t *c = cnt + seg * (pd.rb + 1);
+    int32_t first = INT_MAX, last = -1;
+    for (int32_t r = a + lane; r < z; r += 64)
+        if (c[r] > 0) {
+            first = min(first, r);
+            last = r;
+        }
+    first = -lane_group_max<64>(-first);
+    last = lane_group_max<64>(last);
+    int32_t n = 0;
+    for (int32_t r = a + lane; r < z; r += 64) {
+        int32_t m = c[r];
+        if (m == 0 && r > first && r < last) {
+            m = 1;
+            c[r] = 1;
+        }
+        n += m;
+    }
+    n = wave_sum_i32(n);
+    if (lane == 0)
+        kc[q] = (n + 63) / 64;
+}
+
+// Place of entry j of lane l of a run of k columns from column at.
+__device__ __forceinline__ int64_t lane_place(int32_t at, int32_t k, int32_t j, int32_t l)
+{
+    return (j < (k & ~1)) ? ((int64_t)at + (j & ~1)) * 64 + l * 2 + (j & 1)
+                          : ((int64_t)at + j) * 64 + l;
+}
+
+// Padding, fillers and start rows (the entries are written afterwards; a row
+// of count 1 is written as a filler here, whatever it is).  pos: exclusive
+// scan of the counts.  One wavefront per run.
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_lane_fill(PanelDesc pd,
+                                                      const int32_t *__restrict__ pos,
+                                                      V *__restrict__ vals,
+                                                      uint16_t *__restrict__ words,
+                                                      uint8_t *__restrict__ start)
+{
+    const int64_t q = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
+    if (q >= (int64_t)pd.nblk * pd.np * kPanelWaves)
+        return;  // whole wavefronts
+    const int64_t seg = q / kPanelWaves;
+    const int32_t a = min((int32_t)(q - seg * kPanelWaves) * pd.rw, pd.rb);
+    const int32_t z = min(a + pd.rw, pd.rb);
+    const int32_t *P = pos + seg * (pd.rb + 1);
+    const int32_t base = P[a], n = P[z] - base;
+    const int32_t at = pd.col0[q], k = pd.col0[q + 1] - at;
+    for (int32_t i = n + lane; i < k * 64; i += 64) {
+        const int32_t l = i / k;
+        const int64_t e = lane_place(at, k, i - l * k, l);
+        vals[e] = (V)0;
+        words[e] = (uint16_t)pd.pw;
+    }
+    for (int32_t r = a + lane; r < z; r += 64)
+        if (P[r + 1] - P[r] == 1) {
+            const int32_t i = P[r] - base, l = i / k;
+            const int64_t e = lane_place(at, k, i - l * k, l);
+            vals[e] = (V)0;
+            words[e] = (uint16_t)(pd.pw | kLaneEnd);
+        }
+    // row of the lane's first entry: the last row that starts at or before
+    // it and is not empty; lanes past the end take the last row
+    int32_t lo = a, hi = max(a, z - 1);
+    const int32_t want = base + min(lane * k, max(n - 1, 0));
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (P[mid] <= want)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    start[q * 64 + lane] = (uint8_t)(lo - a);
+}
+
+// The entries: one wavefront per row, 64 entries at a time, positions from
+// ballots as in k_panel_scatter.
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_lane_scatter(
+    PanelDesc pd, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const V *__restrict__ src, const int32_t *__restrict__ pos, V *__restrict__ vals,
+    uint16_t *__restrict__ words)
+{
+    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
+    if (i >= pd.rows)
+        return;  // whole wavefronts
+    const int32_t b = (int32_t)(i / pd.rb), rl = (int32_t)(i - (int64_t)b * pd.rb);
+    const int32_t wv = rl / pd.rw;
+    const int32_t a = rp[i], e = rp[i + 1];
+    // lane p < np: panel p's next position in the run, the row's last one
+    // (-1 on the run's last row, which takes no end mark), the run's first
+    // column and columns
+    int32_t next = 0, last = 0, at = 0, k = 1;
+    if (lane < pd.np) {
+        const int64_t seg = (int64_t)b * pd.np + lane;
+        const int32_t *P = pos + seg * (pd.rb + 1);
+        const int32_t base = P[wv * pd.rw];
+        next = P[rl] - base;
+        last = (P[rl + 1] < P[min((wv + 1) * pd.rw, pd.rb)]) ? P[rl + 1] - base - 1 : -1;
+        at = pd.col0[seg * kPanelWaves + wv];
+        k = max(1, pd.col0[seg * kPanelWaves + wv + 1] - at);
+    }
+    for (int32_t s = a; s < e; s += 64) {
+        const int32_t n = s + lane;
+        const int32_t c = (n < e) ? col[n] : 0;
+        const int32_t pan = (n < e) ? c / pd.pw : -1;
+        int32_t j = 0, end = 0, pat = 0, pk = 1;
+        for (int32_t p = 0; p < pd.np; ++p) {
+            const uint64_t m = __ballot(pan == p);
+            if (!m)
+                continue;   // uniform
+            const int32_t from = __shfl(next, p, 64), to = __shfl(last, p, 64);
+            const int32_t fat = __shfl(at, p, 64), fk = __shfl(k, p, 64);
+            if (pan == p) {
+                j = from + lanes_below(m);
+                end = to;
+                pat = fat;
+                pk = fk;
+            }
+            if (lane == p)
+                next += __popcll(m);
+        }
+        if (n < e) {
+            const int32_t l = j / pk;
+            const int64_t place = lane_place(pat, pk, j - l * pk, l);
+            vals[place] = src[n];
+            words[place] = (uint16_t)((c - pan * pd.pw) | (j == end ? kLaneEnd : 0u));
         }
     }
 }
@@ -2955,6 +3296,21 @@ void launch_spmv_panels(lilac_dtype dt, const PanelDesc &pd, const void *x,
     if (pd.nblk <= 0)
         return;
     dim3 g(pd.nblk), b(kPanelThreads);
+    if (pd.col0) {
+        if (dt == LILAC_F32 && dot_part)
+            fail(LILAC_ERR_UNSUPPORTED, "fused dot is only provided for float64");
+        if (dt == LILAC_F32)
+            hipLaunchKernelGGL((k_spmv_lanes<float, false>), g, b, kPanelLds, s, pd,
+                               (const float *)x, (float *)y, epi, (const float *)w, dot_part);
+        else if (dot_part)
+            hipLaunchKernelGGL((k_spmv_lanes<double, true>), g, b, kPanelLds, s, pd,
+                               (const double *)x, (double *)y, epi, (const double *)w, dot_part);
+        else
+            hipLaunchKernelGGL((k_spmv_lanes<double, false>), g, b, kPanelLds, s, pd,
+                               (const double *)x, (double *)y, epi, (const double *)w, dot_part);
+        check_launch("k_spmv_lanes");
+        return;
+    }
     if (dt == LILAC_F64) {
         if (dot_part)
             hipLaunchKernelGGL((k_spmv_panels<double, true>), g, b, kPanelLds, s, pd,
@@ -3164,6 +3520,12 @@ void panels_prepare()
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_panels<float, false>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lanes<double, true>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lanes<double, false>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lanes<float, false>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     done = true;
 }
 
@@ -3187,6 +3549,42 @@ void launch_panel_scatter(lilac_dtype dt, const PanelDesc &pd, const int32_t *rp
         hipLaunchKernelGGL(k_panel_scatter<float>, g, b, 0, s, pd, rp, col,
                            (const float *)vals, ptr, (float *)pv, prc);
     check_launch("k_panel_scatter");
+}
+
+void launch_lane_runs(const PanelDesc &pd, int32_t *cnt, int32_t *kc, hipStream_t s)
+{
+    const int64_t n = (int64_t)pd.nblk * pd.np * kPanelWaves * 64;
+    hipLaunchKernelGGL(k_lane_runs, dim3(grid_for(n, kBlock, INT_MAX)), dim3(kBlock), 0, s, pd,
+                       cnt, kc);
+    check_launch("k_lane_runs");
+}
+
+void launch_lane_fill(lilac_dtype dt, const PanelDesc &pd, const int32_t *pos, void *vals,
+                      uint16_t *words, uint8_t *start, hipStream_t s)
+{
+    const int64_t n = (int64_t)pd.nblk * pd.np * kPanelWaves * 64;
+    dim3 g(grid_for(n, kBlock, INT_MAX)), b(kBlock);
+    if (dt == LILAC_F64)
+        hipLaunchKernelGGL(k_lane_fill<double>, g, b, 0, s, pd, pos, (double *)vals, words,
+                           start);
+    else
+        hipLaunchKernelGGL(k_lane_fill<float>, g, b, 0, s, pd, pos, (float *)vals, words,
+                           start);
+    check_launch("k_lane_fill");
+}
+
+void launch_lane_scatter(lilac_dtype dt, const PanelDesc &pd, const int32_t *rp,
+                         const int32_t *col, const void *src, const int32_t *pos,
+                         void *vals, uint16_t *words, hipStream_t s)
+{
+    dim3 g(grid_for((int64_t)pd.rows * 64, kBlock, INT_MAX)), b(kBlock);
+    if (dt == LILAC_F64)
+        hipLaunchKernelGGL(k_lane_scatter<double>, g, b, 0, s, pd, rp, col,
+                           (const double *)src, pos, (double *)vals, words);
+    else
+        hipLaunchKernelGGL(k_lane_scatter<float>, g, b, 0, s, pd, rp, col,
+                           (const float *)src, pos, (float *)vals, words);
+    check_launch("k_lane_scatter");
 }
 
 void launch_panel_wptr(const PanelDesc &pd, const int32_t *ptr, int32_t *wptr,

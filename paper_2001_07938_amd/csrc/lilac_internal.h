@@ -106,7 +106,26 @@ struct PanelDesc {
     int32_t rows, cols;
     int32_t pw, np, rb, nblk, rw;
     int32_t pad;
+    // lane form (col0 != null; see below): vals, words and start
+    const uint16_t *words;
+    const uint8_t *start;
+    const int32_t *col0;
 };
+// Lane form of the column-panel layout.  A run is what one wavefront holds of
+// one (row block, panel): the entries of its rows in order, with a filler for
+// every row without an entry between two that have one.  The run is cut into
+// 64 equal pieces of K consecutive entries, one per lane, stored column by
+// column: run q = (b * np + p) * 16 + wave holds the columns col0[q] ..
+// col0[q + 1] (64 entries each), two together (entry j of lane l at column
+// col0[q] + (j & ~1), place l * 2 + (j & 1)), an odd last one alone (place l).
+// An entry is its value and a 16-bit word: its column in the panel, and
+// kLaneEnd on the last entry of its row, the run's last row excepted (so a
+// lane never steps past it).  Fillers and the padding of the last
+// pieces have value 0 and column pw, where the LDS holds a zero.
+// start[q * 64 + l]: row (from the wavefront's first) of the lane's first entry.
+constexpr uint32_t kLaneEnd = 0x8000u;
+constexpr int kLaneMaxWidth = 32752;           // panel columns: 15 bits, pw itself too
+constexpr int kLanePairs = 3;                  // pairs of columns in flight
 // Vectors of one matrix in a grouped panel launch.
 // dot: when set (float64 only), the blocks also write the partial sums of
 // x_i * y_i over their rows (square matrices), one per row block, the
@@ -132,6 +151,13 @@ constexpr int panel_sum_bytes(int rb)
 constexpr int panel_width(int vsize, int rb)
 {
     return (kPanelLds - panel_sum_bytes(rb)) / vsize;
+}
+// the same for the lane form: 16 bytes for the zero after the panel
+constexpr int lane_panel_width(int vsize, int rb)
+{
+    return (kPanelLds - panel_sum_bytes(rb) - 16) / vsize < kLaneMaxWidth
+               ? (kPanelLds - panel_sum_bytes(rb) - 16) / vsize
+               : kLaneMaxWidth;
 }
 
 // Hot-column layout, for matrices whose most referenced columns come first
@@ -239,6 +265,7 @@ struct CsrHandle {
     void *d_pv = nullptr;
     uint32_t *d_prc = nullptr;
     int32_t *d_pw = nullptr;
+    int64_t lane_cols = 0;          // lane form: columns of 64 entries it holds
     // hot-column layout (when use_hot)
     bool use_hot = false;
     HotDesc hot{};
@@ -370,6 +397,15 @@ void launch_panel_count(const PanelDesc &pd, const int32_t *rp,
 void launch_panel_scatter(lilac_dtype dt, const PanelDesc &pd, const int32_t *rp,
                           const int32_t *col, const void *vals, const int32_t *ptr,
                           void *pv, uint32_t *prc, hipStream_t s);
+// Lane form: row counts get the fillers (in place), kc[run] the columns of a
+// run; then, with cnt and kc scanned, col0 = kc: padding, fillers and start
+// rows of every run, and the entries.
+void launch_lane_runs(const PanelDesc &pd, int32_t *cnt, int32_t *kc, hipStream_t s);
+void launch_lane_fill(lilac_dtype dt, const PanelDesc &pd, const int32_t *pos, void *vals,
+                      uint16_t *words, uint8_t *start, hipStream_t s);
+void launch_lane_scatter(lilac_dtype dt, const PanelDesc &pd, const int32_t *rp,
+                         const int32_t *col, const void *src, const int32_t *pos,
+                         void *vals, uint16_t *words, hipStream_t s);
 void launch_panel_wptr(const PanelDesc &pd, const int32_t *ptr, int32_t *wptr,
                        hipStream_t s);
 // Column-panel products of nmat matrices in one launch of nblocks

@@ -382,6 +382,7 @@ static void free_analysis(CsrHandle &h)
     h.use_band = false;
     h.band = BandDesc{};
     h.use_panels = false;
+    h.lane_cols = 0;
     h.pan = PanelDesc{};
     h.use_hot = false;
     h.hot = HotDesc{};
@@ -397,7 +398,11 @@ static int64_t analysis_bytes(const CsrHandle &h)
     int64_t b = (int64_t)h.rows * 4 + h.nchunks * (3 * 4 + 8) +
                 (int64_t)(h.nsplit + 1) * 4 + (int64_t)h.ntiles * sizeof(Tile) +
                 (int64_t)(h.grid + h.fin_blocks) * 8;
-    if (h.use_panels)
+    if (h.use_panels && h.pan.col0)
+        b += h.lane_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
+             ((int64_t)h.pan.nblk * h.pan.np * kPanelWaves + 1) * 4 +
+             (int64_t)h.pan.nblk * h.pan.np * kPanelWaves * 64;
+    else if (h.use_panels)
         b += (h.nnz + kPad) * ((int64_t)dtype_size(h.dt) + 4) +
              (int64_t)h.pan.nblk * h.pan.np * (kPanelWaves + 1) * 4;
     if (h.use_hot)
@@ -495,9 +500,80 @@ static double measure_line_ratio(const CsrHandle &h, hipStream_t s)
 
 static int64_t scan_total(int32_t *a, int64_t n, hipStream_t s);
 
+// Builds the lane form of the column-panel copy (see PanelDesc) if its bytes,
+// with the fillers and the padding of the last lanes, are no more than the
+// scan form's (10 against 12 bytes per float64 entry, 6 against 8 float32):
+// both are streamed once per product.
+static bool build_lanes(CsrHandle &h, hipStream_t s)
+{
+    const size_t vs = dtype_size(h.dt);
+    PanelDesc pd{};
+    pd.rows = h.rows;
+    pd.cols = h.cols;
+    pd.rb = panel_rows(h);
+    pd.pw = lane_panel_width((int)vs, pd.rb);
+    const int64_t np = ((int64_t)h.cols + pd.pw - 1) / pd.pw;
+    if (np < 1 || np > kPanelMaxPanels)
+        return false;
+    pd.np = (int32_t)np;
+    pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
+    pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
+    const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
+    const int64_t nrun = (int64_t)pd.nblk * pd.np * kPanelWaves;
+    int32_t *pos = nullptr;
+    int64_t ncol = 0;
+    try {
+        pos = (int32_t *)tmp_alloc((size_t)nptr * 4);
+        // columns of the runs | start rows | words | values, the last two once
+        // their size is known
+        h.d_pw = (int32_t *)dev_alloc((size_t)(nrun + 1) * 4 + (size_t)nrun * 64);
+        uint8_t *start = (uint8_t *)(h.d_pw + nrun + 1);
+        launch_fill_i32(pos, nptr, 0, s);
+        launch_panel_count(pd, h.d_row_ptr, h.d_col, pos, s);
+        launch_lane_runs(pd, pos, h.d_pw, s);
+        launch_fill_i32(h.d_pw + nrun, 1, 0, s);
+        ncol = scan_total(h.d_pw, nrun + 1, s);
+        const bool fits = ncol * 64 < INT_MAX &&
+                          ncol * 64 * (int64_t)(vs + 2) + nrun * 64 <= h.nnz * (int64_t)(vs + 4);
+        if (fits) {
+            scan_total(pos, nptr, s);
+            h.d_pv = dev_alloc((size_t)ncol * 64 * vs);
+            h.d_prc = (uint32_t *)dev_alloc((size_t)ncol * 64 * 2);
+            pd.vals = h.d_pv;
+            pd.words = (const uint16_t *)h.d_prc;
+            pd.start = start;
+            pd.col0 = h.d_pw;
+            launch_lane_fill(h.dt, pd, pos, h.d_pv, (uint16_t *)h.d_prc, start, s);
+            launch_lane_scatter(h.dt, pd, h.d_row_ptr, h.d_col, h.d_vals, pos, h.d_pv,
+                                (uint16_t *)h.d_prc, s);
+            HIPC(hipStreamSynchronize(s));
+        } else {
+            dev_free_reset(h.d_pw);
+        }
+        tmp_free(pos);
+        if (!fits)
+            return false;
+    } catch (const Error &e) {
+        tmp_free(pos);
+        dev_free_reset(h.d_pw);
+        dev_free_reset(h.d_pv);
+        dev_free_reset(h.d_prc);
+        if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+            throw;
+        return false;
+    }
+    h.lane_cols = ncol;
+    h.pan = pd;
+    h.use_panels = true;
+    return true;
+}
+
 // Builds the column-panel copy of the matrix (see PanelDesc).
 static void build_panels(CsrHandle &h, hipStream_t s)
 {
+    panels_prepare();
+    if (build_lanes(h, s))
+        return;
     PanelDesc pd{};
     pd.rows = h.rows;
     pd.cols = h.cols;
@@ -505,7 +581,6 @@ static void build_panels(CsrHandle &h, hipStream_t s)
     pd.np = (int32_t)panel_count(h);
     if (pd.np < 1 || pd.np > kPanelMaxPanels)
         fail(LILAC_ERR_DEVICE, "column-panel layout needs 1 to 64 panels");
-    panels_prepare();
     pd.rb = panel_rows(h);
     pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
     pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
