@@ -2109,10 +2109,17 @@ __global__ __launch_bounds__(kBlock) void k_slice_span(int32_t rows,
     const int32_t a = rp[min(row, (int64_t)rows)], z = rp[min(row + 1, (int64_t)rows)];
     const int32_t k0 = __shfl(a, 0, 64), k1 = __shfl(z, 63, 64);
     int32_t lo = INT_MAX, hi = -1;
-    for (int64_t k = (int64_t)k0 + lane; k < k1; k += 64) {
-        const int32_t c = col[k];
-        lo = min(lo, c);
-        hi = max(hi, c);
+    constexpr int U = 8;   // loads in flight
+    for (int64_t k = (int64_t)k0 + lane; k < k1; k += 64 * U) {
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            c[u] = col[min(k + 64 * u, (int64_t)k1 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            lo = min(lo, c[u]);
+            hi = max(hi, c[u]);
+        }
     }
     const int32_t wmax = lane_group_max<64>(z - a);
     const int32_t wmin = -lane_group_max<64>(a - z);
@@ -2164,18 +2171,33 @@ __global__ __launch_bounds__(kBlock) void k_sell_pack(BandDesc bd,
         return;
     const i32x4 sl = *(const i32x4 *)(bd.slice + s);
     const int32_t k0 = st[0], k1 = st[64];
-    for (int64_t k = (int64_t)k0 + lane; k < k1; k += 64) {
-        int32_t lo = 0, hi = 63;   // the last row that starts at or before k
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (st[mid] <= k)
-                lo = mid;
-            else
-                hi = mid - 1;
+    constexpr int U = 8;   // loads in flight
+    for (int64_t kb = (int64_t)k0 + lane; kb < k1; kb += 64 * U) {
+        V v[U];
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = min(kb + 64 * u, (int64_t)k1 - 1);
+            v[u] = vals[k];
+            c[u] = col[k];
         }
-        const int32_t j = (int32_t)(k - st[lo]);
-        sv[sell_value_at<VV>(sl, j, lo)] = vals[k];
-        so[sell_value_at<4>(sl, j, lo)] = (uint16_t)(col[k] - sl.y);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = kb + 64 * u;
+            if (k >= k1)
+                break;
+            int32_t lo = 0, hi = 63;   // the last row that starts at or before k
+            while (lo < hi) {
+                const int32_t mid = (lo + hi + 1) >> 1;
+                if (st[mid] <= k)
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+            const int32_t j = (int32_t)(k - st[lo]);
+            sv[sell_value_at<VV>(sl, j, lo)] = v[u];
+            so[sell_value_at<4>(sl, j, lo)] = (uint16_t)(c[u] - sl.y);
+        }
     }
     for (int32_t j = z - a; j < sl.w; ++j) {
         sv[sell_value_at<VV>(sl, j, lane)] = (V)0;
@@ -2459,44 +2481,107 @@ __global__ __launch_bounds__(kBlock) void k_permute_f32(int32_t n,
 
 // ------------------------------------------------------------------ JDS
 
-// Thread p handles the row at JDS position p: diagonal j holds its j-th
-// entry at jd_ptr[j] + p, so consecutive threads read consecutive entries.
-// Entries outside [0, nnz) and diagonals past max_len are never touched,
-// whatever the arrays hold; a position whose original row is unknown (perm
-// not a permutation) is not stored.
-__global__ __launch_bounds__(kBlock) void k_spmv_jds(
-    int32_t rows, int32_t max_len, int32_t nnz, const int32_t *__restrict__ iperm,
-    const int32_t *__restrict__ nzcnt, const int32_t *__restrict__ jd_ptr,
-    const int32_t *__restrict__ jd_col, const double *__restrict__ jd_val,
-    const double *__restrict__ x, double *__restrict__ y)
+// Before the product: iperm[q] = i for perm[i] = q (positions that perm does
+// not name keep what they hold; the product looks at perm again), and
+// status[0] gets 8 if a column index is negative and 16 if the entry count
+// jd_ptr[max_len] is.
+__global__ __launch_bounds__(kBlock) void k_jds_check(
+    int32_t rows, int32_t max_len, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ jd_ptr, const int32_t *__restrict__ jd_col,
+    int32_t *__restrict__ iperm, int32_t *__restrict__ status)
 {
-#pragma clang fp contract(off)
-    const int32_t p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= rows)
-        return;
-    const int32_t n = min(nzcnt[p], max_len);
-    double s = 0.0;
-    for (int32_t j = 0; j < n; ++j) {
-        const int32_t k = jd_ptr[j] + p;
-        if (k < 0 || k >= nnz)
-            break;
-        const double prod = jd_val[k] * x[jd_col[k]];
-        s = s + prod;
-    }
-    const int32_t i = iperm[p];
-    if (i >= 0 && i < rows)
-        y[i] = s;
-}
-
-__global__ __launch_bounds__(kBlock) void k_invert_perm(
-    int32_t rows, const int32_t *__restrict__ perm, int32_t *__restrict__ iperm)
-{
-    const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < rows) {
+    const int32_t nnz = jd_ptr[max_len];
+    int32_t flags = (nnz < 0) ? 16 : 0;
+    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t i = tid; i < rows; i += stride) {
         const int32_t q = perm[i];
         if (q >= 0 && q < rows)
-            iperm[q] = i;
+            iperm[q] = (int32_t)i;
     }
+    if (jd_col) {
+        int32_t any = 0;   // the sign bit of any index
+        int64_t k = tid;
+        for (; k + 3 * stride < nnz; k += 4 * stride)
+            any |= jd_col[k] | jd_col[k + stride] | jd_col[k + 2 * stride] |
+                   jd_col[k + 3 * stride];
+        for (; k < nnz; k += stride)
+            any |= jd_col[k];
+        flags |= (any < 0) ? 8 : 0;
+    }
+    flags = lane_group_or<64>(flags);
+    if (flags && (threadIdx.x & 63) == 0)
+        atomicOr(&status[0], flags);
+}
+
+// Thread p handles the row at JDS position p: diagonal j holds its j-th
+// entry at jd_ptr[j] + p, so consecutive threads read consecutive entries.
+// Each sum is taken in diagonal order without contraction.  The loads of
+// kJdsAhead diagonals are in flight together: rows differ little along a
+// wavefront, and one thread per row leaves few wavefronts to hide a chain of
+// a load and a gather per diagonal (5,000 rows of 2 to 100 entries: the call
+// 52 us with one, 44.6 with eight).  Large matrices are bound by the gathers
+// (200k rows of 5 to 60 entries, 6.5 M gathers: 47 us at any depth).  A
+// wavefront's part of a diagonal starts anywhere in a cache line, so the loads
+// are ordinary ones: non-temporal, each line was fetched twice (65 us).
+// Entries outside [0, nnz) and diagonals past max_len are never touched,
+// whatever the arrays hold; a position whose original row is unknown (perm
+// not a permutation) is not stored.  Nothing is stored if k_jds_check found
+// the arrays at fault; workgroup 0 hands what it found to the host.
+constexpr int kJdsAhead = 8;
+__global__ __launch_bounds__(kBlock) void k_spmv_jds(
+    int32_t rows, int32_t max_len, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ iperm, const int32_t *__restrict__ nzcnt,
+    const int32_t *__restrict__ jd_ptr, const int32_t *__restrict__ jd_col,
+    const double *__restrict__ jd_val, const double *__restrict__ x,
+    double *__restrict__ y, const int32_t *__restrict__ status, int32_t *host_status)
+{
+#pragma clang fp contract(off)
+    typedef const __attribute__((address_space(4))) int32_t *cptr;
+    const int32_t fault = status[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *host_status = fault;
+    if (fault)
+        return;
+    const int32_t p = blockIdx.x * kBlock + threadIdx.x;
+    const int32_t nnz = ((cptr)jd_ptr)[max_len];
+    const int32_t n = (p < rows) ? min(nzcnt[p], max_len) : 0;
+    const int32_t nmax = __builtin_amdgcn_readfirstlane(lane_group_max<64>(n));
+    double s = 0.0;
+    bool on = true;
+    for (int32_t j0 = 0; j0 < nmax; j0 += kJdsAhead) {
+        int32_t k[kJdsAhead], c[kJdsAhead];
+        bool ok[kJdsAhead];
+        double v[kJdsAhead];
+#pragma unroll
+        for (int u = 0; u < kJdsAhead; ++u) {
+            const int32_t j = j0 + u;
+            const uint32_t first = (uint32_t)((cptr)jd_ptr)[min(j, max_len)];
+            k[u] = (int32_t)(first + (uint32_t)p);
+            on = on && (j >= n || (k[u] >= 0 && k[u] < nnz));
+            ok[u] = on && j < n;
+        }
+#pragma unroll
+        for (int u = 0; u < kJdsAhead; ++u) {
+            v[u] = ok[u] ? gld(jd_val + k[u]) : 0.0;
+            c[u] = ok[u] ? gld(jd_col + k[u]) : 0;
+        }
+        double xv[kJdsAhead];
+#pragma unroll
+        for (int u = 0; u < kJdsAhead; ++u)
+            xv[u] = ok[u] ? gld(x + c[u]) : 0.0;
+#pragma unroll
+        for (int u = 0; u < kJdsAhead; ++u) {
+            const double prod = v[u] * xv[u];
+            const double t = s + prod;
+            s = ok[u] ? t : s;
+        }
+    }
+    if (p >= rows)
+        return;
+    const int32_t i = iperm[p];
+    if (i >= 0 && i < rows && perm[i] == p)
+        y[i] = s;
 }
 
 // ---------------------------------------------------------- batched CG
@@ -2616,17 +2701,23 @@ __global__ __launch_bounds__(kBlock) void k_cgb_step(const CgSeg *__restrict__ s
 
 // ---------------------------------------------------------------- analysis
 
+// status (zeroed before): [0] faults found, [1] largest column + 1, [2] longest
+// row.
 __global__ __launch_bounds__(kBlock) void k_validate(
     int32_t rows, const int32_t *__restrict__ rp, int64_t nnz,
     const int32_t *__restrict__ col, int32_t cols_given,
     int32_t *__restrict__ status)
 {
-    int32_t flags = 0, mx = -1;
+    int32_t flags = 0, mx = 0, len = 0;
     const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = tid; i < rows; i += stride)
+    for (int64_t i = tid; i < rows; i += stride) {
+        const int32_t n = rp[i + 1] - rp[i];
         if (rp[i + 1] < rp[i])
             flags |= 2;
+        else
+            len = max(len, n);
+    }
     if (tid == 0) {
         if (rp[0] != 0)
             flags |= 1;
@@ -2637,14 +2728,33 @@ __global__ __launch_bounds__(kBlock) void k_validate(
         const int32_t c = col[k];
         if (c < 0 || (cols_given >= 0 && c >= cols_given))
             flags |= 8;
-        mx = max(mx, c);
+        mx = max(mx, (int32_t)min((uint32_t)c + 1u, (uint32_t)INT_MAX));
     }
+    // one update per workgroup, and none where the maximum is there already:
+    // an update of one word takes some 12 ns, so one of each wavefront of
+    // 4096 workgroups took 190 us whatever the matrix
+    __shared__ int32_t fl[kWaves], top[kWaves], most[kWaves];
     flags = lane_group_or<64>(flags);
     mx = lane_group_max<64>(mx);
+    len = lane_group_max<64>(len);
     if ((threadIdx.x & 63) == 0) {
+        fl[threadIdx.x >> 6] = flags;
+        top[threadIdx.x >> 6] = mx;
+        most[threadIdx.x >> 6] = len;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kWaves; ++i) {
+            flags |= fl[i];
+            mx = max(mx, top[i]);
+            len = max(len, most[i]);
+        }
         if (flags)
             atomicOr(&status[0], flags);
-        atomicMax(&status[1], mx);
+        if (mx > __hip_atomic_load(&status[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&status[1], mx);
+        if (len > __hip_atomic_load(&status[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&status[2], len);
     }
 }
 
@@ -3150,7 +3260,7 @@ void launch_validate(int32_t rows, const int32_t *rp, int64_t nnz,
                      hipStream_t s)
 {
     const int64_t work = nnz > rows ? nnz : (int64_t)rows + 1;
-    hipLaunchKernelGGL(k_validate, dim3(grid_for(work, kBlock * 4, 4096)),
+    hipLaunchKernelGGL(k_validate, dim3(grid_for(work, kBlock * 4, 2048)),
                        dim3(kBlock), 0, s, rows, rp, nnz, col, cols_given,
                        status);
     check_launch("k_validate");
@@ -3607,28 +3717,24 @@ void launch_bfs_step(const Tile *tiles, int32_t ntiles, int32_t grid,
     check_launch("k_bfs_step");
 }
 
-void launch_spmv_jds(int32_t rows, int32_t max_len, int32_t nnz,
-                     const int32_t *iperm, const int32_t *nzcnt,
-                     const int32_t *jd_ptr, const int32_t *jd_col,
-                     const double *jd_val, const double *x, double *y,
-                     hipStream_t s)
+void launch_jds_check(int32_t rows, int32_t max_len, const int32_t *perm,
+                      const int32_t *jd_ptr, const int32_t *jd_col, int32_t *iperm,
+                      int32_t *status, hipStream_t s)
 {
-    if (rows <= 0)
-        return;
-    hipLaunchKernelGGL(k_spmv_jds, dim3(grid_for(rows, kBlock, INT_MAX)), dim3(kBlock),
-                       0, s, rows, max_len, nnz, iperm, nzcnt, jd_ptr, jd_col, jd_val,
-                       x, y);
-    check_launch("k_spmv_jds");
+    hipLaunchKernelGGL(k_jds_check, dim3(1024), dim3(kBlock), 0, s, rows, max_len, perm,
+                       jd_ptr, jd_col, iperm, status);
+    check_launch("k_jds_check");
 }
 
-void launch_invert_perm(int32_t rows, const int32_t *perm, int32_t *iperm,
-                        hipStream_t s)
+void launch_spmv_jds(int32_t rows, int32_t max_len, const int32_t *perm,
+                     const int32_t *iperm, const int32_t *nzcnt, const int32_t *jd_ptr,
+                     const int32_t *jd_col, const double *jd_val, const double *x, double *y,
+                     const int32_t *status, int32_t *host_status, hipStream_t s)
 {
-    if (rows <= 0)
-        return;
-    hipLaunchKernelGGL(k_invert_perm, dim3(grid_for(rows, kBlock, INT_MAX)), dim3(kBlock),
-                       0, s, rows, perm, iperm);
-    check_launch("k_invert_perm");
+    hipLaunchKernelGGL(k_spmv_jds, dim3(grid_for(rows, kBlock, INT_MAX)), dim3(kBlock),
+                       0, s, rows, max_len, perm, iperm, nzcnt, jd_ptr, jd_col, jd_val, x, y,
+                       status, host_status);
+    check_launch("k_spmv_jds");
 }
 
 void launch_count_cols(int64_t nnz, const int32_t *col, int32_t *deg, hipStream_t s)

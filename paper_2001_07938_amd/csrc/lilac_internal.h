@@ -522,14 +522,16 @@ void launch_permute_f32(int32_t n, const int32_t *newid, const float *in, float 
                         bool to, hipStream_t s);
 
 // Jagged Diagonal Storage product, every sum in diagonal order without
-// contraction (bitwise equal to the sequential definition).
-void launch_spmv_jds(int32_t rows, int32_t max_len, int32_t nnz,
-                     const int32_t *iperm, const int32_t *nzcnt,
-                     const int32_t *jd_ptr, const int32_t *jd_col,
-                     const double *jd_val, const double *x, double *y,
-                     hipStream_t s);
-void launch_invert_perm(int32_t rows, const int32_t *perm, int32_t *iperm,
-                        hipStream_t s);
+// contraction (bitwise equal to the sequential definition).  The check inverts
+// perm into iperm and sets bits of status[0] (0 before); the product stores
+// nothing if any is set and copies status[0] to host_status (pinned).
+void launch_jds_check(int32_t rows, int32_t max_len, const int32_t *perm,
+                      const int32_t *jd_ptr, const int32_t *jd_col, int32_t *iperm,
+                      int32_t *status, hipStream_t s);
+void launch_spmv_jds(int32_t rows, int32_t max_len, const int32_t *perm,
+                     const int32_t *iperm, const int32_t *nzcnt, const int32_t *jd_ptr,
+                     const int32_t *jd_col, const double *jd_val, const double *x, double *y,
+                     const int32_t *status, int32_t *host_status, hipStream_t s);
 void launch_sum_parts(const double *part, int32_t nparts, double *out,
                       hipStream_t s);
 void launch_sum_parts_f32(const double *part, int32_t nparts, float *out,

@@ -70,7 +70,10 @@ struct Context {
     double *dot_part = nullptr;     // kDotParts + 1 (result)
     double *dot_a = nullptr, *dot_b = nullptr;
     size_t dot_cap = 0;
-    int32_t *status = nullptr;      // 2 ints for validation
+    void *jds_buf = nullptr;        // inverse permutation of a JDS product
+    size_t jds_cap = 0;
+    int32_t *status = nullptr;      // 4 ints: validation, flags
+    int32_t *host_status = nullptr; // pinned, written by kernels
     int32_t *total = nullptr;       // 1 int for scans
     int occ[2] = {0, 0};            // tile-kernel workgroups per CU (f64, f32)
 };
@@ -138,7 +141,8 @@ static Context &init_ctx(int device)
     if (const char *b = std::getenv("LILAC_HBM_BUDGET"))
         c->budget = parse_bytes(b);
     g_ctx = c;
-    c->status = (int32_t *)dev_alloc(2 * sizeof(int32_t));
+    c->status = (int32_t *)dev_alloc(4 * sizeof(int32_t));
+    HIPC(hipHostMalloc((void **)&c->host_status, 64, hipHostMallocDefault));
     c->total = (int32_t *)dev_alloc(sizeof(int32_t));
     c->dot_part = (double *)dev_alloc((kDotParts + 1) * sizeof(double));
     if (!g_exit_registered) {
@@ -1082,10 +1086,9 @@ static void construct(CsrHandle &h, int cols_given, const int32_t *rp,
     launch_fill_i32(h.d_col + h.nnz, npad - h.nnz, 0, s);
     launch_fill_bytes_zero((char *)h.d_vals + h.nnz * vs, (npad - h.nnz) * vs, s);
     // validation + column count (one pass over row_ptr and col_idx)
-    launch_fill_i32(c.status, 1, 0, s);
-    launch_fill_i32(c.status + 1, 1, -1, s);
+    launch_fill_i32(c.status, 3, 0, s);
     launch_validate(h.rows, h.d_row_ptr, h.nnz, h.d_col, cols_given, c.status, s);
-    int32_t st[2] = {0, -1};
+    int32_t st[3] = {0, 0, 0};
     HIPC(hipMemcpyAsync(st, c.status, sizeof(st), hipMemcpyDeviceToHost, s));
     HIPC(hipStreamSynchronize(s));
     if (st[0]) {
@@ -1096,8 +1099,8 @@ static void construct(CsrHandle &h, int cols_given, const int32_t *rp,
         if (st[0] & 8) why += " column index out of range;";
         fail(LILAC_ERR_CSR, "invalid CSR:" + why);
     }
-    h.cols = cols_given >= 0 ? cols_given : st[1] + 1;
-    h.max_len = jds_max_len(h, c.total, s);
+    h.cols = cols_given >= 0 ? cols_given : st[1];
+    h.max_len = st[2];
     h.line_ratio = -1.0;  // measured again for the new structure
     Plan tuned;
     if (tune_cache_lookup(h, tuned))
@@ -1407,6 +1410,9 @@ static int marshal_mode()
         return 2;
     return 0;
 }
+
+// Largest inverse permutation of a JDS product kept between calls (bytes).
+constexpr size_t kJdsKeep = (size_t)64 << 20;
 
 static void *grow_buffer(void *&buf, size_t &cap, size_t bytes)
 {
@@ -2521,11 +2527,12 @@ int lilac_finalize(void)
         Context &c = *g_ctx;
         dev_free(c.x_buf);
         dev_free(c.y_buf);
+        dev_free(c.jds_buf);
         dev_free(c.dot_a);
         dev_free(c.dot_b);
-        c.x_buf = c.y_buf = nullptr;
+        c.x_buf = c.y_buf = c.jds_buf = nullptr;
         c.dot_a = c.dot_b = nullptr;
-        c.x_cap = c.y_cap = c.dot_cap = 0;
+        c.x_cap = c.y_cap = c.jds_cap = c.dot_cap = 0;
     });
 }
 
@@ -3055,62 +3062,77 @@ int lilac_spmv_jds(int rows, int max_len, const int *perm, const int *nzcnt,
             fail(LILAC_ERR_ARG, "NULL argument");
         Context &c = ctx();
         hipStream_t s = c.stream;
-        const bool any_dev = is_device_ptr(perm) || is_device_ptr(nzcnt) ||
-                             is_device_ptr(jd_ptr) || is_device_ptr(jd_col) ||
-                             is_device_ptr(jd_val) || is_device_ptr(x) || is_device_ptr(y);
-        if (any_dev)
+        const bool perm_dev = is_device_ptr(perm), nz_dev = is_device_ptr(nzcnt);
+        const bool ptr_dev = is_device_ptr(jd_ptr), col_dev = is_device_ptr(jd_col);
+        const bool val_dev = is_device_ptr(jd_val), x_dev = is_device_ptr(x);
+        const bool y_dev = is_device_ptr(y);
+        if (perm_dev || nz_dev || ptr_dev || col_dev || val_dev || x_dev || y_dev)
             HIPC(hipDeviceSynchronize());
-        // jd_ptr[max_len] is the number of entries
+        // jd_ptr[max_len] is the number of entries (needed here only to copy
+        // host arrays; the kernels read it themselves)
         int32_t nnz = 0;
-        if (is_device_ptr(jd_ptr)) {
-            HIPC(hipMemcpyAsync(&nnz, jd_ptr + max_len, 4, hipMemcpyDeviceToHost, s));
-            HIPC(hipStreamSynchronize(s));
-        } else {
+        if (!ptr_dev)
             nnz = jd_ptr[max_len];
-        }
+        else if (!col_dev || !val_dev || !x_dev)
+            HIPC(hipMemcpy(&nnz, jd_ptr + max_len, 4, hipMemcpyDeviceToHost));
         if (nnz < 0)
             fail(LILAC_ERR_ARG, "jd_ptr[max_len] < 0");
         // device copies of host arrays for this call (JDS is not cached)
         std::vector<void *> tmp;
-        auto dev = [&](const void *p, size_t bytes) -> const void * {
-            if (!p || is_device_ptr(p))
+        auto dev = [&](const void *p, bool on_device, size_t bytes) -> const void * {
+            if (!p || on_device)
                 return p;
             void *d = dev_alloc(bytes);
             tmp.push_back(d);
             HIPC(hipMemcpyAsync(d, p, bytes, hipMemcpyHostToDevice, s));
             return d;
         };
-        int32_t cols = 0;
         try {
-            const int32_t *d_perm = (const int32_t *)dev(perm, (size_t)rows * 4);
-            const int32_t *d_nz = (const int32_t *)dev(nzcnt, (size_t)rows * 4);
-            const int32_t *d_ptr = (const int32_t *)dev(jd_ptr, (size_t)(max_len + 1) * 4);
-            const int32_t *d_col = (const int32_t *)dev(jd_col, (size_t)std::max(nnz, 1) * 4);
-            const double *d_val = (const double *)dev(jd_val, (size_t)std::max(nnz, 1) * 8);
-            // the columns bound the x that must be present
-            launch_fill_i32(c.status + 1, 1, -1, s);
-            launch_fill_i32(c.status, 1, 0, s);
-            launch_validate(0, c.total, nnz, d_col, -1, c.status, s);
-            int32_t st[2];
-            HIPC(hipMemcpyAsync(st, c.status, 8, hipMemcpyDeviceToHost, s));
-            HIPC(hipStreamSynchronize(s));
-            if (st[0] & 8)
-                fail(LILAC_ERR_CSR, "negative column index in JDS");
-            cols = st[1] + 1;
-            const double *d_x = (const double *)dev(x, (size_t)std::max(cols, 1) * 8);
-            int32_t *iperm = (int32_t *)dev_alloc((size_t)rows * 4);
-            tmp.push_back(iperm);
-            const bool y_dev = is_device_ptr(y);
+            const int32_t *d_perm = (const int32_t *)dev(perm, perm_dev, (size_t)rows * 4);
+            const int32_t *d_nz = (const int32_t *)dev(nzcnt, nz_dev, (size_t)rows * 4);
+            const int32_t *d_ptr =
+                (const int32_t *)dev(jd_ptr, ptr_dev, (size_t)(max_len + 1) * 4);
+            const int32_t *d_col =
+                (const int32_t *)dev(jd_col, col_dev, (size_t)std::max(nnz, 1) * 4);
+            const double *d_val =
+                (const double *)dev(jd_val, val_dev, (size_t)std::max(nnz, 1) * 8);
+            const double *d_x = x;
+            if (x && !x_dev) {
+                // the columns bound the x that must be present
+                launch_fill_i32(c.status, 3, 0, s);
+                launch_validate(0, c.total, nnz, d_col, -1, c.status, s);
+                int32_t st[2];
+                HIPC(hipMemcpyAsync(st, c.status, 8, hipMemcpyDeviceToHost, s));
+                HIPC(hipStreamSynchronize(s));
+                if (st[0] & 8)
+                    fail(LILAC_ERR_CSR, "negative column index in JDS");
+                d_x = (const double *)dev(x, false, (size_t)std::max(st[1], 1) * 8);
+            }
             double *d_y = y_dev ? y : (double *)dev_alloc((size_t)rows * 8);
             if (!y_dev)
                 tmp.push_back(d_y);
-            launch_fill_i32(iperm, rows, -1, s);
-            launch_invert_perm(rows, d_perm, iperm, s);
-            launch_spmv_jds(rows, max_len, nnz, iperm, d_nz, d_ptr, d_col, d_val, d_x,
-                            d_y, s);
-            if (!y_dev)
-                HIPC(hipMemcpyAsync(y, d_y, (size_t)rows * 8, hipMemcpyDeviceToHost, s));
+            // a permutation of more than kJdsKeep bytes is not kept
+            int32_t *iperm;
+            if ((size_t)rows * 4 <= kJdsKeep) {
+                iperm = (int32_t *)grow_buffer(c.jds_buf, c.jds_cap, (size_t)rows * 4);
+            } else {
+                iperm = (int32_t *)dev_alloc((size_t)rows * 4);
+                tmp.push_back(iperm);
+            }
+            launch_fill_i32(c.status, 1, 0, s);
+            launch_jds_check(rows, max_len, d_perm, d_ptr, d_col, iperm, c.status, s);
+            launch_spmv_jds(rows, max_len, d_perm, iperm, d_nz, d_ptr, d_col, d_val, d_x, d_y,
+                            c.status, c.host_status, s);
             HIPC(hipStreamSynchronize(s));
+            const int32_t fault = *(volatile int32_t *)c.host_status;
+            if (fault & 16)
+                fail(LILAC_ERR_ARG, "jd_ptr[max_len] < 0");
+            if (fault)
+                fail(LILAC_ERR_CSR, "negative column index in JDS");
+            if (!y_dev) {
+                HIPC(hipMemcpyAsync(y, d_y, (size_t)rows * 8, hipMemcpyDeviceToHost, s));
+                HIPC(hipStreamSynchronize(s));
+            }
         } catch (...) {
             (void)hipStreamSynchronize(s);
             for (void *d : tmp)
