@@ -747,13 +747,15 @@ __device__ __forceinline__ void panel_block(const PanelDesc &pd, int32_t b,
 // its bytes; 60.5 us with one panel copied instead of eight, 62.6 without the
 // scan).  Three pairs of columns in flight: two and four took 1% longer, six
 // 5% (registers).
-template <typename V, bool DOT>
+// PART: panel group `grp` only, its sums to part[grp * rows + row]; else all.
+template <typename V, bool DOT, bool PART = false>
 __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
                                            const V *__restrict__ x,
                                            V *__restrict__ y, const Epi &epi,
                                            const V *__restrict__ w,
                                            double *__restrict__ dot_part,
-                                           unsigned char *smem)
+                                           unsigned char *smem, int32_t grp = 0,
+                                           double *__restrict__ part = nullptr)
 {
     constexpr int B = kLanePairs;
     constexpr int VV = 16 / sizeof(V);
@@ -770,12 +772,19 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
         acc[i] = 0.0;
     if (threadIdx.x == 0)
         xs[pd.pw] = (V)0;
+    // this lane's rows: mine, mine + 64, ... below end
+    const int32_t mine = wv * pd.rw + lane, end = min((wv + 1) * pd.rw, nr);
     double wrow = 0.0;
-    if (DOT && (int32_t)threadIdx.x < nr)
-        wrow = (double)gld(w + r0 + threadIdx.x);
+    if (DOT && mine < end)
+        wrow = (double)gld(w + r0 + mine);
     const bool aligned = (((uintptr_t)x) & 15) == 0;
+    // (groups are only formed where there are few blocks: no rotation then)
     const int32_t rot =
         (pd.np > 1 && pd.nblk >= kPanelRotateBlocks) ? (int32_t)((b >> 3) % pd.np) : 0;
+    const int32_t p0 = PART ? grp * pd.pg : 0;
+    const int32_t p1 = PART ? min(p0 + pd.pg, pd.np) : pd.np;
+    constexpr int T = kPanelMaxRb / kPanelThreads;   // rows of a lane
+    double tot[T] = {0.0, 0.0, 0.0, 0.0};            // sums of the groups so far
     auto panel_at = [&](int32_t i) { return (i + rot < pd.np) ? i + rot : i + rot - pd.np; };
     // a run: its first column, its pairs, whether a single column follows
     struct Run {
@@ -811,15 +820,15 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
         nstart = gld(pd.start + ((int64_t)(b * pd.np + p) * kPanelWaves + wv) * 64 + lane);
     };
     Run cur{0, 0, 0}, next{0, 0, 0};
-    if (pd.np > 0) {
-        next = run_of(panel_at(0));
-        request_first(next, panel_at(0));
+    if (p0 < p1) {
+        next = run_of(panel_at(p0));
+        request_first(next, panel_at(p0));
     }
-    for (int32_t pk = 0; pk < pd.np; ++pk) {
+    for (int32_t pk = p0; pk < p1; ++pk) {
         const int32_t c0 = panel_at(pk) * pd.pw;
         const int32_t width = min(pd.pw, pd.cols - c0);
         cur = next;
-        const bool more = pk + 1 < pd.np;
+        const bool more = pk + 1 < p1;
         const int32_t pn = more ? panel_at(pk + 1) : 0;
         if (more)
             next = run_of(pn);
@@ -889,19 +898,37 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
         // rows that go on in the next lane, and the run's last row: rows ascend
         // along the lanes, the last lane of a row adds what they hold of it
         if (cur.pairs + cur.odd > 0) {
-            const double part = seg_scan64<true>(sum, row);
+            const double left = seg_scan64<true>(sum, row);
             if (next_lane_key(row) != row)
-                lds_add_f64(&acc[row], part);
+                lds_add_f64(&acc[row], left);
+        }
+        // a group ends: its sums of the wavefront's own rows (no other adds to
+        // them) move to the totals
+        if (!PART && pd.ng > 1 && ((pk + 1) % pd.pg == 0 || !more)) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int32_t i = mine + t * 64;
+                if (i < end) {
+                    tot[t] += acc[i];
+                    acc[i] = 0.0;
+                }
+            }
         }
     }
-    __syncthreads();
     double dacc = 0.0;
-    for (int32_t i = threadIdx.x; i < nr; i += kPanelThreads) {
-        const V out = epilogue<V>(acc[i], epi);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int32_t i = mine + t * 64;
+        if (i >= end)
+            break;
+        if (PART) {
+            gst(part + (int64_t)grp * pd.rows + r0 + i, acc[i]);
+            continue;
+        }
+        const V out = epilogue<V>(pd.ng > 1 ? tot[t] : acc[i], epi);
         gst(y + r0 + i, out);
         if (DOT)
-            dacc = fma(i == (int32_t)threadIdx.x ? wrow : (double)gld(w + r0 + i),
-                       (double)out, dacc);
+            dacc = fma(t == 0 ? wrow : (double)gld(w + r0 + i), (double)out, dacc);
     }
     if (DOT) {
         const double tot = block_sum<kPanelWaves>(dacc, (double *)xs);
@@ -917,6 +944,53 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_lanes(
 {
     extern __shared__ __align__(16) unsigned char smem[];
     lane_block<V, DOT>(pd, blockIdx.x, x, y, epi, w, dot_part, smem);
+}
+
+// One workgroup for each row block and group of panels: a matrix of few row
+// blocks would leave most compute units idle (200k rows: 49 blocks).
+template <typename V>
+__global__ __launch_bounds__(kPanelThreads) void k_spmv_lane_groups(
+    PanelDesc pd, const V *__restrict__ x, double *__restrict__ part)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Epi epi{EPI_NONE, 0, 0.0, 0.0};
+    const int32_t grp = blockIdx.x / pd.nblk;
+    lane_block<V, false, true>(pd, blockIdx.x - grp * pd.nblk, x, nullptr, epi, nullptr,
+                               nullptr, smem, grp, part);
+}
+
+// The groups' sums of a row block added up in order, with the epilogue and the
+// fused dot of lane_block (the same additions in the same order).
+template <typename V, bool DOT>
+__global__ __launch_bounds__(kPanelThreads) void k_lane_total(
+    PanelDesc pd, const double *__restrict__ part, V *__restrict__ y, Epi epi,
+    const V *__restrict__ w, double *__restrict__ dot_part)
+{
+    __shared__ double lds[kPanelWaves];
+    // with the dot a row block each, every lane the rows lane_block gives it
+    // (its partial's additions in the same order); else a row for each thread
+    const int32_t b = blockIdx.x;
+    const int32_t wv = threadIdx.x >> 6;
+    const int64_t r0 = (int64_t)b * (DOT ? pd.rb : kPanelThreads);
+    const int32_t nr = (int32_t)min((int64_t)(DOT ? pd.rb : kPanelThreads), pd.rows - r0);
+    const int32_t rw = DOT ? pd.rw : 64;
+    const int32_t end = min((wv + 1) * rw, nr);
+    double dacc = 0.0;
+    for (int32_t i = wv * rw + (threadIdx.x & 63); i < end; i += 64) {
+        double sum = 0.0;
+#pragma unroll 4
+        for (int32_t g = 0; g < pd.ng; ++g)
+            sum += gld(part + (int64_t)g * pd.rows + r0 + i);
+        const V out = epilogue<V>(sum, epi);
+        gst(y + r0 + i, out);
+        if (DOT)
+            dacc = fma((double)gld(w + r0 + i), (double)out, dacc);
+    }
+    if (DOT) {
+        const double tot = block_sum<kPanelWaves>(dacc, lds);
+        if (threadIdx.x == 0)
+            dot_part[b] = tot;
+    }
 }
 
 template <typename V, bool DOT>
@@ -3437,6 +3511,34 @@ void launch_spmv_panels(lilac_dtype dt, const PanelDesc &pd, const void *x,
     check_launch("k_spmv_panels");
 }
 
+void launch_spmv_lane_groups(lilac_dtype dt, const PanelDesc &pd, const void *x, void *y,
+                             const Epi &epi, const void *w, double *dot_part, double *part,
+                             hipStream_t s)
+{
+    if (pd.nblk <= 0)
+        return;
+    dim3 g(pd.nblk * pd.ng), b(kPanelThreads);
+    dim3 t(dot_part ? pd.nblk : grid_for(pd.rows, kPanelThreads, INT_MAX));
+    if (dt == LILAC_F64) {
+        hipLaunchKernelGGL(k_spmv_lane_groups<double>, g, b, kPanelLds, s, pd,
+                           (const double *)x, part);
+        if (dot_part)
+            hipLaunchKernelGGL((k_lane_total<double, true>), t, b, 0, s, pd, part, (double *)y,
+                               epi, (const double *)w, dot_part);
+        else
+            hipLaunchKernelGGL((k_lane_total<double, false>), t, b, 0, s, pd, part,
+                               (double *)y, epi, (const double *)w, dot_part);
+    } else {
+        if (dot_part)
+            fail(LILAC_ERR_UNSUPPORTED, "fused dot is only provided for float64");
+        hipLaunchKernelGGL(k_spmv_lane_groups<float>, g, b, kPanelLds, s, pd,
+                           (const float *)x, part);
+        hipLaunchKernelGGL((k_lane_total<float, false>), t, b, 0, s, pd, part, (float *)y, epi,
+                           (const float *)w, dot_part);
+    }
+    check_launch("k_spmv_lane_groups");
+}
+
 void launch_spmv_panels_grouped(lilac_dtype dt, const PanelDesc *descs,
                                 const PanelIO *io, const int32_t *prefix,
                                 int32_t nmat, int32_t nblocks, hipStream_t s)
@@ -3629,6 +3731,10 @@ void panels_prepare()
     HIPC(hipFuncSetAttribute((const void *)k_spmv_panels<double, false>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_panels<float, false>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<double>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<float>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_lanes<double, true>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));

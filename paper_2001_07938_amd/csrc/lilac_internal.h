@@ -110,6 +110,9 @@ struct PanelDesc {
     const uint16_t *words;
     const uint8_t *start;
     const int32_t *col0;
+    // the panels in ng groups of pg: a row's sum is the groups' sums added in
+    // order, whether one workgroup forms them all or one each
+    int32_t ng, pg;
 };
 // Lane form of the column-panel layout.  A run is what one wavefront holds of
 // one (row block, panel): the entries of its rows in order, with a filler for
@@ -392,6 +395,12 @@ void launch_spmv_tiles(lilac_dtype dt, const Tile *tiles, int32_t ntiles,
 void launch_spmv_panels(lilac_dtype dt, const PanelDesc &pd, const void *x,
                         void *y, const Epi &epi, const void *w, double *dot_part,
                         hipStream_t s);
+// The lane form with a workgroup for each row block and group of panels: part
+// (pd.ng * pd.rows doubles) receives the groups' sums, a second kernel adds
+// them up.  Same results as launch_spmv_panels.
+void launch_spmv_lane_groups(lilac_dtype dt, const PanelDesc &pd, const void *x, void *y,
+                             const Epi &epi, const void *w, double *dot_part, double *part,
+                             hipStream_t s);
 void launch_panel_count(const PanelDesc &pd, const int32_t *rp,
                         const int32_t *col, int32_t *cnt, hipStream_t s);
 void launch_panel_scatter(lilac_dtype dt, const PanelDesc &pd, const int32_t *rp,
@@ -583,8 +592,10 @@ CsrHandle *create_handle_adopt(int rows, int cols, int64_t nnz, int32_t *rp,
 void destroy_handle(CsrHandle *h);
 MatDesc make_desc(const CsrHandle &h, const void *x, void *y, const void *w,
                   double *chunk_part);
+// part: space for the groups of a split column-panel product (see
+// split_bytes), or null to take the stream's own.
 void spmv_enqueue(const CsrHandle &h, const void *x, void *y, const Epi &epi,
-                  const void *w, bool dot, hipStream_t s);
+                  const void *w, bool dot, hipStream_t s, double *part = nullptr);
 void run_cg(CsrHandle &h, const double *b, double *x, int iters,
             unsigned flags, hipStream_t s, double *rho_out, int *iters_done);
 // Allocates the handle's CG state now (otherwise done on the first solve).

@@ -76,6 +76,14 @@ struct Context {
     int32_t *host_status = nullptr; // pinned, written by kernels
     int32_t *total = nullptr;       // 1 int for scans
     int occ[2] = {0, 0};            // tile-kernel workgroups per CU (f64, f32)
+    // working memory of a stream: kernels of one stream run in order, so any
+    // of its calls may use it (see stream_space)
+    struct Space {
+        hipStream_t s;
+        void *p;
+        size_t cap;
+    };
+    std::vector<Space> spaces;
 };
 
 static std::recursive_mutex g_mu;
@@ -169,9 +177,81 @@ Account *&thread_account()
     return a;
 }
 
+// Gives the streams' working memory back (waits for the device).
+static bool release_spaces()
+{
+    Context &c = *g_ctx;
+    if (c.spaces.empty())
+        return false;
+    std::vector<Context::Space> old;
+    old.swap(c.spaces);
+    for (const Context::Space &sp : old)
+        dev_free(sp.p);
+    return true;
+}
+
+// The stream's working memory, at least `bytes`, or null: while the stream is
+// being captured (a replay may run on any stream, and nothing may be allocated),
+// for the per-thread stream (one handle, several streams), for a thread that
+// allocates on an account, past kSpaces streams, or when the device is full.
+// At most kSpaces buffers of kSpaceMax bytes are held, until lilac_finalize or
+// until an allocation would fail without them.  Called under the library lock.
+constexpr size_t kSpaces = 8;
+constexpr size_t kSpaceMax = (size_t)16 << 20;
+
+static void *stream_space(hipStream_t s, size_t bytes)
+{
+    Context &c = *g_ctx;
+    if (bytes > kSpaceMax || s == hipStreamPerThread || thread_account())
+        return nullptr;
+    if (s) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        if (st != hipStreamCaptureStatusNone)
+            return nullptr;
+    }
+    for (Context::Space &sp : c.spaces)
+        if (sp.s == s) {
+            if (sp.cap >= bytes)
+                return sp.p;
+            dev_free(sp.p);   // waits for the kernels that use it
+            sp = c.spaces.back();
+            c.spaces.pop_back();
+            break;
+        }
+    if (c.spaces.size() >= kSpaces)
+        return nullptr;
+    try {
+        // whole MiB, so that a stream's buffer seldom has to grow
+        const size_t cap = (bytes + (1u << 20) - 1) & ~(size_t)((1u << 20) - 1);
+        c.spaces.push_back(Context::Space{s, dev_alloc(cap), cap});
+    } catch (const Error &) {
+        return nullptr;
+    }
+    return c.spaces.back().p;
+}
+
+static void *dev_alloc_once(size_t bytes);
+
 void *dev_alloc(size_t bytes)
 {
     std::lock_guard<std::recursive_mutex> lk(g_mu);
+    if (g_ctx->spaces.empty())
+        return dev_alloc_once(bytes);
+    try {
+        return dev_alloc_once(bytes);
+    } catch (const Error &) {
+        if (!release_spaces())
+            throw;
+    }
+    return dev_alloc_once(bytes);
+}
+
+static void *dev_alloc_once(size_t bytes)
+{
     Context &c = *g_ctx;
     if (bytes == 0)
         bytes = 256;
@@ -522,6 +602,12 @@ static bool build_lanes(CsrHandle &h, hipStream_t s)
     pd.np = (int32_t)np;
     pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
     pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
+    // groups of panels: as many as give every CU a workgroup, one fits on each
+    pd.ng = std::max(1, std::min(pd.np, device_cu_count() / pd.nblk));
+    if (pd.nblk >= kPanelRotateBlocks)
+        pd.ng = 1;
+    pd.pg = (pd.np + pd.ng - 1) / pd.ng;
+    pd.ng = (pd.np + pd.pg - 1) / pd.pg;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
     const int64_t nrun = (int64_t)pd.nblk * pd.np * kPanelWaves;
     int32_t *pos = nullptr;
@@ -1183,6 +1269,8 @@ struct CgState {
     int64_t n = 0;
     double *r = nullptr, *p = nullptr, *sv = nullptr, *w = nullptr, *part = nullptr;
     CgScalars *sc = nullptr;
+    double *split = nullptr;    // groups' sums of a split product
+    size_t split_cap = 0;
     struct G {
         const double *b;
         double *x;
@@ -1252,6 +1340,7 @@ void destroy_handle(CsrHandle *h)
         dev_free(h->cg->w);
         dev_free(h->cg->part);
         dev_free(h->cg->sc);
+        dev_free(h->cg->split);
         delete h->cg;
     }
     if (h->pr) {
@@ -1331,12 +1420,29 @@ MatDesc make_desc(const CsrHandle &h, const void *x, void *y,
     return d;
 }
 
+// Bytes of the groups' sums of a split column-panel product (0: not split).
+static size_t split_bytes(const CsrHandle &h)
+{
+    return h.use_panels && h.pan.col0 && h.pan.ng > 1 ? (size_t)h.pan.ng * h.rows * 8 : 0;
+}
+
 void spmv_enqueue(const CsrHandle &h, const void *x, void *y,
                          const Epi &epi, const void *w, bool dot,
-                         hipStream_t s)
+                         hipStream_t s, double *part)
 {
     if (h.rows == 0)
         return;
+    if (const size_t need = split_bytes(h)) {
+        // the space must not be given back between taking it and the launch
+        std::lock_guard<std::recursive_mutex> lk(g_mu);
+        if (!part)
+            part = (double *)stream_space(s, need);
+        if (part) {
+            launch_spmv_lane_groups(h.dt, h.pan, x, y, epi, w, dot ? h.d_dot_part : nullptr,
+                                    part, s);
+            return;
+        }
+    }
     if (h.use_panels) {
         launch_spmv_panels(h.dt, h.pan, x, y, epi, w, dot ? h.d_dot_part : nullptr, s);
         return;
@@ -1606,14 +1712,14 @@ void handle_cg_prepare(CsrHandle &h) { cg_prepare(h); }
 // everything later launches read.
 static void cg_enqueue_state(const CsrHandle &h, const double *b, double *x, int iters,
                              double *r, double *p, double *sv, double *w, double *part,
-                             CgScalars *sc, hipStream_t s)
+                             CgScalars *sc, hipStream_t s, double *split = nullptr)
 {
     const int64_t n = h.rows;
     const int32_t np = blas1_parts(n);
     const int32_t ndot = h.grid + h.fin_blocks;
     launch_cg_init(n, b, x, r, p, sv, part, np, sc, s);
     for (int it = 0; it < iters; ++it) {
-        spmv_enqueue(h, r, w, epi_none(), r, true, s);
+        spmv_enqueue(h, r, w, epi_none(), r, true, s, split);
         launch_cg_step(n, sc, w, p, sv, x, r, h.d_dot_part, ndot, part, np, it, s);
     }
     launch_cg_final(sc, part, np, iters & 1, s);
@@ -1623,7 +1729,7 @@ static void cg_enqueue(const CsrHandle &h, const double *b, double *x,
                        int iters, hipStream_t s)
 {
     const CgState &st = *h.cg;
-    cg_enqueue_state(h, b, x, iters, st.r, st.p, st.sv, st.w, st.part, st.sc, s);
+    cg_enqueue_state(h, b, x, iters, st.r, st.p, st.sv, st.w, st.part, st.sc, s, st.split);
 }
 
 // ------------------------------------------------ CG without allocation
@@ -1714,6 +1820,20 @@ void run_cg(CsrHandle &h, const double *b, double *x, int iters,
         return;
     }
     cg_prepare(h);
+    // a solve owns the space of its split products: its graph keeps the address
+    const size_t need = thread_account() ? 0 : split_bytes(h);
+    if (need > h.cg->split_cap) {
+        drop_graphs(h);
+        dev_free_reset(h.cg->split);
+        h.cg->split_cap = 0;
+        try {
+            h.cg->split = (double *)dev_alloc(need);
+            h.cg->split_cap = need;
+        } catch (const Error &e) {
+            if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+                throw;   // without it the products are not split
+        }
+    }
     if (flags & LILAC_CG_GRAPH) {
         CgState &st = *h.cg;
         CgState::G *hit = nullptr;
@@ -2524,6 +2644,7 @@ int lilac_finalize(void)
         marshal_reset();
         release_all_raw();
         release_group_plans();
+        (void)release_spaces();
         Context &c = *g_ctx;
         dev_free(c.x_buf);
         dev_free(c.y_buf);
