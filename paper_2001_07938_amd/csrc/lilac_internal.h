@@ -262,6 +262,7 @@ struct CsrHandle {
     // distinct 128-byte lines of x per non-zero in sampled groups of 64
     // rows (near 1: scattered columns; -1: not measured)
     double line_ratio = -1.0;
+    double line_group = 0.0;     // distinct lines per sampled group
     // column-panel layout (when use_panels)
     bool use_panels = false;
     PanelDesc pan{};

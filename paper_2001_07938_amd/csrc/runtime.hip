@@ -511,9 +511,15 @@ static int64_t panel_count(const CsrHandle &h)
     return h.cols > 0 ? ((int64_t)h.cols + panel_cols(h) - 1) / panel_cols(h) : 0;
 }
 
-// Rows per block of the column-panel layout: enough blocks for every CU,
-// but at least as many rows as make up the bytes of one copy of x (each
-// block copies all of x into LDS once), and at most kPanelMaxRb.
+// Rows per block of the column-panel layout: enough blocks for every CU; but
+// where such a block's entries weigh less than one copy of x (each block copies
+// all of x into LDS once), as many rows as weigh kPanelCopies copies; at most
+// kPanelMaxRb.  Random rows of 5 to 60 entries, float64, one copy against two
+// and three: batch of 16,000-row matrices 326, 405 and 449 G entries/s, 60,000
+// rows 387, 441 and 484; one product of 30,000 rows 9.3, 10.9 and 11.8 us, of
+// 100,000 16.1, 15.4 and 15.4; 512-matrix batch 1056, 968 and 954 us.  Two
+// takes most of the batch's gain for half of the single product's loss.
+constexpr double kPanelCopies = 2.0;
 static int32_t panel_rows(const CsrHandle &h)
 {
     if (h.rows == 0)
@@ -522,13 +528,24 @@ static int32_t panel_rows(const CsrHandle &h)
     const double row_bytes = std::max(1.0, (double)h.nnz / h.rows * (vs + 4.0));
     const int64_t by_cu = ((int64_t)h.rows + device_cu_count() - 1) / device_cu_count();
     const int64_t by_x = (int64_t)std::ceil((double)h.cols * vs / row_bytes);
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPanelMaxRb, std::max(by_cu, by_x)));
+    const int64_t rb = by_cu >= by_x ? by_cu : (int64_t)(kPanelCopies * (double)by_x);
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPanelMaxRb, rb));
 }
 
 // A matrix is gather-heavy when its non-zeros touch nearly one distinct
 // cache line of x each (scattered columns): then the row-class tiles are
 // bound by the gathers, and copying x through LDS pays.
 constexpr double kGatherHeavy = 0.3;
+// So it is when 64 consecutive rows touch more lines than a CU's 32 KB cache
+// holds (256): they are then read again however often the rows share them.
+// Random rows of 5 to 60 entries, batch, column panels against the scan band:
+// 8000 columns float64 (500 lines) 247 against 153 G entries/s, 8000 float32
+// (250) 233 against 183, 4000 float64 (250) 147 against 163, 4000 float32
+// (125) 123 against 210.  Only where the copies of x cost at most twice the
+// matrix bytes, and where the rows do not suit the sliced form (16 a row, 8000
+// columns float64: 236 sliced, 211 panels).
+constexpr double kGatherLines = 240.0;
+constexpr double kGatherLinesStage = 2.0;
 // Smallest matrix given the column-panel or band layout automatically;
 // smaller ones stay on the row-class tiles (one grouped launch takes them
 // all in a batch).
@@ -547,18 +564,21 @@ static bool panels_eligible(const CsrHandle &h)
         return false;
     if (h.bin_off[NCLASS] - h.bin_off[C_W64 + 1] > 0)
         return false;  // rows longer than the wavefront class bound
-    if (h.line_ratio < kGatherHeavy)
+    const bool spread = h.line_ratio < kGatherHeavy;
+    if (spread && h.line_group < kGatherLines)
         return false;
     const double vs = (double)dtype_size(h.dt);
     const int32_t rb = panel_rows(h);
     const double nblk = std::ceil((double)h.rows / rb);
     const double stage = nblk * (double)h.cols * vs;
-    return stage <= 4.0 * (double)h.nnz * (vs + 4.0);
+    return stage <= (spread ? kGatherLinesStage : 4.0) * (double)h.nnz * (vs + 4.0);
 }
 
-// Distinct x lines per non-zero over up to 256 sampled groups of 64 rows.
-static double measure_line_ratio(const CsrHandle &h, hipStream_t s)
+// Distinct x lines per non-zero over up to 256 sampled groups of 64 rows, and
+// (line_group) per group.
+static double measure_line_ratio(CsrHandle &h, hipStream_t s)
 {
+    h.line_group = 0.0;
     if (h.rows == 0 || h.nnz == 0)
         return 0.0;
     const int32_t ngroups = (int32_t)std::min<int64_t>(256, ((int64_t)h.rows + 63) / 64);
@@ -579,6 +599,7 @@ static double measure_line_ratio(const CsrHandle &h, hipStream_t s)
         e += out[2 * g];
         l += out[2 * g + 1];
     }
+    h.line_group = (double)l / ngroups;
     return e > 0 ? (double)l / (double)e : 0.0;
 }
 
@@ -1121,11 +1142,13 @@ static void analyse(CsrHandle &h, hipStream_t s)
         build_hot(h, s);
         h.grid = h.hot.grid;   // one fused-dot partial per workgroup
         h.fin_blocks = 0;
-    } else if (want_panels && h.rows > 0 && h.nnz > 0) {
+    } else if (want_panels && h.rows > 0 && h.nnz > 0 &&
+               !(h.plan.layout == LAYOUT_AUTO && h.line_ratio < kGatherHeavy &&
+                 build_sell(h, s))) {
         build_panels(h, s);
         h.grid = h.pan.nblk;   // one fused-dot partial per row block
         h.fin_blocks = 0;
-    } else if (want_band && build_band(h, s, h.plan.layout == LAYOUT_AUTO)) {
+    } else if (h.use_band || (want_band && build_band(h, s, h.plan.layout == LAYOUT_AUTO))) {
         h.grid = h.band.nblk;  // one fused-dot partial per row block
         h.fin_blocks = 0;
     }
