@@ -2359,78 +2359,173 @@ __global__ __launch_bounds__(kBlock) void k_hot_scatter(
 
 // ------------------------------------------------------------------ BFS
 
-// Rows of a tile, W lanes per row, Boolean (or, and) product against the
-// current frontier {u : level[u] == depth}.
-template <int W>
-__device__ __forceinline__ void bfs_rows(const MatDesc &m, const Tile &t,
-                                         int32_t *__restrict__ level,
-                                         int32_t depth, int32_t *changed)
+// Start: level -1 but 0 at the source, the first two frontier bitmaps, last = 0.
+__global__ __launch_bounds__(kBlock) void k_bfs_init(int32_t rows, int32_t source,
+                                                     int32_t *__restrict__ level,
+                                                     uint32_t *__restrict__ bits, int32_t words,
+                                                     int32_t *__restrict__ last)
 {
-    constexpr int G = kBlock / W;
-    const int g = threadIdx.x / W;
-    const int lane = threadIdx.x % W;
-    for (int j = g; j < t.count; j += G) {
-        const int32_t row = tile_row(m, t, j);
-        if (level[row] != -1)
-            continue;  // uniform over the group
-        const int32_t k0 = m.row_ptr[row], k1 = m.row_ptr[row + 1];
-        int32_t hit = 0;
-        for (int32_t k = k0 + lane; k < k1 && !hit; k += W)
-            hit = (level[m.col[k]] == depth) ? 1 : 0;
-        hit = lane_group_or<W>(hit);
-        if (hit && lane == 0) {
-            level[row] = depth + 1;
-            *changed = 1;
-        }
-    }
+    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t i = tid; i < rows; i += stride)
+        level[i] = (i == source) ? 0 : -1;
+    for (int64_t i = tid; i < 2 * (int64_t)words; i += stride)
+        bits[i] = (i == (source >> 5)) ? 1u << (source & 31) : 0u;
+    if (tid == 0)
+        *last = 0;
 }
 
-__global__ __launch_bounds__(kBlock) void k_bfs_step(
-    const Tile *__restrict__ tiles, int32_t ntiles, MatDesc m,
-    int32_t *__restrict__ level, int32_t depth, int32_t *__restrict__ changed)
+// The frontier as a wavefront sees it: the bits of the vertices [base, base +
+// 32 * words), in LDS or (LDS = false) in device memory.
+template <bool LDS>
+struct Frontier {
+    const uint32_t *bits;
+    uint32_t base, count;
+    __device__ __forceinline__ bool has(int32_t v) const
+    {
+        const uint32_t i = (uint32_t)v - base;
+        if (LDS)
+            return i < count && ((bits[i >> 5] >> (i & 31)) & 1u);
+        return (gld(bits + (i >> 5)) >> (i & 31)) & 1u;
+    }
+};
+
+// Rows [0, n) of a wavefront's list (lane i holds row, first and last entry of
+// the i-th), W lanes per row: those with a column in the frontier get the
+// level.  U * W entries of a row are looked at together; a row that has a hit
+// is left.
+template <int W, int U, bool LDS>
+__device__ __forceinline__ bool bfs_rows(const int32_t *__restrict__ col, int32_t row,
+                                         int32_t k0, int32_t k1, int32_t n,
+                                         const Frontier<LDS> &f, int32_t *__restrict__ level,
+                                         uint32_t *__restrict__ next, int32_t depth)
 {
-    for (int32_t ti = blockIdx.x; ti < ntiles; ti += gridDim.x) {
-        const Tile t = tiles[ti];
-        switch (t.cls & kTileClassMask) {
-        case C_W1: bfs_rows<1>(m, t, level, depth, changed); break;
-        case C_W2: bfs_rows<2>(m, t, level, depth, changed); break;
-        case C_W4: bfs_rows<4>(m, t, level, depth, changed); break;
-        case C_W8: bfs_rows<8>(m, t, level, depth, changed); break;
-        case C_W16: bfs_rows<16>(m, t, level, depth, changed); break;
-        case C_W32: bfs_rows<32>(m, t, level, depth, changed); break;
-        case C_W64: bfs_rows<64>(m, t, level, depth, changed); break;
-        case C_WG: {
-            for (int j = 0; j < t.count; ++j) {
-                const int32_t row = tile_row(m, t, j);
-                if (level[row] != -1)
-                    continue;  // uniform over the workgroup
-                int32_t hit = 0;
-                for (int32_t k = m.row_ptr[row] + threadIdx.x; k < m.row_ptr[row + 1];
-                     k += kBlock)
-                    hit |= (level[m.col[k]] == depth) ? 1 : 0;
-                if (__syncthreads_or(hit) && threadIdx.x == 0) {
-                    level[row] = depth + 1;
-                    *changed = 1;
-                }
+    const int wl = threadIdx.x & 63;
+    const int q = wl / W, lane = wl % W;
+    constexpr uint64_t ones = W == 64 ? ~0ull : (1ull << (W & 63)) - 1ull;
+    const uint64_t group = ones << (q * W);
+    bool any = false;
+    for (int32_t i = 0; i < n; i += 64 / W) {
+        const int src = min(i + q, 63);
+        const int32_t r = __shfl(row, src, 64);
+        const int32_t a = __shfl(k0, src, 64);
+        const int32_t e = __shfl(k1, src, 64);   // by all lanes: a source must be on
+        const int32_t z = (i + q < n) ? e : a;
+        bool hit = false, on = a < z;
+        // the trips of the wavefront's longest row; a group stops at its own end
+        for (int32_t k = a + lane; __ballot(on); k += U * W) {
+            int32_t c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                c[u] = on ? gld(col + min(k + u * W, z - 1)) : 0;
+            if (on) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    hit = hit || f.has(c[u]);
             }
-            break;
+            const bool found = (__ballot(hit) & group) != 0;
+            on = on && !found && k - lane + U * W < z;
+            if (found)
+                hit = true;
         }
-        default: {  // one chunk of a split row
-            const int32_t c = t.first;
-            const int32_t row = m.c_row[c];
-            if (level[row] != -1)
-                break;
-            int32_t hit = 0;
-            for (int32_t k = m.c_k0[c] + threadIdx.x; k < m.c_k1[c]; k += kBlock)
-                hit |= (level[m.col[k]] == depth) ? 1 : 0;
-            if (__syncthreads_or(hit) && threadIdx.x == 0) {
-                level[row] = depth + 1;
-                *changed = 1;
-            }
-            break;
-        }
+        if (hit && lane == 0) {
+            level[r] = depth + 1;
+            atomicOr(&next[r >> 5], 1u << (r & 31));
+            any = true;
         }
     }
+    return any;
+}
+
+// One level: every row without a level that has a column in the frontier
+// (bitmap depth % 3) gets depth + 1 and its bit in bitmap (depth + 1) % 3; the
+// third one is cleared for the level after.  Nothing is done once a level
+// found nothing (last < depth), so several levels can be enqueued at once.
+// The columns are tested against the copy of the frontier in LDS (one pass for
+// each `lds_words` words of it): a bit per vertex instead of a gather from the
+// levels' 4 bytes, which bounds the search at one line per 4.7 clocks and CU.
+// A wavefront takes tile after tile; of a tile's rows it first looks up level
+// and bounds, 64 at a time, and keeps those that still matter.
+template <bool LDS>
+__global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
+    const Tile *__restrict__ tiles, int32_t ntiles, MatDesc m, int32_t *__restrict__ level,
+    int32_t depth, uint32_t *__restrict__ bits, int32_t words, int32_t lds_words,
+    int32_t *__restrict__ last)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint32_t *fb = (uint32_t *)smem;
+    if (__hip_atomic_load(last, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < depth)
+        return;
+    const uint32_t *cur = bits + (int64_t)(depth % 3) * words;
+    uint32_t *next = bits + (int64_t)((depth + 1) % 3) * words;
+    uint32_t *clear = bits + (int64_t)((depth + 2) % 3) * words;
+    const int64_t tid = (int64_t)blockIdx.x * kBfsThreads + threadIdx.x;
+    for (int64_t i = tid; i < words; i += (int64_t)gridDim.x * kBfsThreads)
+        clear[i] = 0u;
+    const int lane = threadIdx.x & 63;
+    const int32_t waves = (int32_t)gridDim.x * (kBfsThreads / 64);
+    // wavefronts of one workgroup take tiles far apart (longest come first)
+    const int32_t w0 = __builtin_amdgcn_readfirstlane(
+        (int32_t)(threadIdx.x >> 6) * (int32_t)gridDim.x + (int32_t)blockIdx.x);
+    bool any = false;
+    for (int32_t p0 = 0; p0 < words; p0 += lds_words) {
+        Frontier<LDS> f{cur, 0u, 0u};
+        if (LDS) {
+            const int32_t nw = min(lds_words, words - p0);   // a multiple of 4
+            if (p0 > 0)
+                __syncthreads();   // the part before is no longer read
+            for (int32_t i = threadIdx.x * 4; i < nw; i += kBfsThreads * 4)
+                *(i32x4 *)(fb + i) = gld((const i32x4 *)(cur + p0 + i));
+            __syncthreads();
+            f = Frontier<LDS>{fb, (uint32_t)p0 * 32u, (uint32_t)nw * 32u};
+        }
+        for (int32_t ti = w0; ti < ntiles; ti += waves) {
+            const i32x4 tv = *(const __attribute__((address_space(4))) i32x4 *)(tiles + ti);
+            const Tile t{tv.x, tv.y, tv.z, tv.w};
+            const int32_t cls = t.cls & kTileClassMask;
+            for (int32_t j0 = 0; j0 < t.count; j0 += 64) {
+                int32_t row = 0, k0 = 0, k1 = 0;
+                bool on = j0 + lane < t.count;
+                if (on && cls == C_SPLIT) {
+                    row = gld(m.c_row + t.first + j0 + lane);
+                    k0 = gld(m.c_k0 + t.first + j0 + lane);
+                    k1 = gld(m.c_k1 + t.first + j0 + lane);
+                } else if (on) {
+                    row = tile_row(m, t, j0 + lane);
+                    k0 = gld(m.row_ptr + row);
+                    k1 = gld(m.row_ptr + row + 1);
+                }
+                on = on && k0 < k1 && gld(level + row) == -1;
+                const uint64_t left = __ballot(on);
+                if (!left)
+                    continue;
+                const int32_t n = __popcll(left);
+                // rows that matter to the first n lanes (the others send to
+                // lanes that are not looked at)
+                const int to = (on ? lanes_below(left) : n + lanes_below(~left)) * 4;
+                row = __builtin_amdgcn_ds_permute(to, row);
+                k0 = __builtin_amdgcn_ds_permute(to, k0);
+                k1 = __builtin_amdgcn_ds_permute(to, k1);
+                switch (cls) {
+                case C_W1: any |= bfs_rows<1, 2, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                case C_W2: any |= bfs_rows<2, 2, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                case C_W4: any |= bfs_rows<4, 2, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                case C_W8: any |= bfs_rows<8, 4, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                case C_W16: any |= bfs_rows<16, 4, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                case C_W32: any |= bfs_rows<32, 4, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                default: any |= bfs_rows<64, 8, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+                }
+            }
+        }
+    }
+    if (__ballot(any) && lane == 0)
+        *last = depth + 1;
+}
+
+// The deepest level found so far, to the host.
+__global__ void k_bfs_report(const int32_t *__restrict__ last, int32_t *host)
+{
+    *host = *last;
 }
 
 // --------------------------------------------------- graph relabelling
@@ -3812,15 +3907,49 @@ void launch_panel_wptr(const PanelDesc &pd, const int32_t *ptr, int32_t *wptr,
     check_launch("k_panel_wptr");
 }
 
-void launch_bfs_step(const Tile *tiles, int32_t ntiles, int32_t grid,
-                     const MatDesc &m, int32_t *level, int32_t depth,
-                     int32_t *changed, hipStream_t s)
+void launch_bfs_init(int32_t rows, int32_t source, int32_t *level, uint32_t *bits,
+                     int32_t words, int32_t *last, hipStream_t s)
 {
+    hipLaunchKernelGGL(k_bfs_init, dim3(grid_for(rows, kBlock * 4, 2048)), dim3(kBlock), 0, s,
+                       rows, source, level, bits, words, last);
+    check_launch("k_bfs_init");
+}
+
+void launch_bfs_step(const Tile *tiles, int32_t ntiles, const MatDesc &m, int32_t *level,
+                     int32_t depth, uint32_t *bits, int32_t words, int32_t *last,
+                     hipStream_t s)
+{
+    static bool ready = false;
+    if (!ready) {
+        HIPC(hipFuncSetAttribute((const void *)k_bfs_step<true>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+        ready = true;
+    }
     if (ntiles <= 0)
         return;
-    hipLaunchKernelGGL(k_bfs_step, dim3(std::min(grid, ntiles)), dim3(kBlock), 0, s,
-                       tiles, ntiles, m, level, depth, changed);
+    const int32_t cu = device_cu_count();
+    const int32_t full = (ntiles + kBfsThreads / 64 - 1) / (kBfsThreads / 64);
+    // the frontier in LDS in up to kBfsPasses parts; past that (40 M vertices
+    // would read the columns 32 times) it is read from device memory
+    const int32_t most = kPanelLds / 4;
+    if (words <= kBfsPasses * most) {
+        const int32_t passes = (words + most - 1) / most;
+        const int32_t part = ((words + passes - 1) / passes + 3) & ~3;
+        const int32_t per_cu = std::max(1, std::min(2, kPanelLds / (part * 4)));
+        hipLaunchKernelGGL(k_bfs_step<true>, dim3(std::min(full, cu * per_cu)),
+                           dim3(kBfsThreads), part * 4, s,
+                           tiles, ntiles, m, level, depth, bits, words, part, last);
+    } else {
+        hipLaunchKernelGGL(k_bfs_step<false>, dim3(std::min(full, cu * 2)), dim3(kBfsThreads), 0,
+                           s, tiles, ntiles, m, level, depth, bits, words, words, last);
+    }
     check_launch("k_bfs_step");
+}
+
+void launch_bfs_report(const int32_t *last, int32_t *host, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_bfs_report, dim3(1), dim3(1), 0, s, last, host);
+    check_launch("k_bfs_report");
 }
 
 void launch_jds_check(int32_t rows, int32_t max_len, const int32_t *perm,

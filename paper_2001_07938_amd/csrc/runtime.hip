@@ -70,8 +70,8 @@ struct Context {
     double *dot_part = nullptr;     // kDotParts + 1 (result)
     double *dot_a = nullptr, *dot_b = nullptr;
     size_t dot_cap = 0;
-    void *jds_buf = nullptr;        // inverse permutation of a JDS product
-    size_t jds_cap = 0;
+    void *work = nullptr;           // of the calls that return when done (JDS, BFS)
+    size_t work_cap = 0;
     int32_t *status = nullptr;      // 4 ints: validation, flags
     int32_t *host_status = nullptr; // pinned, written by kernels
     int32_t *total = nullptr;       // 1 int for scans
@@ -1540,8 +1540,8 @@ static int marshal_mode()
     return 0;
 }
 
-// Largest inverse permutation of a JDS product kept between calls (bytes).
-constexpr size_t kJdsKeep = (size_t)64 << 20;
+// Most working memory kept between blocking calls (bytes).
+constexpr size_t kWorkKeep = (size_t)64 << 20;
 
 static void *grow_buffer(void *&buf, size_t &cap, size_t bytes)
 {
@@ -2671,12 +2671,12 @@ int lilac_finalize(void)
         Context &c = *g_ctx;
         dev_free(c.x_buf);
         dev_free(c.y_buf);
-        dev_free(c.jds_buf);
+        dev_free(c.work);
         dev_free(c.dot_a);
         dev_free(c.dot_b);
-        c.x_buf = c.y_buf = c.jds_buf = nullptr;
+        c.x_buf = c.y_buf = c.work = nullptr;
         c.dot_a = c.dot_b = nullptr;
-        c.x_cap = c.y_cap = c.jds_cap = c.dot_cap = 0;
+        c.x_cap = c.y_cap = c.work_cap = c.dot_cap = 0;
     });
 }
 
@@ -3174,22 +3174,37 @@ int lilac_bfs(lilac_csr_t hh, int source, int *level, int *nlevels, void *stream
         hipStream_t s = pick_stream(stream);
         refresh(*h, s);
         Context &c = ctx();
-        launch_fill_i32(level, h->rows, -1, s);
-        launch_fill_i32(level + source, 1, 0, s);
         const MatDesc m = make_desc(*h, nullptr, nullptr, nullptr, nullptr);
-        const int32_t grid = own_layout(*h) ? tile_grid(h->dt) : h->grid;
-        int32_t depth = 0;
-        for (;; ++depth) {
-            launch_fill_i32(c.status, 1, 0, s);
-            launch_bfs_step(h->d_tiles, h->ntiles, grid, m, level, depth, c.status, s);
-            int32_t changed = 0;
-            HIPC(hipMemcpyAsync(&changed, c.status, 4, hipMemcpyDeviceToHost, s));
-            HIPC(hipStreamSynchronize(s));
-            if (!changed)
-                break;
+        const int32_t words = bfs_words(h->rows);
+        const size_t bytes = (size_t)words * 3 * 4 + 64;
+        // kept between calls up to kWorkKeep bytes (calls are serial and done
+        // with it when they return)
+        void *own = bytes <= kWorkKeep ? nullptr : dev_alloc(bytes);
+        int32_t found = 0;
+        try {
+            int32_t *last = (int32_t *)(own ? own : grow_buffer(c.work, c.work_cap, bytes));
+            uint32_t *bits = (uint32_t *)(last + 16);
+            launch_bfs_init(h->rows, source, level, bits, words, last, s);
+            // levels are enqueued some at a time, more each time (a step past
+            // the last level does nothing), with one wait for them all
+            int32_t depth = 0, batch = 8;
+            do {
+                for (int32_t i = 0; i < batch; ++i, ++depth)
+                    launch_bfs_step(h->d_tiles, h->ntiles, m, level, depth, bits, words, last,
+                                    s);
+                launch_bfs_report(last, c.host_status, s);
+                HIPC(hipStreamSynchronize(s));
+                found = *(volatile int32_t *)c.host_status;
+                batch = std::min(2 * batch, 64);
+            } while (found >= depth);
+        } catch (...) {
+            (void)hipStreamSynchronize(s);
+            dev_free(own);
+            throw;
         }
+        dev_free(own);
         if (nlevels)
-            *nlevels = depth + 1;
+            *nlevels = found + 1;
     });
 }
 
@@ -3255,10 +3270,10 @@ int lilac_spmv_jds(int rows, int max_len, const int *perm, const int *nzcnt,
             double *d_y = y_dev ? y : (double *)dev_alloc((size_t)rows * 8);
             if (!y_dev)
                 tmp.push_back(d_y);
-            // a permutation of more than kJdsKeep bytes is not kept
+            // a permutation of more than kWorkKeep bytes is not kept
             int32_t *iperm;
-            if ((size_t)rows * 4 <= kJdsKeep) {
-                iperm = (int32_t *)grow_buffer(c.jds_buf, c.jds_cap, (size_t)rows * 4);
+            if ((size_t)rows * 4 <= kWorkKeep) {
+                iperm = (int32_t *)grow_buffer(c.work, c.work_cap, (size_t)rows * 4);
             } else {
                 iperm = (int32_t *)dev_alloc((size_t)rows * 4);
                 tmp.push_back(iperm);
