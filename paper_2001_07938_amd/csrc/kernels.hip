@@ -2359,16 +2359,28 @@ __global__ __launch_bounds__(kBlock) void k_hot_scatter(
 
 // ------------------------------------------------------------------ BFS
 
-// Start: level -1 but 0 at the source, the first two frontier bitmaps, last = 0.
+// Start: level -1 but 0 at the source, the first two frontier bitmaps, last =
+// 0, and the rows still to decide: a bit for every row of 1 to kBfsShort
+// entries but the source.
 __global__ __launch_bounds__(kBlock) void k_bfs_init(int32_t rows, int32_t source,
+                                                     const int32_t *__restrict__ rp,
                                                      int32_t *__restrict__ level,
                                                      uint32_t *__restrict__ bits, int32_t words,
+                                                     uint64_t *__restrict__ todo,
                                                      int32_t *__restrict__ last)
 {
     const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = tid; i < rows; i += stride)
-        level[i] = (i == source) ? 0 : -1;
+    // whole wavefronts: 64 consecutive rows to a word
+    for (int64_t i = tid; i < (((int64_t)rows + 63) & ~(int64_t)63); i += stride) {
+        const bool in = i < rows;
+        const int32_t n = in ? rp[i + 1] - rp[i] : 0;
+        if (in)
+            level[i] = (i == source) ? 0 : -1;
+        const uint64_t m = __ballot(n > 0 && n <= kBfsShort && i != source);
+        if ((threadIdx.x & 63) == 0)
+            todo[i >> 6] = m;
+    }
     for (int64_t i = tid; i < 2 * (int64_t)words; i += stride)
         bits[i] = (i == (source >> 5)) ? 1u << (source & 31) : 0u;
     if (tid == 0)
@@ -2390,67 +2402,84 @@ struct Frontier {
     }
 };
 
-// Rows [0, n) of a wavefront's list (lane i holds row, first and last entry of
-// the i-th), W lanes per row: those with a column in the frontier get the
-// level.  U * W entries of a row are looked at together; a row that has a hit
-// is left.
+// Whether entries [k0, k1) hold a column of the frontier, W lanes for each row
+// (all with the row's bounds), U * W entries at a time; true in every lane of a
+// row that has one.  All 64 lanes call it.
 template <int W, int U, bool LDS>
-__device__ __forceinline__ bool bfs_rows(const int32_t *__restrict__ col, int32_t row,
-                                         int32_t k0, int32_t k1, int32_t n,
-                                         const Frontier<LDS> &f, int32_t *__restrict__ level,
-                                         uint32_t *__restrict__ next, int32_t depth)
+__device__ __forceinline__ bool bfs_hit(const int32_t *__restrict__ col, int32_t k0, int32_t k1,
+                                        const Frontier<LDS> &f)
 {
     const int wl = threadIdx.x & 63;
-    const int q = wl / W, lane = wl % W;
     constexpr uint64_t ones = W == 64 ? ~0ull : (1ull << (W & 63)) - 1ull;
-    const uint64_t group = ones << (q * W);
-    bool any = false;
-    for (int32_t i = 0; i < n; i += 64 / W) {
-        const int src = min(i + q, 63);
-        const int32_t r = __shfl(row, src, 64);
-        const int32_t a = __shfl(k0, src, 64);
-        const int32_t e = __shfl(k1, src, 64);   // by all lanes: a source must be on
-        const int32_t z = (i + q < n) ? e : a;
-        bool hit = false, on = a < z;
-        // the trips of the wavefront's longest row; a group stops at its own end
-        for (int32_t k = a + lane; __ballot(on); k += U * W) {
-            int32_t c[U];
+    const uint64_t group = ones << (wl / W * W);
+    bool hit = false, on = k0 < k1;
+    // the trips of the wavefront's longest row; a row stops at its own end
+    for (int32_t k = k0; __ballot(on); k += U * W) {
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            c[u] = on ? gld(col + min(k + wl % W + u * W, k1 - 1)) : 0;
+        if (on) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                c[u] = on ? gld(col + min(k + u * W, z - 1)) : 0;
-            if (on) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    hit = hit || f.has(c[u]);
-            }
-            const bool found = (__ballot(hit) & group) != 0;
-            on = on && !found && k - lane + U * W < z;
-            if (found)
-                hit = true;
+                hit = f.has(c[u]) || hit;
         }
-        if (hit && lane == 0) {
-            level[r] = depth + 1;
-            atomicOr(&next[r >> 5], 1u << (r & 31));
-            any = true;
-        }
+        hit = (__ballot(hit) & group) != 0;
+        on = on && !hit && k + U * W < k1;
     }
-    return any;
+    return hit;
+}
+
+// The rows of a wavefront's 64 that `want` names (lane l holds the bounds of
+// the l-th), 64 / W at a time; returns the mask of those with a hit.
+template <int W, int U, bool LDS>
+__device__ __forceinline__ uint64_t bfs_rows(const int32_t *__restrict__ col, int32_t k0,
+                                             int32_t k1, uint64_t want,
+                                             const Frontier<LDS> &f)
+{
+    if (!want)
+        return 0;
+    const int wl = threadIdx.x & 63;
+    const bool on = (want >> wl) & 1u;
+    if (W == 1)
+        return __ballot(bfs_hit<W, U, LDS>(col, k0, on ? k1 : k0, f));
+    const int32_t n = __popcll(want);
+    // wanted rows to the first lanes (the others go where nobody looks)
+    const int32_t rank = on ? lanes_below(want) : n + lanes_below(~want);
+    const int32_t a = __builtin_amdgcn_ds_permute(rank * 4, k0);
+    const int32_t z = __builtin_amdgcn_ds_permute(rank * 4, k1);
+    bool mine = false;
+    for (int32_t i = 0; i < n; i += 64 / W) {
+        const int src = min(i + wl / W, 63);
+        // by all lanes: the lane that is read has to take part
+        const int32_t ra = __shfl(a, src, 64), rz = __shfl(z, src, 64);
+        const int hit = bfs_hit<W, U, LDS>(col, ra, i + wl / W < n ? rz : ra, f);
+        // back to the row's own lane
+        const int32_t at = rank - i;
+        const int h = __shfl(hit, (at >= 0 && at < 64 / W) ? at * W : wl, 64);
+        mine = mine || (at >= 0 && at < 64 / W && h);
+    }
+    return __ballot(on && mine);
 }
 
 // One level: every row without a level that has a column in the frontier
 // (bitmap depth % 3) gets depth + 1 and its bit in bitmap (depth + 1) % 3; the
 // third one is cleared for the level after.  Nothing is done once a level
 // found nothing (last < depth), so several levels can be enqueued at once.
-// The columns are tested against the copy of the frontier in LDS (one pass for
-// each `lds_words` words of it): a bit per vertex instead of a gather from the
-// levels' 4 bytes, which bounds the search at one line per 4.7 clocks and CU.
-// A wavefront takes tile after tile; of a tile's rows it first looks up level
-// and bounds, 64 at a time, and keeps those that still matter.
+// Columns are tested against a copy of the frontier in LDS (one pass for each
+// `lds_words` words of it): a bit per vertex instead of a gather of a 4-byte
+// level, which the caches serve at one line per 4.7 clocks and CU.
+// The chunks of split rows and the nlong rows before them in the class order
+// (all of more than kBfsShort entries) go 64 to a wavefront.  The others go 64 consecutive rows to a
+// wavefront, which owns their word of `todo`: what is decided or empty costs a
+// bit.  R-MAT 2^20, 16 M entries: 47 + 37 us for the two levels that look at
+// every entry and 15 us for each late one with tiles for all rows; 43 + 36 and
+// 8 to 12 us with the words (170 us for the call of six levels).
 template <bool LDS>
 __global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
-    const Tile *__restrict__ tiles, int32_t ntiles, MatDesc m, int32_t *__restrict__ level,
-    int32_t depth, uint32_t *__restrict__ bits, int32_t words, int32_t lds_words,
-    int32_t *__restrict__ last)
+    MatDesc m, int32_t nchunk, int32_t nlong, int32_t rows,
+    int32_t *__restrict__ level, int32_t depth, uint32_t *__restrict__ bits, int32_t words,
+    int32_t lds_words, uint64_t *__restrict__ todo, int32_t *__restrict__ last)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *fb = (uint32_t *)smem;
@@ -2464,9 +2493,10 @@ __global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
         clear[i] = 0u;
     const int lane = threadIdx.x & 63;
     const int32_t waves = (int32_t)gridDim.x * (kBfsThreads / 64);
-    // wavefronts of one workgroup take tiles far apart (longest come first)
+    // wavefronts of one workgroup take rows far apart (longest come first)
     const int32_t w0 = __builtin_amdgcn_readfirstlane(
         (int32_t)(threadIdx.x >> 6) * (int32_t)gridDim.x + (int32_t)blockIdx.x);
+    const int32_t groups = (int32_t)(((int64_t)rows + 63) >> 6);
     bool any = false;
     for (int32_t p0 = 0; p0 < words; p0 += lds_words) {
         Frontier<LDS> f{cur, 0u, 0u};
@@ -2479,46 +2509,80 @@ __global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
             __syncthreads();
             f = Frontier<LDS>{fb, (uint32_t)p0 * 32u, (uint32_t)nw * 32u};
         }
-        for (int32_t ti = w0; ti < ntiles; ti += waves) {
-            const i32x4 tv = *(const __attribute__((address_space(4))) i32x4 *)(tiles + ti);
-            const Tile t{tv.x, tv.y, tv.z, tv.w};
-            const int32_t cls = t.cls & kTileClassMask;
-            for (int32_t j0 = 0; j0 < t.count; j0 += 64) {
-                int32_t row = 0, k0 = 0, k1 = 0;
-                bool on = j0 + lane < t.count;
-                if (on && cls == C_SPLIT) {
-                    row = gld(m.c_row + t.first + j0 + lane);
-                    k0 = gld(m.c_k0 + t.first + j0 + lane);
-                    k1 = gld(m.c_k1 + t.first + j0 + lane);
-                } else if (on) {
-                    row = tile_row(m, t, j0 + lane);
-                    k0 = gld(m.row_ptr + row);
-                    k1 = gld(m.row_ptr + row + 1);
+        for (int32_t i0 = w0; i0 < nchunk + nlong; i0 += waves * 64) {
+            // row and bounds of this wavefront's next 64 long rows and chunks
+            const int64_t i = (int64_t)i0 + (int64_t)lane * waves;
+            int32_t row = 0, k0 = 0, k1 = 0;
+            if (i < nchunk) {
+                row = gld(m.c_row + i);
+                k0 = gld(m.c_k0 + i);
+                k1 = gld(m.c_k1 + i);
+            } else if (i < nchunk + nlong) {
+                row = gld(m.bin_rows + m.split_begin - 1 - (i - nchunk));
+                k0 = gld(m.row_ptr + row);
+                k1 = gld(m.row_ptr + row + 1);
+                if (k1 - k0 <= kBfsShort)
+                    k1 = k0;   // its class reaches below: the row is in todo
+            }
+            const int32_t n = (k0 < k1 && gld(level + row) == -1) ? k1 - k0 : 0;
+            uint64_t found = bfs_rows<32, 8, LDS>(m.col, k0, k1, __ballot(n > 0 && n <= 512), f);
+            found |= bfs_rows<64, 8, LDS>(m.col, k0, k1, __ballot(n > 512), f);
+            if (found) {
+                any = true;
+                if ((found >> lane) & 1u) {
+                    level[row] = depth + 1;
+                    atomicOr(&next[row >> 5], 1u << (row & 31));
                 }
-                on = on && k0 < k1 && gld(level + row) == -1;
-                const uint64_t left = __ballot(on);
-                if (!left)
-                    continue;
-                const int32_t n = __popcll(left);
-                // rows that matter to the first n lanes (the others send to
-                // lanes that are not looked at)
-                const int to = (on ? lanes_below(left) : n + lanes_below(~left)) * 4;
-                row = __builtin_amdgcn_ds_permute(to, row);
-                k0 = __builtin_amdgcn_ds_permute(to, k0);
-                k1 = __builtin_amdgcn_ds_permute(to, k1);
-                switch (cls) {
-                case C_W1: any |= bfs_rows<1, 2, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
-                case C_W2: any |= bfs_rows<2, 2, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
-                case C_W4: any |= bfs_rows<4, 2, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
-                case C_W8: any |= bfs_rows<8, 4, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
-                case C_W16: any |= bfs_rows<16, 4, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
-                case C_W32: any |= bfs_rows<32, 4, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
-                default: any |= bfs_rows<64, 8, LDS>(m.col, row, k0, k1, n, f, level, next, depth); break;
+            }
+        }
+        for (int32_t g0 = w0; g0 < groups; g0 += waves * 64) {
+            // the words of this wavefront's next 64 groups
+            const int64_t gl = (int64_t)g0 + (int64_t)lane * waves;
+            const uint64_t word = gl < groups ? todo[gl] : 0;
+            uint64_t live = __ballot(word != 0);
+            // bounds of the next group's rows, asked for one group ahead
+            int32_t nk0 = 0, nk1 = 0;
+            auto request = [&]() {
+                const int64_t g = (int64_t)g0 + (int64_t)__builtin_ctzll(live) * waves;
+                const int64_t row = min(g * 64 + lane, (int64_t)rows - 1);
+                nk0 = gld(m.row_ptr + row);
+                nk1 = gld(m.row_ptr + row + 1);
+            };
+            if (live)
+                request();
+            while (live) {
+                const int l = __builtin_ctzll(live);
+                live &= live - 1;
+                const int32_t g = g0 + l * waves;
+                const int32_t k0 = nk0, k1 = nk1;
+                if (live)
+                    request();
+                const uint64_t want =
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(word >> 32), l) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)word, l);
+                const int32_t row = g * 64 + lane;   // of this matrix where `want` says so
+                const bool on = (want >> lane) & 1u;
+                const int32_t n = on ? k1 - k0 : 0;
+                uint64_t found = bfs_rows<1, 4, LDS>(m.col, k0, k1, __ballot(n > 0 && n <= 4), f);
+                found |= bfs_rows<4, 8, LDS>(m.col, k0, k1, __ballot(n > 4 && n <= 32), f);
+                found |= bfs_rows<16, 8, LDS>(m.col, k0, k1, __ballot(n > 32), f);
+                if (found) {
+                    any = true;
+                    if ((found >> lane) & 1u)
+                        level[row] = depth + 1;
+                    if (lane == 0) {
+                        atomicAnd((unsigned long long *)&todo[g], ~(unsigned long long)found);
+                        // its two words of the frontier hold long rows too
+                        if ((uint32_t)found)
+                            atomicOr(&next[2 * g], (uint32_t)found);
+                        if (found >> 32)
+                            atomicOr(&next[2 * g + 1], (uint32_t)(found >> 32));
+                    }
                 }
             }
         }
     }
-    if (__ballot(any) && lane == 0)
+    if (any && lane == 0)
         *last = depth + 1;
 }
 
@@ -3907,17 +3971,18 @@ void launch_panel_wptr(const PanelDesc &pd, const int32_t *ptr, int32_t *wptr,
     check_launch("k_panel_wptr");
 }
 
-void launch_bfs_init(int32_t rows, int32_t source, int32_t *level, uint32_t *bits,
-                     int32_t words, int32_t *last, hipStream_t s)
+void launch_bfs_init(int32_t rows, int32_t source, const int32_t *rp, int32_t *level,
+                     uint32_t *bits, int32_t words, uint64_t *todo, int32_t *last,
+                     hipStream_t s)
 {
-    hipLaunchKernelGGL(k_bfs_init, dim3(grid_for(rows, kBlock * 4, 2048)), dim3(kBlock), 0, s,
-                       rows, source, level, bits, words, last);
+    hipLaunchKernelGGL(k_bfs_init, dim3(grid_for(rows, kBlock, 2048)), dim3(kBlock), 0, s,
+                       rows, source, rp, level, bits, words, todo, last);
     check_launch("k_bfs_init");
 }
 
-void launch_bfs_step(const Tile *tiles, int32_t ntiles, const MatDesc &m, int32_t *level,
-                     int32_t depth, uint32_t *bits, int32_t words, int32_t *last,
-                     hipStream_t s)
+void launch_bfs_step(const MatDesc &m, int32_t nchunk, int32_t nlong, int32_t rows,
+                     int32_t *level, int32_t depth, uint32_t *bits, int32_t words,
+                     uint64_t *todo, int32_t *last, hipStream_t s)
 {
     static bool ready = false;
     if (!ready) {
@@ -3925,23 +3990,24 @@ void launch_bfs_step(const Tile *tiles, int32_t ntiles, const MatDesc &m, int32_
                                  hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
         ready = true;
     }
-    if (ntiles <= 0)
+    if (rows <= 0)
         return;
     const int32_t cu = device_cu_count();
-    const int32_t full = (ntiles + kBfsThreads / 64 - 1) / (kBfsThreads / 64);
-    // the frontier in LDS in up to kBfsPasses parts; past that (40 M vertices
-    // would read the columns 32 times) it is read from device memory
+    const int64_t work = (int64_t)nchunk + nlong + ((int64_t)rows + 63) / 64;
+    const int32_t full = grid_for(work, kBfsThreads / 64, cu * 2);
+    // the frontier in LDS in up to kBfsPasses parts; past that the columns
+    // would be read too often: it stays in device memory
     const int32_t most = kPanelLds / 4;
     if (words <= kBfsPasses * most) {
         const int32_t passes = (words + most - 1) / most;
         const int32_t part = ((words + passes - 1) / passes + 3) & ~3;
         const int32_t per_cu = std::max(1, std::min(2, kPanelLds / (part * 4)));
         hipLaunchKernelGGL(k_bfs_step<true>, dim3(std::min(full, cu * per_cu)),
-                           dim3(kBfsThreads), part * 4, s,
-                           tiles, ntiles, m, level, depth, bits, words, part, last);
+                           dim3(kBfsThreads), part * 4, s, m, nchunk, nlong, rows, level,
+                           depth, bits, words, part, todo, last);
     } else {
-        hipLaunchKernelGGL(k_bfs_step<false>, dim3(std::min(full, cu * 2)), dim3(kBfsThreads), 0,
-                           s, tiles, ntiles, m, level, depth, bits, words, words, last);
+        hipLaunchKernelGGL(k_bfs_step<false>, dim3(full), dim3(kBfsThreads), 0, s, m, nchunk,
+                           nlong, rows, level, depth, bits, words, words, todo, last);
     }
     check_launch("k_bfs_step");
 }

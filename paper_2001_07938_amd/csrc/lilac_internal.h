@@ -503,22 +503,26 @@ void launch_dot_parts(int64_t n, const double *a, const double *b,
 void launch_dot_parts_f32(int64_t n, const float *a, const float *b,
                           double *part, int32_t nparts, hipStream_t s);
 
-// Breadth-first search by Boolean products over the tiles.  bits: three
-// frontier bitmaps of `words` words (bfs_words of the rows), last: the deepest
-// level given out so far.  A step gives level depth + 1 to every row without a
-// level that has a column of level depth, and does nothing when no row has
-// level depth; the report hands `last` to the host (pinned memory).
+// Breadth-first search by Boolean products.  bits: three frontier bitmaps of
+// `words` words (bfs_words of the rows), todo: a 64-bit word for each 64 rows,
+// last: the deepest level given out so far.  A step gives level depth + 1 to
+// every row without a level that has a column of level depth, and does nothing
+// when no row has level depth; the report hands `last` to the host (pinned
+// memory).  The nchunk chunks of the split rows and the nlong rows before the
+// split ones in the class order hold every row of more than kBfsShort entries.
 constexpr int kBfsThreads = 1024;
 constexpr int kBfsPasses = 4;
+constexpr int32_t kBfsShort = 128;
 inline int32_t bfs_words(int32_t rows)
 {
     return (int32_t)((((int64_t)rows + 31) / 32 + 3) & ~(int64_t)3);   // 16-byte pieces
 }
-void launch_bfs_init(int32_t rows, int32_t source, int32_t *level, uint32_t *bits,
-                     int32_t words, int32_t *last, hipStream_t s);
-void launch_bfs_step(const Tile *tiles, int32_t ntiles, const MatDesc &m, int32_t *level,
-                     int32_t depth, uint32_t *bits, int32_t words, int32_t *last,
+void launch_bfs_init(int32_t rows, int32_t source, const int32_t *rp, int32_t *level,
+                     uint32_t *bits, int32_t words, uint64_t *todo, int32_t *last,
                      hipStream_t s);
+void launch_bfs_step(const MatDesc &m, int32_t nchunk, int32_t nlong, int32_t rows,
+                     int32_t *level, int32_t depth, uint32_t *bits, int32_t words,
+                     uint64_t *todo, int32_t *last, hipStream_t s);
 void launch_bfs_report(const int32_t *last, int32_t *host, hipStream_t s);
 
 // Relabelling of a graph's vertices by decreasing out-degree (locality of the

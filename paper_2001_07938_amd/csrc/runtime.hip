@@ -3176,7 +3176,12 @@ int lilac_bfs(lilac_csr_t hh, int source, int *level, int *nlevels, void *stream
         Context &c = ctx();
         const MatDesc m = make_desc(*h, nullptr, nullptr, nullptr, nullptr);
         const int32_t words = bfs_words(h->rows);
-        const size_t bytes = (size_t)words * 3 * 4 + 64;
+        const size_t bytes = (size_t)words * 3 * 4 + (size_t)words * 4 + 64;
+        // rows of the classes that reach past kBfsShort entries, split ones apart
+        int short_cls = 0;
+        while (short_cls < C_SPLIT && h->plan.upper[short_cls] <= kBfsShort)
+            ++short_cls;
+        const int32_t nlong = h->bin_off[C_SPLIT] - h->bin_off[short_cls];
         // kept between calls up to kWorkKeep bytes (calls are serial and done
         // with it when they return)
         void *own = bytes <= kWorkKeep ? nullptr : dev_alloc(bytes);
@@ -3184,14 +3189,15 @@ int lilac_bfs(lilac_csr_t hh, int source, int *level, int *nlevels, void *stream
         try {
             int32_t *last = (int32_t *)(own ? own : grow_buffer(c.work, c.work_cap, bytes));
             uint32_t *bits = (uint32_t *)(last + 16);
-            launch_bfs_init(h->rows, source, level, bits, words, last, s);
+            uint64_t *todo = (uint64_t *)(bits + 3 * (size_t)words);
+            launch_bfs_init(h->rows, source, h->d_row_ptr, level, bits, words, todo, last, s);
             // levels are enqueued some at a time, more each time (a step past
             // the last level does nothing), with one wait for them all
             int32_t depth = 0, batch = 8;
             do {
                 for (int32_t i = 0; i < batch; ++i, ++depth)
-                    launch_bfs_step(h->d_tiles, h->ntiles, m, level, depth, bits, words, last,
-                                    s);
+                    launch_bfs_step(m, (int32_t)h->nchunks, nlong, h->rows, level, depth, bits,
+                                    words, todo, last, s);
                 launch_bfs_report(last, c.host_status, s);
                 HIPC(hipStreamSynchronize(s));
                 found = *(volatile int32_t *)c.host_status;
