@@ -1378,14 +1378,16 @@ __device__ __forceinline__ void hot_first(const V *__restrict__ pv,
 // gathers are requested too.  NW wavefronts share the part; XG: xsrc is in
 // device memory (else in LDS).  PRE: the first chunk was requested earlier
 // into *pre (hot_first, same part and wavefront).
-template <typename V, bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false>
+template <typename V, bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false,
+          bool MAP = false>
 __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
                                          const uint32_t *__restrict__ prc,
                                          const uint16_t *__restrict__ pkey,
                                          int32_t s, int32_t e, const V *xsrc,
                                          double *acc, int32_t *ckey, double *csum,
                                          int wave, int lane,
-                                         const HotChunk<V> *pre = nullptr)
+                                         const HotChunk<V> *pre = nullptr,
+                                         const int32_t *map = nullptr)
 {
     typedef typename HotChunk<V>::pair_t pair_t;
     typedef typename HotChunk<V>::upair_t upair_t;
@@ -1430,6 +1432,8 @@ __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
     auto column = [&](uint32_t w, bool ok) {
         return ok ? (HOT ? (w & 0xFFFFu) : w) : 0u;
     };
+    // MAP: xsrc is in the caller's column order, map[c] column c's place in it
+    auto gather = [&](uint32_t c) { return gld(xsrc + (MAP ? (uint32_t)gld(map + c) : c)); };
     auto request = [&](int32_t at, pair_t &rv, upair_t &rr, kpair_t &rk) {
         const int32_t nn = at + 2 * lane;
         const int32_t ea = (nn < ke) ? nn : kb;
@@ -1447,8 +1451,8 @@ __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
     upair_t rc2;
     kpair_t kk2;
     if (XG && kb < ke) {
-        gx0 = gld(xsrc + column(rc.x, in_share(kb, 0)));
-        gx1 = gld(xsrc + column(rc.y, in_share(kb, 1)));
+        gx0 = gather(column(rc.x, in_share(kb, 0)));
+        gx1 = gather(column(rc.y, in_share(kb, 1)));
         if (kb + 128 < ke)
             request(kb + 128, v2, rc2, kk2);
     }
@@ -1475,8 +1479,8 @@ __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
                 rc = rc2;
                 if (!HOT)
                     kk = kk2;
-                gx0 = gld(xsrc + column(rc.x, in_share(nb, 0)));
-                gx1 = gld(xsrc + column(rc.y, in_share(nb, 1)));
+                gx0 = gather(column(rc.x, in_share(nb, 0)));
+                gx1 = gather(column(rc.y, in_share(nb, 1)));
                 if (nb + 128 < ke)
                     request(nb + 128, v2, rc2, kk2);
             }
@@ -1545,14 +1549,15 @@ __device__ __forceinline__ void hot_first4(const float *__restrict__ pv,
 // last run enters a segmented scan over the wavefront.  Each row still
 // gets one addition per chunk, from the lane where its run ends, so the
 // order of the additions is fixed by the matrix and the layout.
-template <bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false>
+template <bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false, bool MAP = false>
 __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
                                           const uint32_t *__restrict__ prc,
                                           const uint16_t *__restrict__ pkey,
                                           int32_t s, int32_t e, const float *xsrc,
                                           double *acc, int32_t *ckey, double *csum,
                                           int wave, int lane,
-                                          const HotChunk4 *pre = nullptr)
+                                          const HotChunk4 *pre = nullptr,
+                                          const int32_t *map = nullptr)
 {
     typedef HotChunk4::quad_t quad_t;
     typedef HotChunk4::uquad_t uquad_t;
@@ -1596,6 +1601,8 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
     auto column = [&](uint32_t w, bool ok) {
         return ok ? (HOT ? (w & 0xFFFFu) : w) : 0u;
     };
+    // MAP: xsrc is in the caller's column order, map[c] column c's place in it
+    auto gather = [&](uint32_t c) { return gld(xsrc + (MAP ? (uint32_t)gld(map + c) : c)); };
     auto request = [&](int32_t at, quad_t &rv, uquad_t &rr, kquad_t &rk) {
         const int32_t nn = at + 4 * lane;
         const int32_t ea = (nn < ke) ? nn : kb;
@@ -1612,10 +1619,10 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
     uquad_t rc2;
     kquad_t kk2;
     if (XG && kb < ke) {
-        g[0] = gld(xsrc + column(rc.x, in_share(kb, 0)));
-        g[1] = gld(xsrc + column(rc.y, in_share(kb, 1)));
-        g[2] = gld(xsrc + column(rc.z, in_share(kb, 2)));
-        g[3] = gld(xsrc + column(rc.w, in_share(kb, 3)));
+        g[0] = gather(column(rc.x, in_share(kb, 0)));
+        g[1] = gather(column(rc.y, in_share(kb, 1)));
+        g[2] = gather(column(rc.z, in_share(kb, 2)));
+        g[3] = gather(column(rc.w, in_share(kb, 3)));
         if (kb + CH < ke)
             request(kb + CH, v2, rc2, kk2);
     }
@@ -1648,10 +1655,10 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
                 rc = rc2;
                 if (!HOT)
                     kk = kk2;
-                g[0] = gld(xsrc + column(rc.x, in_share(nb, 0)));
-                g[1] = gld(xsrc + column(rc.y, in_share(nb, 1)));
-                g[2] = gld(xsrc + column(rc.z, in_share(nb, 2)));
-                g[3] = gld(xsrc + column(rc.w, in_share(nb, 3)));
+                g[0] = gather(column(rc.x, in_share(nb, 0)));
+                g[1] = gather(column(rc.y, in_share(nb, 1)));
+                g[2] = gather(column(rc.z, in_share(nb, 2)));
+                g[3] = gather(column(rc.w, in_share(nb, 3)));
                 if (nb + CH < ke)
                     request(nb + CH, v2, rc2, kk2);
             }
@@ -1712,7 +1719,10 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
 // row, and each row's result is its hot sum plus its cold sum: every sum is
 // formed in an order fixed by the matrix and the layout.  float32 matrices
 // take four entries per lane (hot_part4), float64 two (hot_part).
-template <typename V, bool DOT>
+// MAP: x is in the caller's column order and hd.old places the layout's columns
+// in it (twice the gathers, for where no memory is at hand for x in the
+// layout's order; the same sums).
+template <typename V, bool DOT, bool MAP = false>
 __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
     HotDesc hd, const V *__restrict__ x, V *__restrict__ y, Epi epi,
     const V *__restrict__ w, double *__restrict__ dot_part)
@@ -1731,10 +1741,15 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
     const int32_t width = hd.hot;
     const bool aligned = (((uintptr_t)x) & 15) == 0;
     const int32_t nvec = aligned ? width / VV : 0;
-    for (int32_t i = threadIdx.x; i < nvec; i += kPanelThreads)
-        *(vec_t *)(xs + i * VV) = gld((const vec_t *)(x + i * VV));
-    for (int32_t e = nvec * VV + threadIdx.x; e < width; e += kPanelThreads)
-        xs[e] = gld(x + e);
+    if (MAP) {
+        for (int32_t e = threadIdx.x; e < width; e += kPanelThreads)
+            xs[e] = gld(x + gld(hd.old + e));
+    } else {
+        for (int32_t i = threadIdx.x; i < nvec; i += kPanelThreads)
+            *(vec_t *)(xs + i * VV) = gld((const vec_t *)(x + i * VV));
+        for (int32_t e = nvec * VV + threadIdx.x; e < width; e += kPanelThreads)
+            xs[e] = gld(x + e);
+    }
     for (int i = threadIdx.x; i < 2 * kHotRows; i += kPanelThreads)
         acc_h[i] = 0.0;  // both sum arrays
     double dacc = 0.0;
@@ -1776,33 +1791,33 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
             const float *fx = (const float *)x;
             const float *fs = (const float *)xs;
             if (wave & 1) {
-                hot_part4<false, kPanelWaves, true, true>(
+                hot_part4<false, kPanelWaves, true, true, MAP>(
                     fv, hd.rc, hd.key, es, e1, fx, acc_c, ckey + kPanelWaves + wave,
-                    csum + kPanelWaves + wave, wave, lane, &pre4);
+                    csum + kPanelWaves + wave, wave, lane, &pre4, hd.old);
                 hot_part4<true>(fv, hd.rc, hd.key, e0, es, fs, acc_h, ckey + wave,
                                 csum + wave, wave, lane);
             } else {
                 hot_part4<true, kPanelWaves, false, true>(fv, hd.rc, hd.key, e0, es, fs,
                                                           acc_h, ckey + wave, csum + wave,
                                                           wave, lane, &pre4);
-                hot_part4<false>(fv, hd.rc, hd.key, es, e1, fx, acc_c,
-                                 ckey + kPanelWaves + wave, csum + kPanelWaves + wave,
-                                 wave, lane);
+                hot_part4<false, kPanelWaves, true, false, MAP>(
+                    fv, hd.rc, hd.key, es, e1, fx, acc_c, ckey + kPanelWaves + wave,
+                    csum + kPanelWaves + wave, wave, lane, nullptr, hd.old);
             }
         } else {
             if (wave & 1) {
-                hot_part<V, false, kPanelWaves, true, true>(
+                hot_part<V, false, kPanelWaves, true, true, MAP>(
                     pv, hd.rc, hd.key, es, e1, x, acc_c, ckey + kPanelWaves + wave,
-                    csum + kPanelWaves + wave, wave, lane, &pre);
+                    csum + kPanelWaves + wave, wave, lane, &pre, hd.old);
                 hot_part<V, true>(pv, hd.rc, hd.key, e0, es, xs, acc_h, ckey + wave,
                                   csum + wave, wave, lane);
             } else {
                 hot_part<V, true, kPanelWaves, false, true>(pv, hd.rc, hd.key, e0, es, xs,
                                                             acc_h, ckey + wave, csum + wave,
                                                             wave, lane, &pre);
-                hot_part<V, false>(pv, hd.rc, hd.key, es, e1, x, acc_c,
-                                   ckey + kPanelWaves + wave, csum + kPanelWaves + wave,
-                                   wave, lane);
+                hot_part<V, false, kPanelWaves, true, false, MAP>(
+                    pv, hd.rc, hd.key, es, e1, x, acc_c, ckey + kPanelWaves + wave,
+                    csum + kPanelWaves + wave, wave, lane, nullptr, hd.old);
             }
         }
         if (i + 1 < i1)
@@ -1850,6 +1865,18 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
         if (threadIdx.x == 0)
             dot_part[blockIdx.x] = tot;
     }
+}
+
+// xp[i] = x[old[i]]: x in the column order of a layout.
+template <typename V>
+__global__ __launch_bounds__(kBlock) void k_gather_cols(int32_t n,
+                                                        const int32_t *__restrict__ old,
+                                                        const V *__restrict__ x,
+                                                        V *__restrict__ xp)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n)
+        xp[i] = gld(x + old[i]);
 }
 
 // ------------------------------------------------------------- band
@@ -2283,6 +2310,7 @@ __global__ __launch_bounds__(kBlock) void k_sell_pack(BandDesc bd,
 __global__ __launch_bounds__(kBlock) void k_hot_count(HotDesc hd,
                                                       const int32_t *__restrict__ rp,
                                                       const int32_t *__restrict__ col,
+                                                      const int32_t *__restrict__ newid,
                                                       int32_t *__restrict__ cnt)
 {
     const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
@@ -2291,10 +2319,71 @@ __global__ __launch_bounds__(kBlock) void k_hot_count(HotDesc hd,
         return;  // whole wavefronts
     int32_t n = 0;
     for (int32_t k = rp[i] + lane; k < rp[i + 1]; k += 64)
-        n += (col[k] < hd.hot) ? 1 : 0;
+        n += ((newid ? newid[col[k]] : col[k]) < hd.hot) ? 1 : 0;
     n = wave_sum_i32(n);
     if (lane == 0)
         cnt[i] = n;
+}
+
+// 1 for a row with entries, 0 for an empty one (and past the last row).
+__global__ __launch_bounds__(kBlock) void k_row_filled(int32_t rows,
+                                                       const int32_t *__restrict__ rp,
+                                                       int32_t *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i <= rows)
+        out[i] = (i < rows && rp[i + 1] > rp[i]) ? 1 : 0;
+}
+
+// Keys: the number of a row among the non-empty rows of its block.  filled:
+// exclusive scan of k_row_filled.
+__global__ __launch_bounds__(kBlock) void k_hot_rmap(HotDesc hd,
+                                                     const int32_t *__restrict__ filled,
+                                                     uint16_t *__restrict__ rmap)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= hd.rows)
+        return;
+    int32_t lo = 0, hi = hd.nblk - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (hd.brow[mid] <= i)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    rmap[i] = filled[i + 1] > filled[i] ? (uint16_t)(filled[i] - filled[hd.brow[lo]])
+                                        : kHotEmpty;
+}
+
+// out[0] += entries k = 0, step, 2 step, ... whose column's newid is below hot.
+__global__ __launch_bounds__(kBlock) void k_hot_share(int64_t nnz, int32_t step,
+                                                      const int32_t *__restrict__ col,
+                                                      const int32_t *__restrict__ newid,
+                                                      int32_t hot, int32_t *__restrict__ out)
+{
+    int32_t n = 0;
+    for (int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * step; k < nnz;
+         k += (int64_t)gridDim.x * kBlock * step)
+        n += newid[col[k]] < hot ? 1 : 0;
+    n = wave_sum_i32(n);
+    __shared__ int32_t red[kWaves];
+    if ((threadIdx.x & 63) == 0)
+        red[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kWaves; ++i)
+            n += red[i];
+        atomicAdd(out, n);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_invert(int32_t n, const int32_t *__restrict__ p,
+                                                   int32_t *__restrict__ inv)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n)
+        inv[p[i]] = (int32_t)i;
 }
 
 __global__ __launch_bounds__(kBlock) void k_hot_split(HotDesc hd,
@@ -2313,8 +2402,9 @@ __global__ __launch_bounds__(kBlock) void k_hot_split(HotDesc hd,
 template <typename V>
 __global__ __launch_bounds__(kBlock) void k_hot_scatter(
     HotDesc hd, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-    const V *__restrict__ vals, const int32_t *__restrict__ hx,
-    V *__restrict__ hv, uint32_t *__restrict__ hrc, uint16_t *__restrict__ hkey)
+    const V *__restrict__ vals, const int32_t *__restrict__ newid,
+    const int32_t *__restrict__ hx, V *__restrict__ hv, uint32_t *__restrict__ hrc,
+    uint16_t *__restrict__ hkey)
 {
     const int64_t iw = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
@@ -2339,7 +2429,7 @@ __global__ __launch_bounds__(kBlock) void k_hot_scatter(
     for (int32_t base = rp[i]; base < e; base += 64) {
         const int32_t k = base + lane;
         const bool in = k < e;
-        const int32_t c = in ? col[k] : 0;
+        const int32_t c = !in ? 0 : newid ? newid[col[k]] : col[k];
         const bool hot = in && c < hd.hot;
         const uint64_t mh = __ballot(hot), mc = __ballot(in && !hot);
         if (hot) {
@@ -2594,12 +2684,12 @@ __global__ void k_bfs_report(const int32_t *__restrict__ last, int32_t *host)
 
 // --------------------------------------------------- graph relabelling
 
-__global__ __launch_bounds__(kBlock) void k_count_cols(int64_t nnz,
+__global__ __launch_bounds__(kBlock) void k_count_cols(int64_t nnz, int32_t step,
                                                        const int32_t *__restrict__ col,
                                                        int32_t *__restrict__ deg)
 {
-    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < nnz;
-         k += (int64_t)gridDim.x * kBlock)
+    for (int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * step; k < nnz;
+         k += (int64_t)gridDim.x * kBlock * step)
         atomicAdd(&deg[col[k]], 1);
 }
 
@@ -3818,34 +3908,87 @@ void launch_line_reuse(int32_t rows, const int32_t *rp, const int32_t *col,
     check_launch("k_line_reuse");
 }
 
-void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
-                     const Epi &epi, const void *w, double *dot_part, hipStream_t s)
+template <bool MAP>
+static void launch_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
+                       const Epi &epi, const void *w, double *dot_part, hipStream_t s)
 {
-    if (hd.nblk <= 0 || hd.grid <= 0)
-        return;
     dim3 g(hd.grid), b(kPanelThreads);
     if (dt == LILAC_F64) {
         if (dot_part)
-            hipLaunchKernelGGL((k_spmv_hot<double, true>), g, b, kPanelLds, s, hd,
+            hipLaunchKernelGGL((k_spmv_hot<double, true, MAP>), g, b, kPanelLds, s, hd,
                                (const double *)x, (double *)y, epi, (const double *)w, dot_part);
         else
-            hipLaunchKernelGGL((k_spmv_hot<double, false>), g, b, kPanelLds, s, hd,
+            hipLaunchKernelGGL((k_spmv_hot<double, false, MAP>), g, b, kPanelLds, s, hd,
                                (const double *)x, (double *)y, epi, (const double *)w, dot_part);
     } else {
         if (dot_part)
             fail(LILAC_ERR_UNSUPPORTED, "fused dot is only provided for float64");
-        hipLaunchKernelGGL((k_spmv_hot<float, false>), g, b, kPanelLds, s, hd,
+        hipLaunchKernelGGL((k_spmv_hot<float, false, MAP>), g, b, kPanelLds, s, hd,
                            (const float *)x, (float *)y, epi, (const float *)w, dot_part);
     }
     check_launch("k_spmv_hot");
 }
 
+void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
+                     const Epi &epi, const void *w, double *dot_part, void *xp, hipStream_t s)
+{
+    if (hd.nblk <= 0 || hd.grid <= 0)
+        return;
+    if (hd.old && !xp) {
+        launch_hot<true>(dt, hd, x, y, epi, w, dot_part, s);
+        return;
+    }
+    if (hd.old) {
+        dim3 g(grid_for(hd.cols, kBlock, INT_MAX)), b(kBlock);
+        if (dt == LILAC_F64)
+            hipLaunchKernelGGL(k_gather_cols<double>, g, b, 0, s, hd.cols, hd.old,
+                               (const double *)x, (double *)xp);
+        else
+            hipLaunchKernelGGL(k_gather_cols<float>, g, b, 0, s, hd.cols, hd.old,
+                               (const float *)x, (float *)xp);
+        check_launch("k_gather_cols");
+        x = xp;
+    }
+    launch_hot<false>(dt, hd, x, y, epi, w, dot_part, s);
+}
+
 void launch_hot_count(const HotDesc &hd, const int32_t *rp, const int32_t *col,
-                      int32_t *cnt, hipStream_t s)
+                      const int32_t *newid, int32_t *cnt, hipStream_t s)
 {
     hipLaunchKernelGGL(k_hot_count, dim3(grid_for((int64_t)hd.rows * 64, kBlock, INT_MAX)),
-                       dim3(kBlock), 0, s, hd, rp, col, cnt);
+                       dim3(kBlock), 0, s, hd, rp, col, newid, cnt);
     check_launch("k_hot_count");
+}
+
+void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_row_filled, dim3(grid_for((int64_t)rows + 1, kBlock, INT_MAX)),
+                       dim3(kBlock), 0, s, rows, rp, out);
+    check_launch("k_row_filled");
+}
+
+void launch_hot_rmap(const HotDesc &hd, const int32_t *filled, uint16_t *rmap, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_hot_rmap, dim3(grid_for(hd.rows, kBlock, INT_MAX)), dim3(kBlock), 0,
+                       s, hd, filled, rmap);
+    check_launch("k_hot_rmap");
+}
+
+void launch_hot_share(int64_t nnz, int32_t step, const int32_t *col, const int32_t *newid,
+                      int32_t hot, int32_t *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_hot_share, dim3(grid_for(nnz / step, kBlock * 8, 1024)), dim3(kBlock),
+                       0, s, nnz, step, col, newid, hot, out);
+    check_launch("k_hot_share");
+}
+
+void launch_invert(int32_t n, const int32_t *p, int32_t *inv, hipStream_t s)
+{
+    if (n <= 0)
+        return;
+    hipLaunchKernelGGL(k_invert, dim3(grid_for(n, kBlock, INT_MAX)), dim3(kBlock), 0, s, n, p,
+                       inv);
+    check_launch("k_invert");
 }
 
 void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
@@ -3857,16 +4000,17 @@ void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
 }
 
 void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
-                        const int32_t *col, const void *vals, const int32_t *hx,
-                        void *hv, uint32_t *hrc, uint16_t *hkey, hipStream_t s)
+                        const int32_t *col, const void *vals, const int32_t *newid,
+                        const int32_t *hx, void *hv, uint32_t *hrc, uint16_t *hkey,
+                        hipStream_t s)
 {
     dim3 g(grid_for((int64_t)hd.rows * 64, kBlock, INT_MAX)), b(kBlock);
     if (dt == LILAC_F64)
         hipLaunchKernelGGL(k_hot_scatter<double>, g, b, 0, s, hd, rp, col,
-                           (const double *)vals, hx, (double *)hv, hrc, hkey);
+                           (const double *)vals, newid, hx, (double *)hv, hrc, hkey);
     else
         hipLaunchKernelGGL(k_hot_scatter<float>, g, b, 0, s, hd, rp, col,
-                           (const float *)vals, hx, (float *)hv, hrc, hkey);
+                           (const float *)vals, newid, hx, (float *)hv, hrc, hkey);
     check_launch("k_hot_scatter");
 }
 
@@ -3879,9 +4023,15 @@ void panels_prepare()
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_panels_grouped<float>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_hot<double, true, true>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_hot<double, true>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_hot<double, false, true>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_hot<double, false>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_hot<float, false, true>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_hot<float, false>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
@@ -4038,12 +4188,13 @@ void launch_spmv_jds(int32_t rows, int32_t max_len, const int32_t *perm,
     check_launch("k_spmv_jds");
 }
 
-void launch_count_cols(int64_t nnz, const int32_t *col, int32_t *deg, hipStream_t s)
+void launch_count_cols(int64_t nnz, int32_t step, const int32_t *col, int32_t *deg,
+                       hipStream_t s)
 {
     if (nnz <= 0)
         return;
-    hipLaunchKernelGGL(k_count_cols, dim3(grid_for(nnz, kBlock * 8, 8192)), dim3(kBlock),
-                       0, s, nnz, col, deg);
+    hipLaunchKernelGGL(k_count_cols, dim3(grid_for(nnz / step, kBlock * 8, 8192)), dim3(kBlock),
+                       0, s, nnz, step, col, deg);
     check_launch("k_count_cols");
 }
 

@@ -184,6 +184,7 @@ struct HotDesc {
     const int32_t *bsplit;   // [nblk]
     const int32_t *gptr;     // [grid + 1]: workgroup g takes blocks gblk[gptr[g] .. gptr[g+1])
     const int32_t *gblk;     // [nblk]
+    const int32_t *old;      // [cols]: the caller's column of each, or null (the same)
     int32_t rows, cols, nblk, hot, grid, pad;
 };
 constexpr int kHotRows = 1536;                        // non-empty rows per block
@@ -241,6 +242,8 @@ Plan default_plan();
 struct CgState;      // device buffers + graph cache of a CG solve
 struct PrState;      // graph cache of PageRank
 
+enum : int32_t { kBuildAuto = 0, kBuildOnce = 1, kBuildHot = 2 };
+
 struct CsrHandle {
     int32_t rows = 0, cols = 0;
     int32_t cols_given = -1;   // as passed at creation (-1: derived)
@@ -278,6 +281,7 @@ struct CsrHandle {
     uint16_t *d_hkey = nullptr;
     uint16_t *d_hrmap = nullptr;    // rows: key of each row in its block
     int32_t *d_hb = nullptr;        // brow | bent | bsplit
+    int32_t *d_hold = nullptr;      // the caller's column of each (renamed columns)
     // band layout (when use_band)
     bool use_band = false;
     BandDesc band{};
@@ -293,6 +297,7 @@ struct CsrHandle {
     int32_t grid = 0;               // workgroups of the tile kernel
     int32_t fin_blocks = 0;         // workgroups of the finaliser
     Plan plan;
+    int32_t build = 0;              // kBuildAuto, _Once or _Hot
     // remembered host arrays (LILAC_KEEP_HOST or raw-call cache)
     const int32_t *h_row_ptr = nullptr, *h_col = nullptr;
     const void *h_vals = nullptr;
@@ -452,17 +457,30 @@ void launch_line_reuse(int32_t rows, const int32_t *rp, const int32_t *col,
 void panels_prepare();
 // Hot-column product (see HotDesc): hd.grid persistent workgroups take the
 // row blocks in turn; dot_part (or null) receives one partial per workgroup.
+// Where the layout renames columns (hd.old), xp (cols elements) receives x in
+// its order first; without xp the kernel looks every column up (same results).
 void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
-                     const Epi &epi, const void *w, double *dot_part, hipStream_t s);
-// cnt[r] = entries of row r with a column below hd.hot.
+                     const Epi &epi, const void *w, double *dot_part, void *xp,
+                     hipStream_t s);
+// cnt[r] = entries of row r with a column below hd.hot (newid: new number of
+// each column, or null).
 void launch_hot_count(const HotDesc &hd, const int32_t *rp, const int32_t *col,
-                      int32_t *cnt, hipStream_t s);
+                      const int32_t *newid, int32_t *cnt, hipStream_t s);
 // bsplit from the block bounds and the exclusive scan hx of the hot counts.
 void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
                       hipStream_t s);
 void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
-                        const int32_t *col, const void *vals, const int32_t *hx,
-                        void *hv, uint32_t *hrc, uint16_t *hkey, hipStream_t s);
+                        const int32_t *col, const void *vals, const int32_t *newid,
+                        const int32_t *hx, void *hv, uint32_t *hrc, uint16_t *hkey,
+                        hipStream_t s);
+// out[0..rows]: 1 for a row with entries, else 0; row keys from its exclusive
+// scan and the block bounds.
+void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_t s);
+void launch_hot_rmap(const HotDesc &hd, const int32_t *filled, uint16_t *rmap, hipStream_t s);
+// *out += entries 0, step, 2 step, ... whose column has a newid below hot.
+void launch_hot_share(int64_t nnz, int32_t step, const int32_t *col, const int32_t *newid,
+                      int32_t hot, int32_t *out, hipStream_t s);
+void launch_invert(int32_t n, const int32_t *p, int32_t *inv, hipStream_t s);
 // Finaliser for split rows: single matrix (items == null, n = nsplit) or a
 // list of (matrix, split row) items for grouped launches.
 void launch_split_finalize(lilac_dtype dt, const int32_t *items, int32_t n,
@@ -526,9 +544,10 @@ void launch_bfs_step(const MatDesc &m, int32_t nchunk, int32_t nlong, int32_t ro
 void launch_bfs_report(const int32_t *last, int32_t *host, hipStream_t s);
 
 // Relabelling of a graph's vertices by decreasing out-degree (locality of the
-// gathered vector): deg[u] = entries in column u; key = bucket of deg
+// gathered vector): deg[u] = entries in column u (of every step-th); key = bucket of deg
 // (powers of two, largest first); newid = stable position by key.
-void launch_count_cols(int64_t nnz, const int32_t *col, int32_t *deg, hipStream_t s);
+void launch_count_cols(int64_t nnz, int32_t step, const int32_t *col, int32_t *deg,
+                       hipStream_t s);
 void launch_degree_keys(int32_t n, const int32_t *deg, int32_t *key, hipStream_t s);
 constexpr int kDegKeys = 33;
 void launch_key_hist(int32_t n, const int32_t *key, int32_t *hist, int32_t nblk,
@@ -591,11 +610,14 @@ bool is_device_ptr(const void *p);
 std::recursive_mutex &lib_mutex();
 void set_last_error(const std::string &msg);
 int lib_device();
+// build: kBuildOnce for a handle of one product (no renamed columns: they take
+// many products to pay), kBuildHot for the hot-column layout whatever is tuned.
 // inputs_ready: device inputs are complete (the caller synchronised the
 // stream that wrote them), so no device-wide wait is needed.
 CsrHandle *create_handle(int rows, int cols, int64_t nnz, const int32_t *rp,
                          const int32_t *col, const void *vals, lilac_dtype dt,
-                         unsigned flags, bool inputs_ready = false);
+                         unsigned flags, bool inputs_ready = false,
+                         int32_t build = kBuildAuto);
 // A handle that takes over device arrays allocated with dev_alloc and
 // already holding the matrix: rp[rows+1], col and vals with room for
 // padded_nnz(nnz) entries.  They belong to the handle from the call on
@@ -608,10 +630,10 @@ CsrHandle *create_handle_adopt(int rows, int cols, int64_t nnz, int32_t *rp,
 void destroy_handle(CsrHandle *h);
 MatDesc make_desc(const CsrHandle &h, const void *x, void *y, const void *w,
                   double *chunk_part);
-// part: space for the groups of a split column-panel product (see
-// split_bytes), or null to take the stream's own.
+// part: space for the product (see product_space), or null to take the
+// stream's own.
 void spmv_enqueue(const CsrHandle &h, const void *x, void *y, const Epi &epi,
-                  const void *w, bool dot, hipStream_t s, double *part = nullptr);
+                  const void *w, bool dot, hipStream_t s, void *part = nullptr);
 void run_cg(CsrHandle &h, const double *b, double *x, int iters,
             unsigned flags, hipStream_t s, double *rho_out, int *iters_done);
 // Allocates the handle's CG state now (otherwise done on the first solve).

@@ -197,7 +197,7 @@ static bool release_spaces()
 // At most kSpaces buffers of kSpaceMax bytes are held, until lilac_finalize or
 // until an allocation would fail without them.  Called under the library lock.
 constexpr size_t kSpaces = 8;
-constexpr size_t kSpaceMax = (size_t)16 << 20;
+constexpr size_t kSpaceMax = (size_t)64 << 20;
 
 static void *stream_space(hipStream_t s, size_t bytes)
 {
@@ -458,6 +458,7 @@ static void free_analysis(CsrHandle &h)
     dev_free_reset(h.d_hkey);
     dev_free_reset(h.d_hrmap);
     dev_free_reset(h.d_hb);
+    dev_free_reset(h.d_hold);
     dev_free_reset(h.d_brc);
     dev_free_reset(h.d_bb);
     dev_free_reset(h.d_sv);
@@ -491,7 +492,8 @@ static int64_t analysis_bytes(const CsrHandle &h)
              (int64_t)h.pan.nblk * h.pan.np * (kPanelWaves + 1) * 4;
     if (h.use_hot)
         b += (h.nnz + kPad) * ((int64_t)dtype_size(h.dt) + 6) + (int64_t)h.rows * 2 +
-             (int64_t)(4 * h.hot.nblk + h.hot.grid + 3) * 4;
+             (int64_t)(4 * h.hot.nblk + h.hot.grid + 3) * 4 +
+             (h.hot.old ? (int64_t)h.cols * 4 : 0);
     if (h.use_band && h.band.nslice > 0)
         b += h.sell_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
              (int64_t)h.band.nslice * (int64_t)sizeof(SellSlice);
@@ -739,104 +741,135 @@ static bool hot_possible(const CsrHandle &h)
 // large blocks cost the fewest barriers; the assignment below balances
 // them).  Empty rows take no key, so a block of a graph's sparse tail
 // (where most rows are empty) spans more rows than kHotRows.
-static void build_hot(CsrHandle &h, hipStream_t s)
+// newid: the number the layout gives each column (by decreasing use), or null
+// to keep the caller's; old its inverse, which the handle takes over.
+static void fill_hot(CsrHandle &h, const HotDesc &hd, const int32_t *newid, hipStream_t s);
+
+static void build_hot(CsrHandle &h, hipStream_t s, const int32_t *newid = nullptr)
 {
     Context &c = ctx();
     HotDesc hd{};
     hd.rows = h.rows;
     hd.cols = h.cols;
     hd.hot = std::min<int32_t>(h.cols, hot_width((int)dtype_size(h.dt)));
+    hd.old = newid ? h.d_hold : nullptr;
     panels_prepare();
-    std::vector<int32_t> rp((size_t)h.rows + 1);
-    HIPC(hipMemcpyAsync(rp.data(), h.d_row_ptr, rp.size() * 4, hipMemcpyDeviceToHost, s));
-    HIPC(hipStreamSynchronize(s));
-    const int64_t target = std::max<int64_t>(16384, h.nnz / (int64_t)c.cu);
+    // non-empty rows before each row, on the device and here
+    std::vector<int32_t> rp((size_t)h.rows + 1), filled((size_t)h.rows + 1);
+    int32_t *d_filled = (int32_t *)tmp_alloc(filled.size() * 4);
     std::vector<int32_t> brow{0};
-    std::vector<uint16_t> rmap((size_t)h.rows);
-    int32_t start = 0, keys = 0;
-    for (int32_t r = 0; r < h.rows; ++r) {
-        const bool filled = rp[r + 1] > rp[r];
-        if (r > start && ((filled && keys >= kHotRows) || r - start >= kHotSpan ||
-                          (int64_t)rp[r] - rp[start] >= target)) {
-            brow.push_back(r);
-            start = r;
-            keys = 0;
+    try {
+        launch_row_filled(h.rows, h.d_row_ptr, d_filled, s);
+        launch_scan_excl(d_filled, (int64_t)h.rows + 1, nullptr, s);
+        HIPC(hipMemcpyAsync(rp.data(), h.d_row_ptr, rp.size() * 4, hipMemcpyDeviceToHost, s));
+        HIPC(hipMemcpyAsync(filled.data(), d_filled, filled.size() * 4, hipMemcpyDeviceToHost, s));
+        HIPC(hipStreamSynchronize(s));
+        const int64_t target = std::max<int64_t>(16384, h.nnz / (int64_t)c.cu);
+        for (int32_t start = 0;;) {
+            // the first row past the keys, the span or the entries of a block
+            const auto from = filled.begin() + start;
+            const int64_t by_keys =
+                std::upper_bound(from, filled.end(), *from + kHotRows) - filled.begin() - 1;
+            const int64_t by_span = (int64_t)start + kHotSpan;
+            const int64_t by_work =
+                std::lower_bound(rp.begin() + start + 1, rp.end(), rp[start] + target,
+                                 [](int32_t a, int64_t v) { return (int64_t)a < v; }) -
+                rp.begin();
+            const int64_t cut = std::min(by_keys, std::min(by_span, by_work));
+            if (cut >= h.rows)
+                break;
+            start = (int32_t)cut;
+            brow.push_back(start);
         }
-        rmap[r] = filled ? (uint16_t)keys++ : kHotEmpty;
-    }
-    brow.push_back(h.rows);
-    hd.nblk = (int32_t)brow.size() - 1;
-    hd.grid = std::min<int32_t>(hd.nblk, c.cu);
-    // blocks to workgroups: longest first, each to the least loaded
-    // workgroup so far (work = entries + rows), then each workgroup's blocks
-    // in ascending order.  Blocks differ a lot (the densest rows come first
-    // after relabelling), so taking every grid-th block leaves some
-    // workgroups a quarter more work than the mean.
-    std::vector<int32_t> owner((size_t)hd.nblk);
-    {
-        auto work = [&](int32_t b) {
-            return (int64_t)rp[brow[b + 1]] - rp[brow[b]] + (brow[b + 1] - brow[b]);
-        };
-        std::vector<int32_t> order((size_t)hd.nblk);
+        brow.push_back(h.rows);
+        hd.nblk = (int32_t)brow.size() - 1;
+        hd.grid = std::min<int32_t>(hd.nblk, c.cu);
+        // blocks to workgroups: longest first, each to the least loaded
+        // workgroup so far (work = entries + rows), then each workgroup's blocks
+        // in ascending order.  Blocks differ a lot (the densest rows come first
+        // after relabelling), so taking every grid-th block leaves some
+        // workgroups a quarter more work than the mean.
+        std::vector<int32_t> owner((size_t)hd.nblk);
+        {
+            auto work = [&](int32_t b) {
+                return (int64_t)rp[brow[b + 1]] - rp[brow[b]] + (brow[b + 1] - brow[b]);
+            };
+            std::vector<int32_t> order((size_t)hd.nblk);
+            for (int32_t b = 0; b < hd.nblk; ++b)
+                order[b] = b;
+            std::stable_sort(order.begin(), order.end(),
+                             [&](int32_t a, int32_t b) { return work(a) > work(b); });
+            typedef std::pair<int64_t, int32_t> Load;   // (work so far, workgroup)
+            std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
+            for (int32_t g = 0; g < hd.grid; ++g)
+                least.push(Load(0, g));
+            for (int32_t b : order) {
+                Load l = least.top();
+                least.pop();
+                owner[b] = l.second;
+                l.first += work(b);
+                least.push(l);
+            }
+        }
+        const size_t nb1 = (size_t)hd.nblk + 1;
+        std::vector<int32_t> hb(3 * nb1 - 1 + (size_t)hd.grid + 1 + hd.nblk);
+        for (int32_t b = 0; b <= hd.nblk; ++b) {
+            hb[b] = brow[b];
+            hb[nb1 + b] = rp[brow[b]];
+        }
+        int32_t *gptr = hb.data() + 3 * nb1 - 1;
+        int32_t *gblk = gptr + hd.grid + 1;
         for (int32_t b = 0; b < hd.nblk; ++b)
-            order[b] = b;
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int32_t a, int32_t b) { return work(a) > work(b); });
-        typedef std::pair<int64_t, int32_t> Load;   // (work so far, workgroup)
-        std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
+            ++gptr[owner[b] + 1];
         for (int32_t g = 0; g < hd.grid; ++g)
-            least.push(Load(0, g));
-        for (int32_t b : order) {
-            Load l = least.top();
-            least.pop();
-            owner[b] = l.second;
-            l.first += work(b);
-            least.push(l);
+            gptr[g + 1] += gptr[g];
+        {
+            std::vector<int32_t> fill(gptr, gptr + hd.grid);
+            for (int32_t b = 0; b < hd.nblk; ++b)
+                gblk[fill[owner[b]]++] = b;
         }
+        h.d_hb = (int32_t *)dev_alloc(hb.size() * 4);
+        HIPC(hipMemcpyAsync(h.d_hb, hb.data(), hb.size() * 4, hipMemcpyHostToDevice, s));
+        h.d_hrmap = (uint16_t *)dev_alloc((size_t)h.rows * 2);
+        hd.rmap = h.d_hrmap;
+        hd.brow = h.d_hb;
+        hd.bent = h.d_hb + nb1;
+        hd.bsplit = h.d_hb + 2 * nb1;
+        hd.gptr = h.d_hb + 3 * nb1 - 1;
+        hd.gblk = hd.gptr + hd.grid + 1;
+        launch_hot_rmap(hd, d_filled, h.d_hrmap, s);
+        HIPC(hipStreamSynchronize(s));
+    } catch (...) {
+        tmp_free(d_filled);
+        throw;
     }
-    const size_t nb1 = (size_t)hd.nblk + 1;
-    std::vector<int32_t> hb(3 * nb1 - 1 + (size_t)hd.grid + 1 + hd.nblk);
-    for (int32_t b = 0; b <= hd.nblk; ++b) {
-        hb[b] = brow[b];
-        hb[nb1 + b] = rp[brow[b]];
-    }
-    int32_t *gptr = hb.data() + 3 * nb1 - 1;
-    int32_t *gblk = gptr + hd.grid + 1;
-    for (int32_t b = 0; b < hd.nblk; ++b)
-        ++gptr[owner[b] + 1];
-    for (int32_t g = 0; g < hd.grid; ++g)
-        gptr[g + 1] += gptr[g];
-    {
-        std::vector<int32_t> fill(gptr, gptr + hd.grid);
-        for (int32_t b = 0; b < hd.nblk; ++b)
-            gblk[fill[owner[b]]++] = b;
-    }
-    h.d_hb = (int32_t *)dev_alloc(hb.size() * 4);
-    HIPC(hipMemcpyAsync(h.d_hb, hb.data(), hb.size() * 4, hipMemcpyHostToDevice, s));
-    h.d_hrmap = (uint16_t *)dev_alloc(rmap.size() * 2);
-    HIPC(hipMemcpyAsync(h.d_hrmap, rmap.data(), rmap.size() * 2, hipMemcpyHostToDevice, s));
-    hd.rmap = h.d_hrmap;
-    hd.brow = h.d_hb;
-    hd.bent = h.d_hb + nb1;
-    int32_t *bsplit = h.d_hb + 2 * nb1;
-    hd.bsplit = bsplit;
-    hd.gptr = h.d_hb + 3 * nb1 - 1;
-    hd.gblk = hd.gptr + hd.grid + 1;
+    tmp_free(d_filled);
+    const size_t vs = dtype_size(h.dt);
+    h.d_hv = dev_alloc((size_t)(h.nnz + kPad) * vs);
+    h.d_hrc = (uint32_t *)dev_alloc((size_t)(h.nnz + kPad) * 4);
+    h.d_hkey = (uint16_t *)dev_alloc((size_t)(h.nnz + kPad) * 2);
+    launch_fill_bytes_zero((char *)h.d_hv + h.nnz * vs, kPad * vs, s);
+    launch_fill_bytes_zero((char *)(h.d_hrc + h.nnz), kPad * 4, s);
+    // keys of hot entries are never used; keep every byte defined
+    launch_fill_bytes_zero(h.d_hkey, (h.nnz + kPad) * 2, s);
+    hd.vals = h.d_hv;
+    hd.rc = h.d_hrc;
+    hd.key = h.d_hkey;
+    fill_hot(h, hd, newid, s);
+    h.hot = hd;
+    h.use_hot = true;
+}
+
+// The entries of the hot-column copy (structure and values), from the CSR.
+static void fill_hot(CsrHandle &h, const HotDesc &hd, const int32_t *newid, hipStream_t s)
+{
     int32_t *hx = (int32_t *)tmp_alloc((size_t)(h.rows + 1) * 4);
     try {
         launch_fill_i32(hx + h.rows, 1, 0, s);
-        launch_hot_count(hd, h.d_row_ptr, h.d_col, hx, s);
+        launch_hot_count(hd, h.d_row_ptr, h.d_col, newid, hx, s);
         scan_total(hx, (int64_t)h.rows + 1, s);
-        launch_hot_split(hd, hx, bsplit, s);
-        const size_t vs = dtype_size(h.dt);
-        h.d_hv = dev_alloc((size_t)(h.nnz + kPad) * vs);
-        h.d_hrc = (uint32_t *)dev_alloc((size_t)(h.nnz + kPad) * 4);
-        h.d_hkey = (uint16_t *)dev_alloc((size_t)(h.nnz + kPad) * 2);
-        launch_fill_bytes_zero((char *)h.d_hv + h.nnz * vs, kPad * vs, s);
-        launch_fill_bytes_zero((char *)(h.d_hrc + h.nnz), kPad * 4, s);
-        // keys of hot entries are never used; keep every byte defined
-        launch_fill_bytes_zero(h.d_hkey, (h.nnz + kPad) * 2, s);
-        launch_hot_scatter(h.dt, hd, h.d_row_ptr, h.d_col, h.d_vals, hx, h.d_hv,
+        launch_hot_split(hd, hx, (int32_t *)hd.bsplit, s);
+        launch_hot_scatter(h.dt, hd, h.d_row_ptr, h.d_col, h.d_vals, newid, hx, h.d_hv,
                            h.d_hrc, h.d_hkey, s);
         HIPC(hipStreamSynchronize(s));
     } catch (...) {
@@ -844,11 +877,102 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         throw;
     }
     tmp_free(hx);
-    hd.vals = h.d_hv;
-    hd.rc = h.d_hrc;
-    hd.key = h.d_hkey;
-    h.hot = hd;
-    h.use_hot = true;
+}
+
+// New values into a hot-column copy: the arrays and their addresses stay.
+static void refill_hot(CsrHandle &h, hipStream_t s)
+{
+    int32_t *newid = nullptr;
+    try {
+        if (h.hot.old) {
+            newid = (int32_t *)dev_alloc((size_t)h.cols * 4);
+            launch_invert(h.cols, h.hot.old, newid, s);
+        }
+        fill_hot(h, h.hot, newid, s);
+    } catch (...) {
+        dev_free(newid);
+        throw;
+    }
+    dev_free(newid);
+}
+
+// Graph-like matrices: gather-heavy ones that suit no other layout (rows too
+// long for the column panels, or too many panels) get the hot-column layout
+// with the columns renamed by decreasing use, if the columns that fit the LDS
+// hold at least kHotShare of the entries.  The product copies x into that
+// order first.  R-MAT, float32, 16 entries a row: 2^18 vertices 40 -> 24 us,
+// 2^20 148 -> HOT20, 2^21 306 -> HOT21 (row-class tiles before); 2^16 10.9
+// against 13.5 us, hence kHotMinNnz.  The degrees are counted on a sample.
+constexpr int64_t kHotMinNnz = 3000000;
+constexpr double kHotShare = 0.3;
+constexpr int32_t kHotSample = 4;
+
+// newid[c]: number of column c of n by decreasing power of two of its entries
+// (among every step-th one), columns of one power in their order.
+static void rename_columns(int32_t n, int64_t nnz, int32_t step, const int32_t *col,
+                           int32_t *newid, hipStream_t s)
+{
+    const int32_t nblk = (int32_t)(((int64_t)n + kBlock - 1) / kBlock);
+    int32_t *deg = nullptr, *key = nullptr, *hist = nullptr;
+    try {
+        deg = (int32_t *)dev_alloc((size_t)n * 4);
+        key = (int32_t *)dev_alloc((size_t)n * 4);
+        hist = (int32_t *)dev_alloc((size_t)kDegKeys * nblk * 4);
+        launch_fill_i32(deg, n, 0, s);
+        launch_count_cols(nnz, step, col, deg, s);
+        launch_degree_keys(n, deg, key, s);
+        launch_key_hist(n, key, hist, nblk, s);
+        launch_scan_excl(hist, (int64_t)kDegKeys * nblk, nullptr, s);
+        launch_key_scatter(n, key, hist, nblk, newid, s);
+        HIPC(hipStreamSynchronize(s));
+    } catch (...) {
+        dev_free(deg);
+        dev_free(key);
+        dev_free(hist);
+        throw;
+    }
+    dev_free(deg);
+    dev_free(key);
+    dev_free(hist);
+}
+
+static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
+{
+    if (h.build == kBuildOnce || h.nnz < kHotMinNnz || h.cols <= 0 ||
+        h.line_ratio < kGatherHeavy || thread_account())
+        return false;
+    Context &c = ctx();
+    int32_t *newid = nullptr;
+    bool done = false;
+    try {
+        newid = (int32_t *)dev_alloc((size_t)h.cols * 4);
+        rename_columns(h.cols, h.nnz, kHotSample, h.d_col, newid, s);
+        const int32_t hot = std::min<int32_t>(h.cols, hot_width((int)dtype_size(h.dt)));
+        launch_fill_i32(c.total, 1, 0, s);
+        launch_hot_share(h.nnz, kHotSample, h.d_col, newid, hot, c.total, s);
+        int32_t in = 0;
+        HIPC(hipMemcpyAsync(&in, c.total, 4, hipMemcpyDeviceToHost, s));
+        HIPC(hipStreamSynchronize(s));
+        if ((double)in * kHotSample >= kHotShare * (double)h.nnz) {
+            h.d_hold = (int32_t *)dev_alloc((size_t)h.cols * 4);
+            launch_invert(h.cols, newid, h.d_hold, s);
+            build_hot(h, s, newid);
+            done = true;
+        }
+    } catch (const Error &e) {
+        dev_free(newid);
+        dev_free_reset(h.d_hv);
+        dev_free_reset(h.d_hrc);
+        dev_free_reset(h.d_hkey);
+        dev_free_reset(h.d_hrmap);
+        dev_free_reset(h.d_hb);
+        dev_free_reset(h.d_hold);
+        if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+            throw;
+        return false;   // the row-class tiles need no copy
+    }
+    dev_free(newid);
+    return done;
 }
 
 // Sliced form of the band layout (see SellSlice): when every slice of 64
@@ -1151,6 +1275,9 @@ static void analyse(CsrHandle &h, hipStream_t s)
     } else if (h.use_band || (want_band && build_band(h, s, h.plan.layout == LAYOUT_AUTO))) {
         h.grid = h.band.nblk;  // one fused-dot partial per row block
         h.fin_blocks = 0;
+    } else if (h.plan.layout == LAYOUT_AUTO && h.rows > 0 && build_hot_renamed(h, s)) {
+        h.grid = h.hot.grid;
+        h.fin_blocks = 0;
     }
     h.d_dot_part = (double *)dev_alloc((size_t)(std::max(h.grid, 1) + h.fin_blocks + 1) * 8);
     HIPC(hipStreamSynchronize(s));
@@ -1214,6 +1341,8 @@ static void construct(CsrHandle &h, int cols_given, const int32_t *rp,
     Plan tuned;
     if (tune_cache_lookup(h, tuned))
         h.plan = tuned;
+    if (h.build == kBuildHot)
+        h.plan.layout = LAYOUT_HOT;
     analyse(h, s);
     h.dev_bytes += analysis_bytes(h);
     h.dirty_struct = h.dirty_vals = false;
@@ -1224,7 +1353,7 @@ void destroy_handle(CsrHandle *h);
 CsrHandle *create_handle(int rows, int cols, int64_t nnz,
                                 const int32_t *rp, const int32_t *col,
                                 const void *vals, lilac_dtype dt,
-                                unsigned flags, bool inputs_ready)
+                                unsigned flags, bool inputs_ready, int32_t build)
 {
     if (rows < 0)
         fail(LILAC_ERR_ARG, "rows must be >= 0");
@@ -1249,6 +1378,7 @@ CsrHandle *create_handle(int rows, int cols, int64_t nnz,
     h->flags = flags;
     h->cols_given = cols;
     h->plan = default_plan();
+    h->build = build;
     try {
         construct(*h, cols, rp, col, vals, c.stream);
     } catch (...) {
@@ -1292,8 +1422,8 @@ struct CgState {
     int64_t n = 0;
     double *r = nullptr, *p = nullptr, *sv = nullptr, *w = nullptr, *part = nullptr;
     CgScalars *sc = nullptr;
-    double *split = nullptr;    // groups' sums of a split product
-    size_t split_cap = 0;
+    void *space = nullptr;      // of the products (product_space)
+    size_t space_cap = 0;
     struct G {
         const double *b;
         double *x;
@@ -1306,6 +1436,8 @@ struct CgState {
 
 struct PrState {
     float *tmp = nullptr;
+    void *space = nullptr;      // of the products (product_space)
+    size_t space_cap = 0;
     // vertices relabelled by decreasing out-degree (large graphs)
     CsrHandle *g = nullptr;
     int32_t *newid = nullptr;
@@ -1363,11 +1495,12 @@ void destroy_handle(CsrHandle *h)
         dev_free(h->cg->w);
         dev_free(h->cg->part);
         dev_free(h->cg->sc);
-        dev_free(h->cg->split);
+        dev_free(h->cg->space);
         delete h->cg;
     }
     if (h->pr) {
         dev_free(h->pr->tmp);
+        dev_free(h->pr->space);
         dev_free(h->pr->newid);
         dev_free(h->pr->xp);
         if (h->pr->g)
@@ -1386,12 +1519,14 @@ void destroy_handle(CsrHandle *h)
 // hot columns, the relabelled PageRank graph): rebuild those.
 static void values_changed(CsrHandle &h, hipStream_t s)
 {
-    if (h.use_panels || h.use_hot) {
+    if (h.use_panels) {
         h.dev_bytes -= analysis_bytes(h);
         analyse(h, s);
         h.dev_bytes += analysis_bytes(h);
         return;
     }
+    if (h.use_hot)
+        refill_hot(h, s);
     // the scan form of the band layout reads the CSR values; the sliced form
     // is filled again in place
     if (h.use_band && h.band.nslice > 0)
@@ -1443,26 +1578,34 @@ MatDesc make_desc(const CsrHandle &h, const void *x, void *y,
     return d;
 }
 
-// Bytes of the groups' sums of a split column-panel product (0: not split).
-static size_t split_bytes(const CsrHandle &h)
+// Bytes of device memory a product wants beside the handle's: the groups' sums
+// of a split column-panel product, x in the order of renamed hot columns (0:
+// none).
+static size_t product_space(const CsrHandle &h)
 {
+    if (h.use_hot && h.hot.old)
+        return (size_t)h.cols * dtype_size(h.dt);
     return h.use_panels && h.pan.col0 && h.pan.ng > 1 ? (size_t)h.pan.ng * h.rows * 8 : 0;
 }
 
 void spmv_enqueue(const CsrHandle &h, const void *x, void *y,
                          const Epi &epi, const void *w, bool dot,
-                         hipStream_t s, double *part)
+                         hipStream_t s, void *part)
 {
     if (h.rows == 0)
         return;
-    if (const size_t need = split_bytes(h)) {
+    if (const size_t need = product_space(h)) {
         // the space must not be given back between taking it and the launch
         std::lock_guard<std::recursive_mutex> lk(g_mu);
         if (!part)
-            part = (double *)stream_space(s, need);
+            part = stream_space(s, need);
+        if (h.use_hot) {
+            launch_spmv_hot(h.dt, h.hot, x, y, epi, w, dot ? h.d_dot_part : nullptr, part, s);
+            return;
+        }
         if (part) {
             launch_spmv_lane_groups(h.dt, h.pan, x, y, epi, w, dot ? h.d_dot_part : nullptr,
-                                    part, s);
+                                    (double *)part, s);
             return;
         }
     }
@@ -1471,7 +1614,7 @@ void spmv_enqueue(const CsrHandle &h, const void *x, void *y,
         return;
     }
     if (h.use_hot) {
-        launch_spmv_hot(h.dt, h.hot, x, y, epi, w, dot ? h.d_dot_part : nullptr, s);
+        launch_spmv_hot(h.dt, h.hot, x, y, epi, w, dot ? h.d_dot_part : nullptr, nullptr, s);
         return;
     }
     if (h.use_band) {
@@ -1584,7 +1727,7 @@ static void raw_spmv(int rows, const int32_t *rp, const int32_t *col,
     CsrHandle *h = nullptr;
     std::unique_ptr<CsrHandle, void (*)(CsrHandle *)> temp(nullptr, destroy_handle);
     if (mode == 1) {
-        temp.reset(create_handle(rows, -1, nnz, rp, col, vals, dt, 0));
+        temp.reset(create_handle(rows, -1, nnz, rp, col, vals, dt, 0, false, kBuildOnce));
         h = temp.get();
     } else {
         RawKey key{rp, col, vals, rows, nnz, (int)dt};
@@ -1735,14 +1878,14 @@ void handle_cg_prepare(CsrHandle &h) { cg_prepare(h); }
 // everything later launches read.
 static void cg_enqueue_state(const CsrHandle &h, const double *b, double *x, int iters,
                              double *r, double *p, double *sv, double *w, double *part,
-                             CgScalars *sc, hipStream_t s, double *split = nullptr)
+                             CgScalars *sc, hipStream_t s, void *space)
 {
     const int64_t n = h.rows;
     const int32_t np = blas1_parts(n);
     const int32_t ndot = h.grid + h.fin_blocks;
     launch_cg_init(n, b, x, r, p, sv, part, np, sc, s);
     for (int it = 0; it < iters; ++it) {
-        spmv_enqueue(h, r, w, epi_none(), r, true, s, split);
+        spmv_enqueue(h, r, w, epi_none(), r, true, s, space);
         launch_cg_step(n, sc, w, p, sv, x, r, h.d_dot_part, ndot, part, np, it, s);
     }
     launch_cg_final(sc, part, np, iters & 1, s);
@@ -1752,7 +1895,7 @@ static void cg_enqueue(const CsrHandle &h, const double *b, double *x,
                        int iters, hipStream_t s)
 {
     const CgState &st = *h.cg;
-    cg_enqueue_state(h, b, x, iters, st.r, st.p, st.sv, st.w, st.part, st.sc, s, st.split);
+    cg_enqueue_state(h, b, x, iters, st.r, st.p, st.sv, st.w, st.part, st.sc, s, st.space);
 }
 
 // ------------------------------------------------ CG without allocation
@@ -1768,7 +1911,7 @@ static void cg_enqueue(const CsrHandle &h, const double *b, double *x,
 constexpr int64_t kNoAllocRows = 1 << 20;
 constexpr size_t kNoAllocPart = 2 * kDotParts;
 constexpr size_t kNoAllocBytes =
-    4 * (size_t)kNoAllocRows * 8 + kNoAllocPart * 8 + sizeof(CgScalars);
+    5 * (size_t)kNoAllocRows * 8 + kNoAllocPart * 8 + sizeof(CgScalars);
 static __device__ __align__(256) char scratch[kNoAllocBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1843,18 +1986,18 @@ void run_cg(CsrHandle &h, const double *b, double *x, int iters,
         return;
     }
     cg_prepare(h);
-    // a solve owns the space of its split products: its graph keeps the address
-    const size_t need = thread_account() ? 0 : split_bytes(h);
-    if (need > h.cg->split_cap) {
+    // a solve owns the space of its products: its graph keeps the address
+    const size_t need = thread_account() ? 0 : product_space(h);
+    if (need > h.cg->space_cap) {
         drop_graphs(h);
-        dev_free_reset(h.cg->split);
-        h.cg->split_cap = 0;
+        dev_free_reset(h.cg->space);
+        h.cg->space_cap = 0;
         try {
-            h.cg->split = (double *)dev_alloc(need);
-            h.cg->split_cap = need;
+            h.cg->space = dev_alloc(need);
+            h.cg->space_cap = need;
         } catch (const Error &e) {
             if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
-                throw;   // without it the products are not split
+                throw;   // the products do without
         }
     }
     if (flags & LILAC_CG_GRAPH) {
@@ -1904,21 +2047,11 @@ static void build_relabel(CsrHandle &h, PrState &st)
     Context &c = ctx();
     hipStream_t s = c.stream;
     const int32_t n = h.rows;
-    const int32_t nblk = (n + kBlock - 1) / kBlock;
-    int32_t *deg = nullptr, *key = nullptr, *hist = nullptr, *rp2 = nullptr,
-            *col2 = nullptr;
+    int32_t *rp2 = nullptr, *col2 = nullptr;
     void *vals2 = nullptr;
     try {
-        deg = (int32_t *)dev_alloc((size_t)n * 4);
-        key = (int32_t *)dev_alloc((size_t)n * 4);
-        hist = (int32_t *)dev_alloc((size_t)kDegKeys * nblk * 4);
         st.newid = (int32_t *)dev_alloc((size_t)n * 4);
-        launch_fill_i32(deg, n, 0, s);
-        launch_count_cols(h.nnz, h.d_col, deg, s);
-        launch_degree_keys(n, deg, key, s);
-        launch_key_hist(n, key, hist, nblk, s);
-        launch_scan_excl(hist, (int64_t)kDegKeys * nblk, nullptr, s);
-        launch_key_scatter(n, key, hist, nblk, st.newid, s);
+        rename_columns(n, h.nnz, 1, h.d_col, st.newid, s);
         rp2 = (int32_t *)dev_alloc((size_t)(n + 1) * 4);
         launch_perm_lengths(n, h.d_row_ptr, st.newid, rp2, s);
         const int64_t total = scan_total(rp2, (int64_t)n + 1, s);
@@ -1929,29 +2062,17 @@ static void build_relabel(CsrHandle &h, PrState &st)
         launch_perm_entries(h.dt, n, h.nnz, h.d_row_ptr, h.d_col, h.d_vals, st.newid,
                             rp2, col2, vals2, s);
         HIPC(hipStreamSynchronize(s));
-        st.g = create_handle(n, h.cols, h.nnz, rp2, col2, vals2, h.dt, 0);
-        if (hot_possible(*st.g)) {
-            // after relabelling the most gathered columns come first: keep
-            // them in LDS (hot-column layout)
-            CsrHandle &g = *st.g;
-            g.dev_bytes -= analysis_bytes(g);
-            g.plan.layout = LAYOUT_HOT;
-            analyse(g, s);
-            g.dev_bytes += analysis_bytes(g);
-        }
+        // after relabelling the most gathered columns come first: the
+        // hot-column layout keeps them in LDS
+        st.g = create_handle(n, h.cols, h.nnz, rp2, col2, vals2, h.dt, 0, true,
+                             h.nnz > 0 ? kBuildHot : kBuildAuto);
         st.xp = (float *)dev_alloc((size_t)n * 4);
     } catch (...) {
-        dev_free(deg);
-        dev_free(key);
-        dev_free(hist);
         dev_free(rp2);
         dev_free(col2);
         dev_free(vals2);
         throw;
     }
-    dev_free(deg);
-    dev_free(key);
-    dev_free(hist);
     dev_free(rp2);
     dev_free(col2);
     dev_free(vals2);
@@ -1998,6 +2119,14 @@ static void run_pagerank(CsrHandle &h, float d, int iters, float *x,
         const bool relabel = h.rows >= kRelabelRows && h.cols <= h.rows;
         if (relabel && !st.g)
             build_relabel(h, st);
+        const size_t need = relabel ? 0 : product_space(h);
+        if (need > st.space_cap) {
+            drop_graphs(h);   // they hold the old address
+            dev_free_reset(st.space);
+            st.space_cap = 0;
+            st.space = dev_alloc(need);
+            st.space_cap = need;
+        }
         capture(g.graph, g.exec, [&](hipStream_t cs) {
             if (relabel) {
                 // iterate on the relabelled copy: x' = P x, ..., x = P^T x'
@@ -2012,7 +2141,7 @@ static void run_pagerank(CsrHandle &h, float d, int iters, float *x,
             }
             float *cur = x, *nxt = st.tmp;
             for (int it = 0; it < iters; ++it) {
-                spmv_enqueue(h, cur, nxt, epi, nullptr, false, cs);
+                spmv_enqueue(h, cur, nxt, epi, nullptr, false, cs, need ? st.space : nullptr);
                 std::swap(cur, nxt);
             }
             if (cur != x)
@@ -2979,9 +3108,11 @@ int lilac_cg_noalloc(lilac_csr_t hh, const double *b, double *x, int iters, void
         double *p = r + kNoAllocRows;
         double *sv = p + kNoAllocRows;
         double *w = sv + kNoAllocRows;
-        double *part = w + kNoAllocRows;
+        double *space = w + kNoAllocRows;   // of the products
+        double *part = space + kNoAllocRows;
         CgScalars *sc = (CgScalars *)(part + kNoAllocPart);
-        cg_enqueue_state(*h, b, x, iters, r, p, sv, w, part, sc, (hipStream_t)stream);
+        cg_enqueue_state(*h, b, x, iters, r, p, sv, w, part, sc, (hipStream_t)stream,
+                         product_space(*h) <= (size_t)kNoAllocRows * 8 ? space : nullptr);
     });
 }
 
