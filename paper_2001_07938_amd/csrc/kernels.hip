@@ -1867,16 +1867,19 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
     }
 }
 
-// xp[i] = x[old[i]]: x in the column order of a layout.
+// xp[newid[c]] = x[c]: x in the column order of a layout.  Columns of one power
+// of two of entries keep their order, so the stores of a wavefront fall on a
+// few ascending streams (2^20 float32: 3 us; reading x through the inverse
+// instead took 7.4).
 template <typename V>
-__global__ __launch_bounds__(kBlock) void k_gather_cols(int32_t n,
-                                                        const int32_t *__restrict__ old,
-                                                        const V *__restrict__ x,
-                                                        V *__restrict__ xp)
+__global__ __launch_bounds__(kBlock) void k_place_cols(int32_t n,
+                                                       const int32_t *__restrict__ newid,
+                                                       const V *__restrict__ x,
+                                                       V *__restrict__ xp)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < n)
-        xp[i] = gld(x + old[i]);
+        xp[newid[i]] = gld(x + i);
 }
 
 // ------------------------------------------------------------- band
@@ -2306,23 +2309,84 @@ __global__ __launch_bounds__(kBlock) void k_sell_pack(BandDesc bd,
     }
 }
 
-// Hot entries of each row: one wavefront per row, 64 entries at a time.
+// The rows of a workgroup of the two kernels below: 64 consecutive ones, whose
+// entries follow one another, less those of more than `most` entries; or (long
+// rows, `list` given) one such row alone, so that no workgroup has much more
+// than the others.
+struct HotRows {
+    int64_t row;      // this lane's row (rows: none)
+    int32_t a, z;     // its entries
+    __device__ __forceinline__ HotRows(int32_t rows, const int32_t *__restrict__ rp,
+                                       const int32_t *__restrict__ list)
+    {
+        const int lane = threadIdx.x & 63;
+        row = list ? (int64_t)list[blockIdx.x] + (lane ? rows : 0)
+                   : (int64_t)blockIdx.x * 64 + lane;
+        row = min(row, (int64_t)rows);
+        if (list && lane) {
+            a = z = rp[list[blockIdx.x] + 1];
+        } else {
+            a = rp[row];
+            z = rp[min(row + 1, (int64_t)rows)];
+        }
+    }
+};
+
+// Hot entries of each row, 64 entries to a wavefront at a time; lane l counts
+// the hot ones among those that are its row's.
 __global__ __launch_bounds__(kBlock) void k_hot_count(HotDesc hd,
                                                       const int32_t *__restrict__ rp,
                                                       const int32_t *__restrict__ col,
-                                                      const int32_t *__restrict__ newid,
-                                                      int32_t *__restrict__ cnt)
+                                                      const int32_t *__restrict__ list,
+                                                      int32_t most, int32_t *__restrict__ cnt)
 {
-    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (i >= hd.rows)
-        return;  // whole wavefronts
+    __shared__ int32_t sum[64];
+    constexpr int U = 4;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const HotRows R(hd.rows, rp, list);
+    if (threadIdx.x < 64)
+        sum[threadIdx.x] = 0;
+    __syncthreads();
+    const int32_t *newid = hd.newid;
+    uint64_t skip = list ? 0ull : __ballot(R.z - R.a > most);   // the long rows
     int32_t n = 0;
-    for (int32_t k = rp[i] + lane; k < rp[i + 1]; k += 64)
-        n += ((newid ? newid[col[k]] : col[k]) < hd.hot) ? 1 : 0;
-    n = wave_sum_i32(n);
-    if (lane == 0)
-        cnt[i] = n;
+    int64_t k0 = __builtin_amdgcn_readlane(R.a, 0);
+    const int64_t last = __builtin_amdgcn_readlane(R.z, 63);
+    for (;;) {
+        // entries up to the next long row
+        const int l = skip ? __builtin_ctzll(skip) : 64;
+        const int64_t k1 = l < 64 ? __builtin_amdgcn_readlane(R.a, l & 63) : last;
+        for (int64_t kb = k0 + wave * 64 * U; kb < k1; kb += kBlock * U) {
+            int32_t c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                c[u] = col[min(kb + u * 64 + lane, k1 - 1)];
+            if (newid) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    c[u] = newid[c[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t base = kb + u * 64;
+                const uint64_t m = __ballot(base + lane < k1 && c[u] < hd.hot);
+                const int64_t lo = max(R.a - base, (int64_t)0), hi = min(R.z - base, (int64_t)64);
+                if (lo < hi) {
+                    const uint64_t upto = hi == 64 ? ~0ull : (1ull << hi) - 1ull;
+                    n += __popcll(m & upto & ~((1ull << lo) - 1ull));
+                }
+            }
+        }
+        if (l == 64)
+            break;
+        k0 = __builtin_amdgcn_readlane(R.z, l & 63);
+        skip &= skip - 1;
+    }
+    if (n)
+        atomicAdd(&sum[lane], n);
+    __syncthreads();
+    if (threadIdx.x < 64 && R.row < hd.rows && (list ? lane == 0 : R.z - R.a <= most))
+        cnt[R.row] = sum[threadIdx.x];
 }
 
 // 1 for a row with entries, 0 for an empty one (and past the last row).
@@ -2396,54 +2460,115 @@ __global__ __launch_bounds__(kBlock) void k_hot_split(HotDesc hd,
     bsplit[b] = hd.bent[b] + (hx[hd.brow[b + 1]] - hx[hd.brow[b]]);
 }
 
-// Move each row's entries to the hot or cold part of its block (order kept
-// inside a row): one wavefront per row, positions from ballots.  hx:
-// exclusive scan of the per-row hot counts.
+// Moves the entries to the hot or cold part of their row's block, in their
+// order, 256 entries at a time; an entry's place follows from the hot entries
+// before it in the matrix: hx (the exclusive scan of the rows' counts) where
+// the workgroup's entries begin, plus those it has met.
 template <typename V>
 __global__ __launch_bounds__(kBlock) void k_hot_scatter(
     HotDesc hd, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-    const V *__restrict__ vals, const int32_t *__restrict__ newid,
+    const V *__restrict__ vals, const int32_t *__restrict__ list, int32_t most,
     const int32_t *__restrict__ hx, V *__restrict__ hv, uint32_t *__restrict__ hrc,
     uint16_t *__restrict__ hkey)
 {
-    const int64_t iw = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (iw >= hd.rows)
-        return;  // whole wavefronts
-    const int32_t i = (int32_t)iw;
-    // block of row i: the last b with brow[b] <= i
-    int32_t lo = 0, hi = hd.nblk - 1;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (hd.brow[mid] <= i)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    const int32_t b = lo;
-    const uint32_t rl = hd.rmap[i];   // used only if the row has entries
-    const int32_t before = hx[i] - hx[hd.brow[b]];   // hot entries of earlier rows
-    int32_t hp = hd.bent[b] + before;
-    int32_t cp = hd.bsplit[b] + (rp[i] - hd.bent[b]) - before;
-    const int32_t e = rp[i + 1];
-    for (int32_t base = rp[i]; base < e; base += 64) {
-        const int32_t k = base + lane;
-        const bool in = k < e;
-        const int32_t c = !in ? 0 : newid ? newid[col[k]] : col[k];
-        const bool hot = in && c < hd.hot;
-        const uint64_t mh = __ballot(hot), mc = __ballot(in && !hot);
-        if (hot) {
-            const int32_t pos = hp + lanes_below(mh);
-            hv[pos] = vals[k];
-            hrc[pos] = (rl << 16) | (uint32_t)c;
-        } else if (in) {
-            const int32_t pos = cp + lanes_below(mc);
-            hv[pos] = vals[k];
-            hrc[pos] = (uint32_t)c;
-            hkey[pos] = (uint16_t)rl;
+    // per row: first entry, what a hot (cold) entry's place adds to the hot
+    // (cold) entries before it in the matrix, key
+    __shared__ int32_t st[64], to_hot[64], to_cold[64];
+    __shared__ uint16_t key[64];
+    constexpr int U = 4;
+    __shared__ int32_t tot[U * kWaves];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const HotRows R(hd.rows, rp, list);
+    if (wave == 0) {
+        st[lane] = R.a;
+        if (R.row < hd.rows) {
+            int32_t lo = 0, hi = hd.nblk - 1;   // the last block that starts at or before it
+            while (lo < hi) {
+                const int32_t mid = (lo + hi + 1) >> 1;
+                if (hd.brow[mid] <= R.row)
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+            const int32_t before = hd.bent[lo] - hx[hd.brow[lo]];   // cold ones before it
+            to_hot[lane] = before;
+            to_cold[lane] = hd.bsplit[lo] - before;
+            key[lane] = hd.rmap[R.row];
         }
-        hp += __popcll(mh);
-        cp += __popcll(mc);
+    }
+    __syncthreads();
+    const int32_t *newid = hd.newid;
+    const int32_t hot_at = hx[R.row];   // hot entries before this lane's row
+    uint64_t skip = list ? 0ull : __ballot(R.z - R.a > most);   // the long rows
+    int64_t k0 = __builtin_amdgcn_readlane(R.a, 0);
+    int32_t done = __builtin_amdgcn_readlane(hot_at, 0);   // hot entries before kb
+    const int64_t last = __builtin_amdgcn_readlane(R.z, list ? 0 : 63);
+    for (;;) {
+        // entries up to the next long row
+        const int l = skip ? __builtin_ctzll(skip) : 64;
+        const int64_t k1 = l < 64 ? __builtin_amdgcn_readlane(R.a, l & 63) : last;
+        for (int64_t kb = k0; kb < k1; kb += kBlock * U) {
+            int32_t c[U];
+            V v[U];
+            uint64_t m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t k = min(kb + u * kBlock + threadIdx.x, k1 - 1);
+                c[u] = col[k];
+                v[u] = vals[k];
+            }
+            if (newid) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    c[u] = newid[c[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                m[u] = __ballot(kb + u * kBlock + threadIdx.x < k1 && c[u] < hd.hot);
+                if (lane == 0)
+                    tot[u * kWaves + wave] = __popcll(m[u]);
+            }
+            __syncthreads();
+            int32_t before = done;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) {
+                    if (w == wave) {
+                        const int64_t k = kb + u * kBlock + threadIdx.x;
+                        const int32_t hot = before + lanes_below(m[u]);
+                        if (k < k1) {
+                            int32_t lo = 0, hi = 63;   // the last row that starts at or before k
+                            while (lo < hi) {
+                                const int32_t mid = (lo + hi + 1) >> 1;
+                                if (st[mid] <= k)
+                                    lo = mid;
+                                else
+                                    hi = mid - 1;
+                            }
+                            if (c[u] < hd.hot) {
+                                const int64_t at = (int64_t)to_hot[lo] + hot;
+                                hv[at] = v[u];
+                                hrc[at] = ((uint32_t)key[lo] << 16) | (uint32_t)c[u];
+                            } else {
+                                const int64_t at = (int64_t)to_cold[lo] + (k - hot);
+                                hv[at] = v[u];
+                                hrc[at] = (uint32_t)c[u];
+                                hkey[at] = key[lo];
+                            }
+                        }
+                    }
+                    before += tot[u * kWaves + w];
+                }
+            }
+            done = before;
+            __syncthreads();   // tot is read
+        }
+        if (l == 64)
+            break;
+        k0 = __builtin_amdgcn_readlane(R.z, l & 63);
+        done = l < 63 ? __builtin_amdgcn_readlane(hot_at, (l + 1) & 63) : done;
+        skip &= skip - 1;
     }
 }
 
@@ -3941,22 +4066,27 @@ void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
     if (hd.old) {
         dim3 g(grid_for(hd.cols, kBlock, INT_MAX)), b(kBlock);
         if (dt == LILAC_F64)
-            hipLaunchKernelGGL(k_gather_cols<double>, g, b, 0, s, hd.cols, hd.old,
+            hipLaunchKernelGGL(k_place_cols<double>, g, b, 0, s, hd.cols, hd.newid,
                                (const double *)x, (double *)xp);
         else
-            hipLaunchKernelGGL(k_gather_cols<float>, g, b, 0, s, hd.cols, hd.old,
+            hipLaunchKernelGGL(k_place_cols<float>, g, b, 0, s, hd.cols, hd.newid,
                                (const float *)x, (float *)xp);
-        check_launch("k_gather_cols");
+        check_launch("k_place_cols");
         x = xp;
     }
     launch_hot<false>(dt, hd, x, y, epi, w, dot_part, s);
 }
 
 void launch_hot_count(const HotDesc &hd, const int32_t *rp, const int32_t *col,
-                      const int32_t *newid, int32_t *cnt, hipStream_t s)
+                      const int32_t *list, int32_t nlist, int32_t most, int32_t *cnt,
+                      hipStream_t s)
 {
-    hipLaunchKernelGGL(k_hot_count, dim3(grid_for((int64_t)hd.rows * 64, kBlock, INT_MAX)),
-                       dim3(kBlock), 0, s, hd, rp, col, newid, cnt);
+    hipLaunchKernelGGL(k_hot_count, dim3(grid_for(hd.rows, 64, INT_MAX)), dim3(kBlock), 0, s,
+                       hd, rp, col, (const int32_t *)nullptr, most, cnt);
+    check_launch("k_hot_count");
+    if (nlist > 0)
+        hipLaunchKernelGGL(k_hot_count, dim3(nlist), dim3(kBlock), 0, s, hd, rp, col, list, most,
+                           cnt);
     check_launch("k_hot_count");
 }
 
@@ -4000,18 +4130,22 @@ void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
 }
 
 void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
-                        const int32_t *col, const void *vals, const int32_t *newid,
-                        const int32_t *hx, void *hv, uint32_t *hrc, uint16_t *hkey,
-                        hipStream_t s)
+                        const int32_t *col, const void *vals, const int32_t *list,
+                        int32_t nlist, int32_t most, const int32_t *hx, void *hv, uint32_t *hrc,
+                        uint16_t *hkey, hipStream_t s)
 {
-    dim3 g(grid_for((int64_t)hd.rows * 64, kBlock, INT_MAX)), b(kBlock);
-    if (dt == LILAC_F64)
-        hipLaunchKernelGGL(k_hot_scatter<double>, g, b, 0, s, hd, rp, col,
-                           (const double *)vals, newid, hx, (double *)hv, hrc, hkey);
-    else
-        hipLaunchKernelGGL(k_hot_scatter<float>, g, b, 0, s, hd, rp, col,
-                           (const float *)vals, newid, hx, (float *)hv, hrc, hkey);
-    check_launch("k_hot_scatter");
+    auto go = [&](dim3 g, const int32_t *l) {
+        if (dt == LILAC_F64)
+            hipLaunchKernelGGL(k_hot_scatter<double>, g, dim3(kBlock), 0, s, hd, rp, col,
+                               (const double *)vals, l, most, hx, (double *)hv, hrc, hkey);
+        else
+            hipLaunchKernelGGL(k_hot_scatter<float>, g, dim3(kBlock), 0, s, hd, rp, col,
+                               (const float *)vals, l, most, hx, (float *)hv, hrc, hkey);
+        check_launch("k_hot_scatter");
+    };
+    go(dim3(grid_for(hd.rows, 64, INT_MAX)), nullptr);
+    if (nlist > 0)
+        go(dim3(nlist), list);
 }
 
 void panels_prepare()

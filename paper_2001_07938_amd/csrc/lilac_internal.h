@@ -184,7 +184,8 @@ struct HotDesc {
     const int32_t *bsplit;   // [nblk]
     const int32_t *gptr;     // [grid + 1]: workgroup g takes blocks gblk[gptr[g] .. gptr[g+1])
     const int32_t *gblk;     // [nblk]
-    const int32_t *old;      // [cols]: the caller's column of each, or null (the same)
+    const int32_t *newid;    // [cols]: number of the caller's column, or null (the same)
+    const int32_t *old;      // [cols]: its inverse
     int32_t rows, cols, nblk, hot, grid, pad;
 };
 constexpr int kHotRows = 1536;                        // non-empty rows per block
@@ -281,7 +282,7 @@ struct CsrHandle {
     uint16_t *d_hkey = nullptr;
     uint16_t *d_hrmap = nullptr;    // rows: key of each row in its block
     int32_t *d_hb = nullptr;        // brow | bent | bsplit
-    int32_t *d_hold = nullptr;      // the caller's column of each (renamed columns)
+    int32_t *d_hold = nullptr;      // renamed columns: newid | old
     // band layout (when use_band)
     bool use_band = false;
     BandDesc band{};
@@ -462,17 +463,18 @@ void panels_prepare();
 void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
                      const Epi &epi, const void *w, double *dot_part, void *xp,
                      hipStream_t s);
-// cnt[r] = entries of row r with a column below hd.hot (newid: new number of
-// each column, or null).
+// cnt[r] = entries of row r with a column below hd.hot (as hd.newid numbers
+// them).  list: the nlist rows of more than `most` entries.
 void launch_hot_count(const HotDesc &hd, const int32_t *rp, const int32_t *col,
-                      const int32_t *newid, int32_t *cnt, hipStream_t s);
+                      const int32_t *list, int32_t nlist, int32_t most, int32_t *cnt,
+                      hipStream_t s);
 // bsplit from the block bounds and the exclusive scan hx of the hot counts.
 void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
                       hipStream_t s);
 void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
-                        const int32_t *col, const void *vals, const int32_t *newid,
-                        const int32_t *hx, void *hv, uint32_t *hrc, uint16_t *hkey,
-                        hipStream_t s);
+                        const int32_t *col, const void *vals, const int32_t *list,
+                        int32_t nlist, int32_t most, const int32_t *hx, void *hv, uint32_t *hrc,
+                        uint16_t *hkey, hipStream_t s);
 // out[0..rows]: 1 for a row with entries, else 0; row keys from its exclusive
 // scan and the block bounds.
 void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_t s);

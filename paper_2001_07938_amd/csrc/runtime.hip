@@ -493,7 +493,7 @@ static int64_t analysis_bytes(const CsrHandle &h)
     if (h.use_hot)
         b += (h.nnz + kPad) * ((int64_t)dtype_size(h.dt) + 6) + (int64_t)h.rows * 2 +
              (int64_t)(4 * h.hot.nblk + h.hot.grid + 3) * 4 +
-             (h.hot.old ? (int64_t)h.cols * 4 : 0);
+             (h.hot.old ? (int64_t)h.cols * 8 : 0);
     if (h.use_band && h.band.nslice > 0)
         b += h.sell_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
              (int64_t)h.band.nslice * (int64_t)sizeof(SellSlice);
@@ -741,18 +741,18 @@ static bool hot_possible(const CsrHandle &h)
 // large blocks cost the fewest barriers; the assignment below balances
 // them).  Empty rows take no key, so a block of a graph's sparse tail
 // (where most rows are empty) spans more rows than kHotRows.
-// newid: the number the layout gives each column (by decreasing use), or null
-// to keep the caller's; old its inverse, which the handle takes over.
-static void fill_hot(CsrHandle &h, const HotDesc &hd, const int32_t *newid, hipStream_t s);
+// With h.d_hold set the layout renumbers the columns by it.
+static void fill_hot(CsrHandle &h, const HotDesc &hd, hipStream_t s);
 
-static void build_hot(CsrHandle &h, hipStream_t s, const int32_t *newid = nullptr)
+static void build_hot(CsrHandle &h, hipStream_t s)
 {
     Context &c = ctx();
     HotDesc hd{};
     hd.rows = h.rows;
     hd.cols = h.cols;
     hd.hot = std::min<int32_t>(h.cols, hot_width((int)dtype_size(h.dt)));
-    hd.old = newid ? h.d_hold : nullptr;
+    hd.newid = h.d_hold;
+    hd.old = h.d_hold ? h.d_hold + h.cols : nullptr;
     panels_prepare();
     // non-empty rows before each row, on the device and here
     std::vector<int32_t> rp((size_t)h.rows + 1), filled((size_t)h.rows + 1);
@@ -855,45 +855,31 @@ static void build_hot(CsrHandle &h, hipStream_t s, const int32_t *newid = nullpt
     hd.vals = h.d_hv;
     hd.rc = h.d_hrc;
     hd.key = h.d_hkey;
-    fill_hot(h, hd, newid, s);
+    fill_hot(h, hd, s);
     h.hot = hd;
     h.use_hot = true;
 }
 
 // The entries of the hot-column copy (structure and values), from the CSR.
-static void fill_hot(CsrHandle &h, const HotDesc &hd, const int32_t *newid, hipStream_t s)
+static void fill_hot(CsrHandle &h, const HotDesc &hd, hipStream_t s)
 {
+    // the rows of the last two classes are all rows above the bound before them
+    const int32_t *list = h.d_bin_rows + h.bin_off[C_WG];
+    const int32_t nlist = h.rows - h.bin_off[C_WG], most = h.plan.upper[C_W64];
     int32_t *hx = (int32_t *)tmp_alloc((size_t)(h.rows + 1) * 4);
     try {
         launch_fill_i32(hx + h.rows, 1, 0, s);
-        launch_hot_count(hd, h.d_row_ptr, h.d_col, newid, hx, s);
+        launch_hot_count(hd, h.d_row_ptr, h.d_col, list, nlist, most, hx, s);
         scan_total(hx, (int64_t)h.rows + 1, s);
         launch_hot_split(hd, hx, (int32_t *)hd.bsplit, s);
-        launch_hot_scatter(h.dt, hd, h.d_row_ptr, h.d_col, h.d_vals, newid, hx, h.d_hv,
-                           h.d_hrc, h.d_hkey, s);
+        launch_hot_scatter(h.dt, hd, h.d_row_ptr, h.d_col, h.d_vals, list, nlist, most, hx,
+                           h.d_hv, h.d_hrc, h.d_hkey, s);
         HIPC(hipStreamSynchronize(s));
     } catch (...) {
         tmp_free(hx);
         throw;
     }
     tmp_free(hx);
-}
-
-// New values into a hot-column copy: the arrays and their addresses stay.
-static void refill_hot(CsrHandle &h, hipStream_t s)
-{
-    int32_t *newid = nullptr;
-    try {
-        if (h.hot.old) {
-            newid = (int32_t *)dev_alloc((size_t)h.cols * 4);
-            launch_invert(h.cols, h.hot.old, newid, s);
-        }
-        fill_hot(h, h.hot, newid, s);
-    } catch (...) {
-        dev_free(newid);
-        throw;
-    }
-    dev_free(newid);
 }
 
 // Graph-like matrices: gather-heavy ones that suit no other layout (rows too
@@ -942,25 +928,24 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
         h.line_ratio < kGatherHeavy || thread_account())
         return false;
     Context &c = ctx();
-    int32_t *newid = nullptr;
-    bool done = false;
+    bool suits = false;
     try {
-        newid = (int32_t *)dev_alloc((size_t)h.cols * 4);
-        rename_columns(h.cols, h.nnz, kHotSample, h.d_col, newid, s);
+        h.d_hold = (int32_t *)dev_alloc((size_t)h.cols * 8);
+        rename_columns(h.cols, h.nnz, kHotSample, h.d_col, h.d_hold, s);
         const int32_t hot = std::min<int32_t>(h.cols, hot_width((int)dtype_size(h.dt)));
         launch_fill_i32(c.total, 1, 0, s);
-        launch_hot_share(h.nnz, kHotSample, h.d_col, newid, hot, c.total, s);
+        launch_hot_share(h.nnz, kHotSample, h.d_col, h.d_hold, hot, c.total, s);
         int32_t in = 0;
         HIPC(hipMemcpyAsync(&in, c.total, 4, hipMemcpyDeviceToHost, s));
         HIPC(hipStreamSynchronize(s));
-        if ((double)in * kHotSample >= kHotShare * (double)h.nnz) {
-            h.d_hold = (int32_t *)dev_alloc((size_t)h.cols * 4);
-            launch_invert(h.cols, newid, h.d_hold, s);
-            build_hot(h, s, newid);
-            done = true;
+        suits = (double)in * kHotSample >= kHotShare * (double)h.nnz;
+        if (suits) {
+            launch_invert(h.cols, h.d_hold, h.d_hold + h.cols, s);
+            build_hot(h, s);
+        } else {
+            dev_free_reset(h.d_hold);
         }
     } catch (const Error &e) {
-        dev_free(newid);
         dev_free_reset(h.d_hv);
         dev_free_reset(h.d_hrc);
         dev_free_reset(h.d_hkey);
@@ -971,8 +956,7 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
             throw;
         return false;   // the row-class tiles need no copy
     }
-    dev_free(newid);
-    return done;
+    return suits;
 }
 
 // Sliced form of the band layout (see SellSlice): when every slice of 64
@@ -1526,7 +1510,7 @@ static void values_changed(CsrHandle &h, hipStream_t s)
         return;
     }
     if (h.use_hot)
-        refill_hot(h, s);
+        fill_hot(h, h.hot, s);   // in place, as the sliced form below
     // the scan form of the band layout reads the CSR values; the sliced form
     // is filled again in place
     if (h.use_band && h.band.nslice > 0)
