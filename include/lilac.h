@@ -180,21 +180,31 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * copy of the matrix in which the columns are cut into panels that fit the
  * LDS and the rows into blocks; each workgroup stages one panel of x in LDS
  * at a time and gathers from there, with 16-bit column offsets.  Row
- * blocks hold at most 4096 rows, enough blocks for every CU but at least
- * the rows that weigh as much as one copy of x; the block's row sums and
- * one panel share the LDS.  It suits matrices whose
+ * blocks hold at most 4096 rows, enough blocks for every CU or, where such
+ * a block weighs less than one copy of x, the rows that weigh two; the
+ * block's row sums and one panel share the LDS.  A product of few blocks
+ * cuts the panels into groups, a workgroup each, whose sums meet in working
+ * memory of the stream (a workgroup that takes all groups, as in a batch or
+ * under capture, adds the same sums in the same order).  It suits matrices whose
  * non-zeros scatter over x; it is built only for at most 64 panels (else
  * the rows layout is used).  LILAC_LAYOUT_AUTO (the default) picks it for
  * gather-heavy matrices (sampled distinct 128-byte x lines per non-zero at
- * least 0.3, at least 16384 non-zeros) with no row longer than 1024 and
- * copies of x at most four times the matrix bytes.  Batched calls run all
+ * least 0.3, or at least 240 lines per 64 consecutive rows, and at least
+ * 16384 non-zeros) with no row longer than 1024 and copies of x at most four
+ * (in the second case two) times the matrix bytes.  Batched calls run all
  * column-panel matrices of a batch in one launch, with the same results.  LILAC_LAYOUT_HOT: a second copy for
  * matrices whose most referenced columns have the lowest indices (a graph
  * relabelled by decreasing out-degree, as lilac_pagerank does by itself for
  * graphs of at least 65536 vertices): the first 34560 (float32) or 17280
  * (float64) columns of x stay in LDS, the others are read from x in device
  * memory; rows are cut into blocks of at most 1536 non-empty rows (24576
- * rows in all) and about equal non-zeros, and empty rows take no row sum.  Built only on request and only for matrices with non-zeros;
+ * rows in all) and about equal non-zeros, and empty rows take no row sum.  Built on request for any matrix with
+ * non-zeros, and by LILAC_LAYOUT_AUTO, with the columns renamed by
+ * decreasing use, for gather-heavy matrices of at least 3,000,000 non-zeros
+ * that do not suit the column panels, if the columns that fit the LDS hold
+ * at least 30% of a sample of them: the product then first copies x into
+ * that order (working memory of the stream; without any, as under capture,
+ * every column is looked up, with the same results);
  * otherwise the rows layout is used (lilac_csr_info reports which).  Every
  * layout gives deterministic results.  LILAC_LAYOUT_BAND: the CSR order and
  * values with one extra 32-bit word per non-zero packing the row inside a
@@ -273,7 +283,7 @@ int lilac_cg(lilac_csr_t h, const double *b, double *x, int iters,
  * gives), for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation.  It
  * allocates nothing: the solver state (r, p, s, w, partial sums, scalars)
- * lives in one fixed device array of the library, 32 MiB per GPU, held from
+ * lives in one fixed device array of the library, 40 MiB per GPU, held from
  * the library's set-up until the process ends, which limits the matrix to
  * at most 1048576 rows (LILAC_ERR_ARG beyond).  The handle must be up to
  * date: after lilac_csr_invalidate it is refused with LILAC_ERR_STATE until

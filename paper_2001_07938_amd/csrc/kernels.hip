@@ -2399,6 +2399,47 @@ __global__ __launch_bounds__(kBlock) void k_row_filled(int32_t rows,
         out[i] = (i < rows && rp[i + 1] > rp[i]) ? 1 : 0;
 }
 
+// Block bounds of the hot-column layout.  Wavefront g cuts rows [g * part, (g +
+// 1) * part): a block ends before the row that would be its keys + 1st
+// non-empty one, or where it has `target` entries or kHotSpan rows.  Each test,
+// once true, stays true along the rows, so the end is found in three steps of
+// up to 64 rows each.  out[g * cap]: the number of blocks, then first row and
+// first entry of each.
+__global__ __launch_bounds__(64) void k_hot_blocks(int32_t rows, const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ filled,
+                                                   int32_t part, int32_t keys, int32_t target,
+                                                   int32_t cap, int32_t *__restrict__ out)
+{
+    constexpr int32_t S1 = kHotSpan / 64, S2 = S1 / 64;
+    static_assert(S2 * 64 * 64 == kHotSpan && S2 <= 64, "steps of the search");
+    const int lane = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * part;
+    const int32_t end = (int32_t)min(r0 + part, (int64_t)rows);
+    int32_t *o = out + (int64_t)blockIdx.x * cap;
+    int32_t start = (int32_t)r0, n = 0;
+    while (start < end) {
+        const int32_t f0 = filled[start], e0 = rp[start];
+        if (lane == 0 && 2 * n + 2 < cap) {
+            o[1 + 2 * n] = start;
+            o[2 + 2 * n] = e0;
+        }
+        ++n;
+        // the first lane whose row r ends a block that starts here
+        auto first = [&](int64_t r) {
+            const bool ends = r >= end || r - start >= kHotSpan || filled[r + 1] - f0 > keys ||
+                              (int64_t)rp[r] - e0 >= target;
+            return (int64_t)__builtin_ctzll(__ballot(ends) | 1ull << 63);
+        };
+        int64_t at = start;
+        at += first(at + (int64_t)(lane + 1) * S1) * S1;
+        at += first(at + (int64_t)(lane + 1) * S2) * S2;
+        at += first(at + min(lane, S2 - 1) + 1) + 1;
+        start = (int32_t)min(at, (int64_t)end);
+    }
+    if (lane == 0)
+        o[0] = n;
+}
+
 // Keys: the number of a row among the non-empty rows of its block.  filled:
 // exclusive scan of k_row_filled.
 __global__ __launch_bounds__(kBlock) void k_hot_rmap(HotDesc hd,
@@ -4095,6 +4136,14 @@ void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_
     hipLaunchKernelGGL(k_row_filled, dim3(grid_for((int64_t)rows + 1, kBlock, INT_MAX)),
                        dim3(kBlock), 0, s, rows, rp, out);
     check_launch("k_row_filled");
+}
+
+void launch_hot_blocks(int32_t rows, const int32_t *rp, const int32_t *filled, int32_t part,
+                       int32_t keys, int32_t target, int32_t cap, int32_t *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_hot_blocks, dim3(grid_for(rows, part, INT_MAX)), dim3(64), 0, s,
+                       rows, rp, filled, part, keys, target, cap, out);
+    check_launch("k_hot_blocks");
 }
 
 void launch_hot_rmap(const HotDesc &hd, const int32_t *filled, uint16_t *rmap, hipStream_t s)

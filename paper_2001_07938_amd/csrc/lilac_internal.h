@@ -478,6 +478,8 @@ void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
 // out[0..rows]: 1 for a row with entries, else 0; row keys from its exclusive
 // scan and the block bounds.
 void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_t s);
+void launch_hot_blocks(int32_t rows, const int32_t *rp, const int32_t *filled, int32_t part,
+                       int32_t keys, int32_t target, int32_t cap, int32_t *out, hipStream_t s);
 void launch_hot_rmap(const HotDesc &hd, const int32_t *filled, uint16_t *rmap, hipStream_t s);
 // *out += entries 0, step, 2 step, ... whose column has a newid below hot.
 void launch_hot_share(int64_t nnz, int32_t step, const int32_t *col, const int32_t *newid,
@@ -613,7 +615,7 @@ std::recursive_mutex &lib_mutex();
 void set_last_error(const std::string &msg);
 int lib_device();
 // build: kBuildOnce for a handle of one product (no renamed columns: they take
-// many products to pay), kBuildHot for the hot-column layout whatever is tuned.
+// many products to pay for), kBuildHot for the hot-column layout whatever is tuned.
 // inputs_ready: device inputs are complete (the caller synchronised the
 // stream that wrote them), so no device-wide wait is needed.
 CsrHandle *create_handle(int rows, int cols, int64_t nnz, const int32_t *rp,

@@ -734,8 +734,11 @@ static bool hot_possible(const CsrHandle &h)
     return h.rows > 0 && h.nnz > 0 && h.cols > 0;
 }
 
+// Rows whose block bounds one workgroup finds (a block does not cross them).
+constexpr int32_t kHotPart = 8 * kHotSpan;
+
 // Builds the hot-column copy of the matrix (see HotDesc).  Block bounds and
-// row keys are chosen on the host from row_ptr: a new block starts before a
+// row keys are found on the device: a new block starts before a
 // non-empty row when the current one has kHotRows non-empty rows, or when it
 // has at least one workgroup's share of the entries or kHotSpan rows (few,
 // large blocks cost the fewest barriers; the assignment below balances
@@ -754,34 +757,55 @@ static void build_hot(CsrHandle &h, hipStream_t s)
     hd.newid = h.d_hold;
     hd.old = h.d_hold ? h.d_hold + h.cols : nullptr;
     panels_prepare();
-    // non-empty rows before each row, on the device and here
-    std::vector<int32_t> rp((size_t)h.rows + 1), filled((size_t)h.rows + 1);
-    int32_t *d_filled = (int32_t *)tmp_alloc(filled.size() * 4);
-    std::vector<int32_t> brow{0};
+    // non-empty rows before each row, then the block bounds; the rows are cut
+    // kHotPart at a time, each part by a workgroup of its own
+    const int32_t target =
+        (int32_t)std::max<int64_t>(16384, h.nnz / (int64_t)c.cu);
+    const int32_t parts = (h.rows + kHotPart - 1) / kHotPart;
+    std::vector<int32_t> cuts;
+    int32_t *d_filled = (int32_t *)tmp_alloc(((size_t)h.rows + 1) * 4), *d_cuts = nullptr;
+    std::vector<int32_t> brow, bent;   // first row and first entry of each block
     try {
         launch_row_filled(h.rows, h.d_row_ptr, d_filled, s);
-        launch_scan_excl(d_filled, (int64_t)h.rows + 1, nullptr, s);
-        HIPC(hipMemcpyAsync(rp.data(), h.d_row_ptr, rp.size() * 4, hipMemcpyDeviceToHost, s));
-        HIPC(hipMemcpyAsync(filled.data(), d_filled, filled.size() * 4, hipMemcpyDeviceToHost, s));
-        HIPC(hipStreamSynchronize(s));
-        const int64_t target = std::max<int64_t>(16384, h.nnz / (int64_t)c.cu);
-        for (int32_t start = 0;;) {
-            // the first row past the keys, the span or the entries of a block
-            const auto from = filled.begin() + start;
-            const int64_t by_keys =
-                std::upper_bound(from, filled.end(), *from + kHotRows) - filled.begin() - 1;
-            const int64_t by_span = (int64_t)start + kHotSpan;
-            const int64_t by_work =
-                std::lower_bound(rp.begin() + start + 1, rp.end(), rp[start] + target,
-                                 [](int32_t a, int64_t v) { return (int64_t)a < v; }) -
-                rp.begin();
-            const int64_t cut = std::min(by_keys, std::min(by_span, by_work));
-            if (cut >= h.rows)
+        const int64_t filled = scan_total(d_filled, (int64_t)h.rows + 1, s);
+        // keys of a block.  Rows in decreasing order of their columns' use (no
+        // renaming): as many as fit.  Rows in no order: all blocks weigh about
+        // the same, so as many blocks as give every workgroup the same number;
+        // each part may end in a short one, so a little more is tried until
+        // they fit (R-MAT 2^20 float32, 352 blocks on 256 workgroups 77.4 us,
+        // 512 72.2; 2^22 312 and 294).
+        const int64_t slots = (int64_t)c.cu * ((filled + (int64_t)c.cu * kHotRows - 1) /
+                                               ((int64_t)c.cu * kHotRows));
+        int32_t keys = kHotRows;
+        if (h.d_hold && slots > 0)
+            keys = (int32_t)std::min<int64_t>(
+                kHotRows, std::max<int64_t>(kHotRows / 4, (filled + slots - 1) / slots));
+        const int32_t cap = (int32_t)(2 * (kHotPart / keys + kHotPart / kHotSpan +
+                                           h.nnz / target + 4));
+        cuts.resize((size_t)parts * cap);
+        d_cuts = (int32_t *)dev_alloc(cuts.size() * 4);
+        for (;;) {
+            launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, keys, target, cap, d_cuts,
+                              s);
+            HIPC(hipMemcpyAsync(cuts.data(), d_cuts, cuts.size() * 4, hipMemcpyDeviceToHost, s));
+            HIPC(hipStreamSynchronize(s));
+            brow.clear();
+            bent.clear();
+            for (int32_t g = 0; g < parts; ++g) {
+                const int32_t *o = cuts.data() + (size_t)g * cap;
+                if (2 * (int64_t)o[0] + 1 > cap)
+                    fail(LILAC_ERR_DEVICE, "more hot-column blocks than expected");
+                for (int32_t b = 0; b < o[0]; ++b) {
+                    brow.push_back(o[1 + 2 * b]);
+                    bent.push_back(o[2 + 2 * b]);
+                }
+            }
+            if (!h.d_hold || keys >= kHotRows || (int64_t)brow.size() <= slots)
                 break;
-            start = (int32_t)cut;
-            brow.push_back(start);
+            keys = std::min<int32_t>(kHotRows, keys + keys / 64 + 1);
         }
         brow.push_back(h.rows);
+        bent.push_back((int32_t)h.nnz);
         hd.nblk = (int32_t)brow.size() - 1;
         hd.grid = std::min<int32_t>(hd.nblk, c.cu);
         // blocks to workgroups: longest first, each to the least loaded
@@ -792,7 +816,7 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         std::vector<int32_t> owner((size_t)hd.nblk);
         {
             auto work = [&](int32_t b) {
-                return (int64_t)rp[brow[b + 1]] - rp[brow[b]] + (brow[b + 1] - brow[b]);
+                return (int64_t)bent[b + 1] - bent[b] + (brow[b + 1] - brow[b]);
             };
             std::vector<int32_t> order((size_t)hd.nblk);
             for (int32_t b = 0; b < hd.nblk; ++b)
@@ -815,7 +839,7 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         std::vector<int32_t> hb(3 * nb1 - 1 + (size_t)hd.grid + 1 + hd.nblk);
         for (int32_t b = 0; b <= hd.nblk; ++b) {
             hb[b] = brow[b];
-            hb[nb1 + b] = rp[brow[b]];
+            hb[nb1 + b] = bent[b];
         }
         int32_t *gptr = hb.data() + 3 * nb1 - 1;
         int32_t *gblk = gptr + hd.grid + 1;
@@ -841,9 +865,11 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         HIPC(hipStreamSynchronize(s));
     } catch (...) {
         tmp_free(d_filled);
+        dev_free(d_cuts);
         throw;
     }
     tmp_free(d_filled);
+    dev_free(d_cuts);
     const size_t vs = dtype_size(h.dt);
     h.d_hv = dev_alloc((size_t)(h.nnz + kPad) * vs);
     h.d_hrc = (uint32_t *)dev_alloc((size_t)(h.nnz + kPad) * 4);
@@ -886,9 +912,10 @@ static void fill_hot(CsrHandle &h, const HotDesc &hd, hipStream_t s)
 // long for the column panels, or too many panels) get the hot-column layout
 // with the columns renamed by decreasing use, if the columns that fit the LDS
 // hold at least kHotShare of the entries.  The product copies x into that
-// order first.  R-MAT, float32, 16 entries a row: 2^18 vertices 40 -> 24 us,
-// 2^20 148 -> HOT20, 2^21 306 -> HOT21 (row-class tiles before); 2^16 10.9
-// against 13.5 us, hence kHotMinNnz.  The degrees are counted on a sample.
+// order first.  R-MAT, float32, 16 entries a row: 2^18 vertices 40 -> 21 us,
+// 2^20 148 -> 70, 2^22 758 -> 294 (row-class tiles before; float64 49 -> 29, 183
+// -> 99, 917 -> 407); 2^16 10.9 against 13.5 us, hence kHotMinNnz.  The degrees
+// are counted on a sample.
 constexpr int64_t kHotMinNnz = 3000000;
 constexpr double kHotShare = 0.3;
 constexpr int32_t kHotSample = 4;
