@@ -4511,6 +4511,16 @@ void launch_stream(const void *src, void *dst, int64_t bytes, int32_t groups,
     check_launch("k_stream");
 }
 
+void launch_copy_bytes(const void *src, void *dst, int64_t bytes, hipStream_t s)
+{
+    const int64_t n = (bytes + 15) / 16;
+    if (n <= 0)
+        return;
+    hipLaunchKernelGGL(k_copy<i32x4>, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s, n,
+                       (const i32x4 *)src, (i32x4 *)dst);
+    check_launch("k_copy");
+}
+
 void launch_copy_f64(int64_t n, const double *src, double *dst, hipStream_t s)
 {
     if (n <= 0)
