@@ -3669,6 +3669,165 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(
     }
 }
 
+// Iterations of a small sliced band matrix in one kernel each: a step and the
+// next product together, which leaves one launch and one grid-wide dependence
+// per iteration instead of two.  Iteration k reads r, s and w = A r (index 0)
+// with the partials of r.r and r.w, updates p and x of its own rows, and
+// writes the new r, s (index 1) and the new w = A r: the r of a gathered column
+// is formed again from that column's old r, s and w, by the operations its own
+// row uses, so no workgroup waits for another's update.  Three gathers for
+// one, so only where launches, not entries, are the cost.  What does not need
+// the scalars (own vectors, the slice's first entries and their gathers) is
+// read before they are summed.
+struct CgVecs {
+    const double *r0, *s0, *w0;
+    double *r1, *s1, *w1, *p, *x;
+};
+
+__global__ __launch_bounds__(kBandThreads) void k_cg_sell(
+    BandDesc bd, CgVecs v, CgScalars *__restrict__ sc, const double *__restrict__ rr,
+    int32_t nrr, const double *__restrict__ rw, double *__restrict__ rr1,
+    double *__restrict__ rw1, int32_t k, int32_t last)
+{
+    __shared__ double lds[2 * kWaves];
+    typedef SellGroup<double, 4> Quad;
+    const int32_t par = k & 1;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int32_t b = xcd_block(blockIdx.x, bd.nblk);
+    const int32_t done = sc->done;
+    const double g_old = sc->gamma[par ^ 1], a_old = sc->alpha[par ^ 1];
+    double g = 0.0, d = 0.0;
+    for (int32_t i = threadIdx.x; i < nrr; i += kBandThreads)
+        g += rr[i];
+    for (int32_t i = threadIdx.x; i < bd.nblk; i += kBandThreads)
+        d += rw[i];
+    // a column's r, s and w as they are gathered
+    struct Old {
+        double r, s, w;
+    };
+    auto gather = [&](int32_t base, uint16_t off) {
+        const int32_t c = base + off;
+        return Old{gld(v.r0 + c), gld(v.s0 + c), gld(v.w0 + c)};
+    };
+    double alpha = 0.0, beta = 0.0;
+    auto now = [&](const Old &o) { return fma(-alpha, fma(beta, o.s, o.w), o.r); };
+    bool first = true;
+    double arr = 0.0, arw = 0.0;
+    const int32_t send = min((b + 1) * bd.spb, bd.nslice);
+    for (int32_t s = b * bd.spb + wave; first || s < send; s += kBandWaves) {
+        // (a wavefront without a slice takes part in the sums)
+        const bool have = s < send;
+        i32x4 sl{0, 0, 0, 0};
+        if (have)
+            sl = *(const __attribute__((address_space(4))) i32x4 *)(bd.slice + s);
+        const int32_t row = s * 64 + lane;
+        const bool mine = have && row < bd.rows;
+        const double *pv = (const double *)bd.vals + (int64_t)sl.x * 64;
+        const uint16_t *po = bd.off + (int64_t)sl.x * 64;
+        const int32_t width = last ? 0 : sl.w;   // the last iteration needs no product
+        const int32_t nq = width >> 2, tail = width & ~3;
+        Old own{0.0, 0.0, 0.0};
+        double p = 0.0, x = 0.0;
+        int32_t len = width;
+        if (mine) {
+            own = Old{gld(v.r0 + row), gld(v.s0 + row), gld(v.w0 + row)};
+            p = gld(v.p + row);
+            x = gld(v.x + row);
+        }
+        if (sl.z < width)
+            len = mine ? gld(bd.row_ptr + row + 1) - gld(bd.row_ptr + row) : 0;
+        Quad q0, q1;
+        SellGroup<double, 2> pr;
+        double v1 = 0.0;
+        uint16_t o1 = 0;
+        if (nq > 0)
+            q0.load(pv, po, lane);
+        if (nq > 1)
+            q1.load(pv + 256, po + 256, lane);
+        if (width & 2)
+            pr.load(pv + tail * 64, po + tail * 64, lane);
+        if (width & 1) {
+            v1 = ld_stream(pv + (width - 1) * 64 + lane);
+            o1 = ld_stream(po + (width - 1) * 64 + lane);
+        }
+        Old g0[4], g1[4], gp[2], gl{0.0, 0.0, 0.0};
+        if (nq > 0)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                g0[t] = gather(sl.y, q0.o[t]);
+        if (nq > 1)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                g1[t] = gather(sl.y, q1.o[t]);
+        if (width & 2) {
+            gp[0] = gather(sl.y, pr.o.x);
+            gp[1] = gather(sl.y, pr.o.y);
+        }
+        if (width & 1)
+            gl = gather(sl.y, o1);
+        if (first) {
+            first = false;
+            if (done)
+                return;   // every wavefront of the launch
+            block_sum2(g, d, lds);
+            beta = (k > 0) ? g / g_old : 0.0;
+            const double pap = d - beta * g / a_old;
+            if (g == 0.0 || pap == 0.0) {
+                if (blockIdx.x == 0 && threadIdx.x == 0) {
+                    sc->done = 1;
+                    sc->rho = g;
+                }
+                return;
+            }
+            alpha = g / pap;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                sc->gamma[par] = g;
+                sc->alpha[par] = alpha;
+                sc->iters = k + 1;
+            }
+        }
+        if (!have)
+            break;
+        double acc = 0.0;
+        auto add = [&](int32_t j, double val, const Old &o) {
+            if (j < len)
+                acc = fma(val, now(o), acc);
+        };
+        if (nq > 0)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                add(t, q0.val(t), g0[t]);
+        if (nq > 1)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                add(4 + t, q1.val(t), g1[t]);
+        if (width & 2) {
+            add(tail, pr.val(0), gp[0]);
+            add(tail + 1, pr.val(1), gp[1]);
+        }
+        if (width & 1)
+            add(width - 1, v1, gl);
+        if (mine) {
+            const double si = fma(beta, own.s, own.w);
+            const double pi = fma(beta, p, own.r);
+            const double ri = fma(-alpha, si, own.r);
+            v.p[row] = pi;
+            v.x[row] = fma(alpha, pi, x);
+            v.s1[row] = si;
+            v.r1[row] = ri;
+            v.w1[row] = acc;
+            arr = fma(ri, ri, arr);
+            arw = fma(ri, acc, arw);
+        }
+    }
+    block_sum2(arr, arw, lds);
+    if (threadIdx.x == 0) {
+        rr1[b] = arr;
+        rw1[b] = arw;
+    }
+}
+
 // After the last iteration: rho = r.r of the final residual (partials in
 // rr[par]), unless the solve stopped early (rho was set then).
 __global__ __launch_bounds__(1024) void k_cg_final(CgScalars *__restrict__ sc,
@@ -4554,6 +4713,17 @@ void launch_cg_step(int64_t n, CgScalars *sc, const double *w, double *p, double
     hipLaunchKernelGGL(k_cg_step, dim3(nparts), dim3(kBlock), 0, s, n, sc, w, p, sv, x, r,
                        dot_part, ndot, rr, nparts, k);
     check_launch("k_cg_step");
+}
+
+void launch_cg_sell(const BandDesc &bd, const CgFused &f, CgScalars *sc, const double *rr,
+                    int32_t nrr, const double *rw, double *rr1, double *rw1, int32_t k,
+                    bool last, hipStream_t s)
+{
+    const int i = k & 1;
+    const CgVecs v{f.r[i], f.s[i], f.w[i], f.r[i ^ 1], f.s[i ^ 1], f.w[i ^ 1], f.p, f.x};
+    hipLaunchKernelGGL(k_cg_sell, dim3(bd.nblk), dim3(kBandThreads), 0, s, bd, v, sc, rr, nrr,
+                       rw, rr1, rw1, k, last ? 1 : 0);
+    check_launch("k_cg_sell");
 }
 
 void launch_cg_final(CgScalars *sc, const double *rr, int32_t nparts, int32_t par,

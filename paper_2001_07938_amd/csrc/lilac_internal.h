@@ -291,6 +291,7 @@ struct CsrHandle {
     void *d_sv = nullptr;           // sliced form: values | offsets | slices
     uint16_t *d_so = nullptr;       // the offsets in it
     int64_t sell_cols = 0;          // columns of 64 entries it holds
+    int32_t sell_wide = 0;          // longest row
     std::vector<int32_t> bin_off;   // NCLASS+1
     int64_t nchunks = 0;
     int32_t nsplit = 0;
@@ -606,6 +607,15 @@ void launch_cg_init(int64_t n, const double *b, double *x, double *r, double *p,
 void launch_cg_step(int64_t n, CgScalars *sc, const double *w, double *p, double *sv,
                     double *x, double *r, const double *dot_part, int32_t ndot, double *rr,
                     int32_t nparts, int32_t k, hipStream_t s);
+// Iteration k of a sliced band matrix, the step and the next product in one
+// kernel: vectors by parity of the iteration, nrr partials of r.r and bd.nblk
+// of r.w in, bd.nblk of each out (last: no product).
+struct CgFused {
+    double *r[2], *s[2], *w[2], *p, *x;
+};
+void launch_cg_sell(const BandDesc &bd, const CgFused &f, CgScalars *sc, const double *rr,
+                    int32_t nrr, const double *rw, double *rr1, double *rw1, int32_t k,
+                    bool last, hipStream_t s);
 void launch_cg_final(CgScalars *sc, const double *rr, int32_t nparts, int32_t par,
                      hipStream_t s);
 int32_t blas1_parts(int64_t n);

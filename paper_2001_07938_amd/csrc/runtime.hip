@@ -1056,6 +1056,7 @@ static bool build_sell(CsrHandle &h, hipStream_t s)
         return false;   // the scan form needs less (no copy of the values)
     }
     h.sell_cols = at;
+    h.sell_wide = widest;
     h.d_so = (uint16_t *)((char *)h.d_sv + vbytes);
     void *d_slices = (char *)h.d_so + obytes;
     HIPC(hipMemcpyAsync(d_slices, slices.data(), slices.size() * sizeof(SellSlice),
@@ -1429,6 +1430,9 @@ CsrHandle *create_handle_adopt(int rows, int cols, int64_t nnz, int32_t *rp,
     }
     return h;
 }
+
+// Partial sums of a solve: r.r and r.w, two parities each.
+constexpr size_t kCgParts = 4 * kDotParts;
 
 struct CgState {
     int64_t n = 0;
@@ -1899,7 +1903,7 @@ static void cg_prepare(CsrHandle &h)
         st->p = (double *)dev_alloc((size_t)h.rows * 8);
         st->sv = (double *)dev_alloc((size_t)h.rows * 8);
         st->w = (double *)dev_alloc((size_t)h.rows * 8);
-        st->part = (double *)dev_alloc((size_t)2 * kDotParts * 8);
+        st->part = (double *)dev_alloc((size_t)kCgParts * 8);
         st->sc = (CgScalars *)dev_alloc(sizeof(CgScalars));
     } catch (...) {
         dev_free(st->r);
@@ -1915,6 +1919,28 @@ static void cg_prepare(CsrHandle &h)
 
 void handle_cg_prepare(CsrHandle &h) { cg_prepare(h); }
 
+// Whether a solve runs as one kernel per iteration (k_cg_sell): a sliced band
+// matrix of few rows (one round of workgroups, two to a CU) that are short
+// enough for all their gathers to be on their way before the scalars are known.
+// 50 iterations, two kernels each against one: 7-point stencils of 16^3 309 and
+// 264 us, 32^3 349 and 274, 44^3 442 and 383, 63^3 (977 workgroups) 664 and 767;
+// 27-point 16^3 370 and 405, 32^3 448 and 496.
+constexpr int32_t kFuseBlocks = 512;
+constexpr int32_t kFuseWidth = 11;
+static_assert(kFuseBlocks <= kDotParts, "one partial per workgroup");
+
+static bool cg_fuses(const CsrHandle &h)
+{
+    return h.dt == LILAC_F64 && h.use_band && h.band.nslice > 0 &&
+           h.band.nblk <= kFuseBlocks && h.sell_wide <= kFuseWidth;
+}
+
+// Bytes a solve wants beside its state: three more vectors, or the products'.
+static size_t cg_space(const CsrHandle &h)
+{
+    return cg_fuses(h) ? (size_t)h.rows * 3 * 8 : product_space(h);
+}
+
 // One whole solve: initialisation, then `iters` iterations of two kernels
 // (the product w = A r with the w.r partials fused into it; the scalars and
 // the p, s, x, r updates with the next r.r partials), then the final r.r.
@@ -1929,6 +1955,21 @@ static void cg_enqueue_state(const CsrHandle &h, const double *b, double *x, int
     const int32_t np = blas1_parts(n);
     const int32_t ndot = h.grid + h.fin_blocks;
     launch_cg_init(n, b, x, r, p, sv, part, np, sc, s);
+    if (cg_fuses(h) && space && iters > 0) {
+        // part: r.r by parity, then r.w by parity
+        double *more = (double *)space;
+        const CgFused f{{r, more}, {sv, more + n}, {w, more + 2 * n}, p, x};
+        double *rw = part + 2 * kDotParts;
+        launch_spmv_band(h.dt, h.band, r, w, epi_none(), r, rw, s);
+        for (int it = 0; it < iters; ++it) {
+            const int c = it & 1, o = c ^ 1;
+            launch_cg_sell(h.band, f, sc, part + c * kDotParts, it ? h.band.nblk : np,
+                           rw + c * kDotParts, part + o * kDotParts, rw + o * kDotParts, it,
+                           it + 1 == iters, s);
+        }
+        launch_cg_final(sc, part, h.band.nblk, iters & 1, s);
+        return;
+    }
     for (int it = 0; it < iters; ++it) {
         spmv_enqueue(h, r, w, epi_none(), r, true, s, space);
         launch_cg_step(n, sc, w, p, sv, x, r, h.d_dot_part, ndot, part, np, it, s);
@@ -1954,7 +1995,7 @@ static void cg_enqueue(const CsrHandle &h, const double *b, double *x,
 // stand-in for the symbol: its device address, per device, comes from
 // hipGetSymbolAddress and only that address is handed to kernels.
 constexpr int64_t kNoAllocRows = 1 << 20;
-constexpr size_t kNoAllocPart = 2 * kDotParts;
+constexpr size_t kNoAllocPart = kCgParts;
 constexpr size_t kNoAllocBytes =
     5 * (size_t)kNoAllocRows * 8 + kNoAllocPart * 8 + sizeof(CgScalars);
 static __device__ __align__(256) char scratch[kNoAllocBytes];
@@ -2032,7 +2073,7 @@ void run_cg(CsrHandle &h, const double *b, double *x, int iters,
     }
     cg_prepare(h);
     // a solve owns the space of its products: its graph keeps the address
-    const size_t need = thread_account() ? 0 : product_space(h);
+    const size_t need = thread_account() ? 0 : cg_space(h);
     if (need > h.cg->space_cap) {
         drop_graphs(h);
         dev_free_reset(h.cg->space);
@@ -3160,7 +3201,7 @@ int lilac_cg_noalloc(lilac_csr_t hh, const double *b, double *x, int iters, void
         double *part = space + kNoAllocRows;
         CgScalars *sc = (CgScalars *)(part + kNoAllocPart);
         cg_enqueue_state(*h, b, x, iters, r, p, sv, w, part, sc, (hipStream_t)stream,
-                         product_space(*h) <= (size_t)kNoAllocRows * 8 ? space : nullptr);
+                         cg_space(*h) <= (size_t)kNoAllocRows * 8 ? space : nullptr);
     });
 }
 
