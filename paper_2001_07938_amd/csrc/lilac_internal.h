@@ -27,6 +27,12 @@ constexpr int kBlock = 256;       // threads per workgroup (4 wave64)
 constexpr int kWaves = kBlock / 64;
 constexpr int kPad = 64;          // device arrays of nnz are padded to this
 constexpr int kDotParts = 1024;   // partials of a standalone dot
+// Pieces of each vector in flight per thread: 2^26 float64 elements, 2, 4 and 8
+// of them 163, 158 and 159 us (one element at a time 171; float32 145 -> 79).
+constexpr int kDotAhead = 4;
+// Vectors up to here take one workgroup and one launch: 16,000 float64 elements
+// 10.1 -> 7.0 us a call; 40,000 by one workgroup 11.1 against 10.1.
+constexpr int64_t kDotSmall = 16384;
 
 // One unit of work of a product: `count` rows of class `cls`, taken from the
 // class-ordered row list at `first` (for C_SPLIT: chunk index `first`).
@@ -521,10 +527,10 @@ void launch_cgb_init(const CgSeg *segs, int32_t nseg, int32_t blocks, hipStream_
 void launch_cgb_rw(const CgSeg *segs, int32_t nseg, int32_t blocks, hipStream_t s);
 void launch_cgb_step(const CgSeg *segs, int32_t nseg, int32_t blocks, hipStream_t s);
 
-void launch_dot_parts(int64_t n, const double *a, const double *b,
-                      double *part, int32_t nparts, hipStream_t s);
-void launch_dot_parts_f32(int64_t n, const float *a, const float *b,
-                          double *part, int32_t nparts, hipStream_t s);
+// *out = a . b (part: kDotParts doubles of scratch); a float32 result is the
+// binary64 total rounded once.
+template <typename T, typename TOut>
+void launch_dot(int64_t n, const T *a, const T *b, double *part, TOut *out, hipStream_t s);
 
 // Breadth-first search by Boolean products.  bits: three frontier bitmaps of
 // `words` words (bfs_words of the rows), todo: a 64-bit word for each 64 rows,
@@ -583,8 +589,6 @@ void launch_spmv_jds(int32_t rows, int32_t max_len, const int32_t *perm,
                      const int32_t *status, int32_t *host_status, hipStream_t s);
 void launch_sum_parts(const double *part, int32_t nparts, double *out,
                       hipStream_t s);
-void launch_sum_parts_f32(const double *part, int32_t nparts, float *out,
-                          hipStream_t s);
 // Bytes between device and pinned host memory, both 16-byte aligned and with
 // room for whole 16-byte pieces.
 void launch_copy_bytes(const void *src, void *dst, int64_t bytes, hipStream_t s);

@@ -1878,12 +1878,7 @@ static double raw_dot(int64_t n, const T *a, const T *b)
             db = (const T *)c.dot_b;
         }
     }
-    const int32_t np = blas1_parts(n);
-    if constexpr (std::is_same<T, float>::value)
-        launch_dot_parts_f32(n, da, db, c.dot_part, np, s);
-    else
-        launch_dot_parts(n, da, db, c.dot_part, np, s);
-    launch_sum_parts(c.dot_part, np, c.dot_part + kDotParts, s);
+    launch_dot(n, da, db, c.dot_part, c.dot_part + kDotParts, s);
     double r = 0.0;
     HIPC(hipMemcpyAsync(&r, c.dot_part + kDotParts, 8, hipMemcpyDeviceToHost, s));
     HIPC(hipStreamSynchronize(s));
@@ -3143,16 +3138,12 @@ int lilac_dot_dev(int64_t n, const void *a, const void *b, void *out, lilac_dtyp
         if (!a || !b)
             fail(LILAC_ERR_ARG, "NULL vector");
         Context &c = ctx();
-        const int32_t np = blas1_parts(n);
         // partials in the library's scratch: calls on different streams
         // must not overlap
-        if (dtype == LILAC_F32) {
-            launch_dot_parts_f32(n, (const float *)a, (const float *)b, c.dot_part, np, s);
-            launch_sum_parts_f32(c.dot_part, np, (float *)out, s);
-        } else {
-            launch_dot_parts(n, (const double *)a, (const double *)b, c.dot_part, np, s);
-            launch_sum_parts(c.dot_part, np, (double *)out, s);
-        }
+        if (dtype == LILAC_F32)
+            launch_dot(n, (const float *)a, (const float *)b, c.dot_part, (float *)out, s);
+        else
+            launch_dot(n, (const double *)a, (const double *)b, c.dot_part, (double *)out, s);
     });
 }
 
