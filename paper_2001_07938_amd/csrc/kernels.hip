@@ -3653,36 +3653,93 @@ __device__ __forceinline__ void block_sum2(double &a, double &b, double *lds)
     b = tb;
 }
 
+// This thread's share of the sum of part[0..n): kPartsAhead of them requested
+// together (a product of many workgroups leaves up to 8192).
+constexpr int kPartsAhead = 8;
+__device__ __forceinline__ double parts_share(const double *__restrict__ part, int32_t n)
+{
+    if (n <= kBlock)
+        return (int32_t)threadIdx.x < n ? part[threadIdx.x] : 0.0;
+    double acc = 0.0;
+    for (int32_t i = threadIdx.x; i < n; i += kBlock * kPartsAhead) {
+        double v[kPartsAhead];
+#pragma unroll
+        for (int u = 0; u < kPartsAhead; ++u)
+            v[u] = (i + u * kBlock < n) ? part[i + u * kBlock] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kPartsAhead; ++u)
+            acc += v[u];
+    }
+    return acc;
+}
+
 // Iteration k (slot par = k & 1), after w = A r with the w.r partials in
 // dot_part: every workgroup forms gamma, delta, beta and alpha itself, in
 // the same order; the solve stops (x kept) when gamma or p.Ap is exactly 0.
-// Each thread's first elements are read before the sums, so their loads
-// overlap; the partials of the new r.r go to rr[par ^ 1].
+// Each thread's first U pieces of VV elements are read before the sums, so
+// their loads overlap; the partials of the new r.r go to rr[par ^ 1].  A piece
+// is one load where every vector starts on it (WIDE), else one per element;
+// the sums are the same either way.
+// Bound by the latency of its two grid-wide dependences up to 262,144 rows, by
+// L2 and the memory-side cache above: 7-point stencil of 100^3, 75 iterations
+// of product and step, one element per thread and turn 3203 us, pairs with one
+// piece in flight 2772, two 2653, four 2717 (two partials in flight instead of
+// eight: 2750).
+template <int VV, int U, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_cg_step(
     int64_t n, CgScalars *__restrict__ sc, const double *__restrict__ w,
     double *__restrict__ p, double *__restrict__ sv, double *__restrict__ x,
     double *__restrict__ r, const double *__restrict__ dot_part, int32_t ndot,
     double *__restrict__ rr, int32_t nparts, int32_t k)
 {
+    struct Piece {
+        double e[VV];
+    };
     __shared__ double lds[2 * kWaves];
     const int32_t par = k & 1;
-    const int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t nv = n / VV;
     const int64_t step = (int64_t)gridDim.x * kBlock;
-    double w0 = 0.0, p0 = 0.0, s0 = 0.0, x0 = 0.0, r0 = 0.0;
-    if (i0 < n) {
-        w0 = w[i0];
-        p0 = p[i0];
-        s0 = sv[i0];
-        x0 = x[i0];
-        r0 = r[i0];
-    }
+    auto read = [](const double *v, int64_t i) {
+        Piece q;
+        if constexpr (WIDE && VV == 2) {
+            const f64x2 t = gld((const f64x2 *)v + i);
+            q.e[0] = t.x;
+            q.e[1] = t.y;
+        } else {
+#pragma unroll
+            for (int j = 0; j < VV; ++j)
+                q.e[j] = gld(v + i * VV + j);
+        }
+        return q;
+    };
+    auto write = [](double *v, int64_t i, const Piece &q) {
+        if constexpr (WIDE && VV == 2) {
+            gst((f64x2 *)v + i, f64x2{q.e[0], q.e[1]});
+        } else {
+#pragma unroll
+            for (int j = 0; j < VV; ++j)
+                gst(v + i * VV + j, q.e[j]);
+        }
+    };
+    Piece wv[U], pv[U], ss[U], xv[U], rv[U];
+    auto fetch = [&](int64_t i) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i + u * step < nv) {
+                wv[u] = read(w, i + u * step);
+                pv[u] = read(p, i + u * step);
+                ss[u] = read(sv, i + u * step);
+                xv[u] = read(x, i + u * step);
+                rv[u] = read(r, i + u * step);
+            }
+        }
+    };
+    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    fetch(i);
     const int32_t done = sc->done;
     const double g_old = sc->gamma[par ^ 1], a_old = sc->alpha[par ^ 1];
-    double g = 0.0, d = 0.0;
-    for (int32_t i = threadIdx.x; i < nparts; i += kBlock)
-        g += rr[par * kDotParts + i];
-    for (int32_t i = threadIdx.x; i < ndot; i += kBlock)
-        d += dot_part[i];
+    double g = parts_share(rr + par * kDotParts, nparts);
+    double d = parts_share(dot_part, ndot);
     if (done)
         return;
     block_sum2(g, d, lds);
@@ -3697,25 +3754,39 @@ __global__ __launch_bounds__(kBlock) void k_cg_step(
     }
     const double alpha = g / pap;
     double acc = 0.0;
-    if (i0 < n) {
-        const double pi = fma(beta, p0, r0);
-        const double si = fma(beta, s0, w0);
-        p[i0] = pi;
-        sv[i0] = si;
-        x[i0] = fma(alpha, pi, x0);
-        const double ri = fma(-alpha, si, r0);
-        r[i0] = ri;
-        acc = ri * ri;
+    auto update = [&](double &pe, double &se, double &xe, double &re, double we) {
+        pe = fma(beta, pe, re);
+        se = fma(beta, se, we);
+        xe = fma(alpha, pe, xe);
+        re = fma(-alpha, se, re);
+        acc = fma(re, re, acc);
+    };
+    for (;;) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = i + u * step;
+            if (at < nv) {
+#pragma unroll
+                for (int j = 0; j < VV; ++j)
+                    update(pv[u].e[j], ss[u].e[j], xv[u].e[j], rv[u].e[j], wv[u].e[j]);
+                write(p, at, pv[u]);
+                write(sv, at, ss[u]);
+                write(x, at, xv[u]);
+                write(r, at, rv[u]);
+            }
+        }
+        i += U * step;
+        if (i >= nv)
+            break;
+        fetch(i);
     }
-    for (int64_t i = i0 + step; i < n; i += step) {
-        const double pi = fma(beta, p[i], r[i]);
-        const double si = fma(beta, sv[i], w[i]);
-        p[i] = pi;
-        sv[i] = si;
-        x[i] = fma(alpha, pi, x[i]);
-        const double ri = fma(-alpha, si, r[i]);
-        r[i] = ri;
-        acc = fma(ri, ri, acc);
+    if (VV > 1 && (n & (VV - 1)) && blockIdx.x == 0 && threadIdx.x == 0) {
+        double pe = p[n - 1], se = sv[n - 1], xe = x[n - 1], re = r[n - 1];
+        update(pe, se, xe, re, w[n - 1]);
+        p[n - 1] = pe;
+        sv[n - 1] = se;
+        x[n - 1] = xe;
+        r[n - 1] = re;
     }
     const double t = block_sum<kWaves>(acc, lds);
     if (threadIdx.x == 0) {
@@ -4776,8 +4847,18 @@ void launch_cg_step(int64_t n, CgScalars *sc, const double *w, double *p, double
                     double *x, double *r, const double *dot_part, int32_t ndot, double *rr,
                     int32_t nparts, int32_t k, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cg_step, dim3(nparts), dim3(kBlock), 0, s, n, sc, w, p, sv, x, r,
-                       dot_part, ndot, rr, nparts, k);
+    dim3 g(nparts), b(kBlock);
+    // one element per thread up to one round of the workgroups, then pairs
+    if (n <= (int64_t)kDotParts * kBlock)
+        hipLaunchKernelGGL((k_cg_step<1, 1, false>), g, b, 0, s, n, sc, w, p, sv, x, r, dot_part,
+                           ndot, rr, nparts, k);
+    else if ((((uintptr_t)w | (uintptr_t)p | (uintptr_t)sv | (uintptr_t)x | (uintptr_t)r) & 15) ==
+             0)
+        hipLaunchKernelGGL((k_cg_step<2, 2, true>), g, b, 0, s, n, sc, w, p, sv, x, r, dot_part,
+                           ndot, rr, nparts, k);
+    else
+        hipLaunchKernelGGL((k_cg_step<2, 2, false>), g, b, 0, s, n, sc, w, p, sv, x, r, dot_part,
+                           ndot, rr, nparts, k);
     check_launch("k_cg_step");
 }
 
