@@ -748,7 +748,9 @@ __device__ __forceinline__ void panel_block(const PanelDesc &pd, int32_t b,
 // scan).  Three pairs of columns in flight: two and four took 1% longer, six
 // 5% (registers).
 // PART: panel group `grp` only, its sums to part[grp * rows + row]; else all.
-template <typename V, bool DOT, bool PART = false>
+// Blocks b .. b + NB - 1 by one workgroup (grouped launches): each panel is
+// copied once for them; every block's sums are formed as it would alone.
+template <typename V, bool DOT, bool PART = false, int NB = 1>
 __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
                                            const V *__restrict__ x,
                                            V *__restrict__ y, const Epi &epi,
@@ -762,20 +764,22 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
     typedef V pair_t __attribute__((ext_vector_type(2)));
     typedef const __attribute__((address_space(4))) int32_t *cptr;
     double *acc = (double *)smem;                                 // row sums
-    V *xs = (V *)(smem + panel_sum_bytes(pd.rb));                 // x panel
+    V *xs = (V *)(smem + panel_sum_bytes(NB * pd.rb));            // x panel
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int32_t r0 = b * pd.rb;
-    const int32_t nr = min(pd.rb, pd.rows - r0);
     const V *pv = (const V *)pd.vals;
-    for (int i = threadIdx.x; i < pd.rb; i += kPanelThreads)
+    for (int i = threadIdx.x; i < NB * pd.rb; i += kPanelThreads)
         acc[i] = 0.0;
     if (threadIdx.x == 0)
         xs[pd.pw] = (V)0;
-    // this lane's rows: mine, mine + 64, ... below end
-    const int32_t mine = wv * pd.rw + lane, end = min((wv + 1) * pd.rw, nr);
+    // this lane's rows of block b + j: mine, mine + 64, ... below end(j)
+    const int32_t mine = wv * pd.rw + lane;
+    auto end = [&](int32_t j) {
+        return min((wv + 1) * pd.rw, min(pd.rb, pd.rows - r0 - j * pd.rb));
+    };
     double wrow = 0.0;
-    if (DOT && mine < end)
+    if (DOT && mine < end(0))
         wrow = (double)gld(w + r0 + mine);
     const bool aligned = (((uintptr_t)x) & 15) == 0;
     // (groups are only formed where there are few blocks: no rotation then)
@@ -783,15 +787,17 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
         (pd.np > 1 && pd.nblk >= kPanelRotateBlocks) ? (int32_t)((b >> 3) % pd.np) : 0;
     const int32_t p0 = PART ? grp * pd.pg : 0;
     const int32_t p1 = PART ? min(p0 + pd.pg, pd.np) : pd.np;
-    constexpr int T = kPanelMaxRb / kPanelThreads;   // rows of a lane
-    double tot[T] = {0.0, 0.0, 0.0, 0.0};            // sums of the groups so far
+    constexpr int T = kPanelMaxRb / kPanelThreads / NB;   // rows of a lane in a block
+    double tot[NB][T] = {};                               // sums of the groups so far
     auto panel_at = [&](int32_t i) { return (i + rot < pd.np) ? i + rot : i + rot - pd.np; };
     // a run: its first column, its pairs, whether a single column follows
     struct Run {
         int32_t at, pairs, odd;
     };
-    auto run_of = [&](int32_t p) {
-        const int32_t q = (b * pd.np + p) * kPanelWaves + wv;
+    auto run_of = [&](int32_t p, int32_t j) {
+        if (NB > 1 && b + j >= pd.nblk)
+            return Run{0, 0, 0};
+        const int32_t q = ((b + j) * pd.np + p) * kPanelWaves + wv;
         const int32_t c0 = ((cptr)pd.col0)[q], k = ((cptr)pd.col0)[q + 1] - c0;
         return Run{c0, k >> 1, k & 1};
     };
@@ -810,28 +816,25 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
                 nw[u] = ld_stream((const u16x2 *)(o + u * 128) + lane);
             }
     };
-    auto request_first = [&](const Run &r, int32_t p) {
+    auto request_first = [&](const Run &r, int32_t p, int32_t j) {
+        if (NB > 1 && r.pairs + r.odd == 0)
+            return;
         request(r, 0);
         if (r.odd) {
             const int64_t at = ((int64_t)r.at + 2 * r.pairs) * 64 + lane;
             nv1 = ld_stream(pv + at);
             nw1 = ld_stream(pd.words + at);
         }
-        nstart = gld(pd.start + ((int64_t)(b * pd.np + p) * kPanelWaves + wv) * 64 + lane);
+        nstart = gld(pd.start + ((int64_t)((b + j) * pd.np + p) * kPanelWaves + wv) * 64 + lane);
     };
     Run cur{0, 0, 0}, next{0, 0, 0};
     if (p0 < p1) {
-        next = run_of(panel_at(p0));
-        request_first(next, panel_at(p0));
+        next = run_of(panel_at(p0), 0);
+        request_first(next, panel_at(p0), 0);
     }
     for (int32_t pk = p0; pk < p1; ++pk) {
         const int32_t c0 = panel_at(pk) * pd.pw;
         const int32_t width = min(pd.pw, pd.cols - c0);
-        cur = next;
-        const bool more = pk + 1 < p1;
-        const int32_t pn = more ? panel_at(pk + 1) : 0;
-        if (more)
-            next = run_of(pn);
         __syncthreads();  // the previous panel is no longer read
         const int32_t nvec = aligned ? width / VV : 0;
         for (int32_t c = wv; c * 64 < nvec; c += kPanelWaves) {
@@ -845,95 +848,112 @@ __device__ __forceinline__ void lane_block(const PanelDesc &pd, int32_t b,
             xs[e] = gld(x + c0 + e);
         __builtin_amdgcn_s_waitcnt(0);  // the direct loads have landed
         __syncthreads();                 // the panel is in LDS
-        int32_t row = wv * pd.rw + nstart;
-        const V v1 = nv1;
-        const uint32_t w1 = nw1;
-        double sum = 0.0;
-        auto step = [&](V v, V xv, uint32_t word) {
-            sum = fma((double)v, (double)xv, sum);
-            if (word & kLaneEnd) {
-                lds_add_f64(&acc[row], sum);
-                ++row;
-                sum = 0.0;
-            }
-        };
-        for (int32_t k = 0; k < cur.pairs; k += B) {
-            pair_t v[B];
-            u16x2 o[B];
+        // the blocks' runs of this panel, each while the next one's first
+        // entries are on their way
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                v[u] = nv[u];
-                o[u] = nw[u];
-            }
-            if (k + B < cur.pairs)
-                request(cur, k + B);
-            else if (more)
-                request_first(next, pn);
-            if (k + B <= cur.pairs) {
-                V xa[B], xb[B];
+        for (int j = 0; j < NB; ++j) {
+            cur = next;
+            const bool more = j + 1 < NB || pk + 1 < p1;
+            const int32_t jn = j + 1 < NB ? j + 1 : 0;
+            const int32_t pn = !more ? 0 : panel_at(j + 1 < NB ? pk : pk + 1);
+            if (more)
+                next = run_of(pn, jn);
+            double *const sums = acc + j * pd.rb;
+            int32_t row = wv * pd.rw + nstart;
+            const V v1 = nv1;
+            const uint32_t w1 = nw1;
+            double sum = 0.0;
+            auto step = [&](V v, V xv, uint32_t word) {
+                sum = fma((double)v, (double)xv, sum);
+                if (word & kLaneEnd) {
+                    lds_add_f64(&sums[row], sum);
+                    ++row;
+                    sum = 0.0;
+                }
+            };
+            for (int32_t k = 0; k < cur.pairs; k += B) {
+                pair_t v[B];
+                u16x2 o[B];
 #pragma unroll
                 for (int u = 0; u < B; ++u) {
-                    xa[u] = xs[o[u].x & 0x7FFFu];
-                    xb[u] = xs[o[u].y & 0x7FFFu];
+                    v[u] = nv[u];
+                    o[u] = nw[u];
                 }
+                if (k + B < cur.pairs)
+                    request(cur, k + B);
+                else if (more)
+                    request_first(next, pn, jn);
+                if (k + B <= cur.pairs) {
+                    V xa[B], xb[B];
 #pragma unroll
-                for (int u = 0; u < B; ++u) {
-                    step(v[u].x, xa[u], o[u].x);
-                    step(v[u].y, xb[u], o[u].y);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < B - 1; ++u)
-                    if (k + u < cur.pairs) {
-                        const V xa = xs[o[u].x & 0x7FFFu], xb = xs[o[u].y & 0x7FFFu];
-                        step(v[u].x, xa, o[u].x);
-                        step(v[u].y, xb, o[u].y);
+                    for (int u = 0; u < B; ++u) {
+                        xa[u] = xs[o[u].x & 0x7FFFu];
+                        xb[u] = xs[o[u].y & 0x7FFFu];
                     }
-            }
-        }
-        if (cur.pairs == 0 && more)
-            request_first(next, pn);
-        if (cur.odd)
-            step(v1, xs[w1 & 0x7FFFu], w1);
-        // rows that go on in the next lane, and the run's last row: rows ascend
-        // along the lanes, the last lane of a row adds what they hold of it
-        if (cur.pairs + cur.odd > 0) {
-            const double left = seg_scan64<true>(sum, row);
-            if (next_lane_key(row) != row)
-                lds_add_f64(&acc[row], left);
-        }
-        // a group ends: its sums of the wavefront's own rows (no other adds to
-        // them) move to the totals
-        if (!PART && pd.ng > 1 && ((pk + 1) % pd.pg == 0 || !more)) {
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int32_t i = mine + t * 64;
-                if (i < end) {
-                    tot[t] += acc[i];
-                    acc[i] = 0.0;
+                    for (int u = 0; u < B; ++u) {
+                        step(v[u].x, xa[u], o[u].x);
+                        step(v[u].y, xb[u], o[u].y);
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < B - 1; ++u)
+                        if (k + u < cur.pairs) {
+                            const V xa = xs[o[u].x & 0x7FFFu], xb = xs[o[u].y & 0x7FFFu];
+                            step(v[u].x, xa, o[u].x);
+                            step(v[u].y, xb, o[u].y);
+                        }
+                }
+            }
+            if (cur.pairs == 0 && more)
+                request_first(next, pn, jn);
+            if (cur.odd)
+                step(v1, xs[w1 & 0x7FFFu], w1);
+            // rows that go on in the next lane, and the run's last row: rows ascend
+            // along the lanes, the last lane of a row adds what they hold of it
+            if (cur.pairs + cur.odd > 0) {
+                const double left = seg_scan64<true>(sum, row);
+                if (next_lane_key(row) != row)
+                    lds_add_f64(&sums[row], left);
+            }
+            // a group ends: its sums of the wavefront's own rows (no other adds to
+            // them) move to the totals
+            if (!PART && pd.ng > 1 && ((pk + 1) % pd.pg == 0 || pk + 1 == p1)) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const int32_t i = mine + t * 64;
+                    if (i < end(j)) {
+                        tot[j][t] += sums[i];
+                        sums[i] = 0.0;
+                    }
                 }
             }
         }
     }
-    double dacc = 0.0;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int32_t i = mine + t * 64;
-        if (i >= end)
-            break;
-        if (PART) {
-            gst(part + (int64_t)grp * pd.rows + r0 + i, acc[i]);
-            continue;
+    for (int j = 0; j < NB; ++j) {
+        const int32_t rj = r0 + j * pd.rb;
+        const double *const sums = acc + j * pd.rb;
+        double dacc = 0.0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int32_t i = mine + t * 64;
+            if (i >= end(j))
+                break;
+            if (PART) {
+                gst(part + (int64_t)grp * pd.rows + rj + i, sums[i]);
+                continue;
+            }
+            const V out = epilogue<V>(pd.ng > 1 ? tot[j][t] : sums[i], epi);
+            gst(y + rj + i, out);
+            if (DOT)
+                dacc = fma(t == 0 && j == 0 ? wrow : (double)gld(w + rj + i), (double)out, dacc);
         }
-        const V out = epilogue<V>(pd.ng > 1 ? tot[t] : acc[i], epi);
-        gst(y + r0 + i, out);
-        if (DOT)
-            dacc = fma(t == 0 ? wrow : (double)gld(w + r0 + i), (double)out, dacc);
-    }
-    if (DOT) {
-        const double tot = block_sum<kPanelWaves>(dacc, (double *)xs);
-        if (threadIdx.x == 0)
-            dot_part[b] = tot;
+        if (DOT && b + j < pd.nblk) {
+            const double whole = block_sum<kPanelWaves>(dacc, (double *)xs);
+            if (threadIdx.x == 0)
+                dot_part[b + j] = whole;
+        }
     }
 }
 
@@ -1003,8 +1023,9 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_panels(
 }
 
 // Column-panel products of many matrices in one launch: workgroup g takes
-// row block g - prefix[j] of matrix j (prefix[j] <= g < prefix[j + 1]).
-// Each block runs exactly as in the single-matrix kernel.
+// the (g - prefix[j])-th row block of matrix j (prefix[j] <= g < prefix[j + 1]),
+// or its (g - prefix[j])-th two or four (per).  Each block's sums are formed exactly as in
+// the single-matrix kernel.
 template <typename V>
 __global__ __launch_bounds__(kPanelThreads) void k_spmv_panels_grouped(
     const PanelDesc *__restrict__ descs, const PanelIO *__restrict__ io,
@@ -1024,15 +1045,25 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_panels_grouped(
     const Epi epi{EPI_NONE, 0, 0.0, 0.0};
     const PanelIO pio = io[lo];
     if (pd.col0) {
+        const int32_t b = (g - prefix[lo]) * pd.per;
+        const V *x = (const V *)pio.x;
+        V *y = (V *)pio.y;
         if constexpr (sizeof(V) == 8) {
-            if (pio.dot) {
-                lane_block<V, true>(pd, g - prefix[lo], (const V *)pio.x, (V *)pio.y, epi,
-                                    (const V *)pio.x, pio.dot, smem);
+            if (pio.dot && pd.per == 4)
+                lane_block<V, true, false, 4>(pd, b, x, y, epi, x, pio.dot, smem);
+            else if (pio.dot && pd.per == 2)
+                lane_block<V, true, false, 2>(pd, b, x, y, epi, x, pio.dot, smem);
+            else if (pio.dot)
+                lane_block<V, true>(pd, b, x, y, epi, x, pio.dot, smem);
+            if (pio.dot)
                 return;
-            }
         }
-        lane_block<V, false>(pd, g - prefix[lo], (const V *)pio.x, (V *)pio.y, epi, nullptr,
-                             nullptr, smem);
+        if (pd.per == 4)
+            lane_block<V, false, false, 4>(pd, b, x, y, epi, nullptr, nullptr, smem);
+        else if (pd.per == 2)
+            lane_block<V, false, false, 2>(pd, b, x, y, epi, nullptr, nullptr, smem);
+        else
+            lane_block<V, false>(pd, b, x, y, epi, nullptr, nullptr, smem);
         return;
     }
     if constexpr (sizeof(V) == 8) {

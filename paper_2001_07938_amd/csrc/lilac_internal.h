@@ -111,7 +111,7 @@ struct PanelDesc {
     const int32_t *wptr;
     int32_t rows, cols;
     int32_t pw, np, rb, nblk, rw;
-    int32_t pad;
+    int32_t per;    // row blocks to a workgroup of a grouped launch (1, 2, 4)
     // lane form (col0 != null; see below): vals, words and start
     const uint16_t *words;
     const uint8_t *start;
@@ -161,6 +161,8 @@ constexpr int panel_width(int vsize, int rb)
 {
     return (kPanelLds - panel_sum_bytes(rb)) / vsize;
 }
+// workgroups of a matrix in a grouped launch
+inline int32_t panel_groups_of(const PanelDesc &pd) { return (pd.nblk + pd.per - 1) / pd.per; }
 // the same for the lane form: 16 bytes for the zero after the panel
 constexpr int lane_panel_width(int vsize, int rb)
 {

@@ -515,14 +515,8 @@ static int64_t panel_count(const CsrHandle &h)
 }
 
 // Rows per block of the column-panel layout: enough blocks for every CU; but
-// where such a block's entries weigh less than one copy of x (each block copies
-// all of x into LDS once), as many rows as weigh kPanelCopies copies; at most
-// kPanelMaxRb.  Random rows of 5 to 60 entries, float64, one copy against two
-// and three: batch of 16,000-row matrices 326, 405 and 449 G entries/s, 60,000
-// rows 387, 441 and 484; one product of 30,000 rows 9.3, 10.9 and 11.8 us, of
-// 100,000 16.1, 15.4 and 15.4; 512-matrix batch 1056, 968 and 954 us.  Two
-// takes most of the batch's gain for half of the single product's loss.
-constexpr double kPanelCopies = 2.0;
+// as many rows as weigh one copy of x, where that is more (each block copies
+// all of x into LDS once); at most kPanelMaxRb.
 static int32_t panel_rows(const CsrHandle &h)
 {
     if (h.rows == 0)
@@ -531,8 +525,7 @@ static int32_t panel_rows(const CsrHandle &h)
     const double row_bytes = std::max(1.0, (double)h.nnz / h.rows * (vs + 4.0));
     const int64_t by_cu = ((int64_t)h.rows + device_cu_count() - 1) / device_cu_count();
     const int64_t by_x = (int64_t)std::ceil((double)h.cols * vs / row_bytes);
-    const int64_t rb = by_cu >= by_x ? by_cu : (int64_t)(kPanelCopies * (double)by_x);
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPanelMaxRb, rb));
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(kPanelMaxRb, std::max(by_cu, by_x)));
 }
 
 // A matrix is gather-heavy when its non-zeros touch nearly one distinct
@@ -608,6 +601,73 @@ static double measure_line_ratio(CsrHandle &h, hipStream_t s)
 
 static int64_t scan_total(int32_t *a, int64_t n, hipStream_t s);
 
+// Groups of panels, a workgroup for each, are formed where a workgroup is then
+// spared this many bytes (its entries and its copies of x): adding the groups
+// up is another launch.  Random rows, float64, with and without groups: 20,000
+// rows of 5 to 60 (146 KB spared) 10.3 and 8.7 us, 30,000 (220 KB) 10.4 and
+// 10.5, 50,000 11.1 and 15.6, 200,000 26.3 and 60.4.
+constexpr double kPanelGroupBytes = 256e3;
+// Where groups are formed, the lane form may be this much larger than the scan
+// form, which has none: 500,000 rows of 5 to 60, float64, 126 us in the scan
+// form, 72 in a lane form of 1.2 times its bytes.
+constexpr double kLaneGroupBytes = 1.5;
+
+// The lane form with blocks of rb rows, `per` to a workgroup in a grouped launch.
+static PanelDesc lane_shape(const CsrHandle &h, int32_t rb, int32_t per)
+{
+    const double vs = (double)dtype_size(h.dt);
+    const int32_t cu = device_cu_count();
+    PanelDesc pd{};
+    pd.rows = h.rows;
+    pd.cols = h.cols;
+    pd.rb = rb;
+    pd.per = per;
+    pd.pw = lane_panel_width((int)vs, per * rb);
+    pd.np = (int32_t)std::min<int64_t>(((int64_t)h.cols + pd.pw - 1) / pd.pw, INT_MAX);
+    pd.nblk = (int32_t)(((int64_t)h.rows + rb - 1) / rb);
+    pd.rw = (rb + kPanelWaves - 1) / kPanelWaves;
+    // as many groups as give every CU a workgroup, one fits on each
+    pd.ng = pd.nblk < kPanelRotateBlocks ? std::max(1, std::min(pd.np, cu / pd.nblk)) : 1;
+    pd.pg = (pd.np + pd.ng - 1) / std::max(1, pd.ng);
+    pd.ng = pd.pg > 0 ? (pd.np + pd.pg - 1) / pd.pg : 1;
+    const double bytes = (double)h.nnz / pd.nblk * (vs + 2) + (double)h.cols * vs;
+    if (bytes * (1.0 - 1.0 / std::max(1, pd.ng)) < kPanelGroupBytes) {
+        pd.ng = 1;
+        pd.pg = pd.np;
+    }
+    return pd;
+}
+
+// Blocks of the lane form.  Those of panel_rows; where its blocks alone leave
+// CUs idle and groups of panels fill them, twice the rows if that gives as many
+// workgroups (half the copies of x; 120,000 rows of 80, float64, CG of 75
+// iterations 2599 -> 2332 us, four times the rows 2525; 90,000 rows of 5 to 110
+// 21.5, 17.9 and 18.5).  Else, where
+// a block weighs one copy of x, four or two of them to a workgroup in a grouped
+// launch, if that takes no more panels: 512-matrix batch, one, two and four to a
+// workgroup 1028, 997 and 984 us.  (Blocks of twice the rows took 965 there, but
+// 20,000 rows of 5 to 60 alone 12.1 us where these take 7.7.)
+static PanelDesc lane_blocks(const CsrHandle &h)
+{
+    const int32_t rb = panel_rows(h);
+    const PanelDesc base = lane_shape(h, rb, 1);
+    PanelDesc best = base;
+    if (base.ng > 1) {
+        const PanelDesc pd = lane_shape(h, std::min(2 * rb, kPanelMaxRb), 1);
+        if (pd.ng > 1 && pd.nblk * pd.ng >= base.nblk * base.ng)
+            best = pd;
+    }
+    const int64_t by_cu = ((int64_t)h.rows + device_cu_count() - 1) / device_cu_count();
+    for (int32_t per = 4; best.rb > by_cu && per > 1; per /= 2) {
+        if (per * best.rb > kPanelMaxRb || best.nblk < per)
+            continue;
+        const PanelDesc pd = lane_shape(h, best.rb, per);
+        if (pd.np == best.np)
+            return pd;
+    }
+    return best;
+}
+
 // Builds the lane form of the column-panel copy (see PanelDesc) if its bytes,
 // with the fillers and the padding of the last lanes, are no more than the
 // scan form's (10 against 12 bytes per float64 entry, 6 against 8 float32):
@@ -615,23 +675,9 @@ static int64_t scan_total(int32_t *a, int64_t n, hipStream_t s);
 static bool build_lanes(CsrHandle &h, hipStream_t s)
 {
     const size_t vs = dtype_size(h.dt);
-    PanelDesc pd{};
-    pd.rows = h.rows;
-    pd.cols = h.cols;
-    pd.rb = panel_rows(h);
-    pd.pw = lane_panel_width((int)vs, pd.rb);
-    const int64_t np = ((int64_t)h.cols + pd.pw - 1) / pd.pw;
-    if (np < 1 || np > kPanelMaxPanels)
+    PanelDesc pd = lane_blocks(h);
+    if (pd.np < 1 || pd.np > kPanelMaxPanels)
         return false;
-    pd.np = (int32_t)np;
-    pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
-    pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
-    // groups of panels: as many as give every CU a workgroup, one fits on each
-    pd.ng = std::max(1, std::min(pd.np, device_cu_count() / pd.nblk));
-    if (pd.nblk >= kPanelRotateBlocks)
-        pd.ng = 1;
-    pd.pg = (pd.np + pd.ng - 1) / pd.ng;
-    pd.ng = (pd.np + pd.pg - 1) / pd.pg;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
     const int64_t nrun = (int64_t)pd.nblk * pd.np * kPanelWaves;
     int32_t *pos = nullptr;
@@ -648,7 +694,9 @@ static bool build_lanes(CsrHandle &h, hipStream_t s)
         launch_fill_i32(h.d_pw + nrun, 1, 0, s);
         ncol = scan_total(h.d_pw, nrun + 1, s);
         const bool fits = ncol * 64 < INT_MAX &&
-                          ncol * 64 * (int64_t)(vs + 2) + nrun * 64 <= h.nnz * (int64_t)(vs + 4);
+                          (double)(ncol * 64 * (int64_t)(vs + 2) + nrun * 64) <=
+                              (pd.ng > 1 ? kLaneGroupBytes : 1.0) *
+                                  (double)(h.nnz * (int64_t)(vs + 4));
         if (fits) {
             scan_total(pos, nptr, s);
             h.d_pv = dev_alloc((size_t)ncol * 64 * vs);
@@ -696,6 +744,7 @@ static void build_panels(CsrHandle &h, hipStream_t s)
     if (pd.np < 1 || pd.np > kPanelMaxPanels)
         fail(LILAC_ERR_DEVICE, "column-panel layout needs 1 to 64 panels");
     pd.rb = panel_rows(h);
+    pd.per = 1;
     pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
     pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
@@ -2379,7 +2428,7 @@ static GroupPlan *build_group(int count, const lilac_csr_t *hs,
             const CsrHandle *h = g->hs[j];
             pdesc.push_back(h->pan);
             pio.push_back(PanelIO{xs[j], ys[j]});
-            pprefix.push_back(pprefix.back() + h->pan.nblk);
+            pprefix.push_back(pprefix.back() + panel_groups_of(h->pan));
         }
         std::vector<BandDesc> bdesc;
         std::vector<PanelIO> bio;

@@ -534,7 +534,7 @@ void HipExec::launch_tick(int lane, int tick, const std::vector<serve::Request *
         if (m.h->use_panels) {
             pdesc.push_back(m.h->pan);
             pio.push_back(io);
-            pprefix.push_back(pprefix.back() + m.h->pan.nblk);
+            pprefix.push_back(pprefix.back() + panel_groups_of(m.h->pan));
         } else if (m.h->use_band) {
             bdesc.push_back(m.h->band);
             bio.push_back(io);
