@@ -968,15 +968,17 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_lanes(
 
 // One workgroup for each row block and group of panels: a matrix of few row
 // blocks would leave most compute units idle (200k rows: 49 blocks).
-template <typename V>
+// NB row blocks to each of them (pd.gper).
+template <typename V, int NB>
 __global__ __launch_bounds__(kPanelThreads) void k_spmv_lane_groups(
     PanelDesc pd, const V *__restrict__ x, double *__restrict__ part)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const Epi epi{EPI_NONE, 0, 0.0, 0.0};
-    const int32_t grp = blockIdx.x / pd.nblk;
-    lane_block<V, false, true>(pd, blockIdx.x - grp * pd.nblk, x, nullptr, epi, nullptr,
-                               nullptr, smem, grp, part);
+    const int32_t nb = (pd.nblk + NB - 1) / NB;
+    const int32_t grp = blockIdx.x / nb;
+    lane_block<V, false, true, NB>(pd, (blockIdx.x - grp * nb) * NB, x, nullptr, epi, nullptr,
+                                   nullptr, smem, grp, part);
 }
 
 // The groups' sums of a row block added up in order, with the epilogue and the
@@ -4252,11 +4254,15 @@ void launch_spmv_lane_groups(lilac_dtype dt, const PanelDesc &pd, const void *x,
 {
     if (pd.nblk <= 0)
         return;
-    dim3 g(pd.nblk * pd.ng), b(kPanelThreads);
+    dim3 g((pd.nblk + pd.gper - 1) / pd.gper * pd.ng), b(kPanelThreads);
     dim3 t(dot_part ? pd.nblk : grid_for(pd.rows, kPanelThreads, INT_MAX));
     if (dt == LILAC_F64) {
-        hipLaunchKernelGGL(k_spmv_lane_groups<double>, g, b, kPanelLds, s, pd,
-                           (const double *)x, part);
+        if (pd.gper == 2)
+            hipLaunchKernelGGL((k_spmv_lane_groups<double, 2>), g, b, kPanelLds, s, pd,
+                               (const double *)x, part);
+        else
+            hipLaunchKernelGGL((k_spmv_lane_groups<double, 1>), g, b, kPanelLds, s, pd,
+                               (const double *)x, part);
         if (dot_part)
             hipLaunchKernelGGL((k_lane_total<double, true>), t, b, 0, s, pd, part, (double *)y,
                                epi, (const double *)w, dot_part);
@@ -4266,8 +4272,12 @@ void launch_spmv_lane_groups(lilac_dtype dt, const PanelDesc &pd, const void *x,
     } else {
         if (dot_part)
             fail(LILAC_ERR_UNSUPPORTED, "fused dot is only provided for float64");
-        hipLaunchKernelGGL(k_spmv_lane_groups<float>, g, b, kPanelLds, s, pd,
-                           (const float *)x, part);
+        if (pd.gper == 2)
+            hipLaunchKernelGGL((k_spmv_lane_groups<float, 2>), g, b, kPanelLds, s, pd,
+                               (const float *)x, part);
+        else
+            hipLaunchKernelGGL((k_spmv_lane_groups<float, 1>), g, b, kPanelLds, s, pd,
+                               (const float *)x, part);
         hipLaunchKernelGGL((k_lane_total<float, false>), t, b, 0, s, pd, part, (float *)y, epi,
                            (const float *)w, dot_part);
     }
@@ -4544,9 +4554,13 @@ void panels_prepare()
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_panels<float, false>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
-    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<double>,
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<double, 1>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
-    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<float>,
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<double, 2>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<float, 1>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+    HIPC(hipFuncSetAttribute((const void *)k_spmv_lane_groups<float, 2>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
     HIPC(hipFuncSetAttribute((const void *)k_spmv_lanes<double, true>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));

@@ -112,6 +112,7 @@ struct PanelDesc {
     int32_t rows, cols;
     int32_t pw, np, rb, nblk, rw;
     int32_t per;    // row blocks to a workgroup of a grouped launch (1, 2, 4)
+    int32_t gper;   // the same where the groups of panels have a workgroup each (1, 2)
     // lane form (col0 != null; see below): vals, words and start
     const uint16_t *words;
     const uint8_t *start;
@@ -160,6 +161,16 @@ constexpr int panel_sum_bytes(int rb)
 constexpr int panel_width(int vsize, int rb)
 {
     return (kPanelLds - panel_sum_bytes(rb)) / vsize;
+}
+// The row blocks to a workgroup of a grouped launch that holds `total` of them: a
+// matrix's own number, but not so many that CUs are left idle (with four
+// workgroups for each CU instead of one, 160 matrices 246 us, 239; 16: the same).
+inline int32_t panel_per(const PanelDesc &pd, int64_t total, int32_t cu)
+{
+    int32_t per = pd.per;
+    while (per > 1 && total < (int64_t)cu * per)
+        per /= 2;
+    return per;
 }
 // workgroups of a matrix in a grouped launch
 inline int32_t panel_groups_of(const PanelDesc &pd) { return (pd.nblk + pd.per - 1) / pd.per; }

@@ -612,25 +612,27 @@ constexpr double kPanelGroupBytes = 256e3;
 // form, 72 in a lane form of 1.2 times its bytes.
 constexpr double kLaneGroupBytes = 1.5;
 
-// The lane form with blocks of rb rows, `per` to a workgroup in a grouped launch.
-static PanelDesc lane_shape(const CsrHandle &h, int32_t rb, int32_t per)
+// The lane form with `per` and `gper` row blocks to a workgroup.
+static PanelDesc lane_shape(const CsrHandle &h, int32_t per, int32_t gper)
 {
     const double vs = (double)dtype_size(h.dt);
-    const int32_t cu = device_cu_count();
+    const int32_t cu = device_cu_count(), rb = panel_rows(h);
     PanelDesc pd{};
     pd.rows = h.rows;
     pd.cols = h.cols;
     pd.rb = rb;
     pd.per = per;
-    pd.pw = lane_panel_width((int)vs, per * rb);
+    pd.gper = gper;
+    pd.pw = lane_panel_width((int)vs, std::max(per, gper) * rb);
     pd.np = (int32_t)std::min<int64_t>(((int64_t)h.cols + pd.pw - 1) / pd.pw, INT_MAX);
     pd.nblk = (int32_t)(((int64_t)h.rows + rb - 1) / rb);
     pd.rw = (rb + kPanelWaves - 1) / kPanelWaves;
     // as many groups as give every CU a workgroup, one fits on each
-    pd.ng = pd.nblk < kPanelRotateBlocks ? std::max(1, std::min(pd.np, cu / pd.nblk)) : 1;
+    const int32_t wgs = (pd.nblk + gper - 1) / gper;
+    pd.ng = pd.nblk < kPanelRotateBlocks ? std::max(1, std::min(pd.np, cu / wgs)) : 1;
     pd.pg = (pd.np + pd.ng - 1) / std::max(1, pd.ng);
     pd.ng = pd.pg > 0 ? (pd.np + pd.pg - 1) / pd.pg : 1;
-    const double bytes = (double)h.nnz / pd.nblk * (vs + 2) + (double)h.cols * vs;
+    const double bytes = (double)h.nnz / wgs * (vs + 2) + (double)h.cols * vs;
     if (bytes * (1.0 - 1.0 / std::max(1, pd.ng)) < kPanelGroupBytes) {
         pd.ng = 1;
         pd.pg = pd.np;
@@ -638,30 +640,28 @@ static PanelDesc lane_shape(const CsrHandle &h, int32_t rb, int32_t per)
     return pd;
 }
 
-// Blocks of the lane form.  Those of panel_rows; where its blocks alone leave
-// CUs idle and groups of panels fill them, twice the rows if that gives as many
-// workgroups (half the copies of x; 120,000 rows of 80, float64, CG of 75
-// iterations 2599 -> 2332 us, four times the rows 2525; 90,000 rows of 5 to 110
-// 21.5, 17.9 and 18.5).  Else, where
-// a block weighs one copy of x, four or two of them to a workgroup in a grouped
-// launch, if that takes no more panels: 512-matrix batch, one, two and four to a
-// workgroup 1028, 997 and 984 us.  (Blocks of twice the rows took 965 there, but
-// 20,000 rows of 5 to 60 alone 12.1 us where these take 7.7.)
+// How many row blocks of the lane form one workgroup takes, each panel of x
+// copied once for them.  Where the blocks alone leave CUs idle and groups of
+// panels fill them, two if that gives as many workgroups (120,000 rows of 80,
+// float64, CG of 75 iterations 2599 -> 2329 us, 90,000 rows of 5 to 110 21.5 ->
+// 18.1).  In a grouped launch, where a block weighs one copy of x, four or two if
+// that takes no more panels: 512-matrix batch, one, up to two and up to
+// four 1048, 1018 and 1009 us.  (Blocks of twice the rows took 965 there, but
+// 20,000 rows of 5 to 60 alone 12.1 us where these take 7.7, and 16 matrices 74
+// where these take 63.)
 static PanelDesc lane_blocks(const CsrHandle &h)
 {
-    const int32_t rb = panel_rows(h);
-    const PanelDesc base = lane_shape(h, rb, 1);
-    PanelDesc best = base;
-    if (base.ng > 1) {
-        const PanelDesc pd = lane_shape(h, std::min(2 * rb, kPanelMaxRb), 1);
-        if (pd.ng > 1 && pd.nblk * pd.ng >= base.nblk * base.ng)
+    PanelDesc best = lane_shape(h, 1, 1);
+    if (best.ng > 1 && best.nblk > 1 && 2 * best.rb <= kPanelMaxRb) {
+        const PanelDesc pd = lane_shape(h, 2, 2);
+        if (pd.ng > 1 && (pd.nblk + 1) / 2 * pd.ng >= best.nblk * best.ng)
             best = pd;
     }
     const int64_t by_cu = ((int64_t)h.rows + device_cu_count() - 1) / device_cu_count();
-    for (int32_t per = 4; best.rb > by_cu && per > 1; per /= 2) {
+    for (int32_t per = 4; best.rb > by_cu && per > best.per; per /= 2) {
         if (per * best.rb > kPanelMaxRb || best.nblk < per)
             continue;
-        const PanelDesc pd = lane_shape(h, best.rb, per);
+        const PanelDesc pd = lane_shape(h, per, best.gper);
         if (pd.np == best.np)
             return pd;
     }
@@ -744,7 +744,7 @@ static void build_panels(CsrHandle &h, hipStream_t s)
     if (pd.np < 1 || pd.np > kPanelMaxPanels)
         fail(LILAC_ERR_DEVICE, "column-panel layout needs 1 to 64 panels");
     pd.rb = panel_rows(h);
-    pd.per = 1;
+    pd.per = pd.gper = 1;
     pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
     pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
@@ -2424,11 +2424,16 @@ static GroupPlan *build_group(int count, const lilac_csr_t *hs,
         std::vector<PanelDesc> pdesc;
         std::vector<PanelIO> pio;
         std::vector<int32_t> pprefix(1, 0);
+        int64_t pblocks = 0;
+        for (int j = 0; j < count; ++j)
+            pblocks += g->hs[j]->use_panels ? g->hs[j]->pan.nblk : 0;
+        const int32_t cu = device_cu_count();
         for (int j : heavy_first(true)) {
             const CsrHandle *h = g->hs[j];
             pdesc.push_back(h->pan);
+            pdesc.back().per = panel_per(h->pan, pblocks, cu);
             pio.push_back(PanelIO{xs[j], ys[j]});
-            pprefix.push_back(pprefix.back() + panel_groups_of(h->pan));
+            pprefix.push_back(pprefix.back() + panel_groups_of(pdesc.back()));
         }
         std::vector<BandDesc> bdesc;
         std::vector<PanelIO> bio;

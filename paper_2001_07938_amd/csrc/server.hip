@@ -525,6 +525,12 @@ void HipExec::launch_tick(int lane, int tick, const std::vector<serve::Request *
                                                  const serve::Request *b) {
         return per_block(a) > per_block(b);
     });
+    int64_t pblocks = 0;
+    for (const serve::Request *r : own) {
+        const CsrHandle &h = *S->mats[(size_t)r->mid].h;
+        pblocks += h.use_panels ? h.pan.nblk : 0;
+    }
+    const int32_t cu = device_cu_count();
     for (serve::Request *r : own) {
         SMatrix &m = S->mats[(size_t)r->mid];
         Slot &sl = S->slots[(size_t)r->slot];
@@ -533,8 +539,9 @@ void HipExec::launch_tick(int lane, int tick, const std::vector<serve::Request *
                                : PanelIO{sl.r, sl.w, fused_rw_parts(*m.h) ? sl.rw : nullptr};
         if (m.h->use_panels) {
             pdesc.push_back(m.h->pan);
+            pdesc.back().per = panel_per(m.h->pan, pblocks, cu);
             pio.push_back(io);
-            pprefix.push_back(pprefix.back() + panel_groups_of(m.h->pan));
+            pprefix.push_back(pprefix.back() + panel_groups_of(pdesc.back()));
         } else if (m.h->use_band) {
             bdesc.push_back(m.h->band);
             bio.push_back(io);

@@ -41,6 +41,14 @@ def test_grouped_equals_single(dtype):
                      for A, v in zip(mats, xd)] for _ in range(2)]
     for h, v, y in zip(hs, xd, single):
         h.spmv(v, y[:-1])
+    # few blocks (one to a workgroup), then enough of them for four
+    for copies in (1, 2, 8):
+        ys = [[torch.full_like(y, np.nan) for y in many] for _ in range(copies)]
+        L.lilac_spmv_batched(hs * copies, xd * copies, [y[:-1] for some in ys for y in some])
+        torch.cuda.synchronize()
+        for some in ys:
+            assert all(torch.equal(y[:-1], z[:-1]) for y, z in zip(single, some))
+            assert all(bool(torch.isnan(z[-1])) for z in some)
     L.lilac_spmv_batched(hs, xd, [y[:-1] for y in many])
     torch.cuda.synchronize()
     for A, x, y, z in zip(mats, xs, single, many):
@@ -50,7 +58,10 @@ def test_grouped_equals_single(dtype):
     for A, h, y in zip(mats, hs, many):
         h.update_values(gen.int_vector(A.nnz, 5).astype(dtype))
     xi = [gen.int_vector(A.cols, 6).astype(dtype) for A in mats]
-    L.lilac_spmv_batched(hs, [torch.from_numpy(x).to(DEV) for x in xi], [y[:-1] for y in many])
+    ys = [[torch.empty_like(y) for y in many] for _ in range(8)]
+    L.lilac_spmv_batched(hs * 8, [torch.from_numpy(x).to(DEV) for x in xi] * 8,
+                         [y[:-1] for some in ys for y in some])
+    many = ys[7]
     for A, x, y in zip(mats, xi, many):
         want = oracle.spmv_csr(A.row_ptr, A.col_idx, gen.int_vector(A.nnz, 5), x.astype(np.float64))
         assert np.array_equal(y[:-1].cpu().numpy().astype(np.float64), want)
@@ -67,11 +78,11 @@ def test_server_cg():
     bs = [gen.vector(A.rows, 30 + k) for k, A in enumerate(mats)]
     bd = [torch.from_numpy(b).to(DEV) for b in bs]
 
-    def run(together):
-        outs = [torch.full_like(b, np.nan) for b in bd]
+    def run(together, copies=1):
+        outs = [torch.full_like(b, np.nan) for b in bd * copies]
         torch.cuda.synchronize()
         tickets = []
-        for mid, b, o in zip(ids, bd, outs):
+        for mid, b, o in zip(ids * copies, bd * copies, outs):
             tickets.append(S.submit(L.REQ_CG, mid, b, o, iters=12))
             if not together:
                 S.wait(tickets[-1])
@@ -80,7 +91,8 @@ def test_server_cg():
         torch.cuda.synchronize()
         return outs
 
-    alone, mixed = run(False), run(True)
+    alone, mixed, many = run(False), run(True), run(True, 12)
+    assert all(torch.equal(a, m) for a, m in zip(alone * 12, many))
     for A, b, a, m in zip(mats, bs, alone, mixed):
         assert torch.equal(a, m)
         ref, _, _ = oracle.cg(A.row_ptr, A.col_idx, A.vals, b, 12)
