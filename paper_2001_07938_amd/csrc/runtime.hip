@@ -787,6 +787,12 @@ static bool hot_possible(const CsrHandle &h)
 // Rows whose block bounds one workgroup finds (a block does not cross them).
 constexpr int32_t kHotPart = 8 * kHotSpan;
 
+// Fewest entries of a block, its rows permitting; fewer where the rows fill at
+// most half of the workgroups' blocks.  PageRank, 20 iterations: 2^16 vertices, 1.2M
+// edges, at least 4096, 8192 and 16384 entries 256, 269 and 301 us; 2^19
+// vertices, 3.6M edges (rows for 146 blocks) 466, 466 and 429.
+constexpr int64_t kHotTarget = 16384, kHotTargetFew = 4096;
+
 // Builds the hot-column copy of the matrix (see HotDesc).  Block bounds and
 // row keys are found on the device: a new block starts before a
 // non-empty row when the current one has kHotRows non-empty rows, or when it
@@ -809,8 +815,7 @@ static void build_hot(CsrHandle &h, hipStream_t s)
     panels_prepare();
     // non-empty rows before each row, then the block bounds; the rows are cut
     // kHotPart at a time, each part by a workgroup of its own
-    const int32_t target =
-        (int32_t)std::max<int64_t>(16384, h.nnz / (int64_t)c.cu);
+    int64_t target = std::max<int64_t>(kHotTarget, h.nnz / (int64_t)c.cu);
     const int32_t parts = (h.rows + kHotPart - 1) / kHotPart;
     std::vector<int32_t> cuts;
     int32_t *d_filled = (int32_t *)tmp_alloc(((size_t)h.rows + 1) * 4), *d_cuts = nullptr;
@@ -819,7 +824,9 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         launch_row_filled(h.rows, h.d_row_ptr, d_filled, s);
         const int64_t filled = scan_total(d_filled, (int64_t)h.rows + 1, s);
         // keys of a block.  Rows in decreasing order of their columns' use (no
-        // renaming): as many as fit.  Rows in no order: all blocks weigh about
+        // renaming): as many as fit, and where those take few blocks, more entries
+        // to a block until no workgroup has two (PageRank, 20 iterations, 2^18
+        // vertices, 4.7M edges, 298 and 254 blocks 550 and 451 us).  Rows in no order: all blocks weigh about
         // the same, so as many blocks as give every workgroup the same number;
         // each part may end in a short one, so a little more is tried until
         // they fit (R-MAT 2^20 float32, 352 blocks on 256 workgroups 77.4 us,
@@ -830,13 +837,16 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         if (h.d_hold && slots > 0)
             keys = (int32_t)std::min<int64_t>(
                 kHotRows, std::max<int64_t>(kHotRows / 4, (filled + slots - 1) / slots));
+        const bool few = !h.d_hold && filled <= (int64_t)c.cu * kHotRows / 2;
+        if (few)
+            target = std::max<int64_t>(kHotTargetFew, h.nnz / (int64_t)c.cu);
         const int32_t cap = (int32_t)(2 * (kHotPart / keys + kHotPart / kHotSpan +
                                            h.nnz / target + 4));
         cuts.resize((size_t)parts * cap);
         d_cuts = (int32_t *)dev_alloc(cuts.size() * 4);
         for (;;) {
-            launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, keys, target, cap, d_cuts,
-                              s);
+            launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, keys, (int32_t)target, cap,
+                              d_cuts, s);
             HIPC(hipMemcpyAsync(cuts.data(), d_cuts, cuts.size() * 4, hipMemcpyDeviceToHost, s));
             HIPC(hipStreamSynchronize(s));
             brow.clear();
@@ -849,6 +859,12 @@ static void build_hot(CsrHandle &h, hipStream_t s)
                     brow.push_back(o[1 + 2 * b]);
                     bent.push_back(o[2 + 2 * b]);
                 }
+            }
+            if (few) {
+                if ((int64_t)brow.size() <= c.cu || target >= h.nnz)
+                    break;
+                target += target / 8;
+                continue;
             }
             if (!h.d_hold || keys >= kHotRows || (int64_t)brow.size() <= slots)
                 break;
