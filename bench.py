@@ -191,7 +191,7 @@ def run_cg(args, torch, L, gen, extras_only=False):
     ms = time_events(lambda: h.spmv(p, q), max(20, args.steps * 10), stream)
     achieved = kb / (ms * 1e-3) / 1e9
     inf = h.info()
-    kernel_name = ("k_spmv_panels<double, false>" if inf.layout == L.LAYOUT_PANELS
+    kernel_name = ("k_spmv_lanes<double, false>" if inf.layout == L.LAYOUT_PANELS
                    else "k_spmv_tiles<double, false, false>")
     # the library's own stream kernels: a 256 MiB copy (read + write; also
     # the calibration of the hardware byte counters) and a 1 GiB read, the

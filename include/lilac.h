@@ -181,8 +181,9 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * LDS and the rows into blocks; each workgroup stages one panel of x in LDS
  * at a time and gathers from there, with 16-bit column offsets.  Row
  * blocks hold at most 4096 rows, enough blocks for every CU or, where such
- * a block weighs less than one copy of x, the rows that weigh two; the
- * block's row sums and one panel share the LDS.  A product of few blocks
+ * a block weighs less than one copy of x, the rows that weigh one; the
+ * block's row sums (in a batch those of up to four blocks) and one panel
+ * share the LDS.  A product of few blocks
  * cuts the panels into groups, a workgroup each, whose sums meet in working
  * memory of the stream (a workgroup that takes all groups, as in a batch or
  * under capture, adds the same sums in the same order).  It suits matrices whose
@@ -192,8 +193,8 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * least 0.3, or at least 240 lines per 64 consecutive rows, and at least
  * 16384 non-zeros) with no row longer than 1024 and copies of x at most four
  * (in the second case two) times the matrix bytes.  Batched calls run all
- * column-panel matrices of a batch in one launch, with the same results.  LILAC_LAYOUT_HOT: a second copy for
- * matrices whose most referenced columns have the lowest indices (a graph
+ * column-panel matrices of a batch in one launch, with the same results.
+ * LILAC_LAYOUT_HOT: a second copy for matrices whose most referenced columns have the lowest indices (a graph
  * relabelled by decreasing out-degree, as lilac_pagerank does by itself for
  * graphs of at least 65536 vertices): the first 34560 (float32) or 17280
  * (float64) columns of x stay in LDS, the others are read from x in device

@@ -743,9 +743,9 @@ __device__ __forceinline__ void panel_block(const PanelDesc &pd, int32_t b,
 // entry one LDS add to the row's sum.  Only what a lane holds of a row that
 // goes on in the next lane takes the scan across the wavefront, once a run.
 // Bound by the stream of entries (10 bytes each, 12 in the scan form): 150,000
-// rows of 241 random columns, float64, 74.5 -> 63.5 us a product (5.85 TB/s of
-// its bytes; 60.5 us with one panel copied instead of eight, 62.6 without the
-// scan).  Three pairs of columns in flight: two and four took 1% longer, six
+// rows of 241 random columns, float64, 74.5 -> 61.3 us a product (6.28 TB/s of
+// the 385 MB it moves; at 63.5 us, 60.5 with one panel copied instead of eight,
+// 62.6 without the scan).  Three pairs of columns in flight: two and four took 1% longer, six
 // 5% (registers).
 // PART: panel group `grp` only, its sums to part[grp * rows + row]; else all.
 // Blocks b .. b + NB - 1 by one workgroup (grouped launches): each panel is
@@ -4859,15 +4859,6 @@ void launch_copy_bytes(const void *src, void *dst, int64_t bytes, hipStream_t s)
         return;
     hipLaunchKernelGGL(k_copy<i32x4>, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s, n,
                        (const i32x4 *)src, (i32x4 *)dst);
-    check_launch("k_copy");
-}
-
-void launch_copy_f64(int64_t n, const double *src, double *dst, hipStream_t s)
-{
-    if (n <= 0)
-        return;
-    hipLaunchKernelGGL(k_copy<double>, dim3(grid_for(n, kBlock, 8192)),
-                       dim3(kBlock), 0, s, n, src, dst);
     check_launch("k_copy");
 }
 

@@ -605,7 +605,6 @@ void launch_sum_parts(const double *part, int32_t nparts, double *out,
 // Bytes between device and pinned host memory, both 16-byte aligned and with
 // room for whole 16-byte pieces.
 void launch_copy_bytes(const void *src, void *dst, int64_t bytes, hipStream_t s);
-void launch_copy_f64(int64_t n, const double *src, double *dst, hipStream_t s);
 void launch_copy_f32(int64_t n, const float *src, float *dst, hipStream_t s);
 
 // CG building blocks (device scalars in `CgScalars`)

@@ -2005,7 +2005,7 @@ static size_t cg_space(const CsrHandle &h)
 // (the product w = A r with the w.r partials fused into it; the scalars and
 // the p, s, x, r updates with the next r.r partials), then the final r.r.
 // Scalars never leave the device.  r, p, sv (s = A p), w hold rows doubles,
-// part 2 * kDotParts, sc one CgScalars; the initialisation writes
+// part kCgParts, sc one CgScalars; the initialisation writes
 // everything later launches read.
 static void cg_enqueue_state(const CsrHandle &h, const double *b, double *x, int iters,
                              double *r, double *p, double *sv, double *w, double *part,
