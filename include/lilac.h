@@ -129,7 +129,9 @@ int lilac_release_all(void);
 int lilac_csr_create(lilac_csr_t *h, int rows, int cols, int64_t nnz,
                      const int *row_ptr, const int *col_idx, const void *vals,
                      lilac_dtype dt, unsigned flags);
-/* New values for the same structure ("update"); vals host or device. */
+/* New values for the same structure ("update"); vals host or device.  Blocking:
+ * waits for the whole device first, so calls enqueued before on any stream use
+ * the old values. */
 int lilac_csr_update_values(lilac_csr_t h, const void *vals);
 /* With LILAC_KEEP_HOST: re-upload and re-analyse from the remembered host
  * pointers before the next use.  LILAC_ERR_STATE without it. */

@@ -1623,10 +1623,12 @@ static void refresh(CsrHandle &h, hipStream_t s)
     if (h.dirty_struct) {
         if (!h.h_row_ptr)
             fail(LILAC_ERR_STATE, "handle invalidated without remembered host arrays");
+        HIPC(hipDeviceSynchronize());   // products of any stream still read the old arrays
         drop_graphs(h);
         forget_handle_in_groups(&h);
         construct(h, h.cols_given, h.h_row_ptr, h.h_col, h.h_vals, s);
     } else if (h.dirty_vals) {
+        // (only handles of the raw calls, whose products have all returned)
         upload_values(h, h.h_vals, s);
         h.dirty_vals = false;
         values_changed(h, s);
@@ -3030,8 +3032,10 @@ int lilac_csr_update_values(lilac_csr_t hh, const void *vals)
         CsrHandle *h = (CsrHandle *)hh;
         if (!h || (!vals && h->nnz > 0))
             fail(LILAC_ERR_ARG, "NULL handle or vals");
-        if (is_device_ptr(vals))
-            HIPC(hipDeviceSynchronize());
+        // the values and the copies made from them are overwritten in place:
+        // products of any stream that read the old ones must be done (and
+        // device values complete)
+        HIPC(hipDeviceSynchronize());
         upload_values(*h, vals, ctx().stream);
         values_changed(*h, ctx().stream);
         HIPC(hipStreamSynchronize(ctx().stream));
