@@ -2272,8 +2272,13 @@ static void run_pagerank(CsrHandle &h, float d, int iters, float *x,
             drop_graphs(h);   // they hold the old address
             dev_free_reset(st.space);
             st.space_cap = 0;
-            st.space = dev_alloc(need);
-            st.space_cap = need;
+            try {
+                st.space = dev_alloc(need);
+                st.space_cap = need;
+            } catch (const Error &e) {
+                if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+                    throw;   // the products do without
+            }
         }
         capture(g.graph, g.exec, [&](hipStream_t cs) {
             if (relabel) {
@@ -2289,7 +2294,8 @@ static void run_pagerank(CsrHandle &h, float d, int iters, float *x,
             }
             float *cur = x, *nxt = st.tmp;
             for (int it = 0; it < iters; ++it) {
-                spmv_enqueue(h, cur, nxt, epi, nullptr, false, cs, need ? st.space : nullptr);
+                spmv_enqueue(h, cur, nxt, epi, nullptr, false, cs,
+                             need <= st.space_cap ? st.space : nullptr);
                 std::swap(cur, nxt);
             }
             if (cur != x)

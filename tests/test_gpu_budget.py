@@ -1,0 +1,66 @@
+"""Calls that want working memory beside what they cannot do without, where the
+device budget (LILAC_HBM_BUDGET, read when the library starts: a process of its
+own for each test) leaves no room for it: they run all the same."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+HEAD = """
+import numpy as np, torch
+import gen, oracle
+import paper_2001_07938_amd as L
+
+def refused(n):
+    # whether a diagonal matrix of n rows (20 bytes a row) is
+    try:
+        L.Csr.from_gen(gen.identity(n)).destroy()
+        return False
+    except L.LilacError as e:
+        assert e.code == -4, e
+        return True
+
+def fill(n, step):
+    # matrices of `step` rows until one of n rows no longer fits
+    kept = []
+    while not refused(n):
+        kept.append(L.Csr.from_gen(gen.identity(step)))
+    return kept
+"""
+
+
+def _child(budget, body):
+    env = dict(os.environ, LILAC_HBM_BUDGET=str(budget))
+    r = subprocess.run([sys.executable, "-c", HEAD + body + "\nprint('child ok')"], cwd=ROOT,
+                       env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "child ok" in r.stdout, r.stdout + r.stderr
+
+
+def test_pagerank_without_working_memory():
+    """A matrix over renamed hot columns: x in their order (260 KB) does not fit
+    beside the second vector; same result as where it does."""
+    _child("160M", """
+n = 65000
+rng = np.random.default_rng(4)
+lens = rng.integers(30, 71, n)
+lens[7] = 3000
+rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+A = gen.Csr(n, n, rp, rng.integers(0, n, rp[-1]).astype(np.int32),
+            rng.uniform(0, 1 / 50, rp[-1]).astype(np.float32), 'wide')
+def rank(h):
+    x = torch.full((n,), 1.0 / n, dtype=torch.float32, device='cuda')
+    return h.pagerank(0.85, 6, x).clone()
+h = L.Csr.from_gen(A, cols=n)
+assert h.info().layout == L.LAYOUT_HOT
+want = rank(h)
+h.destroy()
+h = L.Csr.from_gen(A, cols=n)
+kept = [fill(400000, 200000), fill(100000, 20000), fill(16000, 500)]
+got = rank(h)
+torch.cuda.synchronize()
+assert torch.equal(got, want)
+""")
