@@ -778,6 +778,23 @@ static void build_panels(CsrHandle &h, hipStream_t s)
     h.use_panels = true;
 }
 
+// The same; with `spare` (a layout of smaller copies suits the matrix too) false
+// where the copies do not fit the memory.
+static bool try_panels(CsrHandle &h, hipStream_t s, bool spare)
+{
+    try {
+        build_panels(h, s);
+    } catch (const Error &e) {
+        if (!spare || (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET))
+            throw;
+        dev_free_reset(h.d_pv);
+        dev_free_reset(h.d_prc);
+        dev_free_reset(h.d_pw);
+        return false;
+    }
+    return true;
+}
+
 // Whether the hot-column layout can be built: it needs entries.
 static bool hot_possible(const CsrHandle &h)
 {
@@ -1335,19 +1352,19 @@ static void analyse(CsrHandle &h, hipStream_t s)
         (h.plan.layout == LAYOUT_AUTO && panels_eligible(h));
     // the band layout: on request, or automatically for matrices whose
     // columns are local (not gather-heavy) and whose rows are not all short
-    // enough for one lane each
+    // enough for one lane each; after the column panels where they were chosen
+    // for the lines that rows share
     const bool want_band =
         h.plan.layout == LAYOUT_BAND ||
-        (h.plan.layout == LAYOUT_AUTO && !want_panels && h.nnz >= kOwnLayoutMinNnz &&
+        (h.plan.layout == LAYOUT_AUTO && h.nnz >= kOwnLayoutMinNnz &&
          h.line_ratio < kGatherHeavy);
+    const bool shared = want_panels && h.plan.layout == LAYOUT_AUTO && want_band;
     if (h.plan.layout == LAYOUT_HOT && hot_possible(h)) {
         build_hot(h, s);
         h.grid = h.hot.grid;   // one fused-dot partial per workgroup
         h.fin_blocks = 0;
-    } else if (want_panels && h.rows > 0 && h.nnz > 0 &&
-               !(h.plan.layout == LAYOUT_AUTO && h.line_ratio < kGatherHeavy &&
-                 build_sell(h, s))) {
-        build_panels(h, s);
+    } else if (want_panels && h.rows > 0 && h.nnz > 0 && !(shared && build_sell(h, s)) &&
+               try_panels(h, s, shared)) {
         h.grid = h.pan.nblk;   // one fused-dot partial per row block
         h.fin_blocks = 0;
     } else if (h.use_band || (want_band && build_band(h, s, h.plan.layout == LAYOUT_AUTO))) {

@@ -64,3 +64,22 @@ got = rank(h)
 torch.cuda.synchronize()
 assert torch.equal(got, want)
 """)
+
+
+def test_band_where_the_panels_do_not_fit():
+    """Local columns that suit the column panels (500 lines of x to 64 rows):
+    with memory for the band layout's word per entry only, that is taken."""
+    _child("64M", """
+A = gen.random_rows(8000, 5, 60, seed=9)
+x = torch.from_numpy(gen.vector(A.cols, 1)).cuda()
+h = L.Csr.from_gen(A, cols=A.cols)
+assert h.info().layout == L.LAYOUT_PANELS
+h.destroy()
+kept = [fill(1000000, 200000), fill(165000, 3000)]
+h = L.Csr.from_gen(A, cols=A.cols)
+assert h.info().layout == L.LAYOUT_BAND
+y = torch.empty(A.rows, dtype=torch.float64, device='cuda')
+h.spmv(x, y)
+from tests.helpers import TOL_F64, check_spmv
+check_spmv(A, gen.vector(A.cols, 1), y.cpu().numpy(), TOL_F64)
+""")
