@@ -2229,10 +2229,12 @@ static void build_relabel(CsrHandle &h, PrState &st)
         HIPC(hipStreamSynchronize(s));
         // after relabelling the most gathered columns come first: the
         // hot-column layout keeps them in LDS
+        st.xp = (float *)dev_alloc((size_t)n * 4);
         st.g = create_handle(n, h.cols, h.nnz, rp2, col2, vals2, h.dt, 0, true,
                              h.nnz > 0 ? kBuildHot : kBuildAuto);
-        st.xp = (float *)dev_alloc((size_t)n * 4);
     } catch (...) {
+        dev_free_reset(st.newid);
+        dev_free_reset(st.xp);
         dev_free(rp2);
         dev_free(col2);
         dev_free(vals2);

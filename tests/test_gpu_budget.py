@@ -83,3 +83,33 @@ h.spmv(x, y)
 from tests.helpers import TOL_F64, check_spmv
 check_spmv(A, gen.vector(A.cols, 1), y.cpu().numpy(), TOL_F64)
 """)
+
+
+def test_pagerank_refused_again_and_again():
+    """The relabelled copy of a graph does not fit: every call says so, and the
+    first one with room gives the result (a copy left half made by a refused call
+    would be used by the next)."""
+    _child("64M", """
+n = 70000
+A = gen.random_rows(n, 4, 12, seed=5).astype(np.float32)
+A.vals = np.abs(A.vals) / 12
+def rank(h):
+    x = torch.full((n,), 1.0 / n, dtype=torch.float32, device='cuda')
+    return h.pagerank(0.85, 6, x).clone()
+h = L.Csr.from_gen(A, cols=n)
+want = rank(h)
+h.destroy()
+h = L.Csr.from_gen(A, cols=n)
+kept = fill(800000, 200000) + fill(100000, 20000) + fill(16000, 500)
+left = len(kept)
+while kept:     # a little more room each time
+    try:
+        got = rank(h)
+        break
+    except L.LilacError as e:
+        assert e.code == -4, e
+    kept.pop().destroy()
+assert 0 < len(kept) < left
+torch.cuda.synchronize()
+assert torch.equal(got, want)
+""")
