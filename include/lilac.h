@@ -205,7 +205,8 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * non-zeros, and by LILAC_LAYOUT_AUTO, with the columns renamed by
  * decreasing use, for gather-heavy matrices of at least 3,000,000 non-zeros
  * that do not suit the column panels, if the columns that fit the LDS hold
- * at least 30% of a sample of them: the product then first copies x into
+ * at least 30% of a sample of them and no row more than three times the
+ * entries of a workgroup (a CU's share): the product then first copies x into
  * that order (working memory of the stream; without any, as under capture,
  * every column is looked up, with the same results);
  * otherwise the rows layout is used (lilac_csr_info reports which).  Every

@@ -1000,6 +1000,13 @@ static void fill_hot(CsrHandle &h, const HotDesc &hd, hipStream_t s)
 // -> 99, 917 -> 407); 2^16 10.9 against 13.5 us, hence kHotMinNnz.  The degrees
 // are counted on a sample.
 constexpr int64_t kHotMinNnz = 3000000;
+// A row is one workgroup's, whole: the longest may hold this many times a
+// workgroup's share of the entries.  R-MAT with one row of 2, 3, 4, 8 and 50
+// shares, against row-class tiles, which split it: 2^18 float32 28, 32, 36, 50
+// and 194 (tiles 43 to 59) us, float64 42, 48, 54, 80 and 349 (51 to 68); 2^20
+// float32 70, 83, 99, 158 and 721 (152 to 209), float64 98, 123, 148, 241 and
+// 1224 (181 to 242).
+constexpr int64_t kHotLongest = 3;
 constexpr double kHotShare = 0.3;
 constexpr int32_t kHotSample = 4;
 
@@ -1038,6 +1045,8 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
         h.line_ratio < kGatherHeavy || thread_account())
         return false;
     Context &c = ctx();
+    if ((int64_t)h.max_len * c.cu > kHotLongest * h.nnz)
+        return false;
     bool suits = false;
     try {
         h.d_hold = (int32_t *)dev_alloc((size_t)h.cols * 8);
