@@ -1080,15 +1080,22 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
 
 // Sliced form of the band layout (see SellSlice): when every slice of 64
 // rows spans fewer than 65536 columns and padding the rows to their slice's
-// longest adds at most kSellPad to the entries.  Rows longer than kSellWidth
-// need kSellMinSlices slices: one lane adds up a row, so a few long rows
-// would leave the chip idle (the scan kernel splits them).  27-point stencil
-// of 128^3, float64: scan form 146 us, sliced 105 us per product (5.9 TB/s);
+// longest adds at most kSellPad to the entries.  One lane adds up a row, some
+// 0.09 us an entry, where the scan kernel shares it among four wavefronts: the
+// longest row may hold one kSellSlices-th of the columns of 64 entries (rows of
+// one length: kSellSlices slices), or kSellWidth where there are fewer slices,
+// kSellWidthMany else.  Stencils with one longer row, scan form and sliced,
+// float64: 27 points of 128^3 (at most 855) without 149 and 106 us, 512 entries
+// 154 and 120, 1024 153 and 167, 16384 151 and 1581; 64^3 (105) without 19.1 and
+// 13.6, 128 19.1 and 19.6; 7 points of 128^3 (223) 256 entries 42 and 45; of 64^3
+// (64) 64 entries 8.7 and 8.0, 128 8.7 and 12.1; float32 at 128^3 27 points, 850
+// entries, 124 and 114.  27-point stencil
+// of 128^3, float64: 146 us, sliced 105 us per product (5.9 TB/s);
 // float32 7-point rows pad nothing either.  Past the padding bound the 10
 // bytes of an entry reach the 12 of the scan form's.
 constexpr double kSellPad = 1.15;
-constexpr int32_t kSellWidth = 32;
-constexpr int32_t kSellMinSlices = 1024;
+constexpr int32_t kSellWidth = 32, kSellWidthMany = 64;
+constexpr int32_t kSellSlices = 1024;
 // Workgroups of a product at most (8192; the fused dot has a partial of
 // each).  Eight per CU in a loop of slices took 119.5 us where this takes
 // 105 (sixteen: 109.5): the slices of one workgroup follow one another.
@@ -1124,7 +1131,8 @@ static bool build_sell(CsrHandle &h, hipStream_t s)
         if ((double)at * 64.0 > kSellPad * (double)h.nnz)
             return false;
     }
-    if (widest > kSellWidth && nslice < kSellMinSlices)
+    if (widest > std::max<int64_t>(nslice < kSellSlices ? kSellWidth : kSellWidthMany,
+                                   at / kSellSlices))
         return false;
     if (h.rows & 63)
         slices.back().wmin = 0;   // lanes past the last row have no entries
