@@ -3,7 +3,6 @@
 // pointer marshaling cache, CG and PageRank drivers (captured as HIP graphs),
 // grouped batched products, the autotuner and the C ABI entry points.
 #include <algorithm>
-#include <queue>
 #include <type_traits>
 #include <cctype>
 #include <atomic>
@@ -22,6 +21,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "hot_plan.h"
 #include "lilac_internal.h"
 #include "marshal.h"
 
@@ -836,14 +836,14 @@ static void build_hot(CsrHandle &h, hipStream_t s)
     const int32_t parts = (h.rows + kHotPart - 1) / kHotPart;
     std::vector<int32_t> cuts;
     int32_t *d_filled = (int32_t *)tmp_alloc(((size_t)h.rows + 1) * 4), *d_cuts = nullptr;
-    std::vector<int32_t> brow, bent;   // first row and first entry of each block
+    HotCut cut;
+    std::vector<int32_t> owner;
     try {
         launch_row_filled(h.rows, h.d_row_ptr, d_filled, s);
         const int64_t filled = scan_total(d_filled, (int64_t)h.rows + 1, s);
         // keys of a block.  Rows in decreasing order of their columns' use (no
-        // renaming): as many as fit, and where those take few blocks, more entries
-        // to a block until no workgroup has two (PageRank, 20 iterations, 2^18
-        // vertices, 4.7M edges, 298 and 254 blocks 550 and 451 us).  Rows in no order: all blocks weigh about
+        // renaming): as many as fit, and where those take few blocks, as
+        // hot_cut_few finds.  Rows in no order: all blocks weigh about
         // the same, so as many blocks as give every workgroup the same number;
         // each part may end in a short one, so a little more is tried until
         // they fit (R-MAT 2^20 float32, 352 blocks on 256 workgroups 77.4 us,
@@ -861,68 +861,42 @@ static void build_hot(CsrHandle &h, hipStream_t s)
                                            h.nnz / target + 4));
         cuts.resize((size_t)parts * cap);
         d_cuts = (int32_t *)dev_alloc(cuts.size() * 4);
-        for (;;) {
-            launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, keys, (int32_t)target, cap,
+        auto cut_at = [&](int64_t entries) {
+            launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, keys, (int32_t)entries, cap,
                               d_cuts, s);
             HIPC(hipMemcpyAsync(cuts.data(), d_cuts, cuts.size() * 4, hipMemcpyDeviceToHost, s));
             HIPC(hipStreamSynchronize(s));
-            brow.clear();
-            bent.clear();
+            HotCut k;
             for (int32_t g = 0; g < parts; ++g) {
                 const int32_t *o = cuts.data() + (size_t)g * cap;
                 if (2 * (int64_t)o[0] + 1 > cap)
                     fail(LILAC_ERR_DEVICE, "more hot-column blocks than expected");
                 for (int32_t b = 0; b < o[0]; ++b) {
-                    brow.push_back(o[1 + 2 * b]);
-                    bent.push_back(o[2 + 2 * b]);
+                    k.brow.push_back(o[1 + 2 * b]);
+                    k.bent.push_back(o[2 + 2 * b]);
                 }
             }
-            if (few) {
-                if ((int64_t)brow.size() <= c.cu || target >= h.nnz)
-                    break;
-                target += target / 8;
-                continue;
+            k.brow.push_back(h.rows);
+            k.bent.push_back((int32_t)h.nnz);
+            return k;
+        };
+        if (few) {
+            cut = hot_cut_few(target, c.cu, cut_at);
+        } else {
+            cut = cut_at(target);
+            while (h.d_hold && keys < kHotRows && cut.blocks() > slots) {
+                keys = std::min<int32_t>(kHotRows, keys + keys / 64 + 1);
+                cut = cut_at(target);
             }
-            if (!h.d_hold || keys >= kHotRows || (int64_t)brow.size() <= slots)
-                break;
-            keys = std::min<int32_t>(kHotRows, keys + keys / 64 + 1);
         }
-        brow.push_back(h.rows);
-        bent.push_back((int32_t)h.nnz);
-        hd.nblk = (int32_t)brow.size() - 1;
+        hd.nblk = cut.blocks();
         hd.grid = std::min<int32_t>(hd.nblk, c.cu);
-        // blocks to workgroups: longest first, each to the least loaded
-        // workgroup so far (work = entries + rows), then each workgroup's blocks
-        // in ascending order.  Blocks differ a lot (the densest rows come first
-        // after relabelling), so taking every grid-th block leaves some
-        // workgroups a quarter more work than the mean.
-        std::vector<int32_t> owner((size_t)hd.nblk);
-        {
-            auto work = [&](int32_t b) {
-                return (int64_t)bent[b + 1] - bent[b] + (brow[b + 1] - brow[b]);
-            };
-            std::vector<int32_t> order((size_t)hd.nblk);
-            for (int32_t b = 0; b < hd.nblk; ++b)
-                order[b] = b;
-            std::stable_sort(order.begin(), order.end(),
-                             [&](int32_t a, int32_t b) { return work(a) > work(b); });
-            typedef std::pair<int64_t, int32_t> Load;   // (work so far, workgroup)
-            std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
-            for (int32_t g = 0; g < hd.grid; ++g)
-                least.push(Load(0, g));
-            for (int32_t b : order) {
-                Load l = least.top();
-                least.pop();
-                owner[b] = l.second;
-                l.first += work(b);
-                least.push(l);
-            }
-        }
+        (void)hot_assign(cut, hd.grid, owner);
         const size_t nb1 = (size_t)hd.nblk + 1;
         std::vector<int32_t> hb(3 * nb1 - 1 + (size_t)hd.grid + 1 + hd.nblk);
         for (int32_t b = 0; b <= hd.nblk; ++b) {
-            hb[b] = brow[b];
-            hb[nb1 + b] = bent[b];
+            hb[b] = cut.brow[b];
+            hb[nb1 + b] = cut.bent[b];
         }
         int32_t *gptr = hb.data() + 3 * nb1 - 1;
         int32_t *gblk = gptr + hd.grid + 1;
