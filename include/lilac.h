@@ -187,7 +187,7 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * block's row sums (in a batch those of up to four blocks) and one panel
  * share the LDS.  A product of few blocks
  * cuts the panels into groups, a workgroup each, whose sums meet in working
- * memory of the stream (a workgroup that takes all groups, as in a batch or
+ * memory of the handle (a workgroup that takes all groups, as in a batch or
  * under capture, adds the same sums in the same order).  It suits matrices whose
  * non-zeros scatter over x; it is built only for at most 64 panels (else
  * the rows layout is used).  LILAC_LAYOUT_AUTO (the default) picks it for
@@ -207,7 +207,7 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * that do not suit the column panels, if the columns that fit the LDS hold
  * at least 30% of a sample of them and no row more than three times the
  * entries of a workgroup (a CU's share): the product then first copies x into
- * that order (working memory of the stream; without any, as under capture,
+ * that order (working memory of the handle; without any, as under capture,
  * every column is looked up, with the same results);
  * otherwise the rows layout is used (lilac_csr_info reports which).  Every
  * layout gives deterministic results.  LILAC_LAYOUT_BAND: the CSR order and

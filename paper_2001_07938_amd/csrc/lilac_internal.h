@@ -311,6 +311,12 @@ struct CsrHandle {
     uint16_t *d_so = nullptr;       // the offsets in it
     int64_t sell_cols = 0;          // columns of 64 entries it holds
     int32_t sell_wide = 0;          // longest row
+    // working memory of the products (product_space), or null; space_done: the
+    // end of the last one that uses it.  space_mu: from the wait for that event
+    // to the launch that sets it again
+    void *d_space = nullptr;
+    hipEvent_t space_done = nullptr;
+    mutable std::mutex space_mu;
     std::vector<int32_t> bin_off;   // NCLASS+1
     int64_t nchunks = 0;
     int32_t nsplit = 0;
@@ -424,10 +430,11 @@ void launch_spmv_panels(lilac_dtype dt, const PanelDesc &pd, const void *x,
                         hipStream_t s);
 // The lane form with a workgroup for each row block and group of panels: part
 // (pd.ng * pd.rows doubles) receives the groups' sums, a second kernel adds
-// them up.  Same results as launch_spmv_panels.
+// them up.  Same results as launch_spmv_panels.  done (or null): an event for the
+// last launch's end, here and in launch_spmv_hot.
 void launch_spmv_lane_groups(lilac_dtype dt, const PanelDesc &pd, const void *x, void *y,
                              const Epi &epi, const void *w, double *dot_part, double *part,
-                             hipStream_t s);
+                             hipStream_t s, hipEvent_t done);
 void launch_panel_count(const PanelDesc &pd, const int32_t *rp,
                         const int32_t *col, int32_t *cnt, hipStream_t s);
 void launch_panel_scatter(lilac_dtype dt, const PanelDesc &pd, const int32_t *rp,
@@ -482,7 +489,7 @@ void panels_prepare();
 // its order first; without xp the kernel looks every column up (same results).
 void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
                      const Epi &epi, const void *w, double *dot_part, void *xp,
-                     hipStream_t s);
+                     hipStream_t s, hipEvent_t done);
 // cnt[r] = entries of row r with a column below hd.hot (as hd.newid numbers
 // them).  list: the nlist rows of more than `most` entries.
 void launch_hot_count(const HotDesc &hd, const int32_t *rp, const int32_t *col,
@@ -664,9 +671,10 @@ void destroy_handle(CsrHandle *h);
 MatDesc make_desc(const CsrHandle &h, const void *x, void *y, const void *w,
                   double *chunk_part);
 // part: space for the product (see product_space), or null to take the
-// stream's own.
+// handle's own.  done: an event for the end of a product that uses it.
 void spmv_enqueue(const CsrHandle &h, const void *x, void *y, const Epi &epi,
-                  const void *w, bool dot, hipStream_t s, void *part = nullptr);
+                  const void *w, bool dot, hipStream_t s, void *part = nullptr,
+                  hipEvent_t done = nullptr);
 void run_cg(CsrHandle &h, const double *b, double *x, int iters,
             unsigned flags, hipStream_t s, double *rho_out, int *iters_done);
 // Allocates the handle's CG state now (otherwise done on the first solve).

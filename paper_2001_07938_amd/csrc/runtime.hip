@@ -77,14 +77,6 @@ struct Context {
     char *pin = nullptr;            // pinned: small vectors of the raw calls (x | y)
     int32_t *total = nullptr;       // 1 int for scans
     int occ[2] = {0, 0};            // tile-kernel workgroups per CU (f64, f32)
-    // working memory of a stream: kernels of one stream run in order, so any
-    // of its calls may use it (see stream_space)
-    struct Space {
-        hipStream_t s;
-        void *p;
-        size_t cap;
-    };
-    std::vector<Space> spaces;
 };
 
 static std::recursive_mutex g_mu;
@@ -178,81 +170,9 @@ Account *&thread_account()
     return a;
 }
 
-// Gives the streams' working memory back (waits for the device).
-static bool release_spaces()
-{
-    Context &c = *g_ctx;
-    if (c.spaces.empty())
-        return false;
-    std::vector<Context::Space> old;
-    old.swap(c.spaces);
-    for (const Context::Space &sp : old)
-        dev_free(sp.p);
-    return true;
-}
-
-// The stream's working memory, at least `bytes`, or null: while the stream is
-// being captured (a replay may run on any stream, and nothing may be allocated),
-// for the per-thread stream (one handle, several streams), for a thread that
-// allocates on an account, past kSpaces streams, or when the device is full.
-// At most kSpaces buffers of kSpaceMax bytes are held, until lilac_finalize or
-// until an allocation would fail without them.  Called under the library lock.
-constexpr size_t kSpaces = 8;
-constexpr size_t kSpaceMax = (size_t)64 << 20;
-
-static void *stream_space(hipStream_t s, size_t bytes)
-{
-    Context &c = *g_ctx;
-    if (bytes > kSpaceMax || s == hipStreamPerThread || thread_account())
-        return nullptr;
-    if (s) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        if (st != hipStreamCaptureStatusNone)
-            return nullptr;
-    }
-    for (Context::Space &sp : c.spaces)
-        if (sp.s == s) {
-            if (sp.cap >= bytes)
-                return sp.p;
-            dev_free(sp.p);   // waits for the kernels that use it
-            sp = c.spaces.back();
-            c.spaces.pop_back();
-            break;
-        }
-    if (c.spaces.size() >= kSpaces)
-        return nullptr;
-    try {
-        // whole MiB, so that a stream's buffer seldom has to grow
-        const size_t cap = (bytes + (1u << 20) - 1) & ~(size_t)((1u << 20) - 1);
-        c.spaces.push_back(Context::Space{s, dev_alloc(cap), cap});
-    } catch (const Error &) {
-        return nullptr;
-    }
-    return c.spaces.back().p;
-}
-
-static void *dev_alloc_once(size_t bytes);
-
 void *dev_alloc(size_t bytes)
 {
     std::lock_guard<std::recursive_mutex> lk(g_mu);
-    if (g_ctx->spaces.empty())
-        return dev_alloc_once(bytes);
-    try {
-        return dev_alloc_once(bytes);
-    } catch (const Error &) {
-        if (!release_spaces())
-            throw;
-    }
-    return dev_alloc_once(bytes);
-}
-
-static void *dev_alloc_once(size_t bytes)
-{
     Context &c = *g_ctx;
     if (bytes == 0)
         bytes = 256;
@@ -463,6 +383,10 @@ static void free_analysis(CsrHandle &h)
     dev_free_reset(h.d_brc);
     dev_free_reset(h.d_bb);
     dev_free_reset(h.d_sv);
+    dev_free_reset(h.d_space);
+    if (h.space_done)
+        (void)hipEventDestroy(h.space_done);
+    h.space_done = nullptr;
     h.d_so = nullptr;
     h.sell_cols = 0;
     h.use_band = false;
@@ -479,11 +403,15 @@ static void free_analysis(CsrHandle &h)
     h.fin_blocks = 0;
 }
 
+static size_t product_space(const CsrHandle &h);
+
 static int64_t analysis_bytes(const CsrHandle &h)
 {
     int64_t b = (int64_t)h.rows * 4 + h.nchunks * (3 * 4 + 8) +
                 (int64_t)(h.nsplit + 1) * 4 + (int64_t)h.ntiles * sizeof(Tile) +
                 (int64_t)(h.grid + h.fin_blocks) * 8;
+    if (h.d_space)
+        b += (int64_t)product_space(h);
     if (h.use_panels && h.pan.col0)
         b += h.lane_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
              ((int64_t)h.pan.nblk * h.pan.np * kPanelWaves + 1) * 4 +
@@ -1248,6 +1176,24 @@ static int64_t scan_total(int32_t *a, int64_t n, hipStream_t s)
 static void drop_graphs(CsrHandle &h);
 void forget_handle_in_groups(const CsrHandle *h);
 
+// The working memory of the handle's products, made with the layout so that a
+// product allocates nothing; without any they run all the same.
+static void make_space(CsrHandle &h)
+{
+    const size_t need = product_space(h);
+    if (need == 0)
+        return;
+    try {
+        h.d_space = dev_alloc(need);
+        HIPC(hipEventCreateWithFlags(&h.space_done,
+                                     hipEventDisableTiming | hipEventDisableSystemFence));
+    } catch (const Error &e) {
+        dev_free_reset(h.d_space);
+        if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+            throw;
+    }
+}
+
 static void analyse(CsrHandle &h, hipStream_t s)
 {
     drop_graphs(h);
@@ -1366,6 +1312,7 @@ static void analyse(CsrHandle &h, hipStream_t s)
         h.fin_blocks = 0;
     }
     h.d_dot_part = (double *)dev_alloc((size_t)(std::max(h.grid, 1) + h.fin_blocks + 1) * 8);
+    make_space(h);
     HIPC(hipStreamSynchronize(s));
     g_extra[&h].tiles = std::move(tiles);
 }
@@ -1679,33 +1626,43 @@ static size_t product_space(const CsrHandle &h)
     return h.use_panels && h.pan.col0 && h.pan.ng > 1 ? (size_t)h.pan.ng * h.rows * 8 : 0;
 }
 
+// Whether work enqueued now is recorded: a replay may run on any stream, so it
+// must not use memory that the handle's other products use.
+static bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 void spmv_enqueue(const CsrHandle &h, const void *x, void *y,
                          const Epi &epi, const void *w, bool dot,
-                         hipStream_t s, void *part)
+                         hipStream_t s, void *part, hipEvent_t done)
 {
     if (h.rows == 0)
         return;
-    if (const size_t need = product_space(h)) {
-        // the space must not be given back between taking it and the launch
-        std::lock_guard<std::recursive_mutex> lk(g_mu);
-        if (!part)
-            part = stream_space(s, need);
-        if (h.use_hot) {
-            launch_spmv_hot(h.dt, h.hot, x, y, epi, w, dot ? h.d_dot_part : nullptr, part, s);
-            return;
-        }
-        if (part) {
-            launch_spmv_lane_groups(h.dt, h.pan, x, y, epi, w, dot ? h.d_dot_part : nullptr,
-                                    (double *)part, s);
-            return;
-        }
+    if (product_space(h) > 0 && !part && h.d_space && !capturing(s)) {
+        // one product after the other in the handle's space, whatever their
+        // streams (a stream may be gone by the time the next one asks)
+        std::lock_guard<std::mutex> lk(h.space_mu);
+        HIPC(hipStreamWaitEvent(s, h.space_done, 0));
+        spmv_enqueue(h, x, y, epi, w, dot, s, h.d_space, h.space_done);
+        return;
+    }
+    if (part && h.use_panels && h.pan.ng > 1) {
+        launch_spmv_lane_groups(h.dt, h.pan, x, y, epi, w, dot ? h.d_dot_part : nullptr,
+                                (double *)part, s, done);
+        return;
     }
     if (h.use_panels) {
         launch_spmv_panels(h.dt, h.pan, x, y, epi, w, dot ? h.d_dot_part : nullptr, s);
         return;
     }
     if (h.use_hot) {
-        launch_spmv_hot(h.dt, h.hot, x, y, epi, w, dot ? h.d_dot_part : nullptr, nullptr, s);
+        launch_spmv_hot(h.dt, h.hot, x, y, epi, w, dot ? h.d_dot_part : nullptr, part, s, done);
         return;
     }
     if (h.use_band) {
@@ -2965,7 +2922,6 @@ int lilac_finalize(void)
         marshal_reset();
         release_all_raw();
         release_group_plans();
-        (void)release_spaces();
         Context &c = *g_ctx;
         dev_free(c.x_buf);
         dev_free(c.y_buf);

@@ -189,6 +189,8 @@ int64_t upload_bound(const SMatrix &m, bool cg_state)
     b += (rows + 1) * 4 + npad * 12;                       // CSR
     b += rows * 28 + (nnz / 2048 + 1) * 24 + (1 << 20);    // classes, tiles, chunks, temps
     b += (nnz + kPad) * 12 + 256 * (rows + 257) + (2 << 20);  // panel or band copy + build
+    // groups' sums of a split column-panel product
+    b += std::min(rows * kPanelMaxPanels, (int64_t)device_cu_count() * kPanelMaxRb) * 8;
     b += (int64_t)std::max(1, m.cols) * 8;                 // trace operand
     if (cg_state)
         b += rows * 32 + 2 * 1024 * 8 + 256;               // CG state of the plain path
