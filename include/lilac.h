@@ -207,8 +207,8 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * that do not suit the column panels, if the columns that fit the LDS hold
  * at least 30% of a sample of them and no row more than three times the
  * entries of a workgroup (a CU's share): the product then first copies x into
- * that order (working memory of the handle; without any, as under capture,
- * every column is looked up, with the same results);
+ * that order (working memory of the handle; without any, as under capture, x
+ * is read as it lies, with the same results);
  * otherwise the rows layout is used (lilac_csr_info reports which).  Every
  * layout gives deterministic results.  LILAC_LAYOUT_BAND: the CSR order and
  * values with one extra 32-bit word per non-zero packing the row inside a

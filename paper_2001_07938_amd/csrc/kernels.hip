@@ -1413,16 +1413,14 @@ __device__ __forceinline__ void hot_first(const V *__restrict__ pv,
 // gathers are requested too.  NW wavefronts share the part; XG: xsrc is in
 // device memory (else in LDS).  PRE: the first chunk was requested earlier
 // into *pre (hot_first, same part and wavefront).
-template <typename V, bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false,
-          bool MAP = false>
+template <typename V, bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false>
 __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
                                          const uint32_t *__restrict__ prc,
                                          const uint16_t *__restrict__ pkey,
                                          int32_t s, int32_t e, const V *xsrc,
                                          double *acc, int32_t *ckey, double *csum,
                                          int wave, int lane,
-                                         const HotChunk<V> *pre = nullptr,
-                                         const int32_t *map = nullptr)
+                                         const HotChunk<V> *pre = nullptr)
 {
     typedef typename HotChunk<V>::pair_t pair_t;
     typedef typename HotChunk<V>::upair_t upair_t;
@@ -1467,8 +1465,6 @@ __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
     auto column = [&](uint32_t w, bool ok) {
         return ok ? (HOT ? (w & 0xFFFFu) : w) : 0u;
     };
-    // MAP: xsrc is in the caller's column order, map[c] column c's place in it
-    auto gather = [&](uint32_t c) { return gld(xsrc + (MAP ? (uint32_t)gld(map + c) : c)); };
     auto request = [&](int32_t at, pair_t &rv, upair_t &rr, kpair_t &rk) {
         const int32_t nn = at + 2 * lane;
         const int32_t ea = (nn < ke) ? nn : kb;
@@ -1486,8 +1482,8 @@ __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
     upair_t rc2;
     kpair_t kk2;
     if (XG && kb < ke) {
-        gx0 = gather(column(rc.x, in_share(kb, 0)));
-        gx1 = gather(column(rc.y, in_share(kb, 1)));
+        gx0 = gld(xsrc + column(rc.x, in_share(kb, 0)));
+        gx1 = gld(xsrc + column(rc.y, in_share(kb, 1)));
         if (kb + 128 < ke)
             request(kb + 128, v2, rc2, kk2);
     }
@@ -1514,8 +1510,8 @@ __device__ __forceinline__ void hot_part(const V *__restrict__ pv,
                 rc = rc2;
                 if (!HOT)
                     kk = kk2;
-                gx0 = gather(column(rc.x, in_share(nb, 0)));
-                gx1 = gather(column(rc.y, in_share(nb, 1)));
+                gx0 = gld(xsrc + column(rc.x, in_share(nb, 0)));
+                gx1 = gld(xsrc + column(rc.y, in_share(nb, 1)));
                 if (nb + 128 < ke)
                     request(nb + 128, v2, rc2, kk2);
             }
@@ -1584,15 +1580,14 @@ __device__ __forceinline__ void hot_first4(const float *__restrict__ pv,
 // last run enters a segmented scan over the wavefront.  Each row still
 // gets one addition per chunk, from the lane where its run ends, so the
 // order of the additions is fixed by the matrix and the layout.
-template <bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false, bool MAP = false>
+template <bool HOT, int NW = kPanelWaves, bool XG = !HOT, bool PRE = false>
 __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
                                           const uint32_t *__restrict__ prc,
                                           const uint16_t *__restrict__ pkey,
                                           int32_t s, int32_t e, const float *xsrc,
                                           double *acc, int32_t *ckey, double *csum,
                                           int wave, int lane,
-                                          const HotChunk4 *pre = nullptr,
-                                          const int32_t *map = nullptr)
+                                          const HotChunk4 *pre = nullptr)
 {
     typedef HotChunk4::quad_t quad_t;
     typedef HotChunk4::uquad_t uquad_t;
@@ -1636,8 +1631,6 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
     auto column = [&](uint32_t w, bool ok) {
         return ok ? (HOT ? (w & 0xFFFFu) : w) : 0u;
     };
-    // MAP: xsrc is in the caller's column order, map[c] column c's place in it
-    auto gather = [&](uint32_t c) { return gld(xsrc + (MAP ? (uint32_t)gld(map + c) : c)); };
     auto request = [&](int32_t at, quad_t &rv, uquad_t &rr, kquad_t &rk) {
         const int32_t nn = at + 4 * lane;
         const int32_t ea = (nn < ke) ? nn : kb;
@@ -1654,10 +1647,10 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
     uquad_t rc2;
     kquad_t kk2;
     if (XG && kb < ke) {
-        g[0] = gather(column(rc.x, in_share(kb, 0)));
-        g[1] = gather(column(rc.y, in_share(kb, 1)));
-        g[2] = gather(column(rc.z, in_share(kb, 2)));
-        g[3] = gather(column(rc.w, in_share(kb, 3)));
+        g[0] = gld(xsrc + column(rc.x, in_share(kb, 0)));
+        g[1] = gld(xsrc + column(rc.y, in_share(kb, 1)));
+        g[2] = gld(xsrc + column(rc.z, in_share(kb, 2)));
+        g[3] = gld(xsrc + column(rc.w, in_share(kb, 3)));
         if (kb + CH < ke)
             request(kb + CH, v2, rc2, kk2);
     }
@@ -1690,10 +1683,10 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
                 rc = rc2;
                 if (!HOT)
                     kk = kk2;
-                g[0] = gather(column(rc.x, in_share(nb, 0)));
-                g[1] = gather(column(rc.y, in_share(nb, 1)));
-                g[2] = gather(column(rc.z, in_share(nb, 2)));
-                g[3] = gather(column(rc.w, in_share(nb, 3)));
+                g[0] = gld(xsrc + column(rc.x, in_share(nb, 0)));
+                g[1] = gld(xsrc + column(rc.y, in_share(nb, 1)));
+                g[2] = gld(xsrc + column(rc.z, in_share(nb, 2)));
+                g[3] = gld(xsrc + column(rc.w, in_share(nb, 3)));
                 if (nb + CH < ke)
                     request(nb + CH, v2, rc2, kk2);
             }
@@ -1754,10 +1747,13 @@ __device__ __forceinline__ void hot_part4(const float *__restrict__ pv,
 // row, and each row's result is its hot sum plus its cold sum: every sum is
 // formed in an order fixed by the matrix and the layout.  float32 matrices
 // take four entries per lane (hot_part4), float64 two (hot_part).
-// MAP: x is in the caller's column order and hd.old places the layout's columns
-// in it (twice the gathers, for where no memory is at hand for x in the
-// layout's order; the same sums).
-template <typename V, bool DOT, bool MAP = false>
+// DIRECT: x is in the caller's column order; hd.old places the hot columns in
+// it, and the cold entries' words are the caller's columns.  For where no memory
+// may be used for x in the layout's order, as under capture: the same sums, but
+// the cold gathers meet x as it lies.  R-MAT, 16 entries a row, x copied first,
+// direct, and row-class tiles: float32 2^18 24, 26 and 39 us, 2^20 70, 86 and 149,
+// 2^22 292, 495 and 771; float64 32, 37 and 48; 97, 114 and 180; 406, 695 and 910.
+template <typename V, bool DOT, bool DIRECT = false>
 __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
     HotDesc hd, const V *__restrict__ x, V *__restrict__ y, Epi epi,
     const V *__restrict__ w, double *__restrict__ dot_part)
@@ -1773,10 +1769,11 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const V *pv = (const V *)hd.vals;
+    const uint32_t *cold = DIRECT ? hd.cold : hd.rc;   // words of the cold entries
     const int32_t width = hd.hot;
     const bool aligned = (((uintptr_t)x) & 15) == 0;
     const int32_t nvec = aligned ? width / VV : 0;
-    if (MAP) {
+    if (DIRECT) {
         for (int32_t e = threadIdx.x; e < width; e += kPanelThreads)
             xs[e] = gld(x + gld(hd.old + e));
     } else {
@@ -1799,12 +1796,12 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
         const int32_t pe1 = ((cptr)hd.bent)[bb + 1];
         if constexpr (Q) {
             if (wave & 1)
-                hot_first4<false>((const float *)pv, hd.rc, hd.key, pes, pe1, wave, lane, pre4);
+                hot_first4<false>((const float *)pv, cold, hd.key, pes, pe1, wave, lane, pre4);
             else
                 hot_first4<true>((const float *)pv, hd.rc, hd.key, pe0, pes, wave, lane, pre4);
         } else {
             if (wave & 1)
-                hot_first<V, false>(pv, hd.rc, hd.key, pes, pe1, wave, lane, pre);
+                hot_first<V, false>(pv, cold, hd.key, pes, pe1, wave, lane, pre);
             else
                 hot_first<V, true>(pv, hd.rc, hd.key, pe0, pes, wave, lane, pre);
         }
@@ -1826,33 +1823,33 @@ __global__ __launch_bounds__(kPanelThreads) void k_spmv_hot(
             const float *fx = (const float *)x;
             const float *fs = (const float *)xs;
             if (wave & 1) {
-                hot_part4<false, kPanelWaves, true, true, MAP>(
-                    fv, hd.rc, hd.key, es, e1, fx, acc_c, ckey + kPanelWaves + wave,
-                    csum + kPanelWaves + wave, wave, lane, &pre4, hd.old);
+                hot_part4<false, kPanelWaves, true, true>(
+                    fv, cold, hd.key, es, e1, fx, acc_c, ckey + kPanelWaves + wave,
+                    csum + kPanelWaves + wave, wave, lane, &pre4);
                 hot_part4<true>(fv, hd.rc, hd.key, e0, es, fs, acc_h, ckey + wave,
                                 csum + wave, wave, lane);
             } else {
                 hot_part4<true, kPanelWaves, false, true>(fv, hd.rc, hd.key, e0, es, fs,
                                                           acc_h, ckey + wave, csum + wave,
                                                           wave, lane, &pre4);
-                hot_part4<false, kPanelWaves, true, false, MAP>(
-                    fv, hd.rc, hd.key, es, e1, fx, acc_c, ckey + kPanelWaves + wave,
-                    csum + kPanelWaves + wave, wave, lane, nullptr, hd.old);
+                hot_part4<false>(fv, cold, hd.key, es, e1, fx, acc_c,
+                                 ckey + kPanelWaves + wave, csum + kPanelWaves + wave,
+                                 wave, lane);
             }
         } else {
             if (wave & 1) {
-                hot_part<V, false, kPanelWaves, true, true, MAP>(
-                    pv, hd.rc, hd.key, es, e1, x, acc_c, ckey + kPanelWaves + wave,
-                    csum + kPanelWaves + wave, wave, lane, &pre, hd.old);
+                hot_part<V, false, kPanelWaves, true, true>(
+                    pv, cold, hd.key, es, e1, x, acc_c, ckey + kPanelWaves + wave,
+                    csum + kPanelWaves + wave, wave, lane, &pre);
                 hot_part<V, true>(pv, hd.rc, hd.key, e0, es, xs, acc_h, ckey + wave,
                                   csum + wave, wave, lane);
             } else {
                 hot_part<V, true, kPanelWaves, false, true>(pv, hd.rc, hd.key, e0, es, xs,
                                                             acc_h, ckey + wave, csum + wave,
                                                             wave, lane, &pre);
-                hot_part<V, false, kPanelWaves, true, false, MAP>(
-                    pv, hd.rc, hd.key, es, e1, x, acc_c, ckey + kPanelWaves + wave,
-                    csum + kPanelWaves + wave, wave, lane, nullptr, hd.old);
+                hot_part<V, false>(pv, cold, hd.key, es, e1, x, acc_c,
+                                   ckey + kPanelWaves + wave, csum + kPanelWaves + wave,
+                                   wave, lane);
             }
         }
         if (i + 1 < i1)
@@ -2518,12 +2515,28 @@ __global__ __launch_bounds__(kBlock) void k_hot_share(int64_t nnz, int32_t step,
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_invert(int32_t n, const int32_t *__restrict__ p,
-                                                   int32_t *__restrict__ inv)
+// 1 for a column below hot, else 0 (and past the last one).
+__global__ __launch_bounds__(kBlock) void k_hot_flag(int32_t n, const int32_t *__restrict__ newid,
+                                                     int32_t hot, int32_t *__restrict__ flag)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n)
-        inv[p[i]] = (int32_t)i;
+    if (i <= n)
+        flag[i] = (i < n && newid[i] < hot) ? 1 : 0;
+}
+
+// The columns below hot renumbered in the caller's order, from the exclusive scan
+// of their flags: 64 consecutive ones then lie near each other in x (and the
+// order inside the LDS does not matter).  old: the inverse of that part.
+__global__ __launch_bounds__(kBlock) void k_hot_order(int32_t n, int32_t hot,
+                                                      const int32_t *__restrict__ before,
+                                                      int32_t *__restrict__ newid,
+                                                      int32_t *__restrict__ old)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n && newid[i] < hot) {
+        newid[i] = before[i];
+        old[before[i]] = (int32_t)i;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_hot_split(HotDesc hd,
@@ -2545,7 +2558,7 @@ __global__ __launch_bounds__(kBlock) void k_hot_scatter(
     HotDesc hd, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
     const V *__restrict__ vals, const int32_t *__restrict__ list, int32_t most,
     const int32_t *__restrict__ hx, V *__restrict__ hv, uint32_t *__restrict__ hrc,
-    uint16_t *__restrict__ hkey)
+    uint16_t *__restrict__ hkey, uint32_t *__restrict__ hcold)
 {
     // per row: first entry, what a hot (cold) entry's place adds to the hot
     // (cold) entries before it in the matrix, key
@@ -2584,13 +2597,13 @@ __global__ __launch_bounds__(kBlock) void k_hot_scatter(
         const int l = skip ? __builtin_ctzll(skip) : 64;
         const int64_t k1 = l < 64 ? __builtin_amdgcn_readlane(R.a, l & 63) : last;
         for (int64_t kb = k0; kb < k1; kb += kBlock * U) {
-            int32_t c[U];
+            int32_t own[U], c[U];   // the caller's column, the layout's
             V v[U];
             uint64_t m[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int64_t k = min(kb + u * kBlock + threadIdx.x, k1 - 1);
-                c[u] = col[k];
+                c[u] = own[u] = col[k];
                 v[u] = vals[k];
             }
             if (newid) {
@@ -2631,6 +2644,8 @@ __global__ __launch_bounds__(kBlock) void k_hot_scatter(
                                 hv[at] = v[u];
                                 hrc[at] = (uint32_t)c[u];
                                 hkey[at] = key[lo];
+                                if (hcold)
+                                    hcold[at] = (uint32_t)own[u];
                             }
                         }
                     }
@@ -4419,7 +4434,7 @@ void launch_line_reuse(int32_t rows, const int32_t *rp, const int32_t *col,
     check_launch("k_line_reuse");
 }
 
-template <bool MAP>
+template <bool DIRECT>
 static void launch_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
                        const Epi &epi, const void *w, double *dot_part, hipStream_t s,
                        hipEvent_t done)
@@ -4427,15 +4442,15 @@ static void launch_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y
     dim3 g(hd.grid), b(kPanelThreads);
     if (dt == LILAC_F64) {
         if (dot_part)
-            launch_done(k_spmv_hot<double, true, MAP>, g, b, kPanelLds, s, done, hd,
+            launch_done(k_spmv_hot<double, true, DIRECT>, g, b, kPanelLds, s, done, hd,
                         (const double *)x, (double *)y, epi, (const double *)w, dot_part);
         else
-            launch_done(k_spmv_hot<double, false, MAP>, g, b, kPanelLds, s, done, hd,
+            launch_done(k_spmv_hot<double, false, DIRECT>, g, b, kPanelLds, s, done, hd,
                         (const double *)x, (double *)y, epi, (const double *)w, dot_part);
     } else {
         if (dot_part)
             fail(LILAC_ERR_UNSUPPORTED, "fused dot is only provided for float64");
-        launch_done(k_spmv_hot<float, false, MAP>, g, b, kPanelLds, s, done, hd,
+        launch_done(k_spmv_hot<float, false, DIRECT>, g, b, kPanelLds, s, done, hd,
                     (const float *)x, (float *)y, epi, (const float *)w, dot_part);
     }
     check_launch("k_spmv_hot");
@@ -4508,13 +4523,20 @@ void launch_hot_share(int64_t nnz, int32_t step, const int32_t *col, const int32
     check_launch("k_hot_share");
 }
 
-void launch_invert(int32_t n, const int32_t *p, int32_t *inv, hipStream_t s)
+void launch_hot_flag(int32_t n, const int32_t *newid, int32_t hot, int32_t *flag,
+                     hipStream_t s)
 {
-    if (n <= 0)
-        return;
-    hipLaunchKernelGGL(k_invert, dim3(grid_for(n, kBlock, INT_MAX)), dim3(kBlock), 0, s, n, p,
-                       inv);
-    check_launch("k_invert");
+    hipLaunchKernelGGL(k_hot_flag, dim3(grid_for((int64_t)n + 1, kBlock, INT_MAX)), dim3(kBlock),
+                       0, s, n, newid, hot, flag);
+    check_launch("k_hot_flag");
+}
+
+void launch_hot_order(int32_t n, int32_t hot, const int32_t *before, int32_t *newid,
+                      int32_t *old, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_hot_order, dim3(grid_for(n, kBlock, INT_MAX)), dim3(kBlock), 0, s, n,
+                       hot, before, newid, old);
+    check_launch("k_hot_order");
 }
 
 void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
@@ -4528,15 +4550,15 @@ void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
 void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
                         const int32_t *col, const void *vals, const int32_t *list,
                         int32_t nlist, int32_t most, const int32_t *hx, void *hv, uint32_t *hrc,
-                        uint16_t *hkey, hipStream_t s)
+                        uint16_t *hkey, uint32_t *hcold, hipStream_t s)
 {
     auto go = [&](dim3 g, const int32_t *l) {
         if (dt == LILAC_F64)
             hipLaunchKernelGGL(k_hot_scatter<double>, g, dim3(kBlock), 0, s, hd, rp, col,
-                               (const double *)vals, l, most, hx, (double *)hv, hrc, hkey);
+                               (const double *)vals, l, most, hx, (double *)hv, hrc, hkey, hcold);
         else
             hipLaunchKernelGGL(k_hot_scatter<float>, g, dim3(kBlock), 0, s, hd, rp, col,
-                               (const float *)vals, l, most, hx, (float *)hv, hrc, hkey);
+                               (const float *)vals, l, most, hx, (float *)hv, hrc, hkey, hcold);
         check_launch("k_hot_scatter");
     };
     go(dim3(grid_for(hd.rows, 64, INT_MAX)), nullptr);

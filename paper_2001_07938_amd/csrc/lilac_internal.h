@@ -204,7 +204,8 @@ struct HotDesc {
     const int32_t *gptr;     // [grid + 1]: workgroup g takes blocks gblk[gptr[g] .. gptr[g+1])
     const int32_t *gblk;     // [nblk]
     const int32_t *newid;    // [cols]: number of the caller's column, or null (the same)
-    const int32_t *old;      // [cols]: its inverse
+    const int32_t *old;      // [hot]: the caller's columns of the hot ones
+    const uint32_t *cold;    // [nnz]: with newid, the caller's columns of the cold entries
     int32_t rows, cols, nblk, hot, grid, pad;
 };
 constexpr int kHotRows = 1536;                        // non-empty rows per block
@@ -302,6 +303,7 @@ struct CsrHandle {
     uint16_t *d_hrmap = nullptr;    // rows: key of each row in its block
     int32_t *d_hb = nullptr;        // brow | bent | bsplit
     int32_t *d_hold = nullptr;      // renamed columns: newid | old
+    uint32_t *d_hcold = nullptr;    // the caller's columns of the cold entries
     // band layout (when use_band)
     bool use_band = false;
     BandDesc band{};
@@ -486,7 +488,7 @@ void panels_prepare();
 // Hot-column product (see HotDesc): hd.grid persistent workgroups take the
 // row blocks in turn; dot_part (or null) receives one partial per workgroup.
 // Where the layout renames columns (hd.old), xp (cols elements) receives x in
-// its order first; without xp the kernel looks every column up (same results).
+// its order first; without xp the kernel reads x as it is (same results).
 void launch_spmv_hot(lilac_dtype dt, const HotDesc &hd, const void *x, void *y,
                      const Epi &epi, const void *w, double *dot_part, void *xp,
                      hipStream_t s, hipEvent_t done);
@@ -501,7 +503,7 @@ void launch_hot_split(const HotDesc &hd, const int32_t *hx, int32_t *bsplit,
 void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
                         const int32_t *col, const void *vals, const int32_t *list,
                         int32_t nlist, int32_t most, const int32_t *hx, void *hv, uint32_t *hrc,
-                        uint16_t *hkey, hipStream_t s);
+                        uint16_t *hkey, uint32_t *hcold, hipStream_t s);
 // out[0..rows]: 1 for a row with entries, else 0; row keys from its exclusive
 // scan and the block bounds.
 void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_t s);
@@ -511,7 +513,12 @@ void launch_hot_rmap(const HotDesc &hd, const int32_t *filled, uint16_t *rmap, h
 // *out += entries 0, step, 2 step, ... whose column has a newid below hot.
 void launch_hot_share(int64_t nnz, int32_t step, const int32_t *col, const int32_t *newid,
                       int32_t hot, int32_t *out, hipStream_t s);
-void launch_invert(int32_t n, const int32_t *p, int32_t *inv, hipStream_t s);
+// flag[0..n]: 1 for a column with a newid below hot; from its exclusive scan, those
+// columns renumbered in the caller's order, and the inverse of that.
+void launch_hot_flag(int32_t n, const int32_t *newid, int32_t hot, int32_t *flag,
+                     hipStream_t s);
+void launch_hot_order(int32_t n, int32_t hot, const int32_t *before, int32_t *newid,
+                      int32_t *old, hipStream_t s);
 // Finaliser for split rows: single matrix (items == null, n = nsplit) or a
 // list of (matrix, split row) items for grouped launches.
 void launch_split_finalize(lilac_dtype dt, const int32_t *items, int32_t n,

@@ -380,6 +380,7 @@ static void free_analysis(CsrHandle &h)
     dev_free_reset(h.d_hrmap);
     dev_free_reset(h.d_hb);
     dev_free_reset(h.d_hold);
+    dev_free_reset(h.d_hcold);
     dev_free_reset(h.d_brc);
     dev_free_reset(h.d_bb);
     dev_free_reset(h.d_sv);
@@ -422,7 +423,7 @@ static int64_t analysis_bytes(const CsrHandle &h)
     if (h.use_hot)
         b += (h.nnz + kPad) * ((int64_t)dtype_size(h.dt) + 6) + (int64_t)h.rows * 2 +
              (int64_t)(4 * h.hot.nblk + h.hot.grid + 3) * 4 +
-             (h.hot.old ? (int64_t)h.cols * 8 : 0);
+             (h.hot.old ? ((int64_t)h.cols + h.hot.hot) * 4 + (h.nnz + kPad) * 4 : 0);
     if (h.use_band && h.band.nslice > 0)
         b += h.sell_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
              (int64_t)h.band.nslice * (int64_t)sizeof(SellSlice);
@@ -863,9 +864,14 @@ static void build_hot(CsrHandle &h, hipStream_t s)
     launch_fill_bytes_zero((char *)(h.d_hrc + h.nnz), kPad * 4, s);
     // keys of hot entries are never used; keep every byte defined
     launch_fill_bytes_zero(h.d_hkey, (h.nnz + kPad) * 2, s);
+    if (hd.old) {
+        h.d_hcold = (uint32_t *)dev_alloc((size_t)(h.nnz + kPad) * 4);
+        launch_fill_bytes_zero(h.d_hcold, (h.nnz + kPad) * 4, s);
+    }
     hd.vals = h.d_hv;
     hd.rc = h.d_hrc;
     hd.key = h.d_hkey;
+    hd.cold = h.d_hcold;
     fill_hot(h, hd, s);
     h.hot = hd;
     h.use_hot = true;
@@ -884,7 +890,7 @@ static void fill_hot(CsrHandle &h, const HotDesc &hd, hipStream_t s)
         scan_total(hx, (int64_t)h.rows + 1, s);
         launch_hot_split(hd, hx, (int32_t *)hd.bsplit, s);
         launch_hot_scatter(h.dt, hd, h.d_row_ptr, h.d_col, h.d_vals, list, nlist, most, hx,
-                           h.d_hv, h.d_hrc, h.d_hkey, s);
+                           h.d_hv, h.d_hrc, h.d_hkey, h.d_hcold, s);
         HIPC(hipStreamSynchronize(s));
     } catch (...) {
         tmp_free(hx);
@@ -950,10 +956,11 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
     if ((int64_t)h.max_len * c.cu > kHotLongest * h.nnz)
         return false;
     bool suits = false;
+    const int32_t hot = std::min<int32_t>(h.cols, hot_width((int)dtype_size(h.dt)));
+    int32_t *flag = nullptr;
     try {
-        h.d_hold = (int32_t *)dev_alloc((size_t)h.cols * 8);
+        h.d_hold = (int32_t *)dev_alloc(((size_t)h.cols + hot) * 4);
         rename_columns(h.cols, h.nnz, kHotSample, h.d_col, h.d_hold, s);
-        const int32_t hot = std::min<int32_t>(h.cols, hot_width((int)dtype_size(h.dt)));
         launch_fill_i32(c.total, 1, 0, s);
         launch_hot_share(h.nnz, kHotSample, h.d_col, h.d_hold, hot, c.total, s);
         int32_t in = 0;
@@ -961,12 +968,20 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
         HIPC(hipStreamSynchronize(s));
         suits = (double)in * kHotSample >= kHotShare * (double)h.nnz;
         if (suits) {
-            launch_invert(h.cols, h.d_hold, h.d_hold + h.cols, s);
+            flag = (int32_t *)tmp_alloc(((size_t)h.cols + 1) * 4);
+            launch_hot_flag(h.cols, h.d_hold, hot, flag, s);
+            launch_scan_excl(flag, (int64_t)h.cols + 1, nullptr, s);
+            launch_hot_order(h.cols, hot, flag, h.d_hold, h.d_hold + h.cols, s);
+            HIPC(hipStreamSynchronize(s));
+            tmp_free(flag);
+            flag = nullptr;
             build_hot(h, s);
         } else {
             dev_free_reset(h.d_hold);
         }
     } catch (const Error &e) {
+        tmp_free(flag);
+        dev_free_reset(h.d_hcold);
         dev_free_reset(h.d_hv);
         dev_free_reset(h.d_hrc);
         dev_free_reset(h.d_hkey);
