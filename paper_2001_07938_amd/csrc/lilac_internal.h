@@ -27,6 +27,8 @@ constexpr int kBlock = 256;       // threads per workgroup (4 wave64)
 constexpr int kWaves = kBlock / 64;
 constexpr int kPad = 64;          // device arrays of nnz are padded to this
 constexpr int kDotParts = 1024;   // partials of a standalone dot
+// Partial sums of a solve: r.r and r.w, two parities each.
+constexpr size_t kCgParts = 4 * kDotParts;
 // Pieces of each vector in flight per thread: 2^26 float64 elements, 2, 4 and 8
 // of them 163, 158 and 159 us (one element at a time 171; float32 145 -> 79).
 constexpr int kDotAhead = 4;

@@ -1466,9 +1466,6 @@ CsrHandle *create_handle_adopt(int rows, int cols, int64_t nnz, int32_t *rp,
     return h;
 }
 
-// Partial sums of a solve: r.r and r.w, two parities each.
-constexpr size_t kCgParts = 4 * kDotParts;
-
 struct CgState {
     int64_t n = 0;
     double *r = nullptr, *p = nullptr, *sv = nullptr, *w = nullptr, *part = nullptr;
@@ -1959,8 +1956,6 @@ static void cg_prepare(CsrHandle &h)
     h.cg = st;
 }
 
-void handle_cg_prepare(CsrHandle &h) { cg_prepare(h); }
-
 // Whether a solve runs as one kernel per iteration (k_cg_sell): a sliced band
 // matrix of few rows (one round of workgroups, two to a CU) that are short
 // enough for all their gathers to be on their way before the scalars are known.
@@ -1983,6 +1978,28 @@ static size_t cg_space(const CsrHandle &h)
     return cg_fuses(h) ? (size_t)h.rows * 3 * 8 : product_space(h);
 }
 
+// The state of a solve and that space (a solve owns the space of its products:
+// its graph keeps the address).  The products do without theirs where it does
+// not fit; the vectors of k_cg_sell are state like the others, so that a solve's
+// bits do not depend on the memory left.
+void handle_cg_prepare(CsrHandle &h)
+{
+    cg_prepare(h);
+    const size_t need = cg_space(h);
+    if (need <= h.cg->space_cap)
+        return;
+    drop_graphs(h);
+    dev_free_reset(h.cg->space);
+    h.cg->space_cap = 0;
+    try {
+        h.cg->space = dev_alloc(need);
+        h.cg->space_cap = need;
+    } catch (const Error &e) {
+        if (cg_fuses(h) || (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET))
+            throw;
+    }
+}
+
 // One whole solve: initialisation, then `iters` iterations of two kernels
 // (the product w = A r with the w.r partials fused into it; the scalars and
 // the p, s, x, r updates with the next r.r partials), then the final r.r.
@@ -1997,7 +2014,7 @@ static void cg_enqueue_state(const CsrHandle &h, const double *b, double *x, int
     const int32_t np = blas1_parts(n);
     const int32_t ndot = h.grid + h.fin_blocks;
     launch_cg_init(n, b, x, r, p, sv, part, np, sc, s);
-    if (cg_fuses(h) && space && iters > 0) {
+    if (cg_fuses(h) && iters > 0) {
         // part: r.r by parity, then r.w by parity
         double *more = (double *)space;
         const CgFused f{{r, more}, {sv, more + n}, {w, more + 2 * n}, p, x};
@@ -2041,6 +2058,8 @@ constexpr size_t kNoAllocPart = kCgParts;
 constexpr size_t kNoAllocBytes =
     5 * (size_t)kNoAllocRows * 8 + kNoAllocPart * 8 + sizeof(CgScalars);
 static __device__ __align__(256) char scratch[kNoAllocBytes];
+// (one slice to a wavefront: k_cg_sell's three vectors fit the space's place)
+static_assert((int64_t)kFuseBlocks * kBandWaves * 64 * 3 <= kNoAllocRows, "noalloc space");
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -2113,21 +2132,7 @@ void run_cg(CsrHandle &h, const double *b, double *x, int iters,
             *iters_done = 0;
         return;
     }
-    cg_prepare(h);
-    // a solve owns the space of its products: its graph keeps the address
-    const size_t need = thread_account() ? 0 : cg_space(h);
-    if (need > h.cg->space_cap) {
-        drop_graphs(h);
-        dev_free_reset(h.cg->space);
-        h.cg->space_cap = 0;
-        try {
-            h.cg->space = dev_alloc(need);
-            h.cg->space_cap = need;
-        } catch (const Error &e) {
-            if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
-                throw;   // the products do without
-        }
-    }
+    handle_cg_prepare(h);
     if (flags & LILAC_CG_GRAPH) {
         CgState &st = *h.cg;
         CgState::G *hit = nullptr;

@@ -193,7 +193,10 @@ int64_t upload_bound(const SMatrix &m, bool cg_state)
     b += std::min(rows * kPanelMaxPanels, (int64_t)device_cu_count() * kPanelMaxRb) * 8;
     b += (int64_t)std::max(1, m.cols) * 8;                 // trace operand
     if (cg_state)
-        b += rows * 32 + 2 * 1024 * 8 + 256;               // CG state of the plain path
+        // CG state of the plain path: four vectors, three more or the products' space
+        b += rows * 32 + (int64_t)kCgParts * 8 + 256 +
+             std::max(rows * 24,
+                      std::min(rows * kPanelMaxPanels, (int64_t)device_cu_count() * kPanelMaxRb) * 8);
     b += 64 * 256;                                         // allocation rounding
     return b;
 }

@@ -113,3 +113,35 @@ assert 0 < len(kept) < left
 torch.cuda.synchronize()
 assert torch.equal(got, want)
 """)
+
+
+def test_solve_takes_the_same_steps_or_none():
+    """The three more vectors of a solve with one kernel per iteration: where they
+    do not fit the call says so; it never gives other bits than with more
+    memory."""
+    _child("64M", """
+A = gen.stencil(32, 7)
+b = torch.from_numpy(gen.vector(A.rows, 1)).cuda()
+def solve(h):
+    x = torch.full_like(b, float('nan'))
+    h.cg(b, x, 10)
+    torch.cuda.synchronize()
+    return x
+h = L.Csr.from_gen(A, cols=A.cols)
+want = solve(h)
+x = torch.full_like(b, float('nan'))
+h.cg_noalloc(b, x, 10)
+torch.cuda.synchronize()
+assert torch.equal(x, want)
+h.destroy()
+h = L.Csr.from_gen(A, cols=A.cols)
+# 1.5 MB left (31 bytes a row refused): four vectors (1 MB), not seven (1.8 MB)
+kept = [fill(800000, 200000), fill(100000, 20000), fill(50000, 2000)]
+for k in range(2):
+    try:
+        assert torch.equal(solve(h), want)
+        assert k == 1
+    except L.LilacError as e:
+        assert e.code == -4 and k == 0, e
+    kept.pop()
+""")
