@@ -950,7 +950,7 @@ static void rename_columns(int32_t n, int64_t nnz, int32_t step, const int32_t *
 static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
 {
     if (h.build == kBuildOnce || h.nnz < kHotMinNnz || h.cols <= 0 ||
-        h.line_ratio < kGatherHeavy || thread_account())
+        h.line_ratio < kGatherHeavy)
         return false;
     Context &c = ctx();
     if ((int64_t)h.max_len * c.cu > kHotLongest * h.nnz)

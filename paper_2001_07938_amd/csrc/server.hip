@@ -177,26 +177,30 @@ struct Server {
 
 // Bound on the device bytes an upload of a float64 matrix holds at any
 // moment: the CSR arrays (padded), the row-class analysis and its
-// temporaries, the larger of the column-panel and band copies with their
-// build temporaries, the trace operand, and the 256-byte rounding of each
-// allocation.  Upload threads run under an account with this limit, so a
-// build that needed more would fail loudly instead of passing the budget.
+// temporaries, the largest copy a layout makes with its build temporaries, the
+// working memory of its products, the trace operand, and the 256-byte rounding
+// of each allocation.  An entry's copy: 18 bytes over hot columns (value, word,
+// key, own column), at most 18 in panels (1.5 times the scan form's 12), 12 in
+// slices, 4 in the scan band.  Upload threads run under an account with this
+// limit.  It leaves room for every layout, so that a matrix gets the layout here
+// that a handle of its own gets, and the same bits; a build that needed more
+// would take a smaller layout or fail rather than pass the budget.
 int64_t upload_bound(const SMatrix &m, bool cg_state)
 {
     const int64_t rows = m.rows, nnz = m.nnz;
+    const int64_t cols = std::max(1, m.cols >= 0 ? m.cols : m.rows);
     const int64_t npad = padded_nnz(nnz);
+    // groups' sums of a split column-panel product, or x in a layout's order
+    const int64_t space = std::max(
+        std::min(rows * kPanelMaxPanels, (int64_t)device_cu_count() * kPanelMaxRb) * 8, cols * 8);
     int64_t b = 0;
     b += (rows + 1) * 4 + npad * 12;                       // CSR
     b += rows * 28 + (nnz / 2048 + 1) * 24 + (1 << 20);    // classes, tiles, chunks, temps
-    b += (nnz + kPad) * 12 + 256 * (rows + 257) + (2 << 20);  // panel or band copy + build
-    // groups' sums of a split column-panel product
-    b += std::min(rows * kPanelMaxPanels, (int64_t)device_cu_count() * kPanelMaxRb) * 8;
-    b += (int64_t)std::max(1, m.cols) * 8;                 // trace operand
-    if (cg_state)
-        // CG state of the plain path: four vectors, three more or the products' space
-        b += rows * 32 + (int64_t)kCgParts * 8 + 256 +
-             std::max(rows * 24,
-                      std::min(rows * kPanelMaxPanels, (int64_t)device_cu_count() * kPanelMaxRb) * 8);
+    b += (nnz + kPad) * 18 + 256 * (rows + 257) + (2 << 20);  // a layout's copy + build
+    b += cols * 24;                                        // renamed columns + build
+    b += space + cols * 8;                                 // and the trace operand
+    if (cg_state)   // of the plain path: four vectors, three more or the products' space
+        b += rows * 32 + (int64_t)kCgParts * 8 + 256 + std::max(rows * 24, space);
     b += 64 * 256;                                         // allocation rounding
     return b;
 }
