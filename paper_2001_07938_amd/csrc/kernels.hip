@@ -2693,18 +2693,15 @@ __global__ __launch_bounds__(kBlock) void k_bfs_init(int32_t rows, int32_t sourc
         *last = 0;
 }
 
-// The frontier as a wavefront sees it: the bits of the vertices [base, base +
-// 32 * words), in LDS or (LDS = false) in device memory.
+// The frontier as a wavefront sees it: a bit per vertex, in LDS or (LDS = false)
+// in device memory.
 template <bool LDS>
 struct Frontier {
     const uint32_t *bits;
-    uint32_t base, count;
     __device__ __forceinline__ bool has(int32_t v) const
     {
-        const uint32_t i = (uint32_t)v - base;
-        if (LDS)
-            return i < count && ((bits[i >> 5] >> (i & 31)) & 1u);
-        return (gld(bits + (i >> 5)) >> (i & 31)) & 1u;
+        const uint32_t i = (uint32_t)v;
+        return ((LDS ? bits[i >> 5] : gld(bits + (i >> 5))) >> (i & 31)) & 1u;
     }
 };
 
@@ -2772,9 +2769,13 @@ __device__ __forceinline__ uint64_t bfs_rows(const int32_t *__restrict__ col, in
 // (bitmap depth % 3) gets depth + 1 and its bit in bitmap (depth + 1) % 3; the
 // third one is cleared for the level after.  Nothing is done once a level
 // found nothing (last < depth), so several levels can be enqueued at once.
-// Columns are tested against a copy of the frontier in LDS (one pass for each
-// `lds_words` words of it): a bit per vertex instead of a gather of a 4-byte
-// level, which the caches serve at one line per 4.7 clocks and CU.
+// Columns are tested against a copy of the frontier in LDS where it fits (1.3M
+// vertices), else in device memory: a bit per vertex instead of a gather of a
+// 4-byte level, which the caches serve at one line per 4.7 clocks and CU.  Larger
+// frontiers by one LDS part after the other read every column again for each
+// part: 2^21 vertices, 32M edges, 418 us by two parts and 370 from memory; 2^22
+// with 16M edges, four parts, 1068 and 412; a 7-point stencil of 160^3 (478
+// levels) 83.5 and 22.5 ms.
 // The chunks of split rows and the nlong rows before them in the class order
 // (all of more than kBfsShort entries) go 64 to a wavefront.  The others go 64 consecutive rows to a
 // wavefront, which owns their word of `todo`: what is decided or empty costs a
@@ -2785,7 +2786,7 @@ template <bool LDS>
 __global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
     MatDesc m, int32_t nchunk, int32_t nlong, int32_t rows,
     int32_t *__restrict__ level, int32_t depth, uint32_t *__restrict__ bits, int32_t words,
-    int32_t lds_words, uint64_t *__restrict__ todo, int32_t *__restrict__ last)
+    uint64_t *__restrict__ todo, int32_t *__restrict__ last)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *fb = (uint32_t *)smem;
@@ -2804,86 +2805,80 @@ __global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
         (int32_t)(threadIdx.x >> 6) * (int32_t)gridDim.x + (int32_t)blockIdx.x);
     const int32_t groups = (int32_t)(((int64_t)rows + 63) >> 6);
     bool any = false;
-    for (int32_t p0 = 0; p0 < words; p0 += lds_words) {
-        Frontier<LDS> f{cur, 0u, 0u};
-        if (LDS) {
-            const int32_t nw = min(lds_words, words - p0);   // a multiple of 4
-            if (p0 > 0)
-                __syncthreads();   // the part before is no longer read
-            for (int32_t i = threadIdx.x * 4; i < nw; i += kBfsThreads * 4)
-                *(i32x4 *)(fb + i) = gld((const i32x4 *)(cur + p0 + i));
-            __syncthreads();
-            f = Frontier<LDS>{fb, (uint32_t)p0 * 32u, (uint32_t)nw * 32u};
+    if (LDS) {
+        for (int32_t i = threadIdx.x * 4; i < words; i += kBfsThreads * 4)
+            *(i32x4 *)(fb + i) = gld((const i32x4 *)(cur + i));
+        __syncthreads();
+    }
+    const Frontier<LDS> f{LDS ? fb : cur};
+    for (int32_t i0 = w0; i0 < nchunk + nlong; i0 += waves * 64) {
+        // row and bounds of this wavefront's next 64 long rows and chunks
+        const int64_t i = (int64_t)i0 + (int64_t)lane * waves;
+        int32_t row = 0, k0 = 0, k1 = 0;
+        if (i < nchunk) {
+            row = gld(m.c_row + i);
+            k0 = gld(m.c_k0 + i);
+            k1 = gld(m.c_k1 + i);
+        } else if (i < nchunk + nlong) {
+            row = gld(m.bin_rows + m.split_begin - 1 - (i - nchunk));
+            k0 = gld(m.row_ptr + row);
+            k1 = gld(m.row_ptr + row + 1);
+            if (k1 - k0 <= kBfsShort)
+                k1 = k0;   // its class reaches below: the row is in todo
         }
-        for (int32_t i0 = w0; i0 < nchunk + nlong; i0 += waves * 64) {
-            // row and bounds of this wavefront's next 64 long rows and chunks
-            const int64_t i = (int64_t)i0 + (int64_t)lane * waves;
-            int32_t row = 0, k0 = 0, k1 = 0;
-            if (i < nchunk) {
-                row = gld(m.c_row + i);
-                k0 = gld(m.c_k0 + i);
-                k1 = gld(m.c_k1 + i);
-            } else if (i < nchunk + nlong) {
-                row = gld(m.bin_rows + m.split_begin - 1 - (i - nchunk));
-                k0 = gld(m.row_ptr + row);
-                k1 = gld(m.row_ptr + row + 1);
-                if (k1 - k0 <= kBfsShort)
-                    k1 = k0;   // its class reaches below: the row is in todo
-            }
-            const int32_t n = (k0 < k1 && gld(level + row) == -1) ? k1 - k0 : 0;
-            uint64_t found = bfs_rows<32, 8, LDS>(m.col, k0, k1, __ballot(n > 0 && n <= 512), f);
-            found |= bfs_rows<64, 8, LDS>(m.col, k0, k1, __ballot(n > 512), f);
-            if (found) {
-                any = true;
-                if ((found >> lane) & 1u) {
-                    level[row] = depth + 1;
-                    atomicOr(&next[row >> 5], 1u << (row & 31));
-                }
+        const int32_t n = (k0 < k1 && gld(level + row) == -1) ? k1 - k0 : 0;
+        uint64_t found = bfs_rows<32, 8, LDS>(m.col, k0, k1, __ballot(n > 0 && n <= 512), f);
+        found |= bfs_rows<64, 8, LDS>(m.col, k0, k1, __ballot(n > 512), f);
+        if (found) {
+            any = true;
+            if ((found >> lane) & 1u) {
+                level[row] = depth + 1;
+                atomicOr(&next[row >> 5], 1u << (row & 31));
             }
         }
-        for (int32_t g0 = w0; g0 < groups; g0 += waves * 64) {
-            // the words of this wavefront's next 64 groups
-            const int64_t gl = (int64_t)g0 + (int64_t)lane * waves;
-            const uint64_t word = gl < groups ? todo[gl] : 0;
-            uint64_t live = __ballot(word != 0);
-            // bounds of the next group's rows, asked for one group ahead
-            int32_t nk0 = 0, nk1 = 0;
-            auto request = [&]() {
-                const int64_t g = (int64_t)g0 + (int64_t)__builtin_ctzll(live) * waves;
-                const int64_t row = min(g * 64 + lane, (int64_t)rows - 1);
-                nk0 = gld(m.row_ptr + row);
-                nk1 = gld(m.row_ptr + row + 1);
-            };
+    }
+    for (int32_t g0 = w0; g0 < groups; g0 += waves * 64) {
+        // the words of this wavefront's next 64 groups
+        const int64_t gl = (int64_t)g0 + (int64_t)lane * waves;
+        const uint64_t word = gl < groups ? todo[gl] : 0;
+        uint64_t live = __ballot(word != 0);
+        // bounds of the next group's rows, asked for one group ahead
+        int32_t nk0 = 0, nk1 = 0;
+        auto request = [&]() {
+            const int64_t g = (int64_t)g0 + (int64_t)__builtin_ctzll(live) * waves;
+            const int64_t row = min(g * 64 + lane, (int64_t)rows - 1);
+            nk0 = gld(m.row_ptr + row);
+            nk1 = gld(m.row_ptr + row + 1);
+        };
+        if (live)
+            request();
+        while (live) {
+            const int l = __builtin_ctzll(live);
+            live &= live - 1;
+            const int32_t g = g0 + l * waves;
+            const int32_t k0 = nk0, k1 = nk1;
             if (live)
                 request();
-            while (live) {
-                const int l = __builtin_ctzll(live);
-                live &= live - 1;
-                const int32_t g = g0 + l * waves;
-                const int32_t k0 = nk0, k1 = nk1;
-                if (live)
-                    request();
-                const uint64_t want =
-                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(word >> 32), l) << 32) |
-                    (uint32_t)__builtin_amdgcn_readlane((int)word, l);
-                const int32_t row = g * 64 + lane;   // of this matrix where `want` says so
-                const bool on = (want >> lane) & 1u;
-                const int32_t n = on ? k1 - k0 : 0;
-                uint64_t found = bfs_rows<1, 4, LDS>(m.col, k0, k1, __ballot(n > 0 && n <= 4), f);
-                found |= bfs_rows<4, 8, LDS>(m.col, k0, k1, __ballot(n > 4 && n <= 32), f);
-                found |= bfs_rows<16, 8, LDS>(m.col, k0, k1, __ballot(n > 32), f);
-                if (found) {
-                    any = true;
-                    if ((found >> lane) & 1u)
-                        level[row] = depth + 1;
-                    if (lane == 0) {
-                        atomicAnd((unsigned long long *)&todo[g], ~(unsigned long long)found);
-                        // its two words of the frontier hold long rows too
-                        if ((uint32_t)found)
-                            atomicOr(&next[2 * g], (uint32_t)found);
-                        if (found >> 32)
-                            atomicOr(&next[2 * g + 1], (uint32_t)(found >> 32));
-                    }
+            const uint64_t want =
+                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(word >> 32), l) << 32) |
+                (uint32_t)__builtin_amdgcn_readlane((int)word, l);
+            const int32_t row = g * 64 + lane;   // of this matrix where `want` says so
+            const bool on = (want >> lane) & 1u;
+            const int32_t n = on ? k1 - k0 : 0;
+            uint64_t found = bfs_rows<1, 4, LDS>(m.col, k0, k1, __ballot(n > 0 && n <= 4), f);
+            found |= bfs_rows<4, 8, LDS>(m.col, k0, k1, __ballot(n > 4 && n <= 32), f);
+            found |= bfs_rows<16, 8, LDS>(m.col, k0, k1, __ballot(n > 32), f);
+            if (found) {
+                any = true;
+                if ((found >> lane) & 1u)
+                    level[row] = depth + 1;
+                if (lane == 0) {
+                    atomicAnd((unsigned long long *)&todo[g], ~(unsigned long long)found);
+                    // its two words of the frontier hold long rows too
+                    if ((uint32_t)found)
+                        atomicOr(&next[2 * g], (uint32_t)found);
+                    if (found >> 32)
+                        atomicOr(&next[2 * g + 1], (uint32_t)(found >> 32));
                 }
             }
         }
@@ -4701,19 +4696,14 @@ void launch_bfs_step(const MatDesc &m, int32_t nchunk, int32_t nlong, int32_t ro
     const int32_t cu = device_cu_count();
     const int64_t work = (int64_t)nchunk + nlong + ((int64_t)rows + 63) / 64;
     const int32_t full = grid_for(work, kBfsThreads / 64, cu * 2);
-    // the frontier in LDS in up to kBfsPasses parts; past that the columns
-    // would be read too often: it stays in device memory
-    const int32_t most = kPanelLds / 4;
-    if (words <= kBfsPasses * most) {
-        const int32_t passes = (words + most - 1) / most;
-        const int32_t part = ((words + passes - 1) / passes + 3) & ~3;
-        const int32_t per_cu = std::max(1, std::min(2, kPanelLds / (part * 4)));
+    if (words * 4 <= kPanelLds) {
+        const int32_t per_cu = std::max(1, std::min(2, kPanelLds / (words * 4)));
         hipLaunchKernelGGL(k_bfs_step<true>, dim3(std::min(full, cu * per_cu)),
-                           dim3(kBfsThreads), part * 4, s, m, nchunk, nlong, rows, level,
-                           depth, bits, words, part, todo, last);
+                           dim3(kBfsThreads), words * 4, s, m, nchunk, nlong, rows, level,
+                           depth, bits, words, todo, last);
     } else {
         hipLaunchKernelGGL(k_bfs_step<false>, dim3(full), dim3(kBfsThreads), 0, s, m, nchunk,
-                           nlong, rows, level, depth, bits, words, words, todo, last);
+                           nlong, rows, level, depth, bits, words, todo, last);
     }
     check_launch("k_bfs_step");
 }

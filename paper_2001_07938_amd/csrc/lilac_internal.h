@@ -569,7 +569,6 @@ void launch_dot(int64_t n, const T *a, const T *b, double *part, TOut *out, hipS
 // memory).  The nchunk chunks of the split rows and the nlong rows before the
 // split ones in the class order hold every row of more than kBfsShort entries.
 constexpr int kBfsThreads = 1024;
-constexpr int kBfsPasses = 4;
 constexpr int32_t kBfsShort = 128;
 inline int32_t bfs_words(int32_t rows)
 {
