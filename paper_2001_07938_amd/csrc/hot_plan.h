@@ -59,23 +59,30 @@ inline int64_t hot_assign(const HotCut &cut, int32_t grid, std::vector<int32_t> 
 }
 
 // The blocks of a matrix whose rows take few of them: more entries to a block,
-// from `target` up to twice that, until no workgroup has two (PageRank, 20
-// iterations, 2^18 vertices, 4.7M edges, 298 and 254 blocks 550 and 451 us).
-// Blocks of empty rows alone end at their rows and do not get fewer (and blocks
-// of entries then get too large: 8M vertices, 100,000 of them with 100M edges,
-// the heaviest workgroup 3.9 times the mean), so where that is not reached, or at
-// the price of a heavier workgroup than another try had, the try whose heaviest
-// workgroup costs least is taken.  cut(target) gives the blocks.
+// from `target` up to twice that (few_targets), until no workgroup has two
+// (PageRank, 20 iterations, 2^18 vertices, 4.7M edges, 298 and 254 blocks 550 and
+// 451 us).  Blocks of empty rows alone end at their rows and do not get fewer (and
+// blocks of entries then get too large: 8M vertices, 100,000 of them with 100M
+// edges, the heaviest workgroup 3.9 times the mean), so where that is not reached,
+// or at the price of a heavier workgroup than another try had, the try whose
+// heaviest workgroup costs least is taken.  cut(i) gives the i-th try's blocks.
 constexpr double kHotFewPrice = 1.25;
 
-inline HotCut hot_cut_few(int64_t target, int32_t cu,
-                          const std::function<HotCut(int64_t)> &cut)
+inline std::vector<int64_t> hot_few_targets(int64_t target)
+{
+    std::vector<int64_t> ts;
+    for (int64_t t = target; t <= 2 * target; t += std::max<int64_t>(1, t / 32))
+        ts.push_back(t);
+    return ts;
+}
+
+inline HotCut hot_cut_few(size_t tries, int32_t cu, const std::function<HotCut(size_t)> &cut)
 {
     HotCut best;
     int64_t least = -1;
     std::vector<int32_t> owner;
-    for (int64_t t = target; t <= 2 * target; t += std::max<int64_t>(1, t / 32)) {
-        HotCut c = cut(t);
+    for (size_t i = 0; i < tries; ++i) {
+        HotCut c = cut(i);
         const bool one = c.blocks() <= cu;
         const int64_t cost = hot_assign(c, std::min(c.blocks(), cu), owner);
         const bool first = least < 0;

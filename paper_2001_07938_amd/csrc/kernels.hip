@@ -2456,18 +2456,20 @@ __global__ __launch_bounds__(kBlock) void k_row_filled(int32_t rows,
 // non-empty one, or where it has `target` entries or kHotSpan rows.  Each test,
 // once true, stays true along the rows, so the end is found in three steps of
 // up to 64 rows each.  out[g * cap]: the number of blocks, then first row and
-// first entry of each.
+// first entry of each.  A chain of loads, 0.2 ms: several rules (blockIdx.y) are
+// tried at once.
 __global__ __launch_bounds__(64) void k_hot_blocks(int32_t rows, const int32_t *__restrict__ rp,
                                                    const int32_t *__restrict__ filled,
-                                                   int32_t part, int32_t keys, int32_t target,
-                                                   int32_t cap, int32_t *__restrict__ out)
+                                                   int32_t part, HotTries tries, int32_t cap,
+                                                   int32_t *__restrict__ out)
 {
     constexpr int32_t S1 = kHotSpan / 64, S2 = S1 / 64;
     static_assert(S2 * 64 * 64 == kHotSpan && S2 <= 64, "steps of the search");
     const int lane = threadIdx.x;
     const int64_t r0 = (int64_t)blockIdx.x * part;
     const int32_t end = (int32_t)min(r0 + part, (int64_t)rows);
-    int32_t *o = out + (int64_t)blockIdx.x * cap;
+    const int32_t keys = tries.keys[blockIdx.y], target = tries.target[blockIdx.y];
+    int32_t *o = out + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * cap;
     int32_t start = (int32_t)r0, n = 0;
     while (start < end) {
         const int32_t f0 = filled[start], e0 = rp[start];
@@ -4517,10 +4519,10 @@ void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_
 }
 
 void launch_hot_blocks(int32_t rows, const int32_t *rp, const int32_t *filled, int32_t part,
-                       int32_t keys, int32_t target, int32_t cap, int32_t *out, hipStream_t s)
+                       const HotTries &tries, int32_t cap, int32_t *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_hot_blocks, dim3(grid_for(rows, part, INT_MAX)), dim3(64), 0, s,
-                       rows, rp, filled, part, keys, target, cap, out);
+    hipLaunchKernelGGL(k_hot_blocks, dim3(grid_for(rows, part, INT_MAX), tries.n), dim3(64), 0,
+                       s, rows, rp, filled, part, tries, cap, out);
     check_launch("k_hot_blocks");
 }
 

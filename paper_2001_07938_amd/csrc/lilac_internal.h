@@ -299,7 +299,7 @@ struct CsrHandle {
     // hot-column layout (when use_hot)
     bool use_hot = false;
     HotDesc hot{};
-    void *d_hv = nullptr;
+    void *d_hv = nullptr;           // values | words | keys | own columns | row keys
     uint32_t *d_hrc = nullptr;
     uint16_t *d_hkey = nullptr;
     uint16_t *d_hrmap = nullptr;    // rows: key of each row in its block
@@ -509,8 +509,14 @@ void launch_hot_scatter(lilac_dtype dt, const HotDesc &hd, const int32_t *rp,
 // out[0..rows]: 1 for a row with entries, else 0; row keys from its exclusive
 // scan and the block bounds.
 void launch_row_filled(int32_t rows, const int32_t *rp, int32_t *out, hipStream_t s);
+// Block bounds by up to kHotTries rules of keys and entries at once: `cap` words for
+// each of the parts of `part` rows, one rule after the other.
+constexpr int kHotTries = 8;
+struct HotTries {
+    int32_t n, keys[kHotTries], target[kHotTries];
+};
 void launch_hot_blocks(int32_t rows, const int32_t *rp, const int32_t *filled, int32_t part,
-                       int32_t keys, int32_t target, int32_t cap, int32_t *out, hipStream_t s);
+                       const HotTries &tries, int32_t cap, int32_t *out, hipStream_t s);
 void launch_hot_rmap(const HotDesc &hd, const int32_t *filled, uint16_t *rmap, hipStream_t s);
 // *out += entries 0, step, 2 step, ... whose column has a newid below hot.
 void launch_hot_share(int64_t nnz, int32_t step, const int32_t *col, const int32_t *newid,

@@ -361,6 +361,15 @@ struct HandleExtra {
 };
 static std::unordered_map<const CsrHandle *, HandleExtra> g_extra;
 
+static void free_hot(CsrHandle &h)
+{
+    dev_free_reset(h.d_hv);   // and what lies in its allocation
+    h.d_hrc = h.d_hcold = nullptr;
+    h.d_hkey = h.d_hrmap = nullptr;
+    dev_free_reset(h.d_hb);
+    dev_free_reset(h.d_hold);
+}
+
 static void free_analysis(CsrHandle &h)
 {
     dev_free_reset(h.d_bin_rows);
@@ -374,13 +383,7 @@ static void free_analysis(CsrHandle &h)
     dev_free_reset(h.d_pv);
     dev_free_reset(h.d_prc);
     dev_free_reset(h.d_pw);
-    dev_free_reset(h.d_hv);
-    dev_free_reset(h.d_hrc);
-    dev_free_reset(h.d_hkey);
-    dev_free_reset(h.d_hrmap);
-    dev_free_reset(h.d_hb);
-    dev_free_reset(h.d_hold);
-    dev_free_reset(h.d_hcold);
+    free_hot(h);
     dev_free_reset(h.d_brc);
     dev_free_reset(h.d_bb);
     dev_free_reset(h.d_sv);
@@ -788,16 +791,37 @@ static void build_hot(CsrHandle &h, hipStream_t s)
             target = std::max<int64_t>(kHotTargetFew, h.nnz / (int64_t)c.cu);
         const int32_t cap = (int32_t)(2 * (kHotPart / keys + kHotPart / kHotSpan +
                                            h.nnz / target + 4));
-        cuts.resize((size_t)parts * cap);
+        // the rules to try, in turn
+        std::vector<std::pair<int32_t, int32_t>> tries;
+        if (few) {
+            for (int64_t t : hot_few_targets(target))
+                tries.emplace_back(keys, (int32_t)std::min<int64_t>(t, INT32_MAX));
+        } else {
+            tries.emplace_back(keys, (int32_t)target);
+            while (h.d_hold && tries.back().first < kHotRows) {
+                const int32_t k = tries.back().first;
+                tries.emplace_back(std::min<int32_t>(kHotRows, k + k / 64 + 1), (int32_t)target);
+            }
+        }
+        const size_t each = (size_t)parts * cap;
+        cuts.resize(std::min<size_t>(tries.size(), kHotTries) * each);
         d_cuts = (int32_t *)dev_alloc(cuts.size() * 4);
-        auto cut_at = [&](int64_t entries) {
-            launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, keys, (int32_t)entries, cap,
-                              d_cuts, s);
-            HIPC(hipMemcpyAsync(cuts.data(), d_cuts, cuts.size() * 4, hipMemcpyDeviceToHost, s));
-            HIPC(hipStreamSynchronize(s));
+        size_t have = 0;   // tries made so far, the last of them in cuts
+        auto cut_at = [&](size_t i) {
+            if (i >= have) {
+                HotTries t{};
+                for (t.n = 0; t.n < kHotTries && have + t.n < tries.size(); ++t.n) {
+                    t.keys[t.n] = tries[have + t.n].first;
+                    t.target[t.n] = tries[have + t.n].second;
+                }
+                launch_hot_blocks(h.rows, h.d_row_ptr, d_filled, kHotPart, t, cap, d_cuts, s);
+                HIPC(hipMemcpyAsync(cuts.data(), d_cuts, t.n * each * 4, hipMemcpyDeviceToHost, s));
+                HIPC(hipStreamSynchronize(s));
+                have += t.n;
+            }
             HotCut k;
             for (int32_t g = 0; g < parts; ++g) {
-                const int32_t *o = cuts.data() + (size_t)g * cap;
+                const int32_t *o = cuts.data() + i % kHotTries * each + (size_t)g * cap;
                 if (2 * (int64_t)o[0] + 1 > cap)
                     fail(LILAC_ERR_DEVICE, "more hot-column blocks than expected");
                 for (int32_t b = 0; b < o[0]; ++b) {
@@ -810,12 +834,12 @@ static void build_hot(CsrHandle &h, hipStream_t s)
             return k;
         };
         if (few) {
-            cut = hot_cut_few(target, c.cu, cut_at);
+            cut = hot_cut_few(tries.size(), c.cu, cut_at);
         } else {
-            cut = cut_at(target);
-            while (h.d_hold && keys < kHotRows && cut.blocks() > slots) {
-                keys = std::min<int32_t>(kHotRows, keys + keys / 64 + 1);
-                cut = cut_at(target);
+            for (size_t i = 0; i < tries.size(); ++i) {
+                cut = cut_at(i);
+                if (cut.blocks() <= slots)
+                    break;
             }
         }
         hd.nblk = cut.blocks();
@@ -840,7 +864,28 @@ static void build_hot(CsrHandle &h, hipStream_t s)
         }
         h.d_hb = (int32_t *)dev_alloc(hb.size() * 4);
         HIPC(hipMemcpyAsync(h.d_hb, hb.data(), hb.size() * 4, hipMemcpyHostToDevice, s));
-        h.d_hrmap = (uint16_t *)dev_alloc((size_t)h.rows * 2);
+        // one allocation for the copy: values, words, keys, own columns, row keys
+        // (large ones cost some 0.3 ms each to make and to free)
+        const size_t n = (size_t)(h.nnz + kPad), vs = dtype_size(h.dt);
+        size_t bytes = 0;
+        auto put = [&](size_t b) {
+            const size_t at = bytes;
+            bytes += (b + 255) & ~(size_t)255;
+            return at;
+        };
+        const size_t at_v = put(n * vs), at_rc = put(n * 4), at_key = put(n * 2);
+        const size_t at_cold = put(hd.old ? n * 4 : 0), at_map = put((size_t)h.rows * 2);
+        h.d_hv = dev_alloc(bytes);
+        char *base = (char *)h.d_hv;
+        h.d_hrc = (uint32_t *)(base + at_rc);
+        h.d_hkey = (uint16_t *)(base + at_key);
+        h.d_hcold = hd.old ? (uint32_t *)(base + at_cold) : nullptr;
+        h.d_hrmap = (uint16_t *)(base + at_map);
+        launch_fill_bytes_zero(base + h.nnz * vs, kPad * vs, s);
+        launch_fill_bytes_zero(h.d_hrc + h.nnz, kPad * 4, s);
+        // keys of hot entries and own columns of theirs are never used; keep every
+        // byte defined
+        launch_fill_bytes_zero(h.d_hkey, (int64_t)(at_map - at_key), s);
         hd.rmap = h.d_hrmap;
         hd.brow = h.d_hb;
         hd.bent = h.d_hb + nb1;
@@ -856,18 +901,6 @@ static void build_hot(CsrHandle &h, hipStream_t s)
     }
     tmp_free(d_filled);
     dev_free(d_cuts);
-    const size_t vs = dtype_size(h.dt);
-    h.d_hv = dev_alloc((size_t)(h.nnz + kPad) * vs);
-    h.d_hrc = (uint32_t *)dev_alloc((size_t)(h.nnz + kPad) * 4);
-    h.d_hkey = (uint16_t *)dev_alloc((size_t)(h.nnz + kPad) * 2);
-    launch_fill_bytes_zero((char *)h.d_hv + h.nnz * vs, kPad * vs, s);
-    launch_fill_bytes_zero((char *)(h.d_hrc + h.nnz), kPad * 4, s);
-    // keys of hot entries are never used; keep every byte defined
-    launch_fill_bytes_zero(h.d_hkey, (h.nnz + kPad) * 2, s);
-    if (hd.old) {
-        h.d_hcold = (uint32_t *)dev_alloc((size_t)(h.nnz + kPad) * 4);
-        launch_fill_bytes_zero(h.d_hcold, (h.nnz + kPad) * 4, s);
-    }
     hd.vals = h.d_hv;
     hd.rc = h.d_hrc;
     hd.key = h.d_hkey;
@@ -924,11 +957,9 @@ static void rename_columns(int32_t n, int64_t nnz, int32_t step, const int32_t *
                            int32_t *newid, hipStream_t s)
 {
     const int32_t nblk = (int32_t)(((int64_t)n + kBlock - 1) / kBlock);
-    int32_t *deg = nullptr, *key = nullptr, *hist = nullptr;
+    int32_t *deg = (int32_t *)dev_alloc(((size_t)2 * n + (size_t)kDegKeys * nblk) * 4);
+    int32_t *key = deg + n, *hist = key + n;
     try {
-        deg = (int32_t *)dev_alloc((size_t)n * 4);
-        key = (int32_t *)dev_alloc((size_t)n * 4);
-        hist = (int32_t *)dev_alloc((size_t)kDegKeys * nblk * 4);
         launch_fill_i32(deg, n, 0, s);
         launch_count_cols(nnz, step, col, deg, s);
         launch_degree_keys(n, deg, key, s);
@@ -938,13 +969,9 @@ static void rename_columns(int32_t n, int64_t nnz, int32_t step, const int32_t *
         HIPC(hipStreamSynchronize(s));
     } catch (...) {
         dev_free(deg);
-        dev_free(key);
-        dev_free(hist);
         throw;
     }
     dev_free(deg);
-    dev_free(key);
-    dev_free(hist);
 }
 
 static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
@@ -981,13 +1008,7 @@ static bool build_hot_renamed(CsrHandle &h, hipStream_t s)
         }
     } catch (const Error &e) {
         tmp_free(flag);
-        dev_free_reset(h.d_hcold);
-        dev_free_reset(h.d_hv);
-        dev_free_reset(h.d_hrc);
-        dev_free_reset(h.d_hkey);
-        dev_free_reset(h.d_hrmap);
-        dev_free_reset(h.d_hb);
-        dev_free_reset(h.d_hold);
+        free_hot(h);
         if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
             throw;
         return false;   // the row-class tiles need no copy

@@ -66,10 +66,11 @@ static HotCut choose(const Graph &g, int32_t *per = nullptr, double *heaviest = 
 {
     tries = 0;
     const int64_t nnz = g.rp.back();
-    HotCut c = hot_cut_few(std::max<int64_t>(4096, nnz / kCu), kCu, [&](int64_t t) {
+    const std::vector<int64_t> ts = hot_few_targets(std::max<int64_t>(4096, nnz / kCu));
+    CHECK(ts.back() <= INT32_MAX);
+    HotCut c = hot_cut_few(ts.size(), kCu, [&](size_t i) {
         ++tries;
-        CHECK(t <= INT32_MAX);
-        return cut(g, t);
+        return cut(g, ts[i]);
     });
     std::vector<int32_t> owner;
     const int32_t grid = std::min(c.blocks(), kCu);
