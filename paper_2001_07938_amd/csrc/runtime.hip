@@ -170,6 +170,18 @@ Account *&thread_account()
     return a;
 }
 
+// Gives back the working memory that blocking calls left for the next (none of
+// them runs now: they hold the library lock).
+static bool release_work()
+{
+    Context &c = *g_ctx;
+    void *p = c.work;
+    c.work = nullptr;
+    c.work_cap = 0;
+    dev_free(p);
+    return p != nullptr;
+}
+
 void *dev_alloc(size_t bytes)
 {
     std::lock_guard<std::recursive_mutex> lk(g_mu);
@@ -177,6 +189,8 @@ void *dev_alloc(size_t bytes)
     if (bytes == 0)
         bytes = 256;
     bytes = (bytes + 255) & ~(size_t)255;
+    if (c.in_use + (int64_t)bytes > c.budget)
+        (void)release_work();
     if (c.in_use + (int64_t)bytes > c.budget)
         fail(LILAC_ERR_BUDGET, "allocation of " + std::to_string(bytes) +
                                    " bytes exceeds the HBM budget (" +
@@ -191,6 +205,8 @@ void *dev_alloc(size_t bytes)
                                        std::to_string(a->limit) + " in use)");
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess && release_work())
+        e = hipMalloc(&p, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         fail(LILAC_ERR_OOM, "hipMalloc of " + std::to_string(bytes) +
@@ -1764,7 +1780,8 @@ static int marshal_mode()
     return 0;
 }
 
-// Most working memory kept between blocking calls (bytes).
+// Most working memory kept between blocking calls (bytes), until an allocation
+// needs it (release_work).
 constexpr size_t kWorkKeep = (size_t)64 << 20;
 
 static void *grow_buffer(void *&buf, size_t &cap, size_t bytes)

@@ -145,3 +145,35 @@ for k in range(2):
         assert e.code == -4 and k == 0, e
     kept.pop()
 """)
+
+
+def test_kept_working_memory_is_given_back():
+    """What BFS (half a byte a row) and the JDS product (four) keep for their next
+    call does not stand in the way of a handle that needs the room."""
+    _child("96M", """
+n = 4000000
+A = gen.identity(n // 8)
+J = L.Csr.from_gen(A, cols=A.cols)
+j = J.to_jds()
+x = torch.ones(A.rows, dtype=torch.float64, device='cuda')
+y = torch.empty_like(x)
+kept = [J] + fill(100000, 20000) + fill(16000, 500)
+level = torch.empty(A.rows, dtype=torch.int32, device='cuda')
+while len(kept) > 1:              # a little more room, until the call runs
+    kept.pop().destroy()
+    try:
+        L.lilac_spmv_jds(A.rows, j['max_len'], j['perm'], j['nzcnt'], j['jd_ptr'], j['col_ind'],
+                         j['val'], x, y)
+        break
+    except L.LilacError as e:
+        assert e.code == -4, e
+assert torch.equal(x, y)
+# the call has kept 2 MB; some 0.6 MB are left (31 bytes a row wanted)
+assert J.bfs(0, level) == 1
+h = L.Csr.from_gen(gen.identity(60000))
+h.destroy()
+assert J.bfs(0, level) == 1
+L.lilac_spmv_jds(A.rows, j['max_len'], j['perm'], j['nzcnt'], j['jd_ptr'], j['col_ind'],
+                 j['val'], x, y)
+assert torch.equal(x, y)
+""")
