@@ -1182,7 +1182,8 @@ __global__ __launch_bounds__(kBlock) void k_panel_scatter(
         }
         if (k < e) {
             pv[pos] = vals[k];
-            prc[pos] = ((uint32_t)rl << 16) | (uint32_t)(c - pan * pd.pw);
+            if (prc)
+                prc[pos] = ((uint32_t)rl << 16) | (uint32_t)(c - pan * pd.pw);
         }
     }
 }
@@ -1277,8 +1278,8 @@ __global__ __launch_bounds__(kBlock) void k_lane_fill(PanelDesc pd,
     start[q * 64 + lane] = (uint8_t)(lo - a);
 }
 
-// The entries: one wavefront per row, 64 entries at a time, positions from
-// ballots as in k_panel_scatter.
+// The entries (words null: their values alone): one wavefront per row, 64 entries
+// at a time, positions from ballots as in k_panel_scatter.
 template <typename V>
 __global__ __launch_bounds__(kBlock) void k_lane_scatter(
     PanelDesc pd, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
@@ -1329,7 +1330,8 @@ __global__ __launch_bounds__(kBlock) void k_lane_scatter(
             const int32_t l = j / pk;
             const int64_t place = lane_place(pat, pk, j - l * pk, l);
             vals[place] = src[n];
-            words[place] = (uint16_t)((c - pan * pd.pw) | (j == end ? kLaneEnd : 0u));
+            if (words)
+                words[place] = (uint16_t)((c - pan * pd.pw) | (j == end ? kLaneEnd : 0u));
         }
     }
 }

@@ -295,6 +295,7 @@ struct CsrHandle {
     void *d_pv = nullptr;
     uint32_t *d_prc = nullptr;
     int32_t *d_pw = nullptr;
+    int32_t *d_ppos = nullptr;      // places of each row's entries in each panel, or null
     int64_t lane_cols = 0;          // lane form: columns of 64 entries it holds
     // hot-column layout (when use_hot)
     bool use_hot = false;

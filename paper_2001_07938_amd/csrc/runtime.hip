@@ -399,6 +399,7 @@ static void free_analysis(CsrHandle &h)
     dev_free_reset(h.d_pv);
     dev_free_reset(h.d_prc);
     dev_free_reset(h.d_pw);
+    dev_free_reset(h.d_ppos);
     free_hot(h);
     dev_free_reset(h.d_brc);
     dev_free_reset(h.d_bb);
@@ -432,6 +433,8 @@ static int64_t analysis_bytes(const CsrHandle &h)
                 (int64_t)(h.grid + h.fin_blocks) * 8;
     if (h.d_space)
         b += (int64_t)product_space(h);
+    if (h.d_ppos)
+        b += (int64_t)h.pan.nblk * h.pan.np * (h.pan.rb + 1) * 4;
     if (h.use_panels && h.pan.col0)
         b += h.lane_cols * 64 * ((int64_t)dtype_size(h.dt) + 2) +
              ((int64_t)h.pan.nblk * h.pan.np * kPanelWaves + 1) * 4 +
@@ -616,6 +619,10 @@ static PanelDesc lane_blocks(const CsrHandle &h)
     return best;
 }
 
+// Whether the places of the panels' entries (of each row's first in each panel)
+// are kept for new values: they are where that costs at most a byte an entry.
+static bool keeps_places(const CsrHandle &h, int64_t nptr) { return nptr * 4 <= h.nnz; }
+
 // Builds the lane form of the column-panel copy (see PanelDesc) if its bytes,
 // with the fillers and the padding of the last lanes, are no more than the
 // scan form's (10 against 12 bytes per float64 entry, 6 against 8 float32):
@@ -628,10 +635,12 @@ static bool build_lanes(CsrHandle &h, hipStream_t s)
         return false;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
     const int64_t nrun = (int64_t)pd.nblk * pd.np * kPanelWaves;
+    const bool keep = keeps_places(h, nptr);
     int32_t *pos = nullptr;
     int64_t ncol = 0;
+    auto free_pos = [&]() { keep ? dev_free(pos) : tmp_free(pos); };
     try {
-        pos = (int32_t *)tmp_alloc((size_t)nptr * 4);
+        pos = (int32_t *)(keep ? dev_alloc((size_t)nptr * 4) : tmp_alloc((size_t)nptr * 4));
         // columns of the runs | start rows | words | values, the last two once
         // their size is known
         h.d_pw = (int32_t *)dev_alloc((size_t)(nrun + 1) * 4 + (size_t)nrun * 64);
@@ -660,11 +669,14 @@ static bool build_lanes(CsrHandle &h, hipStream_t s)
         } else {
             dev_free_reset(h.d_pw);
         }
-        tmp_free(pos);
+        if (fits && keep)
+            h.d_ppos = pos;
+        else
+            free_pos();
         if (!fits)
             return false;
     } catch (const Error &e) {
-        tmp_free(pos);
+        free_pos();
         dev_free_reset(h.d_pw);
         dev_free_reset(h.d_pv);
         dev_free_reset(h.d_prc);
@@ -696,7 +708,8 @@ static void build_panels(CsrHandle &h, hipStream_t s)
     pd.nblk = (int32_t)((h.rows + pd.rb - 1) / pd.rb);
     pd.rw = (pd.rb + kPanelWaves - 1) / kPanelWaves;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
-    int32_t *ptr = (int32_t *)tmp_alloc((size_t)nptr * 4);
+    const bool keep = keeps_places(h, nptr);
+    int32_t *ptr = (int32_t *)(keep ? dev_alloc((size_t)nptr * 4) : tmp_alloc((size_t)nptr * 4));
     try {
         launch_fill_i32(ptr, nptr, 0, s);
         launch_panel_count(pd, h.d_row_ptr, h.d_col, ptr, s);
@@ -715,15 +728,52 @@ static void build_panels(CsrHandle &h, hipStream_t s)
         launch_panel_wptr(pd, ptr, h.d_pw, s);
         HIPC(hipStreamSynchronize(s));
     } catch (...) {
-        tmp_free(ptr);
+        keep ? dev_free(ptr) : tmp_free(ptr);
         throw;
     }
-    tmp_free(ptr);
+    if (keep)
+        h.d_ppos = ptr;
+    else
+        tmp_free(ptr);
     pd.vals = h.d_pv;
     pd.rc = h.d_prc;
     pd.wptr = h.d_pw;
     h.pan = pd;
     h.use_panels = true;
+}
+
+// The values of the column-panel copy again, from the CSR, by the places kept or
+// counted as they were when it was built.
+static void fill_panels(CsrHandle &h, hipStream_t s)
+{
+    const PanelDesc &pd = h.pan;
+    const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
+    const int64_t nrun = pd.col0 ? (int64_t)pd.nblk * pd.np * kPanelWaves : 0;
+    int32_t *pos = h.d_ppos;
+    if (!pos)
+        pos = (int32_t *)tmp_alloc((size_t)(nptr + nrun) * 4);
+    try {
+        if (!h.d_ppos) {
+            launch_fill_i32(pos, nptr, 0, s);
+            launch_panel_count(pd, h.d_row_ptr, h.d_col, pos, s);
+            if (pd.col0)
+                launch_lane_runs(pd, pos, pos + nptr, s);
+            launch_scan_excl(pos, nptr, nullptr, s);
+        }
+        if (pd.col0)
+            launch_lane_scatter(h.dt, pd, h.d_row_ptr, h.d_col, h.d_vals, pos, h.d_pv,
+                                nullptr, s);
+        else
+            launch_panel_scatter(h.dt, pd, h.d_row_ptr, h.d_col, h.d_vals, pos, h.d_pv,
+                                 nullptr, s);
+        HIPC(hipStreamSynchronize(s));
+    } catch (...) {
+        if (!h.d_ppos)
+            tmp_free(pos);
+        throw;
+    }
+    if (!h.d_ppos)
+        tmp_free(pos);
 }
 
 // The same; with `spare` (a layout of smaller copies suits the matrix too) false
@@ -738,6 +788,7 @@ static bool try_panels(CsrHandle &h, hipStream_t s, bool spare)
         dev_free_reset(h.d_pv);
         dev_free_reset(h.d_prc);
         dev_free_reset(h.d_pw);
+        dev_free_reset(h.d_ppos);
         return false;
     }
     return true;
@@ -1600,20 +1651,27 @@ void destroy_handle(CsrHandle *h)
     delete h;
 }
 
-// New values also feed the copies made from the CSR arrays (column panels,
-// hot columns, the relabelled PageRank graph): rebuild those.
+// New values also feed the copies made from the CSR arrays (column panels, hot
+// columns, slices), which are filled again in place (300,000 rows of 1 to 100,
+// 9000 columns, float64, in panels: 224 us a call, 1030 with all of the analysis
+// made again), and the relabelled PageRank graph, which is made again.  The scan
+// form of the band layout reads the CSR values.
 static void values_changed(CsrHandle &h, hipStream_t s)
 {
-    if (h.use_panels) {
+    try {
+        if (h.use_panels)
+            fill_panels(h, s);
+        if (h.use_hot)
+            fill_hot(h, h.hot, s);
+    } catch (const Error &e) {
+        if (e.code != LILAC_ERR_OOM && e.code != LILAC_ERR_BUDGET)
+            throw;
+        // no memory to count in beside the copy: without it
         h.dev_bytes -= analysis_bytes(h);
         analyse(h, s);
         h.dev_bytes += analysis_bytes(h);
         return;
     }
-    if (h.use_hot)
-        fill_hot(h, h.hot, s);   // in place, as the sliced form below
-    // the scan form of the band layout reads the CSR values; the sliced form
-    // is filled again in place
     if (h.use_band && h.band.nslice > 0)
         launch_sell_pack(h.dt, h.band, h.d_col, h.d_vals, h.d_sv, h.d_so, s);
     if (h.pr && h.pr->g)
