@@ -217,7 +217,8 @@ int lilac_csr_set_plan(lilac_csr_t h, const int *upper /* [8] */,
  * and stencil matrices, small matrices).  The wavefronts stream the
  * entries and add up each row's run with a segmented scan.  Where the rows
  * of each 64 in a row have nearly one length (padding them to the longest
- * adds at most 15%) and span less than 65536 columns, the matrix is instead
+ * adds at most 15%, and no row outweighs what a wavefront has of the matrix)
+ * and span less than 65536 columns, the matrix is instead
  * copied column by column of such slices with 16-bit column offsets, one
  * lane per row.  LILAC_LAYOUT_AUTO
  * picks it for matrices with at least 16384 non-zeros whose columns are

@@ -2797,15 +2797,15 @@ __device__ __forceinline__ uint64_t bfs_rows(const int32_t *__restrict__ col, in
 // vertices), else in device memory: a bit per vertex instead of a gather of a
 // 4-byte level, which the caches serve at one line per 4.7 clocks and CU.  Larger
 // frontiers by one LDS part after the other read every column again for each
-// part: 2^21 vertices, 32M edges, 418 us by two parts and 370 from memory; 2^22
-// with 16M edges, four parts, 1068 and 412; a 7-point stencil of 160^3 (478
-// levels) 83.5 and 22.5 ms.
+// part: 2^21 vertices, 32M edges, 413 us by two parts and 360 from memory; 2^22
+// with 16M edges, four parts, 1068 and 357; a 7-point stencil of 160^3 (478
+// levels) 83.5 and 16.2 ms.
 // The chunks of split rows and the nlong rows before them in the class order
 // (all of more than kBfsShort entries) go 64 to a wavefront.  The others go 64 consecutive rows to a
 // wavefront, which owns their word of `todo`: what is decided or empty costs a
 // bit.  R-MAT 2^20, 16 M entries: 47 + 37 us for the two levels that look at
 // every entry and 15 us for each late one with tiles for all rows; 43 + 36 and
-// 8 to 12 us with the words (170 us for the call of six levels).
+// 8 to 12 us with the words (140 us for the call of six levels).
 template <bool LDS>
 __global__ __launch_bounds__(kBfsThreads) void k_bfs_step(
     MatDesc m, int32_t nchunk, int32_t nlong, int32_t rows,

@@ -635,12 +635,16 @@ static bool build_lanes(CsrHandle &h, hipStream_t s)
         return false;
     const int64_t nptr = (int64_t)pd.nblk * pd.np * (pd.rb + 1);
     const int64_t nrun = (int64_t)pd.nblk * pd.np * kPanelWaves;
+    // kept as the places for new values, or, where it is large enough, as the
+    // products' working memory (an allocation and a release less)
     const bool keep = keeps_places(h, nptr);
+    const bool space = !keep && pd.ng > 1 && nptr * 4 >= (int64_t)pd.ng * h.rows * 8;
     int32_t *pos = nullptr;
     int64_t ncol = 0;
-    auto free_pos = [&]() { keep ? dev_free(pos) : tmp_free(pos); };
+    const bool own = keep || space;
+    auto free_pos = [&]() { own ? dev_free(pos) : tmp_free(pos); };
     try {
-        pos = (int32_t *)(keep ? dev_alloc((size_t)nptr * 4) : tmp_alloc((size_t)nptr * 4));
+        pos = (int32_t *)(own ? dev_alloc((size_t)nptr * 4) : tmp_alloc((size_t)nptr * 4));
         // columns of the runs | start rows | words | values, the last two once
         // their size is known
         h.d_pw = (int32_t *)dev_alloc((size_t)(nrun + 1) * 4 + (size_t)nrun * 64);
@@ -671,6 +675,8 @@ static bool build_lanes(CsrHandle &h, hipStream_t s)
         }
         if (fits && keep)
             h.d_ppos = pos;
+        else if (fits && space)
+            h.d_space = pos;
         else
             free_pos();
         if (!fits)
@@ -789,6 +795,7 @@ static bool try_panels(CsrHandle &h, hipStream_t s, bool spare)
         dev_free_reset(h.d_prc);
         dev_free_reset(h.d_pw);
         dev_free_reset(h.d_ppos);
+        dev_free_reset(h.d_space);
         return false;
     }
     return true;
@@ -1287,7 +1294,8 @@ static void make_space(CsrHandle &h)
     if (need == 0)
         return;
     try {
-        h.d_space = dev_alloc(need);
+        if (!h.d_space)
+            h.d_space = dev_alloc(need);
         HIPC(hipEventCreateWithFlags(&h.space_done,
                                      hipEventDisableTiming | hipEventDisableSystemFence));
     } catch (const Error &e) {
