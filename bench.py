@@ -217,6 +217,7 @@ def run_cg(args, torch, L, gen, extras_only=False):
         read_ms = time_events(lambda: L.lilac_hbm_stream(big, rb, groups_per_cu=g), 20, stream)
         read_gbs = max(read_gbs, rb / (read_ms * 1e-3) / 1e9)
     del big
+    traffic = measured_traffic(kernel_name, "cg_spd150k")
     res = {
         "metric": METRIC, "value": round(value, 2), "unit": "GB/s",
         "ms_per_step": round(dt * 1e3, 4),
@@ -226,7 +227,11 @@ def run_cg(args, torch, L, gen, extras_only=False):
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": measured_traffic(kernel_name, "cg_spd150k"),
+                     # frac counts the bytes of the CSR arrays; the kernel
+                     # moves fewer (its own layout's): frac_by_traffic
+                     "traffic": traffic,
+                     "frac_by_traffic": (None if traffic is None else
+                                         round(traffic / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)),
                      "kernel": kernel_name, "npanels": inf.npanels,
                      "read_ceiling": round(read_gbs, 1),
                      "frac_of_read_ceiling": round(achieved / read_gbs, 4),
